@@ -67,9 +67,9 @@ typedef enum { F8_TENSORWISE = 0, F8_ROWWISE = 1, F8_COLWISE = 2 } f8_granularit
  *   F8_NT: A[M,K], B[N,K]   (both contraction-contiguous)
  *   F8_NN: A[M,K], B[K,N]
  *   F8_TN: A[K,M], B[K,N]
- * All three run on the same tiled kernel when K is a multiple of 256 (operands
- * whose contraction index is the slow one are turned inside the kernel);
- * otherwise a slower generic kernel takes over. */
+ * All three run on the same tiled kernel (operands whose contraction index is
+ * the slow one are turned inside the kernel), with any K: a K that is not a
+ * multiple of 256 costs what the next multiple does. */
 typedef enum { F8_NT = 0, F8_NN = 1, F8_TN = 2 } f8_layout;
 
 /* Bytes of device workspace that is enough for any call of this library on

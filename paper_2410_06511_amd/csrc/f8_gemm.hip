@@ -63,7 +63,7 @@ static f8_status gemm_checked(f8_layout layout, int64_t M, int64_t N, int64_t K,
     if (!aligned16(A) || !aligned16(B) || !aligned16(D_bf16)) return F8_ERR_ALIGN;
     if (g == F8_ROWWISE && !aligned16(inv_scale_b)) return F8_ERR_ALIGN;
     if (workspace && !aligned16(workspace)) return F8_ERR_ALIGN;
-    // K == 0: the generic kernel's K loop does not run and it stores zeros
+    // K == 0: every lane of the one pair of K steps lies past the end and loads zeros
     return gemm(layout, M, N, K, A, fa, lda, B, fb, ldb, inv_scale_a, inv_scale_b, g, D_bf16, ldd, amax_d,
                 (hipStream_t)stream, workspace, workspace ? workspace_bytes_ : 0);
 }

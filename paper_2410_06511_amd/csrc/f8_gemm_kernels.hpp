@@ -2,25 +2,18 @@
 // dX = dY W, dW = dY^T X) (kernels and launch logic; f8_gemm.hip holds the entry points,
 // f8_gemm_inst.hip is compiled once per operand-format pair and layout, in parallel).
 //
-// Two kernels:
-//   gemm_tile_kernel    the fast path, K a multiple of 256, all three layouts.
-//                       Persistent workgroups, global -> LDS direct loads (no
-//                       VGPR staging), two LDS stages, v_mfma_f32_16x16x128_f8f6f4,
-//                       scales folded into the fp32 epilogue, bf16 stores staged
-//                       through LDS.  An operand whose contraction index is the
-//                       fast one in memory ("row-major in K": both of F8_NT, A of
-//                       F8_NN) is staged as XOR-swizzled 128-byte rows; one whose
-//                       contraction index is the slow one ("k-major": B of F8_NN,
-//                       both of F8_TN) is staged as it lies in memory and turned
-//                       on its way from LDS to the registers by the transposing
-//                       LDS read, so no transposed copy of any operand is needed.
-//   gemm_generic_kernel any layout, any multiple-of-16 shape; 64x64 tiles and
-//                       the 16x16x32 fp8 MFMA.  The fallback.
+// gemm_tile_kernel serves all three layouts and every shape (multiples of 16):
+// persistent workgroups, global -> LDS direct loads (no VGPR staging), two LDS stages,
+// v_mfma_f32_16x16x128_f8f6f4, scales folded into the fp32 epilogue, bf16 stores staged
+// through LDS.  An operand whose contraction index is the fast one in memory
+// ("row-major in K": both of F8_NT, A of F8_NN) is staged as XOR-swizzled 128-byte rows;
+// one whose contraction index is the slow one ("k-major": B of F8_NN, both of F8_TN) is
+// staged as it lies in memory and turned on its way from LDS to the registers by the
+// transposing LDS read, so no transposed copy of any operand is needed.
 //
-// In both, the MFMA's first operand is fed from the B matrix (n index) and the
-// second from the A matrix (m index): the accumulator registers of a lane then
-// hold four consecutive n for one m, so the bf16 results leave as 8-byte pieces
-// of a row of D.
+// The MFMA's first operand is fed from the B matrix (n index) and the second from the A
+// matrix (m index): the accumulator registers of a lane then hold four consecutive n for
+// one m.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -40,30 +33,6 @@ __device__ inline void static_for(F&& f)
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-
-// ---------------------------------------------------------------------------
-// epilogue helper: four fp32 accumulators -> four bf16 at D[m, n..n+3]
-// ---------------------------------------------------------------------------
-template <int GRAN>
-__device__ inline uint2 store4(uint16_t* __restrict__ D, int64_t ldd, int64_t m, int64_t n, v4f acc,
-                               float s_tensor, const float* __restrict__ isa,
-                               const float* __restrict__ isb)
-{
-    float r0, r1, r2, r3;
-    if constexpr (GRAN == F8_TENSORWISE) {
-        r0 = acc[0] * s_tensor, r1 = acc[1] * s_tensor, r2 = acc[2] * s_tensor, r3 = acc[3] * s_tensor;
-    } else {
-        const float sa = isa[m];
-        const float4 sb = *reinterpret_cast<const float4*>(isb + n);
-        r0 = (acc[0] * sa) * sb.x, r1 = (acc[1] * sa) * sb.y;
-        r2 = (acc[2] * sa) * sb.z, r3 = (acc[3] * sa) * sb.w;
-    }
-    uint2 o;
-    o.x = f32_to_bf16_bits(r0) | (f32_to_bf16_bits(r1) << 16);
-    o.y = f32_to_bf16_bits(r2) | (f32_to_bf16_bits(r3) << 16);
-    *reinterpret_cast<uint2*>(D + m * ldd + n) = o;
-    return o;
-}
 
 // amax of the bf16 output, kept as a bf16 magnitude in the upper half of a word so that the
 // unsigned integer order of the words is the order of the magnitudes; combined across
@@ -122,6 +91,9 @@ __device__ inline void tile_coords(int pid, int tiles_m, int tiles_n, int* tm, i
 // There are two barriers per K step (this stage is free to refill; the other stage has
 // landed), each with MFMAs queued in front of it.
 constexpr int kBK = 128;  // bytes of K per LDS stage
+// Buffer loads of the ragged instances: a lane offset at or past kRecords reads as zero.  Real offsets stay
+// below it: they reach 255 leading dimensions of less than 2^23 bytes into the operand.
+constexpr uint32_t kRecords = 0x7FFFFFF0u, kPastEnd = 0x80000000u;
 
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
@@ -186,13 +158,19 @@ constexpr int kWaitAllVmLgkm = 0x0070;
 // fp32 sums of range s to partial[s][M][ldp]; splitk_reduce_kernel adds the ranges in order,
 // applies the scales and rounds to bf16.  (For products with few output tiles and a long
 // contraction, where whole tiles would leave most compute units idle.)
+// RAGGED: the contraction (a range's, with SPLITK) need not fill its last K steps; what lies past its
+// end is loaded as zero.  Such an instance loads through buffer descriptors, whose range check
+// supplies the zeros.  The plain instances keep the plain global loads: with descriptors
+// everywhere the large products were 0.5 to 1 % slower (16384 x 14336 x 4096, forward and backward:
+// 2.219 ms against 2.206), while a separate 64x64-tile kernel for ragged lengths, which this
+// replaces, took 300 us for a 4096 x 4096 weight gradient over 2000 tokens (now 30).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, int GRAN, bool AMAX, bool AKM, bool BKM,
-          bool SPLITK = false>
+          bool SPLITK = false, bool RAGGED = false>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ D, int M,
     int N, int K, int64_t lda, int64_t ldb, int64_t ldd, const float* __restrict__ isa,
     const float* __restrict__ isb, int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits,
-    int splits = 1, float* __restrict__ partial = nullptr, int64_t ldp = 0)
+    int ksteps /* K steps per work item, even */, int splits = 1, float* __restrict__ partial = nullptr, int64_t ldp = 0)
 {
     static_assert(!(SPLITK && AMAX), "the output amax is taken by the kernel that writes D");
     constexpr int NW = WAVES_M * WAVES_N;
@@ -222,7 +200,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int tiles_mn = tiles_m * tiles_n;
     const int total_tiles = SPLITK ? tiles_mn * splits : tiles_mn;  // work items of the launch
-    const int KT = SPLITK ? K / kBK / splits : K / kBK;             // K steps per work item
+    const int KT = ksteps;
 
     using std::integral_constant;
     auto stage_ptr = [&](auto S) -> uint8_t* {
@@ -271,10 +249,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     // never stored.  k-major: k-row * ld + chunk, with chunks past the edge re-reading the last
     // valid chunk of the k-row.
     uint32_t a_off[A_LOADS], b_off[B_LOADS];
+    int k_left = K;  // contraction length from the item's first k to the end of the operands
     auto load_context = [&](int item) {
         int tm, tn;
         tile_coords(SPLITK ? item % tiles_mn : item, tiles_m, tiles_n, &tm, &tn);
         const int64_t koff = SPLITK ? (int64_t)(item / tiles_mn) * KT * kBK : 0;  // first k of the item's range
+        if constexpr (SPLITK) k_left = K - (int)koff;
         if constexpr (AKM) {
             a_base = A + (int64_t)tm * BM + koff * lda;
             const uint32_t cmax = (uint32_t)(M - 16 - tm * BM);
@@ -310,31 +290,56 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
             }
         }
     };
+    // A contraction that ends inside a K step (or before it: the number of steps is even): the lanes
+    // whose 16 bytes of step kt lie past the end are sent to kPastEnd and load zeros, of both
+    // operands, so that nothing next to the operands in memory can reach a product.  What is cut for
+    // one step is cut for the next one too, so the offsets are changed in place; the next tile's
+    // load_context restores them.
+    auto cut_loads = [&](int kt) {
+        if constexpr (!RAGGED) return;
+        const int valid = k_left - kt * kBK;  // of this step's 128 k; may be negative
+        if (valid >= kBK) return;             // uniform
+#pragma unroll
+        for (int idx = 0; idx < A_LOADS; ++idx) {
+            const int k = AKM ? wave * (kBK / NW) + idx * (1024 / BM) + a_kr : (int)((idx & 1) ? a_c1 : a_c0);
+            if (k >= valid) a_off[idx] = kPastEnd;
+        }
+#pragma unroll
+        for (int j = 0; j < B_LOADS; ++j) {
+            const int k = BKM ? wave * (kBK / NW) + j * (1024 / BN) + b_kr : (int)((j & 1) ? b_c1 : b_c0);
+            if (k >= valid) b_off[j] = kPastEnd;
+        }
+    };
     // Load number `idx` (0 .. LOADS-1: first the A pieces, then the B pieces) of the K step whose
     // base addresses are ga / gb, into stage S.  Written as asm: 32-bit lane offset next to a
-    // scalar base, LDS target in M0.  The compiler therefore does not see these as LDS writes;
+    // scalar base (or buffer descriptor), LDS target in M0.  The compiler therefore does not see these as LDS writes;
     // ordering against the LDS reads is by the barriers and explicit waits of kstep.
-    auto issue_one = [&](const uint8_t* ga, const uint8_t* gb, auto S, auto IDX) {
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    // what a load takes its base from: the address, or a raw buffer of kRecords bytes at it
+    auto source_at = [](const uint8_t* p) {
+        if constexpr (RAGGED) return v4u{(uint32_t)(uint64_t)p, (uint32_t)((uint64_t)p >> 32), kRecords, 0x00020000u};
+        else return p;
+    };
+    auto issue_one = [&](auto ga, auto gb, auto S, auto IDX) {
         constexpr int idx = decltype(IDX)::value;
-        if constexpr (idx < A_LOADS) {
-            uint8_t* lp = stage_ptr(S) + wave * (BM / NW) * kBK + idx * 1024;
-            const uint32_t l32 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lp;
-            const uint32_t o = a_off[idx];
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(l32), "v"(o), "s"(ga) : "memory");
-        } else {
-            constexpr int j = idx - A_LOADS;
-            uint8_t* lp = stage_ptr(S) + A_BYTES + wave * (BN / NW) * kBK + j * 1024;
-            const uint32_t l32 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lp;
-            const uint32_t o = b_off[j];
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(l32), "v"(o), "s"(gb) : "memory");
-        }
+        constexpr bool is_a = idx < A_LOADS;
+        constexpr int j = is_a ? idx : idx - A_LOADS;
+        uint8_t* lp = stage_ptr(S) + (is_a ? 0 : A_BYTES) + wave * ((is_a ? BM : BN) / NW) * kBK + j * 1024;
+        const uint32_t l32 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lp;
+        const auto src = is_a ? ga : gb;
+        uint32_t o;
+        if constexpr (is_a) o = a_off[j];
+        else o = b_off[j];
+        if constexpr (RAGGED)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(l32), "v"(o), "s"(src) : "memory");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(l32), "v"(o), "s"(src) : "memory");
     };
     // base addresses of K step kt of the stream's current tile
     auto step_base_a = [&](int kt) { return AKM ? a_base + (int64_t)kt * kBK * lda : a_base + (int64_t)kt * kBK; };
     auto step_base_b = [&](int kt) { return BKM ? b_base + (int64_t)kt * kBK * ldb : b_base + (int64_t)kt * kBK; };
     auto issue_all = [&](int kt, auto S) {
-        const uint8_t* ga = step_base_a(kt);
-        const uint8_t* gb = step_base_b(kt);
+        const auto ga = source_at(step_base_a(kt)), gb = source_at(step_base_b(kt));
         static_for<A_LOADS + B_LOADS>([&](auto L) { issue_one(ga, gb, S, L); });
     };
     // Move the load stream to this workgroup's next tile.  Past the last tile the stream
@@ -556,7 +561,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
 
     // ---- prologue: two stages in flight, the first K step's starting fragments into registers
     load_context(ld_tile);  // the grid never exceeds the tile count
+    cut_loads(0);
     issue_all(0, I0{});
+    cut_loads(1);
     issue_all(1, I1{});
     zero_acc();
     __builtin_amdgcn_s_waitcnt(kWaitAllVmLgkm);
@@ -605,8 +612,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     auto kstep = [&](auto S, int fetch_kt) {
         constexpr int s = decltype(S)::value;
         using OTHER = integral_constant<int, 1 - s>;
-        const uint8_t* ga = step_base_a(fetch_kt);
-        const uint8_t* gb = step_base_b(fetch_kt);
+        const auto ga = source_at(step_base_a(fetch_kt)), gb = source_at(step_base_b(fetch_kt));
         static_for<SLOTS>([&](auto SLOT) {
             constexpr int slot = decltype(SLOT)::value;
             if constexpr (slot == SYNC_A) {
@@ -657,7 +663,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
         for (int kt = 0; kt < KT; kt += 2) {
             if (kt == KT - 2) next_load_tile();  // the last two steps fetch the next tile's first two
             const int f = kt == KT - 2 ? 0 : kt + 2;
+            cut_loads(f);
             kstep(I0{}, f);
+            cut_loads(f + 1);
             kstep(I1{}, f + 1);
         }
         mfma_drain();
@@ -671,106 +679,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     }
     // no load may still be writing LDS when the workgroup ends
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    if constexpr (AMAX) {
+    if (AMAX && amax_bits) {  // (the ragged instances come with AMAX only: a null amax_bits is theirs)
         __syncthreads();  // every wave is past its last epilogue pass: the staging buffer is free
         amax_publish<NW>(amax_acc, amax_bits, reinterpret_cast<uint32_t*>(epb));
-    }
-}
-
-// ---------------------------------------------------------------------------
-// generic kernel: 64x64 tile, 4 waves of 32x32, K step 64, 16x16x32 MFMA
-// ---------------------------------------------------------------------------
-template <int FOP_A, int FOP_B>  // formats of the MFMA's first / second operand
-__device__ inline v4f mfma32(long a, long b, v4f c)
-{
-    if constexpr (FOP_A == F8_E4M3 && FOP_B == F8_E4M3) return __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a, b, c, 0, 0, 0);
-    else if constexpr (FOP_A == F8_E4M3 && FOP_B == F8_E5M2) return __builtin_amdgcn_mfma_f32_16x16x32_fp8_bf8(a, b, c, 0, 0, 0);
-    else if constexpr (FOP_A == F8_E5M2 && FOP_B == F8_E4M3) return __builtin_amdgcn_mfma_f32_16x16x32_bf8_fp8(a, b, c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_16x16x32_bf8_bf8(a, b, c, 0, 0, 0);
-}
-
-constexpr int kGT = 64;        // generic tile (rows and K bytes)
-constexpr int kGStride = 80;   // LDS row stride in bytes (64 + 16 pad, keeps 16-byte alignment)
-
-// Fill a 64 x 64 (rows x K) LDS tile from an operand stored either [rows, K] (KCONTIG) or [K, rows].
-template <bool KCONTIG>
-__device__ inline void generic_load(uint8_t* __restrict__ tile, const uint8_t* __restrict__ P, int64_t ld,
-                                    int row0, int nrows, int k0, int K)
-{
-    const int t = threadIdx.x;
-    if constexpr (KCONTIG) {
-        const int r = t >> 2, c = (t & 3) * 16;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (row0 + r < nrows && k0 + c < K)  // K is a multiple of 16: whole chunk in or out
-            v = *reinterpret_cast<const uint4*>(P + (int64_t)(row0 + r) * ld + k0 + c);
-        *reinterpret_cast<uint4*>(tile + r * kGStride + c) = v;
-    } else {
-        const int k = t >> 2, c = (t & 3) * 16;  // 16 consecutive rows of the tile at one k
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (k0 + k < K && row0 + c < nrows)
-            v = *reinterpret_cast<const uint4*>(P + (int64_t)(k0 + k) * ld + row0 + c);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) tile[(c + i) * kGStride + k] = (uint8_t)(w[i >> 2] >> (8 * (i & 3)));
-    }
-}
-
-template <int LAYOUT, int FA, int FB, int GRAN>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(
-    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ D, int M,
-    int N, int K, int64_t lda, int64_t ldb, int64_t ldd, const float* __restrict__ isa,
-    const float* __restrict__ isb, uint32_t* __restrict__ amax_bits)
-{
-    __shared__ __attribute__((aligned(16))) uint8_t As[kGT * kGStride];
-    __shared__ __attribute__((aligned(16))) uint8_t Bs[kGT * kGStride];
-    // one-dimensional grid (the y dimension of a grid stops at 65535 blocks): tile = m-tile * tiles_n + n-tile
-    const int tiles_n = (N + kGT - 1) / kGT;
-    const int m0 = (int)(blockIdx.x / (unsigned)tiles_n) * kGT, n0 = (int)(blockIdx.x % (unsigned)tiles_n) * kGT;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int fr = lane & 15, fg = lane >> 4;
-
-    v4f acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    for (int k0 = 0; k0 < K; k0 += kGT) {
-        __syncthreads();
-        generic_load<LAYOUT != F8_TN>(As, A, lda, m0, M, k0, K);
-        generic_load<LAYOUT == F8_NT>(Bs, B, ldb, n0, N, k0, K);
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < kGT; ks += 32) {
-            long af[2], bf[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                af[i] = *reinterpret_cast<const long*>(As + (wm * 32 + 16 * i + fr) * kGStride + ks + 8 * fg);
-                bf[i] = *reinterpret_cast<const long*>(Bs + (wn * 32 + 16 * i + fr) * kGStride + ks + 8 * fg);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma32<FB, FA>(bf[j], af[i], acc[i][j]);
-        }
-    }
-    float s_tensor = 0.f;
-    if constexpr (GRAN == F8_TENSORWISE) s_tensor = isa[0] * isb[0];
-    uint32_t amax_acc = 0;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int m = m0 + wm * 32 + 16 * i + fr;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wn * 32 + 16 * j + 4 * fg;
-            if (n < N) amax_acc = amax_pair(amax_acc, store4<GRAN>(D, ldd, m, n, acc[i][j], s_tensor, isa, isb));
-        }
-    }
-    if (amax_bits) {  // uniform branch; every thread of the block takes part
-        __syncthreads();
-        amax_publish<4>(amax_acc, amax_bits, reinterpret_cast<uint32_t*>(As));
     }
 }
 
@@ -820,7 +731,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 // host side
 // ---------------------------------------------------------------------------
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, int GRAN, bool AKM, bool BKM>
+// K steps of `ranges` equal parts of a contraction of length K: whole pairs of LDS stages, at least one
+static int ksteps_of(int K, int ranges)
+{
+    const int pairs = (K + 2 * kBK - 1) / (2 * kBK), per = (pairs + ranges - 1) / ranges;
+    return 2 * (per > 0 ? per : 1);
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, int GRAN, bool AKM, bool BKM, bool RAGGED>
 static void launch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                         const float* isa, const float* isb, uint16_t* D, int64_t ldd, uint32_t* amax_bits,
                         int max_blocks, hipStream_t st)
@@ -828,12 +746,12 @@ static void launch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, cons
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int total = tiles_m * tiles_n;
     const int grid = total < max_blocks ? total : max_blocks;
-    if (amax_bits)
-        gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, true, AKM, BKM><<<grid, WAVES_M * WAVES_N * 64, 0, st>>>(
-            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, amax_bits);
-    else
-        gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, false, AKM, BKM><<<grid, WAVES_M * WAVES_N * 64, 0, st>>>(
-            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, nullptr);
+    if (amax_bits || RAGGED)
+        gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, true, AKM, BKM, false, RAGGED><<<grid, WAVES_M * WAVES_N * 64, 0, st>>>(
+            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, amax_bits, ksteps_of(K, 1));
+    else if constexpr (!RAGGED)
+        gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, false, AKM, BKM, false, RAGGED><<<grid, WAVES_M * WAVES_N * 64, 0, st>>>(
+            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, nullptr, ksteps_of(K, 1));
 }
 
 static int cu_count()
@@ -850,6 +768,7 @@ static int cu_count()
 // must fit the workspace.  Chosen by estimated time, in units of one whole-K 256x256 tile:
 // 1 / ranges + 0.04 for the fp32 epilogue + the reduction pass (a launch, ranges + 1/2 passes
 // over an M x N fp32 matrix at about 5 TB/s) against the best unsplit configuration.
+// (the ranges need not divide the contraction: the last one may be shorter, but not empty).
 static int splitk_ranges(int M, int N, int K, int cus, double best_unsplit, size_t ws_bytes)
 {
     const int64_t T = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
@@ -858,7 +777,8 @@ static int splitk_ranges(int M, int N, int K, int cus, double best_unsplit, size
     int best = 1;
     double best_cost = best_unsplit;
     for (int s = 2; s <= 8; s *= 2) {
-        if (s * T > cus || K % (s * 2 * kBK) || K / s < 1024) break;
+        if (s * T > cus || K / s < 1024) break;
+        if ((int64_t)(s - 1) * ksteps_of(K, s) * kBK >= K) break;
         if ((size_t)s * (size_t)M * (size_t)N * sizeof(float) > ws_bytes) break;
         const double reduce_us = 3.0 + (s + 0.5) * (double)M * (double)N * 4.0 / 5.0e6;
         const double cost = 1.0 / s + 0.04 + reduce_us / tile_us;
@@ -867,7 +787,7 @@ static int splitk_ranges(int M, int N, int K, int cus, double best_unsplit, size
     return best;
 }
 
-template <int FA, int FB, int GRAN, bool AKM, bool BKM>
+template <int FA, int FB, int GRAN, bool AKM, bool BKM, bool RAGGED>
 static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                           const float* isa, const float* isb, uint16_t* D, int64_t ldd, uint32_t* amax_bits,
                           void* ws, size_t ws_bytes, hipStream_t st)
@@ -897,15 +817,18 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
         const int ranges = splitk_ranges(M, N, K, cus, best, ws_bytes);
         if (ranges > 1) {
             float* partial = static_cast<float*>(ws);
-            gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true><<<(unsigned)(T * ranges), 256, 0, st>>>(
-                A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tm, tn, nullptr, ranges, partial, (int64_t)N);
+            const bool whole_ranges = !RAGGED && K % (ranges * 2 * kBK) == 0;
+            const auto kernel = whole_ranges ? gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, false>
+                                             : gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, true>;
+            kernel<<<(unsigned)(T * ranges), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tm, tn, nullptr,
+                                                           ksteps_of(K, ranges), ranges, partial, (int64_t)N);
             const int64_t threads = (int64_t)M * (N / 8);
             splitk_reduce_kernel<GRAN><<<(unsigned)((threads + 255) / 256), 256, 0, st>>>(partial, ranges, M, N, (int64_t)N,
                                                                                          isa, isb, D, ldd);
             return;
         }
     }
-#define F8_TILE(BM_, BN_) launch_tile<BM_, BN_, 2, 2, FA, FB, GRAN, AKM, BKM>
+#define F8_TILE(BM_, BN_) launch_tile<BM_, BN_, 2, 2, FA, FB, GRAN, AKM, BKM, RAGGED>
     if (c_full <= c_half && c_full <= c_quarter) {
         if (split_rows) {
             const int m1 = (int)(whole / tn) * 256;
@@ -931,28 +854,16 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
 #undef F8_TILE
 }
 
-template <int LAYOUT, int FA, int FB, int GRAN>
-static void launch_generic(int M, int N, int K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
-                           const float* isa, const float* isb, uint16_t* D, int64_t ldd, uint32_t* amax_bits,
-                           hipStream_t st)
-{
-    const unsigned grid = (unsigned)((int64_t)((N + kGT - 1) / kGT) * ((M + kGT - 1) / kGT));
-    gemm_generic_kernel<LAYOUT, FA, FB, GRAN><<<grid, 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb,
-                                                                    amax_bits);
-}
-
-// One layout of one operand-format pair: the fast kernel when the contraction length allows it
-// (it alternates two LDS stages of 128 per tile), else the generic one.
+// One layout of one operand-format pair.  A tile alternates two LDS stages of 128: a contraction that
+// is not a multiple of 256 (zero included) takes the ragged instances.
 template <int LAYOUT, int FA, int FB, int GRAN>
 static void dispatch_layout(int M, int N, int K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                             const float* isa, const float* isb, uint16_t* D, int64_t ldd, uint32_t* amax_bits,
                             void* ws, size_t ws_bytes, hipStream_t st)
 {
-    if (K % (2 * kBK) == 0 && K > 0)
-        dispatch_tile<FA, FB, GRAN, LAYOUT == F8_TN, LAYOUT != F8_NT>(M, N, K, A, lda, B, ldb, isa, isb, D, ldd,
-                                                                       amax_bits, ws, ws_bytes, st);
-    else
-        launch_generic<LAYOUT, FA, FB, GRAN>(M, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, st);
+    const auto dispatch = K % (2 * kBK) == 0 && K > 0 ? dispatch_tile<FA, FB, GRAN, LAYOUT == F8_TN, LAYOUT != F8_NT, false>
+                                                      : dispatch_tile<FA, FB, GRAN, LAYOUT == F8_TN, LAYOUT != F8_NT, true>;
+    dispatch(M, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, ws, ws_bytes, st);
 }
 
 // All launches of one operand-format pair and layout: the granularity is a run-time choice.

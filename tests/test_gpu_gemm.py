@@ -333,3 +333,35 @@ def test_gemm_is_deterministic(M, N, K, layout):
     torch.cuda.synchronize()
     for D in outs[1:]:
         assert torch.equal(D.view(torch.int16), outs[0].view(torch.int16))
+
+
+# Contraction lengths around the K step (128) and the pair of LDS stages (256), and shapes that take the 128x128,
+# 256x128 and 256x256 tiles, the two-launch dispatch and the split contraction (with a workspace).
+RAGGED = [(272, 400, k, False) for k in (16, 112, 128, 144, 240, 272, 400, 528)] + [
+    (4112, 4144, 304, False), (8192, 1040, 1040, False), (4368, 4112, 272, False),
+    (512, 1024, 4112, True), (272, 400, 2080, True), (2048, 4096, 8208, True)]
+
+
+@pytest.mark.parametrize("layout", [o.NT, o.NN, o.TN])
+@pytest.mark.parametrize("M,N,K,split", RAGGED)
+def test_gemm_ragged_contraction_exact_arithmetic(layout, M, N, K, split):
+    """A contraction that is no multiple of 256 ends inside an LDS stage.  The operands lie in larger buffers whose
+    other bytes are NaN codes: whatever the kernel read past the end would show.  Exact-arithmetic grid: bit for bit
+    the fp64 product."""
+    rng = np.random.default_rng(K + layout + M)
+    vals = np.array([0, 64, -64, 128, -128, 256, -256, 448, -448], np.float32)
+    grid = o.encode(vals, o.E4M3)
+    sa, sb = shapes_of(layout, M, N, K)
+    host, dev = [], []
+    for rows, cols in (sa, sb):
+        buf = np.full((rows + 160, cols + 48), 0x7F, np.uint8)
+        buf[:rows, :cols] = grid[rng.integers(0, 9, (rows, cols))]
+        host.append(o.decode(buf[:rows, :cols], o.E4M3).astype(np.float64))
+        dev.append(torch.from_numpy(buf).cuda()[:rows, :cols])
+    inv = torch.full((1,), 2.0 ** -7, device="cuda")
+    D = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    f8.gemm(layout, M, N, K, dev[0], o.E4M3, dev[1], o.E4M3, inv, inv, f8.TENSORWISE, D,
+            workspace=f8.new_workspace(M, N) if split else None)
+    a, b = (torch.from_numpy(h) for h in host)
+    exact = {o.NT: lambda: a @ b.T, o.NN: lambda: a @ b, o.TN: lambda: a.T @ b}[layout]() * 2.0 ** -14
+    assert np.array_equal(bits(D), exact.to(torch.bfloat16).view(torch.uint16).numpy())
