@@ -11,6 +11,11 @@
 // only has to present the same keys in the same slots: it is read from a copy that is contiguous
 // along tokens (V^T here; Q^T, K^T, dO^T in the backward), which the producers write on the way
 // (f8_rope's transposed output, f8_transpose_bf16).  No operand is transposed in registers.
+// Which token a row of the first operand is, is free: lane ln feeds token row_token(ln) of a
+// 32-token block, chosen so that registers 8u .. 8u + 7 hold EIGHT CONSECUTIVE tokens, 16u + 8g ..
+// + 7, and the matching operand of the next product is one 16-byte LDS read.  (In lane order they
+// are two runs of four, two 8-byte reads, which cost 1.5 times the LDS time and twice the
+// instructions; 1.5 % of the attention of 1 x 8192 tokens.)
 #include <atomic>
 
 #include "f8_device.hpp"
@@ -27,8 +32,8 @@ constexpr int kBk = 64;    // keys per step
 // operand reads ahead of their product (deeper did not help)
 constexpr int kFwdAhead = 4, kDqAhead = 4, kDkvAhead = 4;
 constexpr int kKp = kHd + 8;   // LDS row pitch (bf16) of a [tokens][hd] tile: 272 bytes
-constexpr int kTp = kBk + 4;   // LDS row pitch (bf16) of a [hd][tokens] tile: 136 bytes = 34 words, an odd multiple of 2:
-                               // the 8-byte reads of 32 consecutive rows fall into 32 different bank pairs
+constexpr int kTp = kBk + 8;   // LDS row pitch (bf16) of a [hd][tokens] tile: 144 bytes = 36 words, an odd multiple of 4:
+                               // the 16-byte reads of 16 consecutive rows fall into 16 different bank quadruples
 
 template <bool B>
 struct BoolC {
@@ -56,13 +61,16 @@ __device__ inline uint4 slots(const f32x16& c, int u)
                       pack2(c[8 * u + 6], c[8 * u + 7]));
 }
 
+// the token of a 32-token block that lane ln (0 .. 31) feeds as a row of the first operand: ln with
+// bits 2 and 3 exchanged; register r of lane group g then holds token reg_token(r, g) of the block
+__device__ inline int row_token(int ln) { return (ln & 0x13) | ((ln & 4) << 1) | ((ln & 8) >> 1); }
+__device__ inline int reg_token(int r, int g) { return 16 * (r >> 3) + 8 * g + (r & 7); }
+
 // the operand that matches slots(c, u) of a 32-token block starting at column t0 of a
-// [rows][tokens] LDS tile: tokens t0 + 16u + 4g + {0..3} and t0 + 16u + 8 + 4g + {0..3}
+// [rows][tokens] LDS tile: tokens t0 + 16u + 8g + {0..7}
 __device__ inline uint4 token_slots(const uint16_t* tile_row, int t0, int u, int g)
 {
-    const uint2 a = *reinterpret_cast<const uint2*>(tile_row + t0 + 16 * u + 4 * g);
-    const uint2 b = *reinterpret_cast<const uint2*>(tile_row + t0 + 16 * u + 8 + 4 * g);
-    return make_uint4(a.x, a.y, b.x, b.y);
+    return *reinterpret_cast<const uint4*>(tile_row + t0 + 16 * u + 8 * g);
 }
 
 // N products use(i, frag(i)) whose LDS operand reads (one DS instruction each) run AHEAD products
@@ -114,7 +122,7 @@ template <int COLS, int NT = kAttnThreads>
 struct ColTile {
     static constexpr int N = kHd * (COLS / 8) / NT;
     static_assert(N >= 1 && N * NT == kHd * (COLS / 8), "the tile's chunks divide evenly over the threads");
-    static constexpr int P = COLS + 4;  // rows are 8-byte aligned only: stored as two 8-byte halves
+    static constexpr int P = COLS + 8;
     uint4 v[N];
     __device__ void load(const uint16_t* base, int64_t ld, int col0, int limit)
     {
@@ -129,8 +137,7 @@ struct ColTile {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int c = threadIdx.x + NT * i, r = c / (COLS / 8), cc = c % (COLS / 8);
-            *reinterpret_cast<uint2*>(lds + r * P + cc * 8) = make_uint2(v[i].x, v[i].y);
-            *reinterpret_cast<uint2*>(lds + r * P + cc * 8 + 4) = make_uint2(v[i].z, v[i].w);
+            *reinterpret_cast<uint4*>(lds + r * P + cc * 8) = v[i];
         }
     }
 };
@@ -154,7 +161,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     // long (late) query tiles first, over all heads: the tile index varies slowest
     const int nbh = Hq * (int)(M / S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
     const int bh = blockIdx.x % nbh, h = bh % Hq, b = bh / Hq, kvh = h / group;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5, rt = row_token(ln);
     const int q_first = qt * QB + wave * 32;  // of this wave
     const int q_pos = q_first + ln;            // position of this lane's query in its sequence
     const int64_t tok0 = (int64_t)b * S;
@@ -196,7 +203,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         // S^T = K Q^T: [64 keys][32 queries] as two 32x32 results
         f32x16 sc[2] = {f32x16{0}, f32x16{0}};
         pipelined_products<2 * (kHd / 16), kFwdAhead>(
-            [&](int i) { return *reinterpret_cast<const uint4*>(&sK[buf][(32 * (i / 8) + ln) * kKp + 16 * (i % 8) + 8 * g]); },
+            [&](int i) { return *reinterpret_cast<const uint4*>(&sK[buf][(32 * (i / 8) + rt) * kKp + 16 * (i % 8) + 8 * g]); },
             [&](int i, uint4 kf) { sc[i / 8] = mma(kf, qf[i % 8], sc[i / 8]); });
         // The maximum is taken over the raw scores (the scale is positive), so the scaling and the
         // subtraction of the maximum are one fused multiply-add per score.
@@ -207,7 +214,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int key = key0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
+                    const int key = key0 + 32 * kb + reg_token(r, g);
                     if (key > q_pos) sc[kb][r] = -INFINITY;
                 }
         }
@@ -293,7 +300,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
 
     const int nbh = Hq * (int)(M / S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
     const int bh = blockIdx.x % nbh, h = bh % Hq, b = bh / Hq, kvh = h / group;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5, rt = row_token(ln);
     const int q_first = qt * QB + wave * 32, q_pos = q_first + ln;
     const int64_t tok0 = (int64_t)b * S;
     const uint16_t* Kb = K + tok0 * ldk + (int64_t)kvh * kHd;
@@ -355,7 +362,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
         auto block32 = [&](int kb, auto masked) {  // masked: BoolC, two versions of the code
             f32x16 sc = f32x16{0}, dp = f32x16{0};
             pipelined_products<2 * (kHd / 16), kDqAhead>(  // even: a K operand for S^T, odd: a V operand for dP^T
-                [&](int i) { return *reinterpret_cast<const uint4*>(((i & 1) ? tV : tK) + (32 * kb + ln) * kKp + 16 * (i / 2) + 8 * g); },
+                [&](int i) { return *reinterpret_cast<const uint4*>(((i & 1) ? tV : tK) + (32 * kb + rt) * kKp + 16 * (i / 2) + 8 * g); },
                 [&](int i, uint4 f) {
                     if (i & 1) dp = mma(f, dof[i / 2], dp);
                     else sc = mma(f, qf[i / 2], sc);
@@ -364,7 +371,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
             for (int r = 0; r < 16; ++r) {
                 float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - lse2);
                 if constexpr (decltype(masked)::value) {
-                    const int key = key0 + 32 * kb + 8 * (r >> 2) + 4 * g + (r & 3);
+                    const int key = key0 + 32 * kb + reg_token(r, g);
                     if (key > q_pos) p = 0.0f;
                 }
                 sc[r] = p * (dp[r] - dl);
@@ -419,7 +426,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     // early key tiles see the most queries: they are the slowest-varying index, so they start first
     const int bh = blockIdx.x % (Hq * (int)(M / S)), kt = blockIdx.x / (Hq * (int)(M / S));
     const int hq = bh % Hq, b = bh / Hq, kvh = hq / group, gi = hq % group;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5, rt = row_token(ln);
     const int key_first = kt * KB + wave * 32, key_pos = key_first + ln;
     const int64_t tok0 = (int64_t)b * S;
     const bool k_ok = key_pos < S;
@@ -480,26 +487,26 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
         __syncthreads();
         if (it + 1 < steps) load_step(q0 - QS);
         if (q0 + QS - 1 < key_first) continue;  // every query of the step lies before every key of the wave
-        // one 32-query block at a time; registers: queries 32 qb + 8 j + 4 g + i of the step; lane: one key
+        // one 32-query block at a time; registers: queries 32 qb + reg_token(r, g) of the step; lane: one key
         // only the steps at the diagonal or at the end of the sequence have anything to mask (wave-uniform)
         const bool edge = q0 < key_first + 32 || q0 + QS > S;
         auto block32 = [&](int qb, auto masked) {  // masked: integral_constant<bool>, two versions of the code
             f32x16 sc = f32x16{0}, dp = f32x16{0};
             if constexpr (DK) {
                 pipelined_products<2 * (kHd / 16), kDkvAhead>(  // even: a Q operand for S, odd: a dO operand for dP
-                    [&](int i) { return *reinterpret_cast<const uint4*>(((i & 1) ? sD : sQ) + (32 * qb + ln) * kKp + 16 * (i / 2) + 8 * g); },
+                    [&](int i) { return *reinterpret_cast<const uint4*>(((i & 1) ? sD : sQ) + (32 * qb + rt) * kKp + 16 * (i / 2) + 8 * g); },
                     [&](int i, uint4 f) {
                         if (i & 1) dp = mma(f, vf[i / 2], dp);
                         else sc = mma(f, kf[i / 2], sc);
                     });
             } else {
                 pipelined_products<kHd / 16, kDkvAhead>(
-                    [&](int i) { return *reinterpret_cast<const uint4*>(sQ + (32 * qb + ln) * kKp + 16 * i + 8 * g); },
+                    [&](int i) { return *reinterpret_cast<const uint4*>(sQ + (32 * qb + rt) * kKp + 16 * i + 8 * g); },
                     [&](int i, uint4 f) { sc = mma(f, kf[i], sc); });
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int ql = 32 * qb + 8 * j + 4 * g;
+                const int ql = 32 * qb + reg_token(4 * j, g);
                 const float4 l4 = *reinterpret_cast<const float4*>(sLse + ql);
                 const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
                 float dv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
