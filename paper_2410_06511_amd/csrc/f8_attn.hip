@@ -17,6 +17,7 @@
 // are two runs of four, two 8-byte reads, which cost 1.5 times the LDS time and twice the
 // instructions; 1.5 % of the attention of 1 x 8192 tokens.)
 #include <atomic>
+#include <type_traits>
 
 #include "f8_device.hpp"
 #include "f8_host.hpp"
@@ -142,11 +143,99 @@ struct ColTile {
     }
 };
 
+// ---- staging for the staggered kernels ----------------------------------------------------
+// Tiles come straight from memory into LDS (one instruction of a wave: 64 lanes x 16 bytes into 1 KB of
+// consecutive LDS), with no registers in between.  Rows are not padded then; instead the 16-byte chunks
+// of a row are permuted so that the rows a read touches together fall into different banks.
+static __device__ __attribute__((aligned(16))) const uint32_t kZeros[4] = {0, 0, 0, 0};  // what lanes past the end load
+
+// Written as asm, so the compiler does not count these loads: stream_wait before the barrier that
+// publishes the tile.  The second form (uniform base, 32-bit lane offset in bytes) issues faster.
+__device__ inline uint32_t lds_address(uint16_t* lds) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)lds; }
+__device__ inline void load_to_lds(uint16_t* lds, const uint16_t* src)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_address(lds)), "v"(src) : "memory");
+}
+__device__ inline void load_to_lds(uint16_t* lds, const uint16_t* base, uint32_t offset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_address(lds)), "v"(offset), "s"(base) : "memory");
+}
+__device__ inline void stream_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// A barrier between two phases: this wave's LDS reads are done, and nothing moves across it.  Unlike
+// __syncthreads it leaves loads in flight.
+__device__ inline void phase_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+// Values that are complete here: arithmetic without memory operations is not held by a barrier, and the
+// compiler otherwise moves a phase's vector work past it, to the products that use the result.
+__device__ inline void computed(float& v) { asm volatile("" : "+v"(v)); }
+__device__ inline void computed(uint4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+
+// Successive tiles of a tensor, PITCH elements per tile row.  A wave's share is N pieces of 1 KB; lane i of a
+// piece fills physical chunk i % CPR of row i / CPR.  FAR: rows of the tensor so far apart that a lane's
+// offset within a tile does not fit 32 bits.
+template <int ROWS, int PITCH, int NW, bool FAR>
+struct TileStream {
+    static constexpr int CPR = PITCH / 8, RPP = 64 / CPR;  // 16-byte chunks per row, rows per piece
+    static constexpr int N = ROWS / RPP / NW;
+    static_assert(N >= 1 && N * RPP * NW == ROWS, "the pieces divide evenly over the waves");
+    const uint16_t* tile;  // first element of the next tile
+    std::conditional_t<FAR, uint64_t, uint32_t> offset[N];  // of this lane's 16 bytes in it, in bytes
+    int row0, chunk[N];
+    // (row, logical chunk) <-> physical chunk: an involution for a given row
+    static __device__ int swizzle(int row, int c) { return PITCH == kHd ? c ^ (row & 15) : c ^ ((row >> 1) & (CPR - 1)); }
+    __device__ void start(const uint16_t* first, int64_t ld, int wave, int lane)
+    {
+        tile = first;
+        row0 = wave * N * RPP + lane / CPR;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int row = row0 + i * RPP;
+            chunk[i] = swizzle(row, lane % CPR);
+            offset[i] = (std::conditional_t<FAR, uint64_t, uint32_t>)(2 * ((int64_t)row * ld + 8 * chunk[i]));
+        }
+    }
+    // Requests the next tile, and moves on by `along` elements.  EDGE: its tokens start at token0, those at or
+    // beyond limit read as zero (TOKEN_ROWS: a row is a token; otherwise a column is).
+    template <bool EDGE, bool TOKEN_ROWS>
+    __device__ void request(uint16_t* lds, int wave, int64_t along, int token0, int limit)
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            uint16_t* dst = lds + (wave * N + i) * 512;
+            if constexpr (EDGE || FAR) {
+                const uint16_t* p = tile + offset[i] / 2;
+                if (EDGE && token0 + (TOKEN_ROWS ? row0 + i * RPP : 8 * chunk[i]) >= limit) p = reinterpret_cast<const uint16_t*>(kZeros);
+                load_to_lds(dst, p);
+            } else {
+                load_to_lds(dst, tile, offset[i]);
+            }
+        }
+        tile += along;
+    }
+};
+// whether a tile of `rows` rows of pitch ld needs FAR
+static bool far_rows(int64_t rows, int64_t ld) { return 2 * (rows * ld + kHd) >= ((int64_t)1 << 32); }
+
 // ---- forward ------------------------------------------------------------------------------
-// One block: NW waves of 32 queries each of one (sequence, head).  Loop over 64-key
-// steps up to the diagonal; K and V^T tiles double-buffered in LDS, the next step's tiles
-// prefetched into registers while this step computes.
-template <int NW>
+// One block: 8 waves of 32 queries each of one (sequence, head), loop over 64-key steps up to the
+// diagonal.  Two waves share a SIMD, and they work in opposite phases: while waves 0 .. 3 feed the matrix
+// pipe (phase M: S^T of the next step and P V of this one, 32 products), waves 4 .. 7 do the vector
+// work of theirs (phase V: softmax of S^T, 32 exponentials per lane), then they change over.
+//   time slot:            2t        2t + 1    2t + 2
+//   waves 0 .. 3:         M_t       V_t       M_t+1         M_t: S_t+1 = K_t+1 Q, O += P_t V_t
+//   waves 4 .. 7:         V_t-1     M_t       V_t           V_t: P_t+1 = softmax(S_t+1)
+// with a barrier between slots; the second half enters one slot late.  M_t reads the tiles K_t+1 and V_t
+// in slots 2t and 2t + 1.  K_t+3 and V_t+2 are requested at the end of V_t into the third of three buffers
+// (what it held was read up to slot 2t - 1) and waited for at the end of the wave's next phase M.
+// Measured (1 x 8192 tokens, 32/8 heads; cycles of a slot, both phases in it): M 1300 (32 products are 1024), V
+// 1400 (softmax 1080, the four loads the rest: a wave's load holds up its next instruction until the memory
+// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 590 us; this: 490.
+template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(const uint16_t* __restrict__ Q, int64_t ldq,
                                                                 const uint16_t* __restrict__ K, int64_t ldk,
                                                                 const uint16_t* __restrict__ Vt, int64_t M, int S, int Hq,
@@ -154,14 +243,17 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
                                                                 int64_t ldo, float* __restrict__ lse, int nqt,
                                                                 uint32_t* __restrict__ amax_bits /* nullable */)
 {
-    constexpr int NT = 64 * NW, QB = 32 * NW;  // threads and queries per block
-    __shared__ __attribute__((aligned(16))) uint16_t sK[2][kBk * kKp];
-    __shared__ __attribute__((aligned(16))) uint16_t sV[2][kHd * kTp];
+    static_assert(NW == 8, "two waves per SIMD in opposite phases");
+    constexpr int QB = 32 * NW;  // queries per block
+    __shared__ __attribute__((aligned(1024))) uint16_t sK[3][kBk * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sV[3][kHd * kBk];
 
     // long (late) query tiles first, over all heads: the tile index varies slowest
     const int nbh = Hq * (int)(M / S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
     const int bh = blockIdx.x % nbh, h = bh % Hq, b = bh / Hq, kvh = h / group;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5, rt = row_token(ln);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5,
+              rt = row_token(ln);
+    const bool late = wave >= NW / 2;          // the half that runs one slot behind
     const int q_first = qt * QB + wave * 32;  // of this wave
     const int q_pos = q_first + ln;            // position of this lane's query in its sequence
     const int64_t tok0 = (int64_t)b * S;
@@ -179,37 +271,77 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     int key_end = (qt + 1) * QB;  // keys at or beyond it are masked for every query of the block
     if (key_end > S) key_end = S;
     const int nkt = (key_end + kBk - 1) / kBk;
+    const int t_last = min(nkt - 1, (q_first + 31) / kBk);  // the last step that this wave has any query for
 
     f32x16 acc_o[kHd / 32];
 #pragma unroll
     for (int d = 0; d < kHd / 32; ++d) acc_o[d] = f32x16{0};
     float m_run = -INFINITY, l_run = 0.0f;  // running maximum of the raw scores and this lane's share of the sum
+    f32x16 sc[2];                           // S^T of the next step: [64 keys][32 queries] as two 32x32 results
+    uint4 pf[4];                            // P^T of this step as operands, [2 kb + u]
 
-    RowTile<kBk, NT> kt_regs;
-    ColTile<kBk, NT> vt_regs;
-    kt_regs.load(Kb, ldk, 0, S);
-    vt_regs.load(Vb, M, 0, S);
-    for (int t = 0; t < nkt; ++t) {
-        const int buf = t & 1, key0 = t * kBk;
-        kt_regs.store(sK[buf]);
-        vt_regs.store(sV[buf]);
-        __syncthreads();
-        if (t + 1 < nkt) {
-            kt_regs.load(Kb, ldk, key0 + kBk, S);
-            vt_regs.load(Vb, M, key0 + kBk, S);
-        }
-        if (key0 > q_first + 31) continue;  // every key of the step lies after every query of the wave
+    using KStream = TileStream<kBk, kHd, NW, FAR>;
+    using VStream = TileStream<kHd, kBk, NW, FAR>;
+    KStream ks;
+    VStream vs;
+    ks.start(Kb, ldk, wave, lane);
+    vs.start(Vb, M, wave, lane);
+    // K_t and V_t live in buffer t % 3.  Requests V_t and K_t+1, buf = t % 3; EDGE: they may reach past S or
+    // past the last step
+    auto request = [&](auto EDGE, int t, int buf) {
+        constexpr bool edge = decltype(EDGE)::value;
+        if (!edge || t < nkt) vs.template request<edge, false>(sV[buf], wave, kBk, t * kBk, S);
+        if (!edge || t + 1 < nkt) ks.template request<edge, true>(sK[buf == 2 ? 0 : buf + 1], wave, kBk * ldk, (t + 1) * kBk, S);
+    };
+    ks.template request<true, true>(sK[0], wave, kBk * ldk, 0, S);
+    request(std::true_type{}, 0, 0);
 
-        // S^T = K Q^T: [64 keys][32 queries] as two 32x32 results
-        f32x16 sc[2] = {f32x16{0}, f32x16{0}};
-        pipelined_products<2 * (kHd / 16), kFwdAhead>(
-            [&](int i) { return *reinterpret_cast<const uint4*>(&sK[buf][(32 * (i / 8) + rt) * kKp + 16 * (i % 8) + 8 * g]); },
-            [&](int i, uint4 kf) { sc[i / 8] = mma(kf, qf[i % 8], sc[i / 8]); });
+    // LDS offsets of this lane's operand reads: chunk 2 s + g of key row rt, chunk 2 v + g of hd row ln
+    int k_rd[kHd / 16], v_rd[kBk / 16];
+#pragma unroll
+    for (int s = 0; s < kHd / 16; ++s) k_rd[s] = rt * kHd + 8 * KStream::swizzle(rt, 2 * s + g);
+#pragma unroll
+    for (int v = 0; v < kBk / 16; ++v) v_rd[v] = ln * kBk + 8 * VStream::swizzle(ln, 2 * v + g);
+
+    // products [LO, HI) of M_t: 0 .. 15 S^T = K Q^T (tile K_t+1), 16 .. 31 O^T += V^T P^T (tile V_t,
+    // [128 hd][32 queries], contraction over the 64 keys in four 16-slot steps).  The matrix phase goes
+    // before the other wave's vector work: its instructions are few, and the pipe idles without them.
+    auto products = [&](int buf /* of V_t */, auto LO, auto HI) {
+        constexpr int lo = decltype(LO)::value, hi = decltype(HI)::value;
+        const uint16_t *tK = sK[buf == 2 ? 0 : buf + 1], *tV = sV[buf];
+        if constexpr (lo == 0) sc[0] = f32x16{0}, sc[1] = f32x16{0};
+        __builtin_amdgcn_s_setprio(1);
+        pipelined_products<hi - lo, kFwdAhead>(
+            [&](int n) {
+                const int i = n + lo;
+                return *reinterpret_cast<const uint4*>(i < 16 ? tK + 32 * kHd * (i % 2) + k_rd[i / 2 % 8]
+                                                              : tV + 32 * kBk * (i % 4) + v_rd[i / 4 % 4]);
+            },
+            [&](int n, uint4 f) {
+                const int i = n + lo;
+                if (i < 16) sc[i % 2] = mma(f, qf[i / 2 % 8], sc[i % 2]);
+                else acc_o[i % 4] = mma(f, pf[(i - 16) / 4], acc_o[i % 4]);
+            });
+        __builtin_amdgcn_s_setprio(0);
+    };
+    using std::integral_constant;
+    using C0 = integral_constant<int, 0>;
+    using C16 = integral_constant<int, 16>;
+    using C32 = integral_constant<int, 32>;
+
+    // The running maximum of a query follows its scores only when one of the wave's queries has outgrown it by
+    // 2^kSlack: until then the probabilities are taken against the old one (they stay below 2^kSlack, sums and
+    // products keep their relative precision) and nothing has to be rescaled.  Following every new maximum
+    // rescaled the 64 accumulators in about half of the steps.
+    constexpr float kSlack = 8.0f;
+    const float slack = kSlack / scale_log2e;  // in raw scores
+    // of step t.  MASKED: the step at the diagonal, a wave's last one (32 queries from a multiple of 32 on, 64
+    // keys: it is the only one with anything to mask)
+    auto softmax = [&](int t, auto MASKED) {
+        const int key0 = t * kBk;
         // The maximum is taken over the raw scores (the scale is positive), so the scaling and the
         // subtraction of the maximum are one fused multiply-add per score.
-        const bool diagonal = key0 + kBk - 1 > q_first;
-        float mx = -INFINITY;
-        if (diagonal) {  // wave-uniform: only the steps at the diagonal have anything to mask
+        if constexpr (decltype(MASKED)::value) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -218,38 +350,72 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
                     if (key > q_pos) sc[kb][r] = -INFINITY;
                 }
         }
+        float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kb][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-        const float m_new = fmaxf(m_run, mx);  // finite: key 0 is visible to every query
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
-        m_run = m_new;
-        const float neg_m = -m_new * scale_log2e;
-        float psum = 0.0f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], scale_log2e, neg_m));
-                sc[kb][r] = p;
-                psum += p;
-            }
-        l_run = l_run * alpha + psum;
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {  // after the first few steps the maximum rarely moves
+        for (int r = 0; r < 16; ++r) mx[r % 4] = fmaxf(fmaxf(mx[r % 4], sc[0][r]), sc[1][r]);
+        const float m_here = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
+        const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_here), __float_as_uint(m_here), false, false);
+        const float m_new = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));  // of the query: the pair of lanes
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run + slack)) {  // always at step 0: key 0 is visible to every query
+            const float m_next = fmaxf(m_run, m_new);
+            const float alpha = __builtin_amdgcn_exp2f((m_run - m_next) * scale_log2e);
+            m_run = m_next;
+            l_run *= alpha;
 #pragma unroll
             for (int d = 0; d < kHd / 32; ++d)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc_o[d][r] *= alpha;
         }
+        const float neg_m = -m_run * scale_log2e;
+        float psum[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], scale_log2e, neg_m));
+                sc[kb][r] = p;
+                psum[r & 1] += p;
+            }
+            pf[2 * kb] = slots(sc[kb], 0), pf[2 * kb + 1] = slots(sc[kb], 1);
+        }
+        l_run += psum[0] + psum[1];
+        for (int i = 0; i < 4; ++i) computed(pf[i]);
+        computed(l_run);
+    };
 
-        // O^T += V^T P^T: [128 hd][32 queries], contraction over the 64 keys in four 16-slot steps
-        const uint4 pf[4] = {slots(sc[0], 0), slots(sc[0], 1), slots(sc[1], 0), slots(sc[1], 1)};  // [2 kb + u]
-        pipelined_products<16, kFwdAhead>(
-            [&](int i) { return token_slots(&sV[buf][(32 * (i % 4) + ln) * kTp], 32 * (i / 8), (i / 4) % 2, g); },
-            [&](int i, uint4 vf) { acc_o[i % 4] = mma(vf, pf[i / 4], acc_o[i % 4]); });
+    // Every wave runs the same number of slots, whatever it has left to do in them.
+    auto next = [](int buf) { return buf == 2 ? 0 : buf + 1; };
+    int buf = 2, t = -1;  // buf = t % 3
+    auto end_of_m = [&]() {
+        stream_wait();  // for what this wave requested in its last phase V
+        phase_barrier();
+    };
+    auto step = [&](auto EDGE) {
+        end_of_m();
+        softmax(t + 1, std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+        request(EDGE, t + 2, buf == 0 ? 2 : buf - 1);
+        phase_barrier();
+        buf = next(buf);
+        products(buf, C0{}, C32{});
+        ++t;
+    };
+    stream_wait();
+    phase_barrier();
+    if (late) phase_barrier();
+    products(buf, C0{}, C16{});
+    const int t_inside = min(t_last - 1, min(nkt, S / kBk) - 3);  // steps t before it request whole tiles only
+    while (t < t_inside) step(std::false_type{});
+    while (t < t_last - 1) step(std::true_type{});
+    for (; t < nkt; ++t) {
+        end_of_m();
+        if (t == t_last - 1) softmax(t_last, std::true_type{});
+        request(std::true_type{}, t + 2, buf == 0 ? 2 : buf - 1);
+        phase_barrier();
+        buf = next(buf);
+        if (t == t_last - 1) products(buf, C16{}, C32{});
     }
+    if (!late) phase_barrier();
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
     uint32_t mag = 0;  // packed pair of the largest 15-bit magnitudes written
@@ -635,7 +801,8 @@ f8_status f8_sdpa_fwd(const void* q_bf16, int64_t ldq, const void* k_bf16, int64
     const int64_t nqt = (S + 32 * kFwdWaves - 1) / (32 * kFwdWaves), nb = nqt * Hq * B;
     if (nb > (int64_t)0x7FFFFFFF) return F8_ERR_SHAPE;
     const float scale_log2e = (float)(1.4426950408889634074 / sqrt((double)hd));
-    sdpa_fwd_kernel<kFwdWaves><<<(unsigned)nb, 64 * kFwdWaves, 0, (hipStream_t)stream>>>(
+    const auto kernel = far_rows(kBk, ldk) || far_rows(kHd, B * S) ? sdpa_fwd_kernel<kFwdWaves, true> : sdpa_fwd_kernel<kFwdWaves, false>;
+    kernel<<<(unsigned)nb, 64 * kFwdWaves, 0, (hipStream_t)stream>>>(
         (const uint16_t*)q_bf16, ldq, (const uint16_t*)k_bf16, ldk, (const uint16_t*)vt_bf16, B * S, (int)S, (int)Hq,
         (int)(Hq / Hkv), scale_log2e, (uint16_t*)o_bf16, ldo, lse, (int)nqt, reinterpret_cast<uint32_t*>(amax_o));
     return last_launch_status();

@@ -209,3 +209,44 @@ def test_sdpa_argument_errors():
     with pytest.raises(f8.F8Error) as e:
         f8.sdpa_fwd(a.q, a.k, None, 1, 64, 2, 1, HD, a.o, a.lse)
     assert e.value.code == 1
+
+
+# Lengths around the sizes the kernels step by: 32 (a wave's tokens), 64 (tokens per step), 256 (tokens per block).
+@pytest.mark.parametrize("S", [24, 56, 72, 96, 136, 192, 248, 256, 264, 328, 520, 776])
+def test_sdpa_lengths_around_steps_and_blocks(S):
+    a = Attn(1, S, 2, 1, seed=S)
+    a.forward()
+    check_forward(a)
+    do_t = gen((S, 2 * HD), S + 1, 1e-2)
+    dqkv, delta = run_backward(a, do_t)
+    check_backward(a, do_t, dqkv, delta)
+
+
+@pytest.mark.parametrize("S", [72, 264])
+def test_sdpa_reads_nothing_of_the_next_sequence(S):
+    """Tiles reach past the end of a sequence; NaN in the sequence behind it must not show."""
+    Hq, Hkv = 2, 2
+    one, two = Attn(1, S, Hq, Hkv, seed=7), Attn(2, S, Hq, Hkv, seed=8)
+    poisoned = torch.cat((one.qkv, torch.full((S, (Hq + 2 * Hkv) * HD), float("nan"), dtype=torch.bfloat16)))
+    d = poisoned.cuda()
+    two.q, two.k, two.v = d[:, :Hq * HD], d[:, Hq * HD:(Hq + Hkv) * HD], d[:, (Hq + Hkv) * HD:]
+    do_t = gen((S, Hq * HD), 9, 1e-2)
+    one.forward()
+    two.forward()
+    g1, _ = run_backward(one, do_t)
+    g2, _ = run_backward(two, torch.cat((do_t, torch.full_like(do_t, float("nan")))))
+    for x, y in ((one.o, two.o), (g1, g2)):
+        assert torch.equal(x.view(torch.int16), y[:S].view(torch.int16))
+
+
+def test_sdpa_rows_far_apart():
+    """Pitches whose tile spans more than 4 GiB take 64-bit lane offsets: the same bits."""
+    S, pitch = 72, (1 << 25) + 8
+    a = Attn(1, S, 1, 1, seed=3)
+    a.forward()
+    want = a.o.clone()
+    buf = torch.empty(S * pitch, dtype=torch.bfloat16, device="cuda").view(S, pitch)
+    buf[:, :HD].copy_(a.k)
+    a.k = buf[:, :HD]
+    a.forward()
+    assert torch.equal(want.view(torch.int16), a.o.view(torch.int16))
