@@ -18,6 +18,7 @@
 // instructions; 1.5 % of the attention of 1 x 8192 tokens.)
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "f8_device.hpp"
 #include "f8_host.hpp"
@@ -91,6 +92,27 @@ __device__ inline void pipelined_products(Frag frag, Use use)
         if (i + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
     }
+}
+// The same with the first STARTED operands read beforehand (in the phase before), and two DS
+// instructions for an operand i < TWO (transposing reads).
+template <int N, int AHEAD, int TWO, int STARTED, class Frag, class Use>
+__device__ inline void started_products(const uint4 (&started)[STARTED], Frag frag, Use use)
+{
+    static_assert(STARTED <= AHEAD && AHEAD <= TWO && TWO <= N);
+    uint4 f[N];
+#pragma unroll
+    for (int i = 0; i < STARTED; ++i) f[i] = started[i];
+#pragma unroll
+    for (int i = STARTED; i < AHEAD; ++i) f[i] = frag(i);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * (AHEAD - STARTED), 0);
+    [&]<int... I>(std::integer_sequence<int, I...>) {
+        (..., [&] {
+            if constexpr (I + AHEAD < N) f[I + AHEAD] = frag(I + AHEAD);
+            use(I, f[I]);
+            if constexpr (I + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, I + AHEAD < TWO ? 2 : 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }());
+    }(std::make_integer_sequence<int, N>{});
 }
 
 // Tile loaders: global -> registers (issued early) -> LDS (after the barrier that frees it).
@@ -186,8 +208,13 @@ struct TileStream {
     const uint16_t* tile;  // first element of the next tile
     std::conditional_t<FAR, uint64_t, uint32_t> offset[N];  // of this lane's 16 bytes in it, in bytes
     int row0, chunk[N];
-    // (row, logical chunk) <-> physical chunk: an involution for a given row
-    static __device__ int swizzle(int row, int c) { return PITCH == kHd ? c ^ (row & 15) : c ^ ((row >> 1) & (CPR - 1)); }
+    // (row, logical chunk) <-> physical chunk: an involution for a given row.  For a row of 256 bytes (all of the
+    // banks) a read of one chunk of 16 rows wants 16 different permutations, and the transposing read of
+    // TokenFrags, four chunks of four consecutive rows, wants these to differ in bits 2 and 3.
+    static __device__ int swizzle(int row, int c)
+    {
+        return PITCH == kHd ? c ^ ((row & 3) << 2 | (row >> 2 & 3)) : c ^ ((row >> 1) & (CPR - 1));
+    }
     __device__ void start(const uint16_t* first, int64_t ld, int wave, int lane)
     {
         tile = first;
@@ -216,6 +243,45 @@ struct TileStream {
             }
         }
         tile += along;
+    }
+};
+// LDS offsets of this lane's operand reads from a [tokens][kHd] tile of a TileStream.
+// Contraction over hd: chunk 2 s + g of token row_token(ln); the tile's 32-token blocks are 32 * kHd apart.
+struct RowFrags {
+    int at;  // of s = 0; the chunk's permutation is an XOR, so that of s is another one
+    __device__ void start(int lane)
+    {
+        const int row = row_token(lane & 31);
+        at = row * kHd + 8 * TileStream<64, kHd, 8, false>::swizzle(row, lane >> 5);
+    }
+    __device__ uint4 read(const uint16_t* tile, int block32, int s) const
+    {
+        return *reinterpret_cast<const uint4*>(tile + 32 * kHd * block32 + (at ^ (16 * s)));
+    }
+    // Called once a step, it keeps the compiler from holding every s's offset in a register of its own.
+    __device__ void renew() { asm volatile("" : "+v"(at)); }
+};
+// Contraction over tokens: the operand that matches slots(c, u), rows hd 32 d + ln, tokens 16 u + 8 g + {0..7}, formed
+// by two transposing reads: within 16 lanes, lane i gets element i % 4 of the 8-byte pieces that lanes i / 4,
+// 4 + i / 4, 8 + i / 4 and 12 + i / 4 point at.  So lane i points at token i / 4 (of four), hd 4 (i % 4).
+struct TokenFrags {
+    int at;  // of d = 0, first of the two reads
+    __device__ void start(int lane)
+    {
+        const int g = lane >> 5, a = (lane >> 4) & 1, i = lane & 15;
+        const int row = 8 * g + i / 4, col = 16 * a + 4 * (i % 4);
+        at = row * kHd + 8 * TileStream<64, kHd, 8, false>::swizzle(row, col / 8) + col % 8;
+    }
+    __device__ void renew() { asm volatile("" : "+v"(at)); }
+    __device__ uint4 read(const uint16_t* tile, int block16, int d) const
+    {
+        typedef short v4s __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) v4s* lds_v4s;
+        const uint16_t* p = tile + 16 * kHd * block16;
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + (at ^ (32 * d)))));
+        // four tokens further down: the permutation of those rows differs in its lowest bit
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 4 * kHd + (at ^ (32 * d + 8)))));
+        return make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
 };
 // whether a tile of `rows` rows of pitch ld needs FAR
@@ -251,8 +317,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     // long (late) query tiles first, over all heads: the tile index varies slowest
     const int nbh = Hq * (int)(M / S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
     const int bh = blockIdx.x % nbh, h = bh % Hq, b = bh / Hq, kvh = h / group;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5,
-              rt = row_token(ln);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
     const bool late = wave >= NW / 2;          // the half that runs one slot behind
     const int q_first = qt * QB + wave * 32;  // of this wave
     const int q_pos = q_first + ln;            // position of this lane's query in its sequence
@@ -296,10 +361,10 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     ks.template request<true, true>(sK[0], wave, kBk * ldk, 0, S);
     request(std::true_type{}, 0, 0);
 
-    // LDS offsets of this lane's operand reads: chunk 2 s + g of key row rt, chunk 2 v + g of hd row ln
-    int k_rd[kHd / 16], v_rd[kBk / 16];
-#pragma unroll
-    for (int s = 0; s < kHd / 16; ++s) k_rd[s] = rt * kHd + 8 * KStream::swizzle(rt, 2 * s + g);
+    // LDS offsets of this lane's operand reads: of a key's row, chunk 2 v + g of hd row ln
+    RowFrags k_rd;
+    k_rd.start(lane);
+    int v_rd[kBk / 16];
 #pragma unroll
     for (int v = 0; v < kBk / 16; ++v) v_rd[v] = ln * kBk + 8 * VStream::swizzle(ln, 2 * v + g);
 
@@ -314,8 +379,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         pipelined_products<hi - lo, kFwdAhead>(
             [&](int n) {
                 const int i = n + lo;
-                return *reinterpret_cast<const uint4*>(i < 16 ? tK + 32 * kHd * (i % 2) + k_rd[i / 2 % 8]
-                                                              : tV + 32 * kBk * (i % 4) + v_rd[i / 4 % 4]);
+                return i < 16 ? k_rd.read(tK, i % 2, i / 2 % 8)
+                              : *reinterpret_cast<const uint4*>(tV + 32 * kBk * (i % 4) + v_rd[i / 4 % 4]);
             },
             [&](int n, uint4 f) {
                 const int i = n + lo;
@@ -451,29 +516,49 @@ __global__ void zero_amax_kernel(uint32_t* p) { p[0] = 0; }
 // orientation: one key per lane); with grouped heads the shares of a group's query heads are
 // kept in fp32 and summed in head order by a small fourth kernel.
 
-// dQ^T = K^T dS^T.  Per 64-key step: S^T = K Q^T, dP^T = V dO^T, dS^T, then the product over keys.
-template <int NW>
+// dQ^T = K^T dS^T.  In two staggered halves like the forward (see there), per 64-key step:
+//   M_t: dQ += K_t^T dS_t (16 products), then S^T = K_t+1 Q^T and dP^T = V_t+1 dO^T (32 products)
+//   V_t: dS_t+1 = P (dP - delta)
+// Tiles t live in buffer t % 4: M_t reads K_t, K_t+1 and V_t+1; K_t+3 and V_t+3 are requested at the end of V_t.
+// K^T comes from the K tile itself, by transposing reads.
+template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
-    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk, const uint16_t* __restrict__ Kt,
+    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
     const uint16_t* __restrict__ V, int64_t ldv, const uint16_t* __restrict__ O, int64_t ldo, const uint16_t* __restrict__ dO,
     int64_t lddo, const float* __restrict__ lse, int64_t M, int S, int Hq, int group, float scale_log2e, float scale,
     uint16_t* __restrict__ dQ, int64_t lddq, float* __restrict__ delta, int nqt)
 {
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    constexpr int NT = 64 * NW, QB = 32 * NW;  // threads and queries per block
-    constexpr int kBufElems = 2 * kBk * kKp + kHd * kTp;  // K rows, V rows, K^T; twice: the next step's
-                                                          // tiles are stored while slower waves still read this step's
+    static_assert(NW == 8, "two waves per SIMD in opposite phases");
+    constexpr int QB = 32 * NW;  // queries per block
+    __shared__ __attribute__((aligned(1024))) uint16_t sK[4][kBk * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sV[4][kBk * kHd];
 
     const int nbh = Hq * (int)(M / S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
     const int bh = blockIdx.x % nbh, h = bh % Hq, b = bh / Hq, kvh = h / group;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5, rt = row_token(ln);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const bool late = wave >= NW / 2;
     const int q_first = qt * QB + wave * 32, q_pos = q_first + ln;
     const int64_t tok0 = (int64_t)b * S;
-    const uint16_t* Kb = K + tok0 * ldk + (int64_t)kvh * kHd;
-    const uint16_t* Vb = V + tok0 * ldv + (int64_t)kvh * kHd;
-    const uint16_t* Ktb = Kt + (int64_t)kvh * kHd * M + tok0;
     const bool q_ok = q_pos < S;
     const int64_t tok = tok0 + (q_ok ? q_pos : 0);
+
+    int key_end = (qt + 1) * QB;
+    if (key_end > S) key_end = S;
+    const int nkt = (key_end + kBk - 1) / kBk;
+    const int t_last = min(nkt - 1, (q_first + 31) / kBk);
+
+    using Stream = TileStream<kBk, kHd, NW, FAR>;
+    Stream ks, vs;
+    ks.start(K + tok0 * ldk + (int64_t)kvh * kHd, ldk, wave, lane);
+    vs.start(V + tok0 * ldv + (int64_t)kvh * kHd, ldv, wave, lane);
+    auto request = [&](auto EDGE, int t) {  // tiles t
+        constexpr bool edge = decltype(EDGE)::value;
+        if (edge && t >= nkt) return;
+        ks.template request<edge, true>(sK[t & 3], wave, kBk * ldk, t * kBk, S);
+        vs.template request<edge, true>(sV[t & 3], wave, kBk * ldv, t * kBk, S);
+    };
+    request(std::true_type{}, 0);
+    request(std::true_type{}, 1);
 
     uint4 qf[kHd / 16], dof[kHd / 16];
     float dl = 0.0f;
@@ -495,66 +580,95 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
     if (q_ok && g == 0) delta[(int64_t)h * M + tok] = dl;
     const float lse2 = q_ok ? lse[(int64_t)h * M + tok] * 1.4426950408889634074f : 0.0f;
 
-    int key_end = (qt + 1) * QB;
-    if (key_end > S) key_end = S;
-    const int nkt = (key_end + kBk - 1) / kBk;
-
-    f32x16 acc[kHd / 32];
+    f32x16 acc[kHd / 32], sc[2], dp[2];
+    uint4 ds[4];  // dS^T of this step as operands, one per 16 keys
 #pragma unroll
     for (int d = 0; d < kHd / 32; ++d) acc[d] = f32x16{0};
+    RowFrags row_rd;
+    TokenFrags tok_rd;
+    row_rd.start(lane);
+    tok_rd.start(lane);
 
-    RowTile<kBk, NT> k_regs, v_regs;
-    ColTile<kBk, NT> kt_regs;
-    k_regs.load(Kb, ldk, 0, S);
-    v_regs.load(Vb, ldv, 0, S);
-    kt_regs.load(Ktb, M, 0, S);
-    for (int t = 0; t < nkt; ++t) {
-        const int key0 = t * kBk;
-        uint16_t* sK = smem + (t & 1) * kBufElems;  // [kBk][hd]
-        uint16_t* sV = sK + kBk * kKp;              // [kBk][hd]
-        uint16_t* sKt = sV + kBk * kKp;             // [hd][kBk]
-        k_regs.store(sK);
-        v_regs.store(sV);
-        kt_regs.store(sKt);
-        __syncthreads();
-        if (t + 1 < nkt) {
-            k_regs.load(Kb, ldk, key0 + kBk, S);
-            v_regs.load(Vb, ldv, key0 + kBk, S);
-            kt_regs.load(Ktb, M, key0 + kBk, S);
-        }
-        if (key0 > q_first + 31) continue;
-        const uint16_t *tK = sK, *tV = sV, *tKt = sKt;
-        const bool diagonal = key0 + kBk - 1 > q_first;
-        auto block32 = [&](int kb, auto masked) {  // masked: BoolC, two versions of the code
-            f32x16 sc = f32x16{0}, dp = f32x16{0};
-            pipelined_products<2 * (kHd / 16), kDqAhead>(  // even: a K operand for S^T, odd: a V operand for dP^T
-                [&](int i) { return *reinterpret_cast<const uint4*>(((i & 1) ? tV : tK) + (32 * kb + rt) * kKp + 16 * (i / 2) + 8 * g); },
-                [&](int i, uint4 f) {
-                    if (i & 1) dp = mma(f, dof[i / 2], dp);
-                    else sc = mma(f, qf[i / 2], sc);
-                });
+    // products [LO, HI) of M_t: 0 .. 15 dQ^T += K_t^T dS_t^T, 16 .. 47 S^T and dP^T of step t + 1.  The first operands
+    // (of K_t, which landed a step ago) are read at the end of phase V.
+    constexpr int STARTED = 2;  // (four do not fit the registers)
+    uint4 started[STARTED];
+    auto start_products = [&](int t) {
+        tok_rd.renew();
+#pragma unroll
+        for (int i = 0; i < STARTED; ++i) started[i] = tok_rd.read(sK[t & 3], i / 4, i % 4);
+    };
+    auto score_operand = [&](int t, int i) { return row_rd.read(i & 1 ? sV[t & 3] : sK[t & 3], (i >> 1) & 1, i / 4); };
+    auto score_product = [&](int i, uint4 f) {
+        const int kb = (i >> 1) & 1;
+        if (i & 1) dp[kb] = mma(f, dof[i / 4], dp[kb]);
+        else sc[kb] = mma(f, qf[i / 4], sc[kb]);
+    };
+    auto products = [&](int t, auto HI) {
+        constexpr int hi = decltype(HI)::value;
+        row_rd.renew();
+        if constexpr (hi > 16) sc[0] = sc[1] = dp[0] = dp[1] = f32x16{0};
+        __builtin_amdgcn_s_setprio(1);
+        started_products<hi, kDqAhead, 16>(
+            started, [&](int i) { return i < 16 ? tok_rd.read(sK[t & 3], i / 4, i % 4) : score_operand(t + 1, i - 16); },
+            [&](int i, uint4 f) {
+                if (i < 16) acc[i % 4] = mma(f, ds[i / 4], acc[i % 4]);
+                else score_product(i - 16, f);
+            });
+        __builtin_amdgcn_s_setprio(0);
+    };
+    using C16 = std::integral_constant<int, 16>;
+    using C48 = std::integral_constant<int, 48>;
+    auto grad_scores = [&](int t, auto MASKED) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - lse2);
-                if constexpr (decltype(masked)::value) {
-                    const int key = key0 + 32 * kb + reg_token(r, g);
-                    if (key > q_pos) p = 0.0f;
+                float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], scale_log2e, -lse2));
+                if constexpr (decltype(MASKED)::value) {
+                    if (t * kBk + 32 * kb + reg_token(r, g) > q_pos) p = 0.0f;
                 }
-                sc[r] = p * (dp[r] - dl);
+                sc[kb][r] = p * (dp[kb][r] - dl);
             }
-            const uint4 df[2] = {slots(sc, 0), slots(sc, 1)};
-            pipelined_products<8, kDqAhead>(
-                [&](int i) { return token_slots(tKt + (32 * (i % 4) + ln) * kTp, 32 * kb, i / 4, g); },
-                [&](int i, uint4 f) { acc[i % 4] = mma(f, df[i / 4], acc[i % 4]); });
-        };
-        if (diagonal) {
-#pragma unroll 1
-            for (int kb = 0; kb < 2; ++kb) block32(kb, BoolC<true>{});   // one 32-key block at a time (not unrolled: registers)
-        } else {
-#pragma unroll 1
-            for (int kb = 0; kb < 2; ++kb) block32(kb, BoolC<false>{});
+            ds[2 * kb] = slots(sc[kb], 0), ds[2 * kb + 1] = slots(sc[kb], 1);
         }
+        for (int i = 0; i < 4; ++i) computed(ds[i]);
+    };
+
+    int t = -1;
+    auto end_of_m = [&]() {
+        stream_wait();
+        phase_barrier();
+    };
+    auto step = [&](auto EDGE) {
+        end_of_m();
+        grad_scores(t + 1, std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+        request(EDGE, t + 3);
+        start_products(++t);
+        phase_barrier();
+        products(t, C48{});
+    };
+    stream_wait();
+    phase_barrier();
+    if (late) phase_barrier();
+    sc[0] = sc[1] = dp[0] = dp[1] = f32x16{0};
+    pipelined_products<32, kDqAhead>([&](int i) { return score_operand(0, i); }, score_product);
+    const int t_inside = min(t_last - 1, min(nkt, S / kBk) - 3);
+    while (t < t_inside) step(std::false_type{});
+    while (t < t_last - 1) step(std::true_type{});
+    for (; t < nkt; ++t) {
+        end_of_m();
+        if (t == t_last - 1) {
+            grad_scores(t_last, std::true_type{});
+            start_products(t_last);
+        }
+        request(std::true_type{}, t + 3);
+        phase_barrier();
+        if (t == t_last - 1) products(t_last, C16{});
     }
+    if (!late) phase_barrier();
+
     if (q_ok) {
         uint16_t* row = dQ + tok * lddq + (int64_t)h * kHd + 4 * g;
 #pragma unroll
@@ -762,12 +876,11 @@ __global__ __launch_bounds__(kAttnThreads) void sdpa_group_sum_kernel(const floa
 }
 
 constexpr int kDqWaves = 8;  // 256 queries per block, one block per compute unit
-constexpr size_t kDqLds = 2 * (size_t)(2 * kBk * kKp + kHd * kTp) * sizeof(uint16_t);
 constexpr int kDkvWaves = 8;             // 256 keys per block, one block per compute unit
 constexpr int kDkQs = 64, kDvQs = 64;    // queries per step of the dK and the dV kernel
 constexpr size_t kDkLds = 2 * ((size_t)(2 * kDkQs * kKp + kHd * ColTile<kDkQs>::P) * sizeof(uint16_t) + 2 * kDkQs * sizeof(float));
 constexpr size_t kDvLds = 2 * ((size_t)(kDvQs * kKp + kHd * ColTile<kDvQs>::P) * sizeof(uint16_t) + 2 * kDvQs * sizeof(float));
-static_assert(kDkLds <= 160 * 1024 && kDvLds <= 160 * 1024 && kDqLds <= 160 * 1024, "the tiles fit the LDS of a compute unit");
+static_assert(kDkLds <= 160 * 1024 && kDvLds <= 160 * 1024, "the tiles fit the LDS of a compute unit");
 
 static f8_status check_attn(const void* q, int64_t ldq, const void* k, int64_t ldk, int64_t B, int64_t S, int64_t Hq,
                             int64_t Hkv, int64_t hd)
@@ -843,7 +956,6 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
     static std::atomic<bool> configured{false};
     if (!configured.load(std::memory_order_acquire)) {
         const bool ok =
-            hipFuncSetAttribute((const void*)sdpa_bwd_dq_kernel<kDqWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDqLds) == hipSuccess &&
             hipFuncSetAttribute((const void*)sdpa_bwd_dkv_kernel<true, kDkQs, kDkvWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDkLds) == hipSuccess &&
             hipFuncSetAttribute((const void*)sdpa_bwd_dkv_kernel<false, kDvQs, kDkvWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDvLds) == hipSuccess;
         if (!ok) {
@@ -858,8 +970,9 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
     const double sc = 1.0 / sqrt((double)hd);
     const float scale = (float)sc, scale_log2e = (float)(sc * 1.4426950408889634074);
     const int64_t nqt = (S + 32 * kDqWaves - 1) / (32 * kDqWaves);
-    sdpa_bwd_dq_kernel<kDqWaves><<<(unsigned)(nqt * Hq * B), 64 * kDqWaves, kDqLds, st>>>(
-        (const uint16_t*)q_bf16, ldq, (const uint16_t*)k_bf16, ldk, (const uint16_t*)kt_bf16, (const uint16_t*)v_bf16, ldv,
+    const auto dq_kernel = far_rows(kBk, ldk) || far_rows(kBk, ldv) ? sdpa_bwd_dq_kernel<kDqWaves, true> : sdpa_bwd_dq_kernel<kDqWaves, false>;
+    dq_kernel<<<(unsigned)(nqt * Hq * B), 64 * kDqWaves, 0, st>>>(
+        (const uint16_t*)q_bf16, ldq, (const uint16_t*)k_bf16, ldk, (const uint16_t*)v_bf16, ldv,
         (const uint16_t*)o_bf16, ldo, (const uint16_t*)do_bf16, lddo, lse, M, (int)S, (int)Hq, (int)(Hq / Hkv), scale_log2e, scale,
         (uint16_t*)dq_bf16, lddq, delta, (int)nqt);
     float* part_k = group > 1 ? (float*)workspace : nullptr;
