@@ -517,7 +517,8 @@ f8_status f8_sdpa_fwd(const void* q_bf16, int64_t ldq, const void* k_bf16, int64
  * Token-major inputs: q, k, v, o, do (with their pitches); the copies that are
  * contiguous along tokens, packed with pitch B*S: qt [Hq*hd, B*S], kt
  * [Hkv*hd, B*S] (f8_rope's transposed outputs) and dot [Hq*hd, B*S]
- * (f8_transpose_bf16 of do); lse from the forward.  Outputs: dq [B*S, Hq*hd],
+ * (f8_transpose_bf16 of do): checked, but the kernels read the token-major
+ * tensors; lse from the forward.  Outputs: dq [B*S, Hq*hd],
  * dk, dv [B*S, Hkv*hd] bf16 with their pitches (dq and dk are gradients of the
  * ROTATED q and k: f8_rope with inverse != 0 turns them back), and delta
  * [Hq, B*S] fp32, scratch that the call fills.  With grouped heads (Hq > Hkv)

@@ -9,8 +9,8 @@
 // probabilities are already laid out as the operand of the next product, whose contraction runs
 // over keys: 8 consecutive registers are the 8 contraction slots of a lane.  The other operand
 // only has to present the same keys in the same slots: it is read from a copy that is contiguous
-// along tokens (V^T here; Q^T, K^T, dO^T in the backward), which the producers write on the way
-// (f8_rope's transposed output, f8_transpose_bf16).  No operand is transposed in registers.
+// along tokens (V^T in the forward, which f8_transpose_bf16 writes) or from the token-major tile by
+// transposing LDS reads (the backward).  No operand is transposed in registers.
 // Which token a row of the first operand is, is free: lane ln feeds token row_token(ln) of a
 // 32-token block, chosen so that registers 8u .. 8u + 7 hold EIGHT CONSECUTIVE tokens, 16u + 8g ..
 // + 7, and the matching operand of the next product is one 16-byte LDS read.  (In lane order they
@@ -32,15 +32,7 @@ constexpr int kAttnThreads = 256;
 constexpr int kHd = 128;   // head dimension of every model the paper trains
 constexpr int kBk = 64;    // keys per step
 // operand reads ahead of their product (deeper did not help)
-constexpr int kFwdAhead = 4, kDqAhead = 4, kDkvAhead = 4;
-constexpr int kKp = kHd + 8;   // LDS row pitch (bf16) of a [tokens][hd] tile: 272 bytes
-constexpr int kTp = kBk + 8;   // LDS row pitch (bf16) of a [hd][tokens] tile: 144 bytes = 36 words, an odd multiple of 4:
-                               // the 16-byte reads of 16 consecutive rows fall into 16 different bank quadruples
-
-template <bool B>
-struct BoolC {
-    static constexpr bool value = B;
-};
+constexpr int kFwdAhead = 4, kDqAhead = 4, kDkvAhead = 3;
 
 __device__ inline f32x16 mma(uint4 first, uint4 second, f32x16 acc)
 {
@@ -68,13 +60,6 @@ __device__ inline uint4 slots(const f32x16& c, int u)
 __device__ inline int row_token(int ln) { return (ln & 0x13) | ((ln & 4) << 1) | ((ln & 8) >> 1); }
 __device__ inline int reg_token(int r, int g) { return 16 * (r >> 3) + 8 * g + (r & 7); }
 
-// the operand that matches slots(c, u) of a 32-token block starting at column t0 of a
-// [rows][tokens] LDS tile: tokens t0 + 16u + 8g + {0..7}
-__device__ inline uint4 token_slots(const uint16_t* tile_row, int t0, int u, int g)
-{
-    return *reinterpret_cast<const uint4*>(tile_row + t0 + 16 * u + 8 * g);
-}
-
 // N products use(i, frag(i)) whose LDS operand reads (one DS instruction each) run AHEAD products
 // ahead of their use.  Left to itself the scheduler reads each operand right before its product
 // and every product waits out the LDS latency; the group barriers pin the interleaving.
@@ -94,76 +79,27 @@ __device__ inline void pipelined_products(Frag frag, Use use)
     }
 }
 // The same with the first STARTED operands read beforehand (in the phase before), and two DS
-// instructions for an operand i < TWO (transposing reads).
-template <int N, int AHEAD, int TWO, int STARTED, class Frag, class Use>
-__device__ inline void started_products(const uint4 (&started)[STARTED], Frag frag, Use use)
+// instructions for operand i if two(i) (transposing reads, or both operands from LDS).  frag(i) may be
+// a pair of operands.
+template <int N, int AHEAD, int STARTED, class Frag, class Use, class Two, class F>
+__device__ inline void started_products(const F (&started)[STARTED], Frag frag, Use use, Two two)
 {
-    static_assert(STARTED <= AHEAD && AHEAD <= TWO && TWO <= N);
-    uint4 f[N];
+    static_assert(STARTED <= AHEAD && AHEAD <= N);
+    F f[N];
 #pragma unroll
     for (int i = 0; i < STARTED; ++i) f[i] = started[i];
 #pragma unroll
     for (int i = STARTED; i < AHEAD; ++i) f[i] = frag(i);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * (AHEAD - STARTED), 0);
+    if constexpr (AHEAD > STARTED) __builtin_amdgcn_sched_group_barrier(0x100, 2 * (AHEAD - STARTED), 0);
     [&]<int... I>(std::integer_sequence<int, I...>) {
         (..., [&] {
             if constexpr (I + AHEAD < N) f[I + AHEAD] = frag(I + AHEAD);
             use(I, f[I]);
-            if constexpr (I + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, I + AHEAD < TWO ? 2 : 1, 0);
+            if constexpr (I + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, two(I + AHEAD) ? 2 : 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }());
     }(std::make_integer_sequence<int, N>{});
 }
-
-// Tile loaders: global -> registers (issued early) -> LDS (after the barrier that frees it).
-// [ROWS tokens][kHd] from a token-major tensor; rows at or beyond `limit` read as zero.
-template <int ROWS, int NT = kAttnThreads>
-struct RowTile {
-    static constexpr int N = ROWS * (kHd / 8) / NT;
-    static_assert(N >= 1 && N * NT == ROWS * (kHd / 8), "the tile's chunks divide evenly over the threads");
-    uint4 v[N];
-    __device__ void load(const uint16_t* base, int64_t ld, int row0, int limit)
-    {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int c = threadIdx.x + NT * i, r = c / (kHd / 8), cc = c % (kHd / 8);
-            v[i] = (row0 + r < limit) ? *reinterpret_cast<const uint4*>(base + (int64_t)(row0 + r) * ld + cc * 8) : make_uint4(0, 0, 0, 0);
-        }
-    }
-    __device__ void store(uint16_t* lds) const
-    {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int c = threadIdx.x + NT * i, r = c / (kHd / 8), cc = c % (kHd / 8);
-            *reinterpret_cast<uint4*>(lds + r * kKp + cc * 8) = v[i];
-        }
-    }
-};
-// [kHd][COLS tokens] from a transposed (token-minor) tensor with row pitch ld; columns at or beyond
-// `limit` read as zero (limit and col0 are multiples of 8).
-template <int COLS, int NT = kAttnThreads>
-struct ColTile {
-    static constexpr int N = kHd * (COLS / 8) / NT;
-    static_assert(N >= 1 && N * NT == kHd * (COLS / 8), "the tile's chunks divide evenly over the threads");
-    static constexpr int P = COLS + 8;
-    uint4 v[N];
-    __device__ void load(const uint16_t* base, int64_t ld, int col0, int limit)
-    {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int c = threadIdx.x + NT * i, r = c / (COLS / 8), cc = c % (COLS / 8);
-            v[i] = (col0 + cc * 8 < limit) ? *reinterpret_cast<const uint4*>(base + (int64_t)r * ld + col0 + cc * 8) : make_uint4(0, 0, 0, 0);
-        }
-    }
-    __device__ void store(uint16_t* lds) const
-    {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int c = threadIdx.x + NT * i, r = c / (COLS / 8), cc = c % (COLS / 8);
-            *reinterpret_cast<uint4*>(lds + r * P + cc * 8) = v[i];
-        }
-    }
-};
 
 // ---- staging for the staggered kernels ----------------------------------------------------
 // Tiles come straight from memory into LDS (one instruction of a wave: 64 lanes x 16 bytes into 1 KB of
@@ -511,16 +447,17 @@ __global__ void zero_amax_kernel(uint32_t* p) { p[0] = 0; }
 // ---- backward -----------------------------------------------------------------------------
 // With P = exp(S / sqrt(hd) - lse) recomputed from the saved lse and delta[q] = sum_d dO O:
 //   dV = P^T dO,  dP = dO V^T,  dS = P (dP - delta),  dQ = dS K / sqrt(hd),  dK = dS^T Q / sqrt(hd)
-// Three kernels, none with atomics: dQ per query tile (loop over keys, S^T orientation, which
+// Two kernels, neither with atomics: dQ per query tile (loop over keys, S^T orientation, which
 // also produces delta), then dK and dV per key tile and query head (loop over queries, S
 // orientation: one key per lane); with grouped heads the shares of a group's query heads are
-// kept in fp32 and summed in head order by a small fourth kernel.
+// kept in fp32 and summed in head order by a small third kernel.
 
 // dQ^T = K^T dS^T.  In two staggered halves like the forward (see there), per 64-key step:
 //   M_t: dQ += K_t^T dS_t (16 products), then S^T = K_t+1 Q^T and dP^T = V_t+1 dO^T (32 products)
 //   V_t: dS_t+1 = P (dP - delta)
 // Tiles t live in buffer t % 4: M_t reads K_t, K_t+1 and V_t+1; K_t+3 and V_t+3 are requested at the end of V_t.
-// K^T comes from the K tile itself, by transposing reads.
+// K^T comes from the K tile itself, by transposing reads.  (All waves in step, three tiles through registers: 821 us for
+// 1 x 8192 tokens, 32/8 heads; this: 690.  Phase M is what it waits for: 48 products, 1536 cycles, in about 1900.)
 template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
     const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
@@ -609,12 +546,13 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
         row_rd.renew();
         if constexpr (hi > 16) sc[0] = sc[1] = dp[0] = dp[1] = f32x16{0};
         __builtin_amdgcn_s_setprio(1);
-        started_products<hi, kDqAhead, 16>(
+        started_products<hi, kDqAhead>(
             started, [&](int i) { return i < 16 ? tok_rd.read(sK[t & 3], i / 4, i % 4) : score_operand(t + 1, i - 16); },
             [&](int i, uint4 f) {
                 if (i < 16) acc[i % 4] = mma(f, ds[i / 4], acc[i % 4]);
                 else score_product(i - 16, f);
-            });
+            },
+            [](int i) { return i < 16; });
         __builtin_amdgcn_s_setprio(0);
     };
     using C16 = std::integral_constant<int, 16>;
@@ -681,166 +619,220 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
     }
 }
 
-// dK^T = Q^T dS and dV^T = dO^T P, as two instantiations of one kernel (DK: the dK half).  One
-// block: NW waves, 32 keys each (one key per lane), of one (sequence, query head); loop over
-// QS-query steps.  Eight waves (256 keys) per block: every block streams the Q / dO tiles of all
-// later queries of its head, and a larger key tile halves that traffic and the prefetch
-// registers per thread.  Both halves recompute S = Q K^T; taken together they
-// would need the key and value operands, two sets of accumulators and four tiles per step, more
-// than the 256 registers a wave has at two waves per SIMD.
-template <bool DK, int QS, int NW>
+// dV^T = dO^T P and dK^T = Q^T dS in one pass over the scores.  One block: 8 waves, 32 keys each (one key per lane),
+// of one (sequence, query head); 32-query steps from the end of the sequence down to the diagonal, in two
+// staggered halves like the forward (see there):
+//   M_t: dV += dO_t^T P_t, dK += Q_t^T dS_t (8 products each), then S = Q_t+1 K^T, dP = dO_t+1 V^T (8 each)
+//   V_t: P_t+1 = exp(S - lse), dS_t+1 = P (dP - delta)
+// Tiles t (Q, dO and their lse, delta) live in buffer t % 4; those of step t + 3 are requested at the end of V_t.
+// Q^T and dO^T come from the same tiles by transposing reads.  The two accumulators (128 registers), the K
+// operand (32), scores and operands leave no room for the V operand: the block's 256 rows of V stay in LDS.
+// (dK and dV in a kernel each, 40 products a step instead of 32 and the exponentials twice, all waves in step: 1490 us for
+// 1 x 8192 tokens, 32/8 heads; this: 990.)
+constexpr int kDkvQ = 32;  // queries per step
+template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
-    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ Qt, const uint16_t* __restrict__ K, int64_t ldk,
-    const uint16_t* __restrict__ V, int64_t ldv, const uint16_t* __restrict__ dO, int64_t lddo, const uint16_t* __restrict__ dOt,
-    const float* __restrict__ lse, const float* __restrict__ delta, int64_t M, int S, int Hq, int group, float scale_log2e,
-    float scale, uint16_t* __restrict__ dst, int64_t ldd, float* __restrict__ part)
+    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk, const uint16_t* __restrict__ V,
+    int64_t ldv, const uint16_t* __restrict__ dO, int64_t lddo, const float* __restrict__ lse, const float* __restrict__ delta,
+    int64_t M, int S, int Hq, int group, float scale_log2e, float scale, uint16_t* __restrict__ dK, int64_t lddk,
+    uint16_t* __restrict__ dV, int64_t lddv, float* __restrict__ part_k, float* __restrict__ part_v)
 {
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    constexpr int NT = 64 * NW, KB = 32 * NW;  // threads and keys per block
-    constexpr int TP = ColTile<QS, NT>::P;     // row pitch of the [hd][queries] tile
-    // every tile twice: the next step's tiles are stored while slower waves still read this step's
-    constexpr int kTileElems = QS * kKp + kHd * TP + (DK ? QS * kKp : 0);  // bf16 elements of one buffer
-    constexpr int kBufElems = kTileElems + 4 * QS;                          // + lse and delta (2 QS floats)
-    static_assert((kBufElems * 2) % 16 == 0, "buffers stay 16-byte aligned");
+    static_assert(NW == 8, "two waves per SIMD in opposite phases");
+    constexpr int KB = 32 * NW;  // keys per block
+    __shared__ __attribute__((aligned(1024))) uint16_t sQ[4][kDkvQ * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sD[4][kDkvQ * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sV[KB * kHd];
+    __shared__ __attribute__((aligned(1024))) float sStat[4][2 * kDkvQ];  // lse, then delta
 
     // early key tiles see the most queries: they are the slowest-varying index, so they start first
     const int bh = blockIdx.x % (Hq * (int)(M / S)), kt = blockIdx.x / (Hq * (int)(M / S));
     const int hq = bh % Hq, b = bh / Hq, kvh = hq / group, gi = hq % group;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5, rt = row_token(ln);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const bool late = wave >= NW / 2;
     const int key_first = kt * KB + wave * 32, key_pos = key_first + ln;
     const int64_t tok0 = (int64_t)b * S;
     const bool k_ok = key_pos < S;
     const int64_t tok = tok0 + (k_ok ? key_pos : 0);
 
-    uint4 kf[kHd / 16], vf[DK ? kHd / 16 : 1];
-    {
-        const uint16_t* krow = K + tok * ldk + (int64_t)kvh * kHd + 8 * g;
-        const uint16_t* vrow = V + tok * ldv + (int64_t)kvh * kHd + 8 * g;
-#pragma unroll
-        for (int s = 0; s < kHd / 16; ++s) {
-            kf[s] = k_ok ? *reinterpret_cast<const uint4*>(krow + 16 * s) : make_uint4(0, 0, 0, 0);
-            if constexpr (DK) vf[s] = k_ok ? *reinterpret_cast<const uint4*>(vrow + 16 * s) : make_uint4(0, 0, 0, 0);
-        }
-    }
-    f32x16 acc[kHd / 32];
-#pragma unroll
-    for (int d = 0; d < kHd / 32; ++d) acc[d] = f32x16{0};
+    const int q_start = kt * KB;
+    const int steps = (S - q_start + kDkvQ - 1) / kDkvQ;  // >= 1: the block exists only if q_start < S
+    const int t_last = max(0, steps - 1 - wave);          // step t: queries q0(t) ..; this wave's last one is its diagonal
+    auto q0 = [&](int t) { return q_start + (steps - 1 - t) * kDkvQ; };
 
-    const int q_start = kt * KB;                        // a multiple of the query step
-    const int steps = (S - q_start + QS - 1) / QS;    // >= 1: the block exists only if q_start < S
-    const uint16_t* Qb = Q + tok0 * ldq + (int64_t)hq * kHd;
-    const uint16_t* Db = dO + tok0 * lddo + (int64_t)hq * kHd;
-    const uint16_t* Tb = (DK ? Qt : dOt) + (int64_t)hq * kHd * M + tok0;
-    const float* lse_b = lse + (int64_t)hq * M + tok0;
-    const float* del_b = delta + (int64_t)hq * M + tok0;
-
-    RowTile<QS, NT> q_regs, d_regs;
-    ColTile<QS, NT> t_regs;
-    float stat_reg = 0.0f;  // threads 0..63: lse of query threadIdx.x of the step; 64..127: delta (DK)
-    auto load_step = [&](int q0) {
-        q_regs.load(Qb, ldq, q0, S);
-        t_regs.load(Tb, M, q0, S);
-        if constexpr (DK) d_regs.load(Db, lddo, q0, S);
-        if (threadIdx.x < (DK ? 2 : 1) * QS) {
-            const int i = threadIdx.x & (QS - 1);
-            const float* src = threadIdx.x < QS ? lse_b : del_b;
-            stat_reg = (q0 + i < S) ? src[q0 + i] : 0.0f;
-            if (threadIdx.x < QS) stat_reg *= 1.4426950408889634074f;
+    using Stream = TileStream<kDkvQ, kHd, NW, FAR>;
+    Stream qs, os;
+    qs.start(Q + (tok0 + q0(0)) * ldq + (int64_t)hq * kHd, ldq, wave, lane);
+    os.start(dO + (tok0 + q0(0)) * lddo + (int64_t)hq * kHd, lddo, wave, lane);
+    const float *lse_b = lse + (int64_t)hq * M + tok0, *delta_b = delta + (int64_t)hq * M + tok0;
+    auto request = [&](auto EDGE, int t) {  // EDGE: may lie past the last step, or (step 0) reach past S
+        constexpr bool edge = decltype(EDGE)::value;
+        if (edge && t >= steps) return;
+        const int buf = t & 3;
+        qs.template request<edge, true>(sQ[buf], wave, -kDkvQ * ldq, q0(t), S);
+        os.template request<edge, true>(sD[buf], wave, -kDkvQ * lddo, q0(t), S);
+        if (wave == NW - 1) {
+            int l64 = threadIdx.x;  // (formed anew: held over the loop, the pointer costs registers that are not there)
+            asm volatile("" : "+v"(l64));
+            const int q = q0(t) + (l64 & 31);
+            const float* p = ((l64 & 32) ? delta_b : lse_b) + q;
+            if (edge && q >= S) p = reinterpret_cast<const float*>(kZeros);
+            const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)sStat[buf];
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(l), "v"(p) : "memory");
         }
     };
-    // Queries from the end of the sequence down to the diagonal: the blocks of one head (which share
-    // an XCD: the head index is the fastest-varying part of blockIdx) then walk the same Q / dO tiles
-    // at the same time.
-    load_step(q_start + (steps - 1) * QS);
-    for (int it = 0; it < steps; ++it) {
-        const int q0 = q_start + (steps - 1 - it) * QS;
-        uint16_t* sQ = smem + (it & 1) * kBufElems;            // [QS queries][hd]: Q rows
-        uint16_t* sT = sQ + QS * kKp;                          // [hd][QS]: DK: Q^T, else dO^T
-        uint16_t* sD = sT + kHd * TP;                          // [QS][hd], DK only: dO rows
-        float* sLse = reinterpret_cast<float*>(sQ + kTileElems);  // [QS], already times log2(e)
-        float* sDel = sLse + QS;                               // [QS], DK only
-        q_regs.store(sQ);
-        t_regs.store(sT);
-        if constexpr (DK) d_regs.store(sD);
-        if (threadIdx.x < QS) sLse[threadIdx.x] = stat_reg;
-        else if (DK && threadIdx.x < 2 * QS) sDel[threadIdx.x - QS] = stat_reg;
-        __syncthreads();
-        if (it + 1 < steps) load_step(q0 - QS);
-        if (q0 + QS - 1 < key_first) continue;  // every query of the step lies before every key of the wave
-        // one 32-query block at a time; registers: queries 32 qb + reg_token(r, g) of the step; lane: one key
-        // only the steps at the diagonal or at the end of the sequence have anything to mask (wave-uniform)
-        const bool edge = q0 < key_first + 32 || q0 + QS > S;
-        auto block32 = [&](int qb, auto masked) {  // masked: integral_constant<bool>, two versions of the code
-            f32x16 sc = f32x16{0}, dp = f32x16{0};
-            if constexpr (DK) {
-                pipelined_products<2 * (kHd / 16), kDkvAhead>(  // even: a Q operand for S, odd: a dO operand for dP
-                    [&](int i) { return *reinterpret_cast<const uint4*>(((i & 1) ? sD : sQ) + (32 * qb + rt) * kKp + 16 * (i / 2) + 8 * g); },
-                    [&](int i, uint4 f) {
-                        if (i & 1) dp = mma(f, vf[i / 2], dp);
-                        else sc = mma(f, kf[i / 2], sc);
-                    });
-            } else {
-                pipelined_products<kHd / 16, kDkvAhead>(
-                    [&](int i) { return *reinterpret_cast<const uint4*>(sQ + (32 * qb + rt) * kKp + 16 * i + 8 * g); },
-                    [&](int i, uint4 f) { sc = mma(f, kf[i], sc); });
-            }
+    {
+        TileStream<KB, kHd, NW, FAR> vs;
+        vs.start(V + (tok0 + q_start) * ldv + (int64_t)kvh * kHd, ldv, wave, lane);
+        vs.template request<true, true>(sV, wave, 0, q_start, S);
+    }
+    request(std::true_type{}, 0);
+    request(std::true_type{}, 1);
+
+    uint4 kf[kHd / 16];
+    {
+        const uint16_t* krow = K + tok * ldk + (int64_t)kvh * kHd + 8 * g;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int ql = 32 * qb + reg_token(4 * j, g);
-                const float4 l4 = *reinterpret_cast<const float4*>(sLse + ql);
-                const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
-                float dv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                if constexpr (DK) {
-                    const float4 d4 = *reinterpret_cast<const float4*>(sDel + ql);
-                    dv[0] = d4.x, dv[1] = d4.y, dv[2] = d4.z, dv[3] = d4.w;
-                }
+        for (int s = 0; s < kHd / 16; ++s) kf[s] = k_ok ? *reinterpret_cast<const uint4*>(krow + 16 * s) : make_uint4(0, 0, 0, 0);
+    }
+    f32x16 acc_k[kHd / 32], acc_v[kHd / 32], sc, dp;
+    uint4 pf[2], ds[2];  // P and dS of this step as operands, one per 16 queries
+#pragma unroll
+    for (int d = 0; d < kHd / 32; ++d) acc_k[d] = acc_v[d] = f32x16{0};
+    RowFrags row_rd;
+    TokenFrags tok_rd;
+    row_rd.start(lane);
+    tok_rd.start(lane);
+    int v_at = (32 * wave + ln) * kHd + 8 * Stream::swizzle(ln, g);  // chunk 2 s + g of this lane's key: s enters as an XOR
+
+    struct Operands {
+        uint4 first, second;
+    };
+    // products of M_t: 0 .. 7 dV, 8 .. 15 dK, 16 .. 31 S and dP of step t + 1
+    auto score_operands = [&](int t, int j) {
+        const int s = j / 2;
+        if (j & 1) return Operands{row_rd.read(sD[t & 3], 0, s), *reinterpret_cast<const uint4*>(sV + (v_at ^ (16 * s)))};
+        return Operands{row_rd.read(sQ[t & 3], 0, s), kf[s]};
+    };
+    auto score_product = [&](int j, const Operands& f) {
+        if (j & 1) dp = mma(f.first, f.second, dp);
+        else sc = mma(f.first, f.second, sc);
+    };
+    auto grad_operands = [&](int t, int i) {
+        return Operands{tok_rd.read(i < 8 ? sD[t & 3] : sQ[t & 3], (i / 4) % 2, i % 4), i < 8 ? pf[(i / 4) % 2] : ds[(i / 4) % 2]};
+    };
+    constexpr int STARTED = 1;  // (two, or four operands ahead, do not fit the registers)
+    Operands started[STARTED];  // read at the end of phase V: these tiles landed a step ago
+    auto start_products = [&](int t) {
+        tok_rd.renew();
+#pragma unroll
+        for (int i = 0; i < STARTED; ++i) started[i] = grad_operands(t, i);
+    };
+    auto products = [&](int t, auto HI) {
+        constexpr int hi = decltype(HI)::value;
+        row_rd.renew();
+        asm volatile("" : "+v"(v_at));
+        if constexpr (hi > 16) sc = dp = f32x16{0};
+        __builtin_amdgcn_s_setprio(1);
+        started_products<hi, kDkvAhead>(
+            started, [&](int i) { return i < 16 ? grad_operands(t, i) : score_operands(t + 1, i - 16); },
+            [&](int i, const Operands& f) {
+                if (i < 8) acc_v[i % 4] = mma(f.first, f.second, acc_v[i % 4]);
+                else if (i < 16) acc_k[i % 4] = mma(f.first, f.second, acc_k[i % 4]);
+                else score_product(i - 16, f);
+            },
+            [](int i) { return i < 16 || (i & 1); });
+        __builtin_amdgcn_s_setprio(0);
+    };
+    using C16 = std::integral_constant<int, 16>;
+    using C32 = std::integral_constant<int, 32>;
+    // Queries at or beyond S read as zero rows with lse = delta = 0: they add nothing.  MASKED: the wave's diagonal.
+    auto grad_scores = [&](int t, auto MASKED) {
+        const float* st = sStat[t & 3];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float ds8[8];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int ql = reg_token(8 * u + 4 * j, g);
+                const float4 l4 = *reinterpret_cast<const float4*>(st + ql), d4 = *reinterpret_cast<const float4*>(st + kDkvQ + ql);
+                const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int r = 4 * j + i, qp = q0 + ql + i;
-                    float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - lv[i]);
-                    if constexpr (decltype(masked)::value) {
-                        if (key_pos > qp || qp >= S) p = 0.0f;
+                    const int r = 8 * u + 4 * j + i;
+                    float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, lv[i] * -1.4426950408889634074f));
+                    if constexpr (decltype(MASKED)::value) {
+                        if (key_pos > q0(t) + ql + i) p = 0.0f;
                     }
-                    sc[r] = DK ? p * (dp[r] - dv[i]) : p;
+                    sc[r] = p;
+                    ds8[4 * j + i] = p * (dp[r] - dv[i]);
                 }
             }
-            const uint4 pf[2] = {slots(sc, 0), slots(sc, 1)};
-            pipelined_products<8, kDkvAhead>(
-                [&](int i) { return token_slots(sT + (32 * (i % 4) + ln) * TP, 32 * qb, i / 4, g); },
-                [&](int i, uint4 f) { acc[i % 4] = mma(f, pf[i / 4], acc[i % 4]); });
-        };
-        auto step = [&](auto masked) {
-            if constexpr (DK) {
-#pragma unroll 1
-                for (int qb = 0; qb < QS / 32; ++qb) block32(qb, masked);  // not unrolled: two blocks in flight would not fit the registers
-            } else {
+            pf[u] = slots(sc, u);
+            ds[u] = make_uint4(pack2(ds8[0], ds8[1]), pack2(ds8[2], ds8[3]), pack2(ds8[4], ds8[5]), pack2(ds8[6], ds8[7]));
+        }
+        for (int u = 0; u < 2; ++u) computed(pf[u]), computed(ds[u]);
+    };
+
+    int t = -1;
+    auto end_of_m = [&]() {
+        stream_wait();
+        phase_barrier();
+    };
+    auto step = [&](auto EDGE) {
+        end_of_m();
+        grad_scores(t + 1, std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+        request(EDGE, t + 3);
+        start_products(++t);
+        phase_barrier();
+        products(t, C32{});
+    };
+    stream_wait();
+    phase_barrier();
+    if (late) phase_barrier();
+    sc = dp = f32x16{0};
 #pragma unroll
-                for (int qb = 0; qb < QS / 32; ++qb) block32(qb, masked);  // unrolled: one block's exponentials overlap the other's products
-            }
-        };
-        if (edge) step(BoolC<true>{});
-        else step(BoolC<false>{});
+    for (int j = 0; j < 16; ++j) score_product(j, score_operands(0, j));
+    const int t_inside = min(t_last - 1, steps - 3);
+    while (t < t_inside) step(std::false_type{});
+    while (t < t_last - 1) step(std::true_type{});
+    for (; t < steps; ++t) {
+        end_of_m();
+        if (t == t_last - 1) {
+            grad_scores(t_last, std::true_type{});
+            start_products(t_last);
+        }
+        request(std::true_type{}, t + 3);
+        phase_barrier();
+        if (t == t_last - 1) products(t_last, C16{});
     }
+    if (!late) phase_barrier();
+
     if (!k_ok) return;
-    const float mul = DK ? scale : 1.0f;
     if (group == 1) {
-        uint16_t* row = dst + tok * ldd + (int64_t)kvh * kHd + 4 * g;
+        auto store = [&](const f32x16 (&acc)[kHd / 32], float mul, uint16_t* row) {
 #pragma unroll
-        for (int d = 0; d < kHd / 32; ++d)
+            for (int d = 0; d < kHd / 32; ++d)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<uint2*>(row + 32 * d + 8 * j) =
-                    make_uint2(pack2(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul), pack2(acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul));
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<uint2*>(row + 32 * d + 8 * j) =
+                        make_uint2(pack2(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul), pack2(acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul));
+        };
+        store(acc_k, scale, dK + tok * lddk + (int64_t)kvh * kHd + 4 * g);
+        store(acc_v, 1.0f, dV + tok * lddv + (int64_t)kvh * kHd + 4 * g);
     } else {
         // this query head's share, fp32: [group][token][Hkv * hd]; summed in a fixed order afterwards
-        const int64_t w = (int64_t)(Hq / group) * kHd;
-        float* row = part + ((int64_t)gi * M + tok) * w + (int64_t)kvh * kHd + 4 * g;
+        const int64_t w = (int64_t)(Hq / group) * kHd, at = ((int64_t)gi * M + tok) * w + (int64_t)kvh * kHd + 4 * g;
+        auto store = [&](const f32x16 (&acc)[kHd / 32], float mul, float* row) {
 #pragma unroll
-        for (int d = 0; d < kHd / 32; ++d)
+            for (int d = 0; d < kHd / 32; ++d)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<float4*>(row + 32 * d + 8 * j) =
-                    make_float4(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul, acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul);
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<float4*>(row + 32 * d + 8 * j) =
+                        make_float4(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul, acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul);
+        };
+        store(acc_k, scale, part_k + at);
+        store(acc_v, 1.0f, part_v + at);
     }
 }
 
@@ -877,11 +869,6 @@ __global__ __launch_bounds__(kAttnThreads) void sdpa_group_sum_kernel(const floa
 
 constexpr int kDqWaves = 8;  // 256 queries per block, one block per compute unit
 constexpr int kDkvWaves = 8;             // 256 keys per block, one block per compute unit
-constexpr int kDkQs = 64, kDvQs = 64;    // queries per step of the dK and the dV kernel
-constexpr size_t kDkLds = 2 * ((size_t)(2 * kDkQs * kKp + kHd * ColTile<kDkQs>::P) * sizeof(uint16_t) + 2 * kDkQs * sizeof(float));
-constexpr size_t kDvLds = 2 * ((size_t)(kDvQs * kKp + kHd * ColTile<kDvQs>::P) * sizeof(uint16_t) + 2 * kDvQs * sizeof(float));
-static_assert(kDkLds <= 160 * 1024 && kDvLds <= 160 * 1024, "the tiles fit the LDS of a compute unit");
-
 static f8_status check_attn(const void* q, int64_t ldq, const void* k, int64_t ldk, int64_t B, int64_t S, int64_t Hq,
                             int64_t Hkv, int64_t hd)
 {
@@ -950,20 +937,6 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
     if (group > 1 && (!workspace || workspace_bytes_ < f8_sdpa_bwd_workspace_bytes(B, S, Hq, Hkv, hd))) return F8_ERR_WORKSPACE;
     if (group > 1 && !aligned16(workspace)) return F8_ERR_ALIGN;
     if (B == 0 || S == 0) return F8_OK;
-    // More dynamic LDS than the default limit of a launch: raised once per process.  Only success
-    // is remembered, so that a failure (a call made while the stream is being captured, a
-    // transient error) is tried again by the next call instead of being final.
-    static std::atomic<bool> configured{false};
-    if (!configured.load(std::memory_order_acquire)) {
-        const bool ok =
-            hipFuncSetAttribute((const void*)sdpa_bwd_dkv_kernel<true, kDkQs, kDkvWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDkLds) == hipSuccess &&
-            hipFuncSetAttribute((const void*)sdpa_bwd_dkv_kernel<false, kDvQs, kDkvWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDvLds) == hipSuccess;
-        if (!ok) {
-            (void)hipGetLastError();
-            return F8_ERR_LAUNCH;
-        }
-        configured.store(true, std::memory_order_release);
-    }
     hipStream_t st = (hipStream_t)stream;
     const int64_t M = B * S;
     if ((S + 255) / 256 * Hq * B > (int64_t)0x7FFFFFFF) return F8_ERR_SHAPE;  // one block per 256 tokens and head
@@ -978,14 +951,13 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
     float* part_k = group > 1 ? (float*)workspace : nullptr;
     float* part_v = group > 1 ? part_k + group * M * wk : nullptr;
     const int64_t nkt = (S + 32 * kDkvWaves - 1) / (32 * kDkvWaves);
-    sdpa_bwd_dkv_kernel<true, kDkQs, kDkvWaves><<<(unsigned)(nkt * Hq * B), 64 * kDkvWaves, kDkLds, st>>>(
-        (const uint16_t*)q_bf16, ldq, (const uint16_t*)qt_bf16, (const uint16_t*)k_bf16, ldk, (const uint16_t*)v_bf16, ldv,
-        (const uint16_t*)do_bf16, lddo, (const uint16_t*)dot_bf16, lse, delta, M, (int)S, (int)Hq, (int)group, scale_log2e,
-        scale, (uint16_t*)dk_bf16, lddk, part_k);
-    sdpa_bwd_dkv_kernel<false, kDvQs, kDkvWaves><<<(unsigned)(nkt * Hq * B), 64 * kDkvWaves, kDvLds, st>>>(
-        (const uint16_t*)q_bf16, ldq, (const uint16_t*)qt_bf16, (const uint16_t*)k_bf16, ldk, (const uint16_t*)v_bf16, ldv,
-        (const uint16_t*)do_bf16, lddo, (const uint16_t*)dot_bf16, lse, delta, M, (int)S, (int)Hq, (int)group, scale_log2e,
-        scale, (uint16_t*)dv_bf16, lddv, part_v);
+    const auto dkv_kernel = far_rows(kDkvQ, ldq) || far_rows(kDkvQ, lddo) || far_rows(32 * kDkvWaves, ldv)
+                                ? sdpa_bwd_dkv_kernel<kDkvWaves, true>
+                                : sdpa_bwd_dkv_kernel<kDkvWaves, false>;
+    dkv_kernel<<<(unsigned)(nkt * Hq * B), 64 * kDkvWaves, 0, st>>>(
+        (const uint16_t*)q_bf16, ldq, (const uint16_t*)k_bf16, ldk, (const uint16_t*)v_bf16, ldv, (const uint16_t*)do_bf16, lddo,
+        lse, delta, M, (int)S, (int)Hq, (int)group, scale_log2e, scale, (uint16_t*)dk_bf16, lddk, (uint16_t*)dv_bf16, lddv, part_k,
+        part_v);
     if (group > 1) {
         int64_t nb = (2 * M * (wk / 8) + kAttnThreads - 1) / kAttnThreads;
         if (nb > 8192) nb = 8192;
