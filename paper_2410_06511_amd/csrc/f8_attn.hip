@@ -235,8 +235,8 @@ static bool far_rows(int64_t rows, int64_t ld) { return 2 * (rows * ld + kHd) >=
 // in slots 2t and 2t + 1.  K_t+3 and V_t+2 are requested at the end of V_t into the third of three buffers
 // (what it held was read up to slot 2t - 1) and waited for at the end of the wave's next phase M.
 // Measured (1 x 8192 tokens, 32/8 heads; cycles of a slot, both phases in it): M 1300 (32 products are 1024), V
-// 1400 (softmax 1080, the four loads the rest: a wave's load holds up its next instruction until the memory
-// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 590 us; this: 490.
+// 1400 (softmax 1080 to 1300, the four loads the rest: a wave's load holds up its next instruction until the memory
+// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 590 us; this: 530.
 template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(const uint16_t* __restrict__ Q, int64_t ldq,
                                                                 const uint16_t* __restrict__ K, int64_t ldk,
@@ -330,12 +330,6 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     using C16 = integral_constant<int, 16>;
     using C32 = integral_constant<int, 32>;
 
-    // The running maximum of a query follows its scores only when one of the wave's queries has outgrown it by
-    // 2^kSlack: until then the probabilities are taken against the old one (they stay below 2^kSlack, sums and
-    // products keep their relative precision) and nothing has to be rescaled.  Following every new maximum
-    // rescaled the 64 accumulators in about half of the steps.
-    constexpr float kSlack = 8.0f;
-    const float slack = kSlack / scale_log2e;  // in raw scores
     // of step t.  MASKED: the step at the diagonal, a wave's last one (32 queries from a multiple of 32 on, 64
     // keys: it is the only one with anything to mask)
     auto softmax = [&](int t, auto MASKED) {
@@ -357,11 +351,13 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         const float m_here = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
         const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_here), __float_as_uint(m_here), false, false);
         const float m_new = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));  // of the query: the pair of lanes
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run + slack)) {  // always at step 0: key 0 is visible to every query
-            const float m_next = fmaxf(m_run, m_new);
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_next) * scale_log2e);
-            m_run = m_next;
-            l_run *= alpha;
+        const float m_next = fmaxf(m_run, m_new);  // finite: key 0 is visible to every query
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_next) * scale_log2e);
+        m_run = m_next;
+        l_run *= alpha;
+        // (Following the maximum only when it has grown by 2^8 saves 4 % of the kernel, but puts the probabilities
+        // on another rounding grid: 2e-3 of the output, which the fp8 casts of a whole block turn into 5e-2.)
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {
 #pragma unroll
             for (int d = 0; d < kHd / 32; ++d)
 #pragma unroll
