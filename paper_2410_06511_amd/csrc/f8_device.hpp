@@ -187,9 +187,24 @@ __device__ inline float scale_from_amax(float amax, float fm)
 
 // ---- feed-forward glue arithmetic (shared by the glue kernels and the cast that fuses it) ----
 
-__device__ inline float sigmoidf_fast(float t) { return 1.0f / (1.0f + __expf(-t)); }
+// 1 / (1 + e^-t) by the reciprocal instruction and one Newton step (within an ulp of the division, which takes
+// three times as many instructions and made the glue kernels VALU-bound).  The denominator is scaled by 2^-64
+// and the result back, since the instruction does not form subnormal results (t below -87); an infinite
+// denominator leaves a NaN that the maximum turns into its limit 0.
+__device__ inline float sigmoidf_fast(float t)
+{
+    const float d = (1.0f + __expf(-t)) * 0x1p-64f;
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __builtin_fmaf(r, __builtin_fmaf(-d, r, 1.0f), r);
+    return fmaxf(r, 0.0f) * 0x1p-64f;
+}
 
-__device__ inline uint32_t pack_bf16(float lo, float hi) { return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16); }
+// two fp32 -> two bf16 in a word, round to nearest even (v_cvt_pk_bf16_f32)
+__device__ inline uint32_t pack_bf16(float lo, float hi)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
+}
 
 // one 32-bit word = two bf16: h = bf16(silu(a) * b), silu(t) = t / (1 + e^-t)
 __device__ inline uint32_t silu_mul2(uint32_t a, uint32_t b)
