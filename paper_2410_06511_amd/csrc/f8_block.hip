@@ -216,6 +216,96 @@ __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dx_kernel(const uint4* __
     }
 }
 
+// dx and dg from one read of x and dy (D up to 4096): a wave walks rows and keeps, beside the row, the sums of
+// dy * x * rstd of its own rows for its 64 columns in registers; the block's four sets meet in LDS and leave one
+// partial row, partial[block][D].  8192 x 4096 with the residual: 94 us
+// with the final sum, 105 as two passes.
+constexpr int kFusedChunks = 8;  // 16-byte chunks of a row per lane
+__global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const uint4* __restrict__ x, const uint4* __restrict__ g,
+                                                                           const float* __restrict__ rstd, const uint4* __restrict__ dy,
+                                                                           int64_t M, int dc, float inv_d, uint4* __restrict__ dx /* nullable */,
+                                                                           const uint4* __restrict__ res /* nullable: added to dx */,
+                                                                           float* __restrict__ partial,
+                                                                           uint32_t* __restrict__ amax_bits /* nullable: max-updated */)
+{
+    constexpr int NC = kFusedChunks;
+    __shared__ float sum[kBlkWaves][NC * kWave * 8];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint32_t mag = 0;
+    float acc[NC][8];
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = 0.0f;
+    for (int64_t m = (int64_t)blockIdx.x * kBlkWaves + wave; m < M; m += (int64_t)gridDim.x * kBlkWaves) {
+        const uint4 *xr = x + m * dc, *dr = dy + m * dc;
+        uint4 kx[NC], kd[NC];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const int c = lane + kWave * i;
+            kx[i] = c < dc ? xr[c] : make_uint4(0, 0, 0, 0);
+            kd[i] = c < dc ? dr[c] : make_uint4(0, 0, 0, 0);
+        }
+        const float r = rstd[m];
+        float t = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const int c = lane + kWave * i;
+            if (c < dc) {
+                const uint4 v = kx[i], w = g[c], d = kd[i];
+                t += (xgd_word(v.x, w.x, d.x) + xgd_word(v.y, w.y, d.y)) + (xgd_word(v.z, w.z, d.z) + xgd_word(v.w, w.w, d.w));
+            }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, kWave);
+        const float k = ((r * r) * r) * (t * inv_d);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const int c = lane + kWave * i;
+            const uint32_t vw[4] = {kx[i].x, kx[i].y, kx[i].z, kx[i].w}, dw[4] = {kd[i].x, kd[i].y, kd[i].z, kd[i].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[i][2 * j] += bf16_lo(dw[j]) * (bf16_lo(vw[j]) * r);
+                acc[i][2 * j + 1] += bf16_hi(dw[j]) * (bf16_hi(vw[j]) * r);
+            }
+            if (dx && c < dc) {
+                const uint4 v = kx[i], w = g[c], d = kd[i];
+                uint4 o = make_uint4(dx_word(v.x, w.x, d.x, r, k), dx_word(v.y, w.y, d.y, r, k), dx_word(v.z, w.z, d.z, r, k),
+                                     dx_word(v.w, w.w, d.w, r, k));
+                if (res) {
+                    const uint4 a = res[m * dc + c];
+                    o = make_uint4(add_word(a.x, o.x), add_word(a.y, o.y), add_word(a.z, o.z), add_word(a.w, o.w));
+                }
+                dx[m * dc + c] = o;
+                mag = absmax_acc(mag, o);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[wave][(i * 8 + j) * kWave + lane] = acc[i][j];
+    __syncthreads();
+    // thread (i, lane) adds the four waves' sums of its chunks in wave order
+    for (int i = wave; i < NC; i += kBlkWaves) {
+        const int c = lane + kWave * i;
+        if (c >= dc) continue;
+        float s[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int at = (i * 8 + j) * kWave + lane;
+            s[j] = ((sum[0][at] + sum[1][at]) + sum[2][at]) + sum[3][at];
+        }
+        float4* out = reinterpret_cast<float4*>(partial + (int64_t)blockIdx.x * dc * 8 + c * 8);
+        out[0] = make_float4(s[0], s[1], s[2], s[3]);
+        out[1] = make_float4(s[4], s[5], s[6], s[7]);
+    }
+    if (amax_bits) {
+        const uint32_t m = wave_max_u32(pk_collapse(mag)) << 16;
+        if (lane == 0 && m > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, m);
+    }
+}
+
 // partial[strip][col] = sum over the strip's rows of dy * x * rstd.  Block: 64 columns x one strip
 // of rows; thread (cc, rr) owns 8 columns and every 32nd row.
 __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dg_partial_kernel(const uint16_t* __restrict__ x,
@@ -253,20 +343,32 @@ __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dg_partial_kernel(const u
     }
 }
 
-// dg[c] = sum over the strips, always in the same order: 64 columns per block, four groups of
-// threads take every fourth strip each, their four sums are added in group order.
+// dg[c] = sum over the strips, always in the same order: 16 columns per block, sixteen groups of
+// threads take every sixteenth strip each, their sums are added in group order.
 __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dg_final_kernel(const float* __restrict__ partial, int strips, int64_t D,
                                                                        float* __restrict__ dg)
 {
-    __shared__ float red[4][64];
-    const int cl = threadIdx.x & 63, part = threadIdx.x >> 6;
-    const int64_t c = (int64_t)blockIdx.x * 64 + cl;
+    __shared__ float red[16][16];
+    const int cl = threadIdx.x & 15, part = threadIdx.x >> 4;
+    const int64_t c = (int64_t)blockIdx.x * 16 + cl;
     float s = 0.0f;
-    if (c < D)
-        for (int i = part; i < strips; i += 4) s += partial[(int64_t)i * D + c];
+    if (c < D) {
+        int i = part;
+        for (; i + 48 < strips; i += 64) {
+            const float p0 = partial[(int64_t)i * D + c], p1 = partial[(int64_t)(i + 16) * D + c];
+            const float p2 = partial[(int64_t)(i + 32) * D + c], p3 = partial[(int64_t)(i + 48) * D + c];
+            s = (((s + p0) + p1) + p2) + p3;
+        }
+        for (; i < strips; i += 16) s += partial[(int64_t)i * D + c];
+    }
     red[part][cl] = s;
     __syncthreads();
-    if (part == 0 && c < D) dg[c] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
+    if (part == 0 && c < D) {
+        float v = red[0][cl];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) v += red[k][cl];
+        dg[c] = v;
+    }
 }
 
 static int elementwise_blocks(int64_t chunks)
@@ -357,6 +459,17 @@ static f8_status rmsnorm_bwd(const void* x_bf16, const void* g_bf16, const float
     if (dg && (!workspace || workspace_bytes_ < (size_t)(strips * D) * sizeof(float))) return F8_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (D == 0) return F8_OK;
+    // One pass (also for dg alone, so that its sums are the same) where a row fits the registers and the workspace holds a partial row of every block (two blocks per
+    // compute unit; f8_workspace_bytes always does from 16 rows on, a caller's smaller one may not).
+    const int64_t fused_blocks = (M + kBlkWaves - 1) / kBlkWaves < 512 ? (M + kBlkWaves - 1) / kBlkWaves : 512;
+    if (dg && M && D <= kFusedChunks * kWave * 8 && aligned16(workspace) &&
+        workspace_bytes_ >= (size_t)(fused_blocks * D) * sizeof(float)) {
+        rmsnorm_bwd_fused_kernel<<<(unsigned)fused_blocks, kBlkThreads, 0, st>>>(
+            (const uint4*)x_bf16, (const uint4*)g_bf16, rstd, (const uint4*)dy_bf16, M, (int)(D / 8), 1.0f / (float)D, (uint4*)dx_bf16,
+            (const uint4*)add_bf16, (float*)workspace, reinterpret_cast<uint32_t*>(amax_dx));
+        rmsnorm_dg_final_kernel<<<(unsigned)((D + 15) / 16), kBlkThreads, 0, st>>>((const float*)workspace, (int)fused_blocks, D, dg);
+        return last_launch_status();
+    }
     if (dx_bf16 && M) {
         int64_t nb = (M + kBlkWaves - 1) / kBlkWaves;
         if (nb > 8192) nb = 8192;
@@ -374,8 +487,7 @@ static f8_status rmsnorm_bwd(const void* x_bf16, const void* g_bf16, const float
         if (strips)
             rmsnorm_dg_partial_kernel<<<(unsigned)(strips * tiles_c), kBlkThreads, 0, st>>>(
                 (const uint16_t*)x_bf16, rstd, (const uint16_t*)dy_bf16, M, D, strip_rows, (float*)workspace, (int)tiles_c);
-        rmsnorm_dg_final_kernel<<<(unsigned)((D + 63) / 64), kBlkThreads, 0, st>>>(
-            (const float*)workspace, (int)strips, D, dg);
+        rmsnorm_dg_final_kernel<<<(unsigned)((D + 15) / 16), kBlkThreads, 0, st>>>((const float*)workspace, (int)strips, D, dg);
     }
     return last_launch_status();
 }

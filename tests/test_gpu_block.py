@@ -162,3 +162,41 @@ def test_block_glue_argument_errors():
     with pytest.raises(f8.F8Error) as e:
         f8.rmsnorm_bwd(x, x[0], rs, x, None, dg, None)   # dg needs the workspace
     assert e.value.code == 5
+
+
+@pytest.mark.parametrize("M,D,small_ws", [(48, 4096, False), (2064, 4112, False), (4112, 1024, True)])
+def test_rmsnorm_backward_one_pass_and_two(M, D, small_ws):
+    """Rows up to 4096 elements go through one kernel for dx and dg, longer ones (and callers with room for fewer
+    partial rows than blocks) through two: dx has the same bits either way, dg is the fp64 sum to 1e-5 of its terms."""
+    x, g, dy = gen((M, D), M).cuda(), gen((D,), D, 0.5).cuda(), gen((M, D), M + D, 1e-2).cuda()
+    rstd = 1.0 / torch.sqrt(x.float().square().mean(1) + 1e-5)
+    ws = torch.empty(64 * D * 4, dtype=torch.uint8, device="cuda") if small_ws else f8.new_workspace(M, D)
+    dx, dx2, dg = torch.empty_like(x), torch.empty_like(x), torch.empty(D, device="cuda")
+    f8.rmsnorm_bwd(x, g, rstd, dy, dx, dg, ws)
+    f8.rmsnorm_bwd(x, g, rstd, dy, dx2, None)
+    assert torch.equal(dx.view(torch.int16), dx2.view(torch.int16))
+    terms = dy.double() * x.double() * rstd.double()[:, None]
+    assert bool(((dg.double() - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0) + 1e-30).all())
+
+
+@pytest.mark.parametrize("S", [16, 4096, 1 << 20])
+def test_rope_angles_of_every_quadrant(S):
+    """The rotation of (1, 0) is (cos, sin) of the angle: against fp64, within one bf16 rounding, up to angles of
+    thousands of radians (position S - 1 of a long sequence, every frequency)."""
+    M, HD, theta = 16, 128, 500000.0
+    x = torch.zeros((M, HD), dtype=torch.bfloat16)
+    x[:, ::2] = 1.0
+    pos = torch.arange(M, dtype=torch.float64) if S == M else None
+    rows = x.repeat(S // M, 1) if S <= 4096 else None
+    if rows is None:                       # a long sequence: only its last 16 positions are compared
+        rows = torch.zeros((S, HD), dtype=torch.bfloat16)
+        rows[-M:] = x
+    out = torch.empty((S, HD), dtype=torch.bfloat16, device="cuda")
+    f8.rope(rows.cuda(), S, 1, HD, out, None, theta)
+    p = torch.arange(S - M, S, dtype=torch.float64) if pos is None else pos
+    a = p[:, None] * theta ** (-2.0 * torch.arange(HD // 2, dtype=torch.float64) / HD)[None, :]
+    got = out[-M:].cpu().double()
+    for c, ref in ((got[:, ::2], torch.cos(a)), (got[:, 1::2], torch.sin(a))):
+        # bf16 keeps seven bits after the leading one: half a unit is at most 2^-8 of the value (1 % more where the
+        # fp32 value falls the other way); and the fp32 of sine and cosine (absolute, near their zeros)
+        assert bool(((c - ref).abs() <= 2.0 ** -8 * ref.abs() * 1.01 + 2.0 ** -23).all())

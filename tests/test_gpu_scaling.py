@@ -247,3 +247,18 @@ def test_full_size_delayed_linear():
         sampled_check("dX", bits(dX), o.NN, qdy, o.E4M3, qw, o.E4M3, isdy, isw, o.TENSORWISE, rng)
         sampled_check("dW", bits(dW), o.TN, qdy, o.E4M3, qx, o.E4M3, isdy, isx, o.TENSORWISE, rng)
     assert (u8(saved.x.q) & 0x7F).max() == 0x7E             # the doubled batch saturated
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 255, 256, 257, 511, 1024])
+def test_history_push_lengths(n):
+    """Shift, maximum and scale at history lengths around the block's 256 threads, the largest entry anywhere."""
+    rng = np.random.default_rng(n)
+    hist = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    dev, new = torch.from_numpy(hist).cuda(), torch.full((1,), 0.25, device="cuda")
+    scale, inv = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    want = hist
+    for _ in range(3):
+        f8.amax_history_push(dev, new, f8.E4M3, scale, inv)
+        want = np.concatenate((np.float32([0.25]), want[:-1]))
+        assert np.array_equal(dev.cpu().numpy(), want)
+        assert scale.item() == np.float32(448.0) / want.max() and inv.item() == np.float32(1.0) / np.float32(scale.item())
