@@ -2,7 +2,8 @@
 // dX = dY W, dW = dY^T X) (kernels and launch logic; f8_gemm.hip holds the entry points,
 // f8_gemm_inst.hip is compiled once per operand-format pair and layout, in parallel).
 //
-// gemm_tile_kernel serves all three layouts and every shape (multiples of 16):
+// gemm_tile_kernel serves all three layouts and every shape (multiples of 16) but the smallest,
+// which gemm_small_kernel takes:
 // persistent workgroups, global -> LDS direct loads (no VGPR staging), two LDS stages,
 // v_mfma_f32_16x16x128_f8f6f4, scales folded into the fp32 epilogue, bf16 stores staged
 // through LDS.  An operand whose contraction index is the fast one in memory
@@ -686,6 +687,155 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// small products: 64 x 64 tiles, one per workgroup, a deep load queue
+// ---------------------------------------------------------------------------
+// A product with few tiles is bound by the latency of its loads: two LDS stages of a 128 x 128 tile hold 64 KB, and
+// a K step of 128 took 0.6 us where its arithmetic takes 0.25.  Here four waves (32 x 32 each) work on a 64 x 64
+// tile, so that four times as many compute units load, and 128 KB of LDS hold four pairs of K steps: three pairs are
+// under way while one is used, with one barrier per pair.  Loads past the end of the contraction or of the
+// matrix read zeros (buffer range check), also those that keep the queue's length constant at the end.  Same
+// instruction, same order of the contraction: the bits of gemm_tile_kernel.
+constexpr int kSm = 64, kSmPairs = 4;
+__device__ inline int kswz_small(int krow) { return ((krow >> 2) & 1) | (((krow >> 5) & 1) << 1); }  // four chunks per k-row
+
+template <int FA, int FB, int GRAN, bool AKM, bool BKM>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
+                                                         uint16_t* __restrict__ D, int M, int N, int K, int64_t lda, int64_t ldb,
+                                                         int64_t ldd, const float* __restrict__ isa, const float* __restrict__ isb,
+                                                         int tiles_n, uint32_t* __restrict__ amax_bits /* nullable */)
+{
+    constexpr int OP = kSm * kBK;  // bytes of an operand's K step
+    __shared__ __attribute__((aligned(1024))) uint8_t st[kSmPairs][2][2 * OP];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, fr = lane & 15, fg = lane >> 4;
+    const int m0 = (int)(blockIdx.x / (unsigned)tiles_n) * kSm, n0 = (int)(blockIdx.x % (unsigned)tiles_n) * kSm;
+
+    // this lane's 16 bytes of its wave's two 1 KB pieces of an operand's K step: offset from the step's base, k
+    struct Piece {
+        uint32_t off[2];
+        int k[2];
+    };
+    auto pieces = [&](auto KM, int64_t ld, int left /* rows of the matrix from the tile's first on */) {
+        Piece p;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            int row, chunk, inside;
+            if constexpr (decltype(KM)::value) {  // 16 k-rows of 64 bytes
+                row = 32 * wave + 16 * i + lane / 4, chunk = (lane & 3) ^ kswz_small(row), inside = 16 * chunk < left;
+                p.k[i] = row;
+            } else {  // 8 rows of 128 bytes
+                row = 16 * wave + 8 * i + lane / 8, chunk = (lane & 7) ^ swz(row), inside = row < left;
+                p.k[i] = 16 * chunk;
+            }
+            p.off[i] = (uint32_t)row * (uint32_t)ld + 16 * chunk;
+            if (!inside) p.k[i] = 1 << 30;  // never before the end of the contraction
+        }
+        return p;
+    };
+    const Piece pa = pieces(std::bool_constant<AKM>{}, lda, M - m0), pb = pieces(std::bool_constant<BKM>{}, ldb, N - n0);
+    const uint8_t* a_base = AKM ? A + m0 : A + (int64_t)m0 * lda;
+    const uint8_t* b_base = BKM ? B + n0 : B + (int64_t)n0 * ldb;
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    auto load = [&](const uint8_t* base, const Piece& p, int valid, uint8_t* lds) {
+        const v4u src = {(uint32_t)(uint64_t)base, (uint32_t)((uint64_t)base >> 32), kRecords, 0x00020000u};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t l32 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(lds + (2 * wave + i) * 1024);
+            const uint32_t o = p.k[i] < valid ? p.off[i] : kPastEnd;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(l32), "v"(o), "s"(src) : "memory");
+        }
+    };
+    auto request = [&](int pair) {  // eight loads per wave
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int kt = 2 * pair + s, valid = K - kt * kBK;
+            uint8_t* lds = st[pair % kSmPairs][s];
+            load(AKM ? a_base + (int64_t)kt * kBK * lda : a_base + (int64_t)kt * kBK, pa, valid, lds);
+            load(BKM ? b_base + (int64_t)kt * kBK * ldb : b_base + (int64_t)kt * kBK, pb, valid, lds + OP);
+        }
+    };
+    // fragment idx of the wave's 32 rows: 16 rows x 128 k, lane: row fr, k 32 fg .. + 31 (see gemm_tile_kernel)
+    auto fragment = [&](auto KM, const uint8_t* op, int w, int idx) {
+        if constexpr (decltype(KM)::value) {
+            const int krow = 32 * fg + (fr >> 1);
+            const uint8_t* p = op + krow * kSm + 16 * ((2 * w + idx) ^ kswz_small(krow)) + 8 * (fr & 1);
+            const v2i t0 = lds_read_tr8(p), t1 = lds_read_tr8(p + 8 * kSm), t2 = lds_read_tr8(p + 16 * kSm), t3 = lds_read_tr8(p + 24 * kSm);
+            return v8i{t0.x, t0.y, t1.x, t1.y, t2.x, t2.y, t3.x, t3.y};
+        } else {
+            const uint8_t* row = op + (32 * w + 16 * idx + fr) * kBK;
+            const int4 lo = *reinterpret_cast<const int4*>(row + 16 * ((2 * fg) ^ swz(fr)));
+            const int4 hi = *reinterpret_cast<const int4*>(row + 16 * ((2 * fg + 1) ^ swz(fr)));
+            return v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        }
+    };
+
+    v4f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int pairs = (K + 2 * kBK - 1) / (2 * kBK);
+#pragma unroll
+    for (int p = 0; p < kSmPairs - 1; ++p) request(p);
+    for (int p = 0; p < pairs; ++p) {
+        // all but the two newest pairs (16 loads) have landed; every wave is done with the pair before, whose
+        // place the request takes
+        static_assert(kSmPairs == 4, "the wait count");
+        asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        request(p + kSmPairs - 1);
+        v8i a[2][2], b[2][2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[s][i] = fragment(std::bool_constant<AKM>{}, st[p % kSmPairs][s], wm, i);
+                b[s][i] = fragment(std::bool_constant<BKM>{}, st[p % kSmPairs][s] + OP, wn, i);
+            }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b[s][j], a[s][i], acc[i][j], FB, FA, 0, 0, 0, 0);
+    }
+    // no load may still be writing LDS when the workgroup ends
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    float s_tensor = 0.f;
+    if constexpr (GRAN == F8_TENSORWISE) s_tensor = isa[0] * isb[0];
+    uint32_t amax_acc = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m = m0 + 32 * wm + 16 * i + fr;
+        if (m >= M) continue;
+        float sa = 0.f;
+        if constexpr (GRAN != F8_TENSORWISE) sa = isa[m];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = n0 + 32 * wn + 16 * j + 4 * fg;
+            if (n >= N) continue;
+            f2 lo, hi;
+            if constexpr (GRAN == F8_TENSORWISE) {
+                lo = f2{acc[i][j][0] * s_tensor, acc[i][j][1] * s_tensor}, hi = f2{acc[i][j][2] * s_tensor, acc[i][j][3] * s_tensor};
+            } else {
+                const float4 sb = *reinterpret_cast<const float4*>(isb + n);
+                lo = f2{(acc[i][j][0] * sa) * sb.x, (acc[i][j][1] * sa) * sb.y};
+                hi = f2{(acc[i][j][2] * sa) * sb.z, (acc[i][j][3] * sa) * sb.w};
+            }
+            uint2 o;
+            o.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2));
+            o.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2));
+            *reinterpret_cast<uint2*>(D + (int64_t)m * ldd + n) = o;
+            amax_acc = amax_pair(amax_acc, o);
+        }
+    }
+    if (amax_bits) {  // uniform; every thread of the block takes part
+        __syncthreads();
+        amax_publish<4>(amax_acc, amax_bits, reinterpret_cast<uint32_t*>(&st[0][0][0]));
+    }
+}
+
+// ---------------------------------------------------------------------------
 // split-K: sum of the ranges' partial results, scales, bf16
 // ---------------------------------------------------------------------------
 // partial[s][M][ldp] fp32, s < splits, added in the order s = 0, 1, ... (fixed: results are
@@ -812,7 +962,17 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
     const double c_half = rounds(tiles(256, 128)) * kHalfTile;
     const double c_quarter = rounds(tiles(128, 128)) * kQuarterTile;
     const bool rw = GRAN != F8_TENSORWISE;
-    if (ws && !amax_bits) {
+    // At most one 64 x 64 tile per compute unit: the deep load queue wins (operands not in the L2, old best / new in us:
+    // 64 x 4096 x 4096 19.5 / 10.2, 1008 x 1024 x 2816 15.0 / 8.8, 256 x 1024 x 512 5.6 / 4.1); with two rounds
+    // of tiles it does not (512 x 4096 x 4096 15.4 / 20.0).  A long contraction is better split (512 x 512 x 16384 31 /
+    // 31 row-major, 32 / 44 k-major; 1024 x 512 x 8192 26 / 18 and 27 / 28).
+    const bool small = tiles(kSm, kSm) <= cus, may_split = ws && !amax_bits;
+    if (small && !(may_split && K >= (AKM ? 8192 : 16384))) {
+        gemm_small_kernel<FA, FB, GRAN, AKM, BKM><<<(unsigned)tiles(kSm, kSm), 256, 0, st>>>(
+            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (N + kSm - 1) / kSm, amax_bits);
+        return;
+    }
+    if (may_split) {
         const double best = c_full < c_half ? (c_full < c_quarter ? c_full : c_quarter) : (c_half < c_quarter ? c_half : c_quarter);
         const int ranges = splitk_ranges(M, N, K, cus, best, ws_bytes);
         if (ranges > 1) {

@@ -335,11 +335,13 @@ def test_gemm_is_deterministic(M, N, K, layout):
         assert torch.equal(D.view(torch.int16), outs[0].view(torch.int16))
 
 
-# Contraction lengths around the K step (128) and the pair of LDS stages (256), and shapes that take the 128x128,
-# 256x128 and 256x256 tiles, the two-launch dispatch and the split contraction (with a workspace).
-RAGGED = [(272, 400, k, False) for k in (16, 112, 128, 144, 240, 272, 400, 528)] + [
+# Contraction lengths around the K step (128) and the pair of LDS stages (256), and shapes that take the 64x64,
+# 128x128, 256x128 and 256x256 tiles, the two-launch dispatch and the split contraction (with a workspace).
+RAGGED = [(272, 400, k, False) for k in (16, 112, 128, 144, 240, 272, 400, 528, 1040)] + [
+    (16, 16, 1296, False), (80, 64, 768, False),
     (4112, 4144, 304, False), (8192, 1040, 1040, False), (4368, 4112, 272, False),
-    (512, 1024, 4112, True), (272, 400, 2080, True), (2048, 4096, 8208, True)]
+    (1008, 1552, 272, False), (1040, 1040, 16, False), (1040, 1040, 528, False),
+    (512, 1024, 4112, True), (272, 400, 2080, True), (512, 512, 16400, True), (2048, 4096, 8208, True)]
 
 
 @pytest.mark.parametrize("layout", [o.NT, o.NN, o.TN])
@@ -365,3 +367,24 @@ def test_gemm_ragged_contraction_exact_arithmetic(layout, M, N, K, split):
     a, b = (torch.from_numpy(h) for h in host)
     exact = {o.NT: lambda: a @ b.T, o.NN: lambda: a @ b, o.TN: lambda: a.T @ b}[layout]() * 2.0 ** -14
     assert np.array_equal(bits(D), exact.to(torch.bfloat16).view(torch.uint16).numpy())
+
+
+@pytest.mark.parametrize("layout", [o.NT, o.NN, o.TN])
+@pytest.mark.parametrize("fa,fb", [(o.E4M3, o.E4M3), (o.E5M2, o.E4M3)])
+@pytest.mark.parametrize("M,N,K", [(16, 16, 256), (64, 128, 1280), (144, 208, 2064)])
+def test_gemm_small_kernel_has_the_bits_of_the_tile_kernel(layout, fa, fb, M, N, K):
+    """Same instruction, same order of the contraction: a product small enough for the 64x64-tile kernel equals the
+    corner of a larger one that embeds it (more rows and columns, same K), rowwise scales and amax included."""
+    rng = np.random.default_rng(M + K + layout)
+    BM, BN = 1040, 1104                                   # 17 x 18 tiles of 64: more than there are compute units
+    sa, sb = shapes_of(layout, BM, BN, K)
+    A, B = torch.from_numpy(rand_codes(rng, sa, fa)).cuda(), torch.from_numpy(rand_codes(rng, sb, fb)).cuda()
+    isa, isb = torch.rand(BM, device="cuda") + 0.5, torch.rand(BN, device="cuda") + 0.5
+    big = torch.empty((BM, BN), dtype=torch.bfloat16, device="cuda")
+    f8.gemm(layout, BM, BN, K, A, fa, B, fb, isa, isb, f8.ROWWISE, big)
+    D, amax = torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), torch.zeros(1, device="cuda")
+    a = A[:, :M] if layout == o.TN else A[:M]
+    b = B[:N] if layout == o.NT else B[:, :N]
+    f8.gemm(layout, M, N, K, a, fa, b, fb, isa, isb, f8.ROWWISE, D, amax_d=amax)
+    assert torch.equal(D.view(torch.int16), big[:M, :N].contiguous().view(torch.int16))
+    assert amax.item() == D.float().abs().max().item()
