@@ -11,11 +11,10 @@
 // only has to present the same keys in the same slots: it is read from a copy that is contiguous
 // along tokens (V^T in the forward, which f8_transpose_bf16 writes) or from the token-major tile by
 // transposing LDS reads (the backward).  No operand is transposed in registers.
-// Which token a row of the first operand is, is free: lane ln feeds token row_token(ln) of a
-// 32-token block, chosen so that registers 8u .. 8u + 7 hold EIGHT CONSECUTIVE tokens, 16u + 8g ..
-// + 7, and the matching operand of the next product is one 16-byte LDS read.  (In lane order they
-// are two runs of four, two 8-byte reads, which cost 1.5 times the LDS time and twice the
-// instructions; 1.5 % of the attention of 1 x 8192 tokens.)
+// Registers 8u .. 8u + 7 of lane group g hold tokens 16u + 4g + {0..3} and 16u + 8 + 4g + {0..3} of their 32-token
+// block (reg_token), which the other operand presents in two reads of four.  (An order with eight consecutive
+// tokens, one 16-byte read, is 1.5 % faster; but the sums then round differently, which the fp8 casts of a block
+// amplify to 1e-2 and more of its gradients, and results would not compare with earlier ones.)
 #include <atomic>
 #include <type_traits>
 #include <utility>
@@ -55,28 +54,28 @@ __device__ inline uint4 slots(const f32x16& c, int u)
                       pack2(c[8 * u + 6], c[8 * u + 7]));
 }
 
-// the token of a 32-token block that lane ln (0 .. 31) feeds as a row of the first operand: ln with
-// bits 2 and 3 exchanged; register r of lane group g then holds token reg_token(r, g) of the block
-__device__ inline int row_token(int ln) { return (ln & 0x13) | ((ln & 4) << 1) | ((ln & 8) >> 1); }
-__device__ inline int reg_token(int r, int g) { return 16 * (r >> 3) + 8 * g + (r & 7); }
+// the token of a 32-token block that register r of lane group g holds
+__device__ inline int reg_token(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
 
-// N products use(i, frag(i)) whose LDS operand reads (one DS instruction each) run AHEAD products
+// N products use(i, frag(i)) whose LDS operand reads run AHEAD products
 // ahead of their use.  Left to itself the scheduler reads each operand right before its product
 // and every product waits out the LDS latency; the group barriers pin the interleaving.
-template <int N, int AHEAD, class Frag, class Use>
+// ONE: the first ONE operands take one DS read, the others two.
+template <int N, int AHEAD, int ONE = N, class Frag, class Use>
 __device__ inline void pipelined_products(Frag frag, Use use)
 {
     uint4 f[N];
 #pragma unroll
-    for (int i = 0; i < AHEAD && i < N; ++i) f[i] = frag(i);
-    __builtin_amdgcn_sched_group_barrier(0x100, AHEAD < N ? AHEAD : N, 0);  // DS reads
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if (i + AHEAD < N) f[i + AHEAD] = frag(i + AHEAD);
-        use(i, f[i]);
-        if (i + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
-    }
+    for (int i = 0; i < AHEAD; ++i) f[i] = frag(i);
+    __builtin_amdgcn_sched_group_barrier(0x100, AHEAD <= ONE ? AHEAD : 2 * AHEAD - ONE, 0);  // DS reads
+    [&]<int... I>(std::integer_sequence<int, I...>) {
+        (..., [&] {
+            if constexpr (I + AHEAD < N) f[I + AHEAD] = frag(I + AHEAD);
+            use(I, f[I]);
+            if constexpr (I + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, I + AHEAD < ONE ? 1 : 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+        }());
+    }(std::make_integer_sequence<int, N>{});
 }
 // The same with the first STARTED operands read beforehand (in the phase before), and two DS
 // instructions for operand i if two(i) (transposing reads, or both operands from LDS).  frag(i) may be
@@ -182,12 +181,12 @@ struct TileStream {
     }
 };
 // LDS offsets of this lane's operand reads from a [tokens][kHd] tile of a TileStream.
-// Contraction over hd: chunk 2 s + g of token row_token(ln); the tile's 32-token blocks are 32 * kHd apart.
+// Contraction over hd: chunk 2 s + g of token ln; the tile's 32-token blocks are 32 * kHd apart.
 struct RowFrags {
     int at;  // of s = 0; the chunk's permutation is an XOR, so that of s is another one
     __device__ void start(int lane)
     {
-        const int row = row_token(lane & 31);
+        const int row = lane & 31;
         at = row * kHd + 8 * TileStream<64, kHd, 8, false>::swizzle(row, lane >> 5);
     }
     __device__ uint4 read(const uint16_t* tile, int block32, int s) const
@@ -197,15 +196,15 @@ struct RowFrags {
     // Called once a step, it keeps the compiler from holding every s's offset in a register of its own.
     __device__ void renew() { asm volatile("" : "+v"(at)); }
 };
-// Contraction over tokens: the operand that matches slots(c, u), rows hd 32 d + ln, tokens 16 u + 8 g + {0..7}, formed
-// by two transposing reads: within 16 lanes, lane i gets element i % 4 of the 8-byte pieces that lanes i / 4,
+// Contraction over tokens: the operand that matches slots(c, u), rows hd 32 d + ln, tokens 16 u + 4 g + {0..3} and
+// 16 u + 8 + 4 g + {0..3}, by a transposing read each: within 16 lanes, lane i gets element i % 4 of the 8-byte pieces that lanes i / 4,
 // 4 + i / 4, 8 + i / 4 and 12 + i / 4 point at.  So lane i points at token i / 4 (of four), hd 4 (i % 4).
 struct TokenFrags {
     int at;  // of d = 0, first of the two reads
     __device__ void start(int lane)
     {
         const int g = lane >> 5, a = (lane >> 4) & 1, i = lane & 15;
-        const int row = 8 * g + i / 4, col = 16 * a + 4 * (i % 4);
+        const int row = 4 * g + i / 4, col = 16 * a + 4 * (i % 4);
         at = row * kHd + 8 * TileStream<64, kHd, 8, false>::swizzle(row, col / 8) + col % 8;
     }
     __device__ void renew() { asm volatile("" : "+v"(at)); }
@@ -215,8 +214,8 @@ struct TokenFrags {
         typedef __attribute__((address_space(3))) v4s* lds_v4s;
         const uint16_t* p = tile + 16 * kHd * block16;
         const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + (at ^ (32 * d)))));
-        // four tokens further down: the permutation of those rows differs in its lowest bit
-        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 4 * kHd + (at ^ (32 * d + 8)))));
+        // eight tokens further down: the permutation of those rows differs in bit 1
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 8 * kHd + (at ^ (32 * d + 16)))));
         return make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
 };
@@ -236,7 +235,7 @@ static bool far_rows(int64_t rows, int64_t ld) { return 2 * (rows * ld + kHd) >=
 // (what it held was read up to slot 2t - 1) and waited for at the end of the wave's next phase M.
 // Measured (1 x 8192 tokens, 32/8 heads; cycles of a slot, both phases in it): M 1300 (32 products are 1024), V
 // 1400 (softmax 1080 to 1300, the four loads the rest: a wave's load holds up its next instruction until the memory
-// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 590 us; this: 530.
+// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 590 us; this: 550.
 template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(const uint16_t* __restrict__ Q, int64_t ldq,
                                                                 const uint16_t* __restrict__ K, int64_t ldk,
@@ -297,12 +296,13 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     ks.template request<true, true>(sK[0], wave, kBk * ldk, 0, S);
     request(std::true_type{}, 0, 0);
 
-    // LDS offsets of this lane's operand reads: of a key's row, chunk 2 v + g of hd row ln
+    // LDS offsets of this lane's operand reads: of a key's row; of hd row ln, 4 g tokens into chunk 2 v, and (the
+    // permutation is an XOR) the same of chunk 2 v + 1
     RowFrags k_rd;
     k_rd.start(lane);
     int v_rd[kBk / 16];
 #pragma unroll
-    for (int v = 0; v < kBk / 16; ++v) v_rd[v] = ln * kBk + 8 * VStream::swizzle(ln, 2 * v + g);
+    for (int v = 0; v < kBk / 16; ++v) v_rd[v] = ln * kBk + 8 * VStream::swizzle(ln, 2 * v) + 4 * g;
 
     // products [LO, HI) of M_t: 0 .. 15 S^T = K Q^T (tile K_t+1), 16 .. 31 O^T += V^T P^T (tile V_t,
     // [128 hd][32 queries], contraction over the 64 keys in four 16-slot steps).  The matrix phase goes
@@ -312,11 +312,13 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         const uint16_t *tK = sK[buf == 2 ? 0 : buf + 1], *tV = sV[buf];
         if constexpr (lo == 0) sc[0] = f32x16{0}, sc[1] = f32x16{0};
         __builtin_amdgcn_s_setprio(1);
-        pipelined_products<hi - lo, kFwdAhead>(
+        pipelined_products<hi - lo, kFwdAhead, 16 - lo>(
             [&](int n) {
                 const int i = n + lo;
-                return i < 16 ? k_rd.read(tK, i % 2, i / 2 % 8)
-                              : *reinterpret_cast<const uint4*>(tV + 32 * kBk * (i % 4) + v_rd[i / 4 % 4]);
+                if (i < 16) return k_rd.read(tK, i % 2, i / 2 % 8);
+                const uint16_t* v = tV + 32 * kBk * (i % 4);
+                const uint2 a = *reinterpret_cast<const uint2*>(v + v_rd[i / 4 % 4]), b = *reinterpret_cast<const uint2*>(v + (v_rd[i / 4 % 4] ^ 8));
+                return make_uint4(a.x, a.y, b.x, b.y);
             },
             [&](int n, uint4 f) {
                 const int i = n + lo;
@@ -364,18 +366,18 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
                 for (int r = 0; r < 16; ++r) acc_o[d][r] *= alpha;
         }
         const float neg_m = -m_run * scale_log2e;
-        float psum[2] = {0.0f, 0.0f};
+        float psum = 0.0f;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], scale_log2e, neg_m));
                 sc[kb][r] = p;
-                psum[r & 1] += p;
+                psum += p;
             }
             pf[2 * kb] = slots(sc[kb], 0), pf[2 * kb + 1] = slots(sc[kb], 1);
         }
-        l_run += psum[0] + psum[1];
+        l_run += psum;
         for (int i = 0; i < 4; ++i) computed(pf[i]);
         computed(l_run);
     };
@@ -453,7 +455,7 @@ __global__ void zero_amax_kernel(uint32_t* p) { p[0] = 0; }
 //   V_t: dS_t+1 = P (dP - delta)
 // Tiles t live in buffer t % 4: M_t reads K_t, K_t+1 and V_t+1; K_t+3 and V_t+3 are requested at the end of V_t.
 // K^T comes from the K tile itself, by transposing reads.  (All waves in step, three tiles through registers: 821 us for
-// 1 x 8192 tokens, 32/8 heads; this: 690.  Phase M is what it waits for: 48 products, 1536 cycles, in about 1900.)
+// 1 x 8192 tokens, 32/8 heads; this: 700.  Phase M is what it waits for: 48 products, 1536 cycles, in about 1900.)
 template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
     const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
@@ -558,7 +560,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
         for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][r], scale_log2e, -lse2));
+                float p = __builtin_amdgcn_exp2f(sc[kb][r] * scale_log2e - lse2);
                 if constexpr (decltype(MASKED)::value) {
                     if (t * kBk + 32 * kb + reg_token(r, g) > q_pos) p = 0.0f;
                 }
@@ -616,15 +618,15 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
 }
 
 // dV^T = dO^T P and dK^T = Q^T dS in one pass over the scores.  One block: 8 waves, 32 keys each (one key per lane),
-// of one (sequence, query head); 32-query steps from the end of the sequence down to the diagonal, in two
-// staggered halves like the forward (see there):
+// of one (sequence, query head); steps of 32 queries, in pairs from the end of the sequence down to the diagonal (the
+// lower half of a pair first), in two staggered halves like the forward (see there):
 //   M_t: dV += dO_t^T P_t, dK += Q_t^T dS_t (8 products each), then S = Q_t+1 K^T, dP = dO_t+1 V^T (8 each)
 //   V_t: P_t+1 = exp(S - lse), dS_t+1 = P (dP - delta)
 // Tiles t (Q, dO and their lse, delta) live in buffer t % 4; those of step t + 3 are requested at the end of V_t.
 // Q^T and dO^T come from the same tiles by transposing reads.  The two accumulators (128 registers), the K
 // operand (32), scores and operands leave no room for the V operand: the block's 256 rows of V stay in LDS.
 // (dK and dV in a kernel each, 40 products a step instead of 32 and the exponentials twice, all waves in step: 1490 us for
-// 1 x 8192 tokens, 32/8 heads; this: 990.)
+// 1 x 8192 tokens, 32/8 heads; this: 1010.)
 constexpr int kDkvQ = 32;  // queries per step
 template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
@@ -651,21 +653,23 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     const int64_t tok = tok0 + (k_ok ? key_pos : 0);
 
     const int q_start = kt * KB;
-    const int steps = (S - q_start + kDkvQ - 1) / kDkvQ;  // >= 1: the block exists only if q_start < S
-    const int t_last = max(0, steps - 1 - wave);          // step t: queries q0(t) ..; this wave's last one is its diagonal
-    auto q0 = [&](int t) { return q_start + (steps - 1 - t) * kDkvQ; };
+    const int pairs = (S - q_start + 2 * kDkvQ - 1) / (2 * kDkvQ);  // >= 1: the block exists only if q_start < S
+    const int steps = 2 * pairs;
+    const int t_last = 2 * max(0, pairs - 1 - wave / 2) + 1;  // the pair of steps t_last - 1, t_last holds this wave's diagonal
+    auto q0 = [&](int t) { return q_start + (pairs - 1 - t / 2) * (2 * kDkvQ) + (t & 1) * kDkvQ; };  // step t: queries q0(t) ..
 
     using Stream = TileStream<kDkvQ, kHd, NW, FAR>;
     Stream qs, os;
     qs.start(Q + (tok0 + q0(0)) * ldq + (int64_t)hq * kHd, ldq, wave, lane);
     os.start(dO + (tok0 + q0(0)) * lddo + (int64_t)hq * kHd, lddo, wave, lane);
     const float *lse_b = lse + (int64_t)hq * M + tok0, *delta_b = delta + (int64_t)hq * M + tok0;
-    auto request = [&](auto EDGE, int t) {  // EDGE: may lie past the last step, or (step 0) reach past S
+    auto request = [&](auto EDGE, int t) {  // in order.  EDGE: may lie past the last step, or (the first pair) past S
         constexpr bool edge = decltype(EDGE)::value;
         if (edge && t >= steps) return;
         const int buf = t & 3;
-        qs.template request<edge, true>(sQ[buf], wave, -kDkvQ * ldq, q0(t), S);
-        os.template request<edge, true>(sD[buf], wave, -kDkvQ * lddo, q0(t), S);
+        const int on = (t & 1) ? -3 * kDkvQ : kDkvQ;  // rows to the next step's tile
+        qs.template request<edge, true>(sQ[buf], wave, on * ldq, q0(t), S);
+        os.template request<edge, true>(sD[buf], wave, on * lddo, q0(t), S);
         if (wave == NW - 1) {
             int l64 = threadIdx.x;  // (formed anew: held over the loop, the pointer costs registers that are not there)
             asm volatile("" : "+v"(l64));
@@ -741,7 +745,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     };
     using C16 = std::integral_constant<int, 16>;
     using C32 = std::integral_constant<int, 32>;
-    // Queries at or beyond S read as zero rows with lse = delta = 0: they add nothing.  MASKED: the wave's diagonal.
+    // Queries at or beyond S read as zero rows with lse = delta = 0: they add nothing.  MASKED: the diagonal's pair.
     auto grad_scores = [&](int t, auto MASKED) {
         const float* st = sStat[t & 3];
 #pragma unroll
@@ -755,7 +759,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 8 * u + 4 * j + i;
-                    float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, lv[i] * -1.4426950408889634074f));
+                    float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - lv[i] * 1.4426950408889634074f);
                     if constexpr (decltype(MASKED)::value) {
                         if (key_pos > q0(t) + ql + i) p = 0.0f;
                     }
@@ -774,9 +778,9 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
         stream_wait();
         phase_barrier();
     };
-    auto step = [&](auto EDGE) {
+    auto step = [&](auto EDGE, auto MASKED) {
         end_of_m();
-        grad_scores(t + 1, std::false_type{});
+        grad_scores(t + 1, MASKED);
         __builtin_amdgcn_sched_barrier(0);
         request(EDGE, t + 3);
         start_products(++t);
@@ -789,9 +793,10 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     sc = dp = f32x16{0};
 #pragma unroll
     for (int j = 0; j < 16; ++j) score_product(j, score_operands(0, j));
-    const int t_inside = min(t_last - 1, steps - 3);
-    while (t < t_inside) step(std::false_type{});
-    while (t < t_last - 1) step(std::true_type{});
+    const int t_inside = min(t_last - 2, steps - 3);
+    while (t < t_inside) step(std::false_type{}, std::false_type{});
+    while (t < t_last - 2) step(std::true_type{}, std::false_type{});
+    step(std::true_type{}, std::true_type{});  // scores of t_last - 1
     for (; t < steps; ++t) {
         end_of_m();
         if (t == t_last - 1) {
