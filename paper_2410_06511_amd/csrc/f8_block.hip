@@ -31,29 +31,6 @@ __device__ inline uint32_t rotate_word(uint32_t w, float c, float s)
     return pack_bf16(x0 * c - x1 * s, x0 * s + x1 * c);
 }
 
-// Sine and cosine of a in fp32: the angle reaches thousands of radians, so the multiple of pi / 2 is taken off in
-// fp64; what is left, within +-pi / 4, goes into the Taylor polynomials (the first terms left out are 2e-9 of the
-// sine and 2e-9 of the cosine).  A third of the instructions of sincosf on an argument up to pi, which bound the kernel
-// where a block has few heads: 4000 x 16 heads, both outputs, 16.4 -> 13.3 us; one output 12.3 -> 9.8.
-__device__ inline void sincos_of(double a, float* sn, float* cs)
-{
-    const double q = rint(a * 0.63661977236758134307553505349006);
-    const float x = (float)__builtin_fma(-q, 1.5707963267948966192313216916398, a);
-    const int n = (int)(q - 4.0 * floor(q * 0.25));  // quadrant, 0 .. 3
-    const float z = x * x;
-    float s = __builtin_fmaf(z, 2.7557319e-6f, -1.9841270e-4f);
-    s = __builtin_fmaf(z, s, 8.3333333e-3f);
-    s = __builtin_fmaf(z, s, -1.6666667e-1f);
-    s = __builtin_fmaf(x * z, s, x);
-    float c = __builtin_fmaf(z, -2.7557319e-7f, 2.4801587e-5f);
-    c = __builtin_fmaf(z, c, -1.3888889e-3f);
-    c = __builtin_fmaf(z, c, 4.1666667e-2f);
-    c = __builtin_fmaf(z * z, c, __builtin_fmaf(-0.5f, z, 1.0f));
-    const float u = (n & 1) ? c : s, v = (n & 1) ? s : c;
-    *sn = (n & 2) ? -u : u;
-    *cs = ((n + 1) & 2) ? -v : v;
-}
-
 // x [rows, nh * hd] (row pitch ldx) -> out (row pitch ldo; ROTATE: pairs of adjacent columns turned
 // by pos * freq) and out_t [nh * hd, rows] (packed).  One block: a 64x64 tile at the same place of
 // `hpb` consecutive heads, one head after the other: the sines and cosines depend on the row and
@@ -84,7 +61,11 @@ __global__ __launch_bounds__(kBlkThreads) void rope_tile_kernel(const uint16_t* 
             const double pos = (double)(r % S);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                sincos_of(pos * fr.f[col_ok ? (cih >> 1) + j : 0], &sn[i][j], &cs[i][j]);
+                // the angle reaches thousands of radians: product and reduction to
+                // [-pi, pi] in fp64, sine and cosine of the remainder in fp32
+                const double a = pos * fr.f[col_ok ? (cih >> 1) + j : 0];
+                const double red = a - 6.283185307179586476925286766559 * rint(a * 0.15915494309189533576888376337251);
+                sincosf((float)red, &sn[i][j], &cs[i][j]);
                 sn[i][j] *= sign;
             }
         }
@@ -383,9 +364,10 @@ template <bool ROTATE>
 static f8_status launch_rope_tiles(const void* x, int64_t rows, int64_t nh, int64_t hd, int64_t ldx, int64_t ldo, int64_t S,
                                    float sign, const RopeFreq& fr, void* out, void* out_t, float* amax, hipStream_t st)
 {
-    // heads per block: as many as leave about four blocks per compute unit
+    // heads per block: as many as leave about four blocks per compute unit, or, since the sines and cosines bound a
+    // block of few heads, two where they are taken (4000 x 16 heads: one output 12.3 -> 9.6 us, both 16.4 -> 16.1)
     const int64_t tiles_r = (rows + kRt - 1) / kRt, tph = (hd + kRt - 1) / kRt;
-    int64_t hpb = (tiles_r * tph * nh) / 1024;
+    int64_t hpb = (tiles_r * tph * nh) / (ROTATE ? 512 : 1024);
     if (hpb < 1) hpb = 1;
     if (hpb > 8) hpb = 8;
     if (hpb > nh) hpb = nh;
