@@ -720,7 +720,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     auto grad_operands = [&](int t, int i) {
         return Operands{tok_rd.read(i < 8 ? sD[t & 3] : sQ[t & 3], (i / 4) % 2, i % 4), i < 8 ? pf[(i / 4) % 2] : ds[(i / 4) % 2]};
     };
-    constexpr int STARTED = 1;  // (two, or four operands ahead, do not fit the registers)
+    constexpr int STARTED = 1;  // (two, and four operands ahead, were no faster)
     Operands started[STARTED];  // read at the end of phase V: these tiles landed a step ago
     auto start_products = [&](int t) {
         tok_rd.renew();
