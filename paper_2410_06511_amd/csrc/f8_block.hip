@@ -198,18 +198,18 @@ __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dx_kernel(const uint4* __
 }
 
 // dx and dg from one read of x and dy (D up to 4096): a wave walks rows and keeps, beside the row, the sums of
-// dy * x * rstd of its own rows for its 64 columns in registers; the block's four sets meet in LDS and leave one
-// partial row, partial[block][D].  8192 x 4096 with the residual: 94 us
-// with the final sum, 105 as two passes.
-constexpr int kFusedChunks = 8;  // 16-byte chunks of a row per lane
+// dy * x * rstd of its own rows for its columns in registers; the block's four sets meet in LDS and leave one
+// partial row, partial[block][D].  NC: 16-byte chunks of a row per lane, so that a short row pays for no more
+// registers, LDS and chunks than it has (2048 x 512 with eight always 10.5 us, as two passes 9.2, so 8.1).
+// 8192 x 4096 with the residual: 94 us with the final sum, 105 as two passes.
+template <int NC>
 __global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const uint4* __restrict__ x, const uint4* __restrict__ g,
                                                                            const float* __restrict__ rstd, const uint4* __restrict__ dy,
-                                                                           int64_t M, int dc, float inv_d, uint4* __restrict__ dx /* nullable */,
+                                                                           int64_t M, int dc, float inv_d, uint4* __restrict__ dx,
                                                                            const uint4* __restrict__ res /* nullable: added to dx */,
                                                                            float* __restrict__ partial,
                                                                            uint32_t* __restrict__ amax_bits /* nullable: max-updated */)
 {
-    constexpr int NC = kFusedChunks;
     __shared__ float sum[kBlkWaves][NC * kWave * 8];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     uint32_t mag = 0;
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const
                 acc[i][2 * j] += bf16_lo(dw[j]) * (bf16_lo(vw[j]) * r);
                 acc[i][2 * j + 1] += bf16_hi(dw[j]) * (bf16_hi(vw[j]) * r);
             }
-            if (dx && c < dc) {
+            if (c < dc) {
                 const uint4 v = kx[i], w = g[c], d = kd[i];
                 uint4 o = make_uint4(dx_word(v.x, w.x, d.x, r, k), dx_word(v.y, w.y, d.y, r, k), dx_word(v.z, w.z, d.z, r, k),
                                      dx_word(v.w, w.w, d.w, r, k));
@@ -285,6 +285,46 @@ __global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const
         const uint32_t m = wave_max_u32(pk_collapse(mag)) << 16;
         if (lane == 0 && m > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, m);
     }
+}
+
+// dg alone, with the sums of rmsnorm_bwd_fused_kernel and rmsnorm_dg_final_kernel in their order.  No sum over a row is
+// needed here, so the rows are cut into pieces of 64 columns, and of a piece one block takes every sixteenth of the
+// fused kernel's row blocks: what one of the final kernel's groups adds, which leaves 16 partial rows (read as if by
+// one block each) instead of up to 512.  Thread (cl, w, rl): 8 columns of wave w's rows of row block part + 16 rl.
+// 1008 x 4096 6.6 us, 2048 x 4096 9.8, 8192 x 4096 25; by the fused kernel 13, 18 and 39, as strips of rows (below) 6.4, 10.7
+// and 28.
+constexpr int kFinalGroups = 16;  // of the final kernel
+constexpr int kDgParts = kFinalGroups, kDgPieces = 8 /* of 16 bytes */, kRowBlocks = 512;
+static_assert(2 * kDgPieces * kBlkWaves == kWave, "a wave holds two row blocks");
+__global__ __launch_bounds__(kDgPieces* kBlkWaves*(kRowBlocks / kDgParts)) void rmsnorm_dg_only_kernel(
+    const uint4* __restrict__ x, const float* __restrict__ rstd, const uint4* __restrict__ dy, int64_t M, int dc, int row_blocks,
+    float* __restrict__ partial, int parts)
+{
+    __shared__ float sum[kRowBlocks / kDgParts][kBlkWaves][kDgPieces * 8];
+    const int cl = threadIdx.x % kDgPieces, w = threadIdx.x / kDgPieces % kBlkWaves, rl = threadIdx.x / (kDgPieces * kBlkWaves);
+    const int part = (int)(blockIdx.x % (unsigned)parts), c0 = (int)(blockIdx.x / (unsigned)parts) * kDgPieces;
+    const int rb = part + kDgParts * rl, c = c0 + cl;
+    float acc[8] = {};
+    if (rb < row_blocks && c < dc)
+        for (int64_t m = (int64_t)rb * kBlkWaves + w; m < M; m += (int64_t)row_blocks * kBlkWaves) {
+            const uint4 v = x[m * dc + c], d = dy[m * dc + c];
+            const float r = rstd[m];
+            const uint32_t vw[4] = {v.x, v.y, v.z, v.w}, dw[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[2 * j] += bf16_lo(dw[j]) * (bf16_lo(vw[j]) * r);
+                acc[2 * j + 1] += bf16_hi(dw[j]) * (bf16_hi(vw[j]) * r);
+            }
+        }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum[rl][w][8 * cl + j] = acc[j];
+    __syncthreads();
+    const int col = c0 * 8 + (int)threadIdx.x;
+    if (threadIdx.x >= kDgPieces * 8 || col >= dc * 8) return;
+    float s = 0.0f;
+    for (int i = 0; part + kDgParts * i < row_blocks; ++i)
+        s += ((sum[i][0][threadIdx.x] + sum[i][1][threadIdx.x]) + sum[i][2][threadIdx.x]) + sum[i][3][threadIdx.x];
+    partial[(int64_t)part * dc * 8 + col] = s;
 }
 
 // partial[strip][col] = sum over the strip's rows of dy * x * rstd.  Block: 64 columns x one strip
@@ -324,32 +364,41 @@ __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dg_partial_kernel(const u
     }
 }
 
-// dg[c] = sum over the strips, always in the same order: 16 columns per block, sixteen groups of
+// dg[c] = sum over the strips, always in the same order: 32 columns per block, sixteen groups of
 // threads take every sixteenth strip each, their sums are added in group order.
-__global__ __launch_bounds__(kBlkThreads) void rmsnorm_dg_final_kernel(const float* __restrict__ partial, int strips, int64_t D,
+constexpr int kFinalCols = 32;
+__global__ __launch_bounds__(kFinalGroups * kFinalCols) void rmsnorm_dg_final_kernel(const float* __restrict__ partial, int strips, int64_t D,
                                                                        float* __restrict__ dg)
 {
-    __shared__ float red[16][16];
-    const int cl = threadIdx.x & 15, part = threadIdx.x >> 4;
-    const int64_t c = (int64_t)blockIdx.x * 16 + cl;
+    __shared__ float red[kFinalGroups][kFinalCols];
+    const int cl = threadIdx.x % kFinalCols, part = threadIdx.x / kFinalCols;
+    const int64_t c = (int64_t)blockIdx.x * kFinalCols + cl;
     float s = 0.0f;
     if (c < D) {
-        int i = part;
-        for (; i + 48 < strips; i += 64) {
-            const float p0 = partial[(int64_t)i * D + c], p1 = partial[(int64_t)(i + 16) * D + c];
-            const float p2 = partial[(int64_t)(i + 32) * D + c], p3 = partial[(int64_t)(i + 48) * D + c];
-            s = (((s + p0) + p1) + p2) + p3;
+        constexpr int AHEAD = 8;  // loads in flight: the sum is one chain, and its loads are what it waits for
+        for (int i = part; i < strips; i += kFinalGroups * AHEAD) {
+            float p[AHEAD];
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) {
+                const int at = i + kFinalGroups * k;
+                p[k] = at < strips ? partial[(int64_t)at * D + c] : 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) s += p[k];
         }
-        for (; i < strips; i += 16) s += partial[(int64_t)i * D + c];
     }
     red[part][cl] = s;
     __syncthreads();
     if (part == 0 && c < D) {
         float v = red[0][cl];
 #pragma unroll
-        for (int k = 1; k < 16; ++k) v += red[k][cl];
+        for (int k = 1; k < kFinalGroups; ++k) v += red[k][cl];
         dg[c] = v;
     }
+}
+static void launch_dg_final(const float* partial, int64_t strips, int64_t D, float* dg, hipStream_t st)
+{
+    rmsnorm_dg_final_kernel<<<(unsigned)((D + kFinalCols - 1) / kFinalCols), kFinalGroups * kFinalCols, 0, st>>>(partial, (int)strips, D, dg);
 }
 
 static int elementwise_blocks(int64_t chunks)
@@ -441,15 +490,27 @@ static f8_status rmsnorm_bwd(const void* x_bf16, const void* g_bf16, const float
     if (dg && (!workspace || workspace_bytes_ < (size_t)(strips * D) * sizeof(float))) return F8_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (D == 0) return F8_OK;
-    // One pass (also for dg alone, so that its sums are the same) where a row fits the registers and the workspace holds a partial row of every block (two blocks per
+    // One pass where a row fits the registers and the workspace holds a partial row of every block (two per
     // compute unit; f8_workspace_bytes always does from 16 rows on, a caller's smaller one may not).
-    const int64_t fused_blocks = (M + kBlkWaves - 1) / kBlkWaves < 512 ? (M + kBlkWaves - 1) / kBlkWaves : 512;
-    if (dg && M && D <= kFusedChunks * kWave * 8 && aligned16(workspace) &&
-        workspace_bytes_ >= (size_t)(fused_blocks * D) * sizeof(float)) {
-        rmsnorm_bwd_fused_kernel<<<(unsigned)fused_blocks, kBlkThreads, 0, st>>>(
-            (const uint4*)x_bf16, (const uint4*)g_bf16, rstd, (const uint4*)dy_bf16, M, (int)(D / 8), 1.0f / (float)D, (uint4*)dx_bf16,
-            (const uint4*)add_bf16, (float*)workspace, reinterpret_cast<uint32_t*>(amax_dx));
-        rmsnorm_dg_final_kernel<<<(unsigned)((D + 15) / 16), kBlkThreads, 0, st>>>((const float*)workspace, (int)fused_blocks, D, dg);
+    const int64_t blocks = (M + kBlkWaves - 1) / kBlkWaves < kRowBlocks ? (M + kBlkWaves - 1) / kBlkWaves : kRowBlocks;
+    if (dg && M && D <= 8 * kWave * 8 && aligned16(workspace) && workspace_bytes_ >= (size_t)(blocks * D) * sizeof(float)) {
+        const int dc = (int)(D / 8), chunks = (dc + kWave - 1) / kWave;  // 16-byte chunks of a row, in all and per lane
+        int strips = (int)blocks;
+        if (dx_bf16) {
+            const auto kernel = chunks == 1   ? rmsnorm_bwd_fused_kernel<1>
+                                : chunks == 2 ? rmsnorm_bwd_fused_kernel<2>
+                                : chunks <= 4 ? rmsnorm_bwd_fused_kernel<4>
+                                              : rmsnorm_bwd_fused_kernel<8>;
+            kernel<<<(unsigned)blocks, kBlkThreads, 0, st>>>((const uint4*)x_bf16, (const uint4*)g_bf16, rstd, (const uint4*)dy_bf16, M, dc,
+                                                             1.0f / (float)D, (uint4*)dx_bf16, (const uint4*)add_bf16,
+                                                             (float*)workspace, reinterpret_cast<uint32_t*>(amax_dx));
+        } else {
+            strips = blocks < kDgParts ? (int)blocks : kDgParts;
+            const unsigned dg_threads = (unsigned)((blocks + 2 * kDgParts - 1) / (2 * kDgParts)) * 2 * kDgPieces * kBlkWaves;  // whole waves
+            rmsnorm_dg_only_kernel<<<(unsigned)(strips * ((dc + kDgPieces - 1) / kDgPieces)), dg_threads, 0, st>>>(
+                (const uint4*)x_bf16, rstd, (const uint4*)dy_bf16, M, dc, (int)blocks, (float*)workspace, strips);
+        }
+        launch_dg_final((const float*)workspace, strips, D, dg, st);
         return last_launch_status();
     }
     if (dx_bf16 && M) {
@@ -469,7 +530,7 @@ static f8_status rmsnorm_bwd(const void* x_bf16, const void* g_bf16, const float
         if (strips)
             rmsnorm_dg_partial_kernel<<<(unsigned)(strips * tiles_c), kBlkThreads, 0, st>>>(
                 (const uint16_t*)x_bf16, rstd, (const uint16_t*)dy_bf16, M, D, strip_rows, (float*)workspace, (int)tiles_c);
-        rmsnorm_dg_final_kernel<<<(unsigned)((D + 15) / 16), kBlkThreads, 0, st>>>((const float*)workspace, (int)strips, D, dg);
+        launch_dg_final((const float*)workspace, strips, D, dg, st);
     }
     return last_launch_status();
 }
