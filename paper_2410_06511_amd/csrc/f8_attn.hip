@@ -15,7 +15,6 @@
 // block (reg_token), which the other operand presents in two reads of four.  (An order with eight consecutive
 // tokens, one 16-byte read, is 1.5 % faster; but the sums then round differently, which the fp8 casts of a block
 // amplify to 1e-2 and more of its gradients, and results would not compare with earlier ones.)
-#include <atomic>
 #include <type_traits>
 #include <utility>
 
@@ -235,7 +234,8 @@ static bool far_rows(int64_t rows, int64_t ld) { return 2 * (rows * ld + kHd) >=
 // (what it held was read up to slot 2t - 1) and waited for at the end of the wave's next phase M.
 // Measured (1 x 8192 tokens, 32/8 heads; cycles of a slot, both phases in it): M 1300 (32 products are 1024), V
 // 1400 (softmax 1080 to 1300, the four loads the rest: a wave's load holds up its next instruction until the memory
-// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 590 us; this: 550.
+// pipe of the compute unit takes it).  All waves in step instead, tiles through registers: 550 us; this: 497
+// (1000 tokens, 4 heads: 33.2 and 29.6; 256 tokens: 13.4 and 13.0; 64 tokens, a single step: 5.7 and 6.2).
 template <int NW, bool FAR>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(const uint16_t* __restrict__ Q, int64_t ldq,
                                                                 const uint16_t* __restrict__ K, int64_t ldk,
@@ -295,6 +295,30 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
     };
     ks.template request<true, true>(sK[0], wave, kBk * ldk, 0, S);
     request(std::true_type{}, 0, 0);
+
+    // Every wave runs the same number of slots, whatever it has left to do in them.  One without queries (the last
+    // block of a short sequence) only loads its share of the tiles: scores of zero rows and their softmax held up the
+    // waves that share its SIMD (8 tokens, 4 heads 6.1 us, so 5.6; 128 tokens 8.3, 8.05; without the skip 9.1).
+    auto end_of_m = [&]() {
+        stream_wait();  // for what this wave requested in its last phase V
+        phase_barrier();
+    };
+    auto end_of_slots = [&]() {  // after it nothing reads the tiles any more
+        if (!late) phase_barrier();
+        phase_barrier();
+    };
+    auto next = [](int buf) { return buf == 2 ? 0 : buf + 1; };
+    if (q_first >= S) {
+        end_of_m();
+        if (late) phase_barrier();
+        for (int t = -1, buf = 1; t < nkt - 1; ++t, buf = next(buf)) {
+            end_of_m();
+            request(std::true_type{}, t + 2, buf);
+            phase_barrier();
+        }
+        end_of_slots();
+        return;
+    }
 
     // LDS offsets of this lane's operand reads: of a key's row; of hd row ln, 4 g tokens into chunk 2 v, and (the
     // permutation is an XOR) the same of chunk 2 v + 1
@@ -382,13 +406,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         computed(l_run);
     };
 
-    // Every wave runs the same number of slots, whatever it has left to do in them.
-    auto next = [](int buf) { return buf == 2 ? 0 : buf + 1; };
     int buf = 2, t = -1;  // buf = t % 3
-    auto end_of_m = [&]() {
-        stream_wait();  // for what this wave requested in its last phase V
-        phase_barrier();
-    };
     auto step = [&](auto EDGE) {
         end_of_m();
         softmax(t + 1, std::false_type{});
@@ -399,14 +417,13 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         products(buf, C0{}, C32{});
         ++t;
     };
-    stream_wait();
-    phase_barrier();
+    end_of_m();
     if (late) phase_barrier();
     products(buf, C0{}, C16{});
     const int t_inside = min(t_last - 1, min(nkt, S / kBk) - 3);  // steps t before it request whole tiles only
     while (t < t_inside) step(std::false_type{});
     while (t < t_last - 1) step(std::true_type{});
-    for (; t < nkt; ++t) {
+    for (; t < nkt - 1; ++t) {
         end_of_m();
         if (t == t_last - 1) softmax(t_last, std::true_type{});
         request(std::true_type{}, t + 2, buf == 0 ? 2 : buf - 1);
@@ -414,23 +431,32 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_fwd_kernel(cons
         buf = next(buf);
         if (t == t_last - 1) products(buf, C16{}, C32{});
     }
-    if (!late) phase_barrier();
+    end_of_slots();
 
+    // O: a lane has 16 pieces of 8 bytes of one row.  Stored from here they would touch 32 rows per instruction, and all
+    // eight waves get here together, with nothing to hide the stores behind (7500 cycles: 2 us of every block, 256 tokens
+    // 15.3 us); so they go through the LDS, which nothing reads any more, to 16-byte pieces of which 16 lanes cover a
+    // row (13.0 us; a row's chunks are permuted by its number: no bank conflicts).
     const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
     uint32_t mag = 0;  // packed pair of the largest 15-bit magnitudes written
-    if (q_pos < S) {
-        const float inv = 1.0f / l_tot;
-        uint16_t* orow = O + (tok0 + q_pos) * ldo + (int64_t)h * kHd + 4 * g;
+    uint16_t* stage = (wave < NW / 2 ? sK[0] : sV[0]) + (wave % (NW / 2)) * 32 * kHd;  // this wave's 32 rows
+    const float inv = 1.0f / l_tot;
 #pragma unroll
-        for (int d = 0; d < kHd / 32; ++d)
+    for (int d = 0; d < kHd / 32; ++d)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint2 w = make_uint2(pack2(acc_o[d][4 * j] * inv, acc_o[d][4 * j + 1] * inv),
-                                           pack2(acc_o[d][4 * j + 2] * inv, acc_o[d][4 * j + 3] * inv));
-                *reinterpret_cast<uint2*>(orow + 32 * d + 8 * j) = w;
-                mag = pkmax(pkmax(mag, w.x & 0x7FFF7FFFu), w.y & 0x7FFF7FFFu);
-            }
-        if (g == 0) lse[(int64_t)h * M + tok0 + q_pos] = (m_run * scale_log2e + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994530942f;
+        for (int j = 0; j < 4; ++j) {
+            const uint2 w = make_uint2(pack2(acc_o[d][4 * j] * inv, acc_o[d][4 * j + 1] * inv),
+                                       pack2(acc_o[d][4 * j + 2] * inv, acc_o[d][4 * j + 3] * inv));
+            *reinterpret_cast<uint2*>(stage + ln * kHd + 8 * ((4 * d + j) ^ (ln & 15)) + 4 * g) = w;
+            if (q_pos < S) mag = pkmax(pkmax(mag, w.x & 0x7FFF7FFFu), w.y & 0x7FFF7FFFu);
+        }
+    if (q_pos < S && g == 0) lse[(int64_t)h * M + tok0 + q_pos] = (m_run * scale_log2e + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994530942f;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = 4 * i + lane / 16, c = lane % 16;
+        const uint4 v = *reinterpret_cast<const uint4*>(stage + row * kHd + 8 * (c ^ (row & 15)));
+        if (q_first + row < S) *reinterpret_cast<uint4*>(O + (tok0 + q_first + row) * ldo + (int64_t)h * kHd + 8 * c) = v;
     }
     if (amax_bits) {
         // the exact maximum magnitude of the bf16 values written, as float bits: a maximum of

@@ -222,6 +222,20 @@ def test_sdpa_lengths_around_steps_and_blocks(S):
     check_backward(a, do_t, dqkv, delta)
 
 
+@pytest.mark.parametrize("S", [8, 40, 64, 232, 264, 488])
+def test_sdpa_forward_writes_its_rows_and_columns_only(S):
+    """The output leaves in 16-byte row pieces, 32 rows per wave, by waves that have queries: into a column slice of a
+    wider tensor, with a guard row behind the sequence, the bits of the packed output and nothing else."""
+    a = Attn(1, S, 2, 1, seed=S)
+    a.forward()
+    want = a.o.clone()
+    wide = torch.full((S + 1, 4 * HD), 7.0, dtype=torch.bfloat16, device="cuda")
+    a.o = wide[:S, HD:3 * HD]
+    a.forward()
+    assert torch.equal(a.o.contiguous().view(torch.int16), want.view(torch.int16))
+    assert bool((wide[:, :HD] == 7).all() and (wide[:, 3 * HD:] == 7).all() and (wide[S] == 7).all())
+
+
 @pytest.mark.parametrize("S", [72, 264])
 def test_sdpa_reads_nothing_of_the_next_sequence(S):
     """Tiles reach past the end of a sequence; NaN in the sequence behind it must not show."""
