@@ -680,7 +680,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     }
     // no load may still be writing LDS when the workgroup ends
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    if (AMAX && amax_bits) {  // (the ragged instances come with AMAX only: a null amax_bits is theirs)
+    if constexpr (AMAX) {
         __syncthreads();  // every wave is past its last epilogue pass: the staging buffer is free
         amax_publish<NW>(amax_acc, amax_bits, reinterpret_cast<uint32_t*>(epb));
     }
@@ -695,17 +695,17 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
 // under way while one is used, with one barrier per pair.  Loads past the end of the contraction or of the
 // matrix read zeros (buffer range check), also those that keep the queue's length constant at the end.  Same
 // instruction, same order of the contraction: the bits of gemm_tile_kernel.
-constexpr int kSm = 64, kSmPairs = 4;
+constexpr int kSm = 64;
 __device__ inline int kswz_small(int krow) { return ((krow >> 2) & 1) | (((krow >> 5) & 1) << 1); }  // four chunks per k-row
 
-template <int FA, int FB, int GRAN, bool AKM, bool BKM>
+template <int FA, int FB, int GRAN, bool AKM, bool BKM, int PAIRS>
 __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
                                                          uint16_t* __restrict__ D, int M, int N, int K, int64_t lda, int64_t ldb,
                                                          int64_t ldd, const float* __restrict__ isa, const float* __restrict__ isb,
                                                          int tiles_n, uint32_t* __restrict__ amax_bits /* nullable */)
 {
     constexpr int OP = kSm * kBK;  // bytes of an operand's K step
-    __shared__ __attribute__((aligned(1024))) uint8_t st[kSmPairs][2][2 * OP];
+    __shared__ __attribute__((aligned(1024))) uint8_t st[PAIRS][2][2 * OP];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, fr = lane & 15, fg = lane >> 4;
     const int m0 = (int)(blockIdx.x / (unsigned)tiles_n) * kSm, n0 = (int)(blockIdx.x % (unsigned)tiles_n) * kSm;
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int kt = 2 * pair + s, valid = K - kt * kBK;
-            uint8_t* lds = st[pair % kSmPairs][s];
+            uint8_t* lds = st[pair % PAIRS][s];
             load(AKM ? a_base + (int64_t)kt * kBK * lda : a_base + (int64_t)kt * kBK, pa, valid, lds);
             load(BKM ? b_base + (int64_t)kt * kBK * ldb : b_base + (int64_t)kt * kBK, pb, valid, lds + OP);
         }
@@ -775,21 +775,25 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
     const int pairs = (K + 2 * kBK - 1) / (2 * kBK);
+    static_assert(PAIRS == 1 || PAIRS == 4, "the wait counts");
 #pragma unroll
-    for (int p = 0; p < kSmPairs - 1; ++p) request(p);
+    for (int p = 0; p < (PAIRS > 1 ? PAIRS - 1 : 1); ++p) request(p);
     for (int p = 0; p < pairs; ++p) {
-        // all but the two newest pairs (16 loads) have landed; every wave is done with the pair before, whose
-        // place the request takes
-        static_assert(kSmPairs == 4, "the wait count");
-        asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        request(p + kSmPairs - 1);
+        if constexpr (PAIRS > 1) {
+            // all but the two newest pairs (16 loads) have landed; every wave is done with the pair before, whose
+            // place the request takes
+            asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            request(p + PAIRS - 1);
+        } else {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the only pair
+        }
         v8i a[2][2], b[2][2];
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                a[s][i] = fragment(std::bool_constant<AKM>{}, st[p % kSmPairs][s], wm, i);
-                b[s][i] = fragment(std::bool_constant<BKM>{}, st[p % kSmPairs][s] + OP, wn, i);
+                a[s][i] = fragment(std::bool_constant<AKM>{}, st[p % PAIRS][s], wm, i);
+                b[s][i] = fragment(std::bool_constant<BKM>{}, st[p % PAIRS][s] + OP, wn, i);
             }
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -896,10 +900,10 @@ static void launch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, cons
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int total = tiles_m * tiles_n;
     const int grid = total < max_blocks ? total : max_blocks;
-    if (amax_bits || RAGGED)
+    if (amax_bits)
         gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, true, AKM, BKM, false, RAGGED><<<grid, WAVES_M * WAVES_N * 64, 0, st>>>(
             A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, amax_bits, ksteps_of(K, 1));
-    else if constexpr (!RAGGED)
+    else
         gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, false, AKM, BKM, false, RAGGED><<<grid, WAVES_M * WAVES_N * 64, 0, st>>>(
             A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, nullptr, ksteps_of(K, 1));
 }
@@ -959,8 +963,10 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
     const bool split_rows = whole > 0 && rest > 0 && 2 * rest <= cus && whole % tn == 0;
     const bool split_cols = !split_rows && whole > 0 && rest > 0 && 2 * rest <= cus && whole % tm == 0;
     const double c_full = (split_rows || split_cols) ? (double)(whole / cus) + kHalfTile : rounds(T);
-    const double c_half = rounds(tiles(256, 128)) * kHalfTile;
-    const double c_quarter = rounds(tiles(128, 128)) * kQuarterTile;
+    // With one pair of K steps a tile is its epilogue, which costs what its area does.
+    const bool one_pair = RAGGED && K <= 2 * kBK;
+    const double c_half = rounds(tiles(256, 128)) * (one_pair ? 0.5 : kHalfTile);
+    const double c_quarter = rounds(tiles(128, 128)) * (one_pair ? 0.25 : kQuarterTile);
     const bool rw = GRAN != F8_TENSORWISE;
     // At most one 64 x 64 tile per compute unit: the deep load queue wins (operands not in the L2, old best / new in us:
     // 64 x 4096 x 4096 19.5 / 10.2, 1008 x 1024 x 2816 15.0 / 8.8, 256 x 1024 x 512 5.6 / 4.1); with two rounds
@@ -968,9 +974,18 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
     // 31 row-major, 32 / 44 k-major; 1024 x 512 x 8192 26 / 18 and 27 / 28).
     const bool small = tiles(kSm, kSm) <= cus, may_split = ws && !amax_bits;
     if (small && !(may_split && K >= (AKM ? 8192 : 16384))) {
-        gemm_small_kernel<FA, FB, GRAN, AKM, BKM><<<(unsigned)tiles(kSm, kSm), 256, 0, st>>>(
+        gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 4><<<(unsigned)tiles(kSm, kSm), 256, 0, st>>>(
             A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (N + kSm - 1) / kSm, amax_bits);
         return;
+    }
+    if constexpr (RAGGED) {
+        // One pair of K steps, and so few tiles that all of them are resident at once: without the ring (32 KB of LDS)
+        // (9328 x 160 x 128 5.8 / 4.5 us, 2816 x 1024 x 64 6.3 / 5.4; 1024 x 4096 x 240, four tiles per unit, 7.2 / 7.4).
+        if (one_pair && tiles(kSm, kSm) <= 3 * cus) {
+            gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 1><<<(unsigned)tiles(kSm, kSm), 256, 0, st>>>(
+                A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (N + kSm - 1) / kSm, amax_bits);
+            return;
+        }
     }
     if (may_split) {
         const double best = c_full < c_half ? (c_full < c_quarter ? c_full : c_quarter) : (c_half < c_quarter ? c_half : c_quarter);

@@ -204,6 +204,31 @@ def test_gemm_split_contraction_random_codes(layout, fa, fb):
     assert np.array_equal(unsplit, run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, f8.TENSORWISE, workspace=small))
 
 
+def closely(got, layout, A, fa, B, fb, isa, isb, g, K, what):
+    assert_gemm_close(got, o.gemm(layout, A, fa, B, fb, isa, isb, g), what)
+    if got.size > 1 << 21:
+        return                                  # (the larger ones: the oracle's time)
+    d64, dabs = o.gemm_f64(layout, A, fa, B, fb, isa, isb, g)
+    assert_gemm_tight(got, d64, dabs, K, what, group_max_sum(layout, A, fa, B, fb, isa, isb, g))
+
+
+@pytest.mark.parametrize("layout", [o.NT, o.NN, o.TN])
+@pytest.mark.parametrize("fa,fb,g", [(o.E5M2, o.E4M3, f8.TENSORWISE), (o.E4M3, o.E5M2, f8.ROWWISE)])
+@pytest.mark.parametrize("M,N,K", [(1040, 1104, 144), (1040, 1104, 400), (1040, 1104, 512), (2064, 3600, 272), (4368, 4112, 272)])
+def test_gemm_larger_tiles_formats_scales_and_amax(layout, fa, fb, g, M, N, K):
+    """Products of more than one 64x64 tile per compute unit, contraction ragged and whole: e5m2 operands, scales per
+    row, and (run_gemm) the output's amax, of the one-pair kernel and of every tile shape."""
+    rng = np.random.default_rng(M + N + K)
+    sa, sb = shapes_of(layout, M, N, K)
+    A, B = rand_codes(rng, sa, fa), rand_codes(rng, sb, fb)
+    if g == f8.TENSORWISE:
+        isa, isb = np.float32(2.0 ** -5), np.float32(2.0 ** -9)
+    else:
+        isa, isb = ((rng.uniform(0.5, 2.0, n) * 2.0 ** -7).astype(np.float32) for n in (M, N))
+    got = run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, g)
+    closely(got, layout, A, fa, B, fb, isa, isb, g, K, (M, N, K, layout))
+
+
 def test_gemm_output_guard_band_and_ldd():
     """D with a leading dimension larger than N: columns beyond N stay untouched."""
     rng = np.random.default_rng(5)
@@ -341,7 +366,11 @@ RAGGED = [(272, 400, k, False) for k in (16, 112, 128, 144, 240, 272, 400, 528, 
     (16, 16, 1296, False), (80, 64, 768, False),
     (4112, 4144, 304, False), (8192, 1040, 1040, False), (4368, 4112, 272, False),
     (1008, 1552, 272, False), (1040, 1040, 16, False), (1040, 1040, 528, False),
-    (512, 1024, 4112, True), (272, 400, 2080, True), (512, 512, 16400, True), (2048, 4096, 8208, True)]
+    (512, 1024, 4112, True), (272, 400, 2080, True), (512, 512, 16400, True), (2048, 4096, 8208, True),
+    # one pair of K steps and up to three 64x64 tiles per compute unit, then one tile row more
+    (1040, 1104, 112, False), (1040, 1104, 144, False), (2064, 1456, 240, False), (2064, 1488, 240, False),
+    # more than one 64x64 tile per compute unit: these split (the first two above have fewer, and do not)
+    (1040, 1104, 4112, True), (2064, 528, 2320, True)]
 
 
 @pytest.mark.parametrize("layout", [o.NT, o.NN, o.TN])
