@@ -689,6 +689,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
 // ---------------------------------------------------------------------------
 // small products: 64 x 64 tiles, one per workgroup, a deep load queue
 // ---------------------------------------------------------------------------
+// Tiles are dealt to the XCDs as in gemm_tile_kernel, so that those that share rows (or halves of a k-major operand's
+// lines) share an L2: 128 x 7392 x 2048 with k-major B 14.3 -> 10.4 us, 64 x 4096 x 4096 no change.
 // A product with few tiles is bound by the latency of its loads: two LDS stages of a 128 x 128 tile hold 64 KB, and
 // a K step of 128 took 0.6 us where its arithmetic takes 0.25.  Here four waves (32 x 32 each) work on a 64 x 64
 // tile, so that four times as many compute units load, and 128 KB of LDS hold four pairs of K steps: three pairs are
@@ -702,13 +704,15 @@ template <int FA, int FB, int GRAN, bool AKM, bool BKM, int PAIRS>
 __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
                                                          uint16_t* __restrict__ D, int M, int N, int K, int64_t lda, int64_t ldb,
                                                          int64_t ldd, const float* __restrict__ isa, const float* __restrict__ isb,
-                                                         int tiles_n, uint32_t* __restrict__ amax_bits /* nullable */)
+                                                         int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits /* nullable */)
 {
     constexpr int OP = kSm * kBK;  // bytes of an operand's K step
     __shared__ __attribute__((aligned(1024))) uint8_t st[PAIRS][2][2 * OP];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, fr = lane & 15, fg = lane >> 4;
-    const int m0 = (int)(blockIdx.x / (unsigned)tiles_n) * kSm, n0 = (int)(blockIdx.x % (unsigned)tiles_n) * kSm;
+    int tm, tn;
+    tile_coords((int)blockIdx.x, tiles_m, tiles_n, &tm, &tn);
+    const int m0 = tm * kSm, n0 = tn * kSm;
 
     // this lane's 16 bytes of its wave's two 1 KB pieces of an operand's K step: offset from the step's base, k
     struct Piece {
@@ -769,6 +773,19 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
         }
     };
 
+    // the scales, requested before the operands: after the products their latency would be in the open
+    float s_tensor = 0.f, sa[2];
+    float4 sb[2];
+    if constexpr (GRAN == F8_TENSORWISE) {
+        s_tensor = isa[0] * isb[0];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int m = m0 + 32 * wm + 16 * i + fr, n = n0 + 32 * wn + 16 * i + 4 * fg;
+            sa[i] = isa[m < M ? m : M - 1];
+            sb[i] = *reinterpret_cast<const float4*>(isb + (n < N ? n : N - 4));
+        }
+    }
     v4f acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -805,15 +822,11 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
     }
     // no load may still be writing LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    float s_tensor = 0.f;
-    if constexpr (GRAN == F8_TENSORWISE) s_tensor = isa[0] * isb[0];
     uint32_t amax_acc = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int m = m0 + 32 * wm + 16 * i + fr;
         if (m >= M) continue;
-        float sa = 0.f;
-        if constexpr (GRAN != F8_TENSORWISE) sa = isa[m];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int n = n0 + 32 * wn + 16 * j + 4 * fg;
@@ -822,9 +835,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
             if constexpr (GRAN == F8_TENSORWISE) {
                 lo = f2{acc[i][j][0] * s_tensor, acc[i][j][1] * s_tensor}, hi = f2{acc[i][j][2] * s_tensor, acc[i][j][3] * s_tensor};
             } else {
-                const float4 sb = *reinterpret_cast<const float4*>(isb + n);
-                lo = f2{(acc[i][j][0] * sa) * sb.x, (acc[i][j][1] * sa) * sb.y};
-                hi = f2{(acc[i][j][2] * sa) * sb.z, (acc[i][j][3] * sa) * sb.w};
+                lo = f2{(acc[i][j][0] * sa[i]) * sb[j].x, (acc[i][j][1] * sa[i]) * sb[j].y};
+                hi = f2{(acc[i][j][2] * sa[i]) * sb[j].z, (acc[i][j][3] * sa[i]) * sb[j].w};
             }
             uint2 o;
             o.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2));
@@ -968,40 +980,43 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
     const double c_half = rounds(tiles(256, 128)) * (one_pair ? 0.5 : kHalfTile);
     const double c_quarter = rounds(tiles(128, 128)) * (one_pair ? 0.25 : kQuarterTile);
     const bool rw = GRAN != F8_TENSORWISE;
-    // At most one 64 x 64 tile per compute unit: the deep load queue wins (operands not in the L2, old best / new in us:
-    // 64 x 4096 x 4096 19.5 / 10.2, 1008 x 1024 x 2816 15.0 / 8.8, 256 x 1024 x 512 5.6 / 4.1); with two rounds
-    // of tiles it does not (512 x 4096 x 4096 15.4 / 20.0).  A long contraction is better split (512 x 512 x 16384 31 /
-    // 31 row-major, 32 / 44 k-major; 1024 x 512 x 8192 26 / 18 and 27 / 28).
-    const bool small = tiles(kSm, kSm) <= cus, may_split = ws && !amax_bits;
-    if (small && !(may_split && K >= (AKM ? 8192 : 16384))) {
-        gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 4><<<(unsigned)tiles(kSm, kSm), 256, 0, st>>>(
-            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (N + kSm - 1) / kSm, amax_bits);
+    const bool may_split = ws && !amax_bits;
+    const double best = c_full < c_half ? (c_full < c_quarter ? c_full : c_quarter) : (c_half < c_quarter ? c_half : c_quarter);
+    const int ranges = may_split ? splitk_ranges(M, N, K, cus, best, ws_bytes) : 1;
+    const int64_t small_tiles = tiles(kSm, kSm);
+    // At most one 64 x 64 tile per compute unit: the deep load queue wins (operands not in the L2, 128 x 128 or 256-wide
+    // tiles / this in us: 64 x 4096 x 4096 20 / 10, 1008 x 1024 x 2816 15.0 / 8.8, 256 x 1024 x 512 5.6 / 4.1); with
+    // two rounds of tiles it does not (512 x 4096 x 4096 15.4 / 20.0).
+    // A long contraction is better split, if it can be: k-major B, split / this, 64 x 4096 x 8192 21 / 24, 128 x 6160 x
+    // 8192 28 / 30; row-major 1024 x 1024 x 8192 28 / 17, but 64 x 4096 x 16384 28 / 35.
+    // With an amax of the output, whose atomics then come from 200 blocks at once (1 to 2 us), a short product keeps the
+    // larger tiles unless there are few (1024 x 1024 x 512, operands in the L2: 9.3 / 10.6; 2048 long, not in the L2: 16 / 14).
+    const int64_t most = amax_bits && !RAGGED && K < 2048 ? cus / 2 : cus;
+    if (small_tiles <= most && (ranges == 1 || K < (BKM ? 8192 : 16384))) {
+        gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 4><<<(unsigned)small_tiles, 256, 0, st>>>(
+            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (M + kSm - 1) / kSm, (N + kSm - 1) / kSm, amax_bits);
         return;
     }
     if constexpr (RAGGED) {
         // One pair of K steps, and so few tiles that all of them are resident at once: without the ring (32 KB of LDS)
         // (9328 x 160 x 128 5.8 / 4.5 us, 2816 x 1024 x 64 6.3 / 5.4; 1024 x 4096 x 240, four tiles per unit, 7.2 / 7.4).
-        if (one_pair && tiles(kSm, kSm) <= 3 * cus) {
-            gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 1><<<(unsigned)tiles(kSm, kSm), 256, 0, st>>>(
-                A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (N + kSm - 1) / kSm, amax_bits);
+        if (one_pair && small_tiles <= 3 * cus) {
+            gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 1><<<(unsigned)small_tiles, 256, 0, st>>>(
+                A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (M + kSm - 1) / kSm, (N + kSm - 1) / kSm, amax_bits);
             return;
         }
     }
-    if (may_split) {
-        const double best = c_full < c_half ? (c_full < c_quarter ? c_full : c_quarter) : (c_half < c_quarter ? c_half : c_quarter);
-        const int ranges = splitk_ranges(M, N, K, cus, best, ws_bytes);
-        if (ranges > 1) {
-            float* partial = static_cast<float*>(ws);
-            const bool whole_ranges = !RAGGED && K % (ranges * 2 * kBK) == 0;
-            const auto kernel = whole_ranges ? gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, false>
-                                             : gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, true>;
-            kernel<<<(unsigned)(T * ranges), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tm, tn, nullptr,
-                                                           ksteps_of(K, ranges), ranges, partial, (int64_t)N);
-            const int64_t threads = (int64_t)M * (N / 8);
-            splitk_reduce_kernel<GRAN><<<(unsigned)((threads + 255) / 256), 256, 0, st>>>(partial, ranges, M, N, (int64_t)N,
-                                                                                         isa, isb, D, ldd);
-            return;
-        }
+    if (ranges > 1) {
+        float* partial = static_cast<float*>(ws);
+        const bool whole_ranges = !RAGGED && K % (ranges * 2 * kBK) == 0;
+        const auto kernel = whole_ranges ? gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, false>
+                                         : gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, true>;
+        kernel<<<(unsigned)(T * ranges), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tm, tn, nullptr,
+                                                       ksteps_of(K, ranges), ranges, partial, (int64_t)N);
+        const int64_t threads = (int64_t)M * (N / 8);
+        splitk_reduce_kernel<GRAN><<<(unsigned)((threads + 255) / 256), 256, 0, st>>>(partial, ranges, M, N, (int64_t)N,
+                                                                                     isa, isb, D, ldd);
+        return;
     }
 #define F8_TILE(BM_, BN_) launch_tile<BM_, BN_, 2, 2, FA, FB, GRAN, AKM, BKM, RAGGED>
     if (c_full <= c_half && c_full <= c_quarter) {

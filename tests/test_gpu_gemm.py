@@ -212,6 +212,28 @@ def closely(got, layout, A, fa, B, fb, isa, isb, g, K, what):
     assert_gemm_tight(got, d64, dabs, K, what, group_max_sum(layout, A, fa, B, fb, isa, isb, g))
 
 
+@pytest.mark.parametrize("layout,fa,fb,g", [(o.TN, o.E5M2, o.E4M3, f8.TENSORWISE), (o.NT, o.E4M3, o.E4M3, f8.ROWWISE),
+                                            (o.NN, o.E4M3, o.E5M2, f8.TENSORWISE), (o.TN, o.E4M3, o.E4M3, f8.ROWWISE)])
+@pytest.mark.parametrize("M,N,K", [(1040, 1104, 4096), (1040, 1104, 4112), (272, 400, 16384)])
+def test_gemm_split_contraction_of_more_tiles_than_units(layout, fa, fb, g, M, N, K):
+    """Products that do split: more 64x64 tiles than compute units, or a contraction long enough for fewer.  Against
+    the oracle; not the bits of the unsplit product (another order of the sums), which a workspace too small gives."""
+    rng = np.random.default_rng(layout + K)
+    sa, sb = shapes_of(layout, M, N, K)
+    A, B = rand_codes(rng, sa, fa), rand_codes(rng, sb, fb)
+    if g == f8.TENSORWISE:
+        isa, isb = np.float32(0.0131), np.float32(0.73)
+    else:
+        isa, isb = (rng.uniform(0.5, 2.0, n).astype(np.float32) for n in (M, N))
+    got = run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, g, workspace=f8.new_workspace(M, N))
+    closely(got, layout, A, fa, B, fb, isa, isb, g, K, (layout, fa, fb, g))
+    assert np.array_equal(got, run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, g, workspace=f8.new_workspace(M, N)))
+    unsplit = run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, g)
+    assert not np.array_equal(got, unsplit)
+    small = torch.empty(4096, dtype=torch.uint8, device="cuda")
+    assert np.array_equal(unsplit, run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, g, workspace=small))
+
+
 @pytest.mark.parametrize("layout", [o.NT, o.NN, o.TN])
 @pytest.mark.parametrize("fa,fb,g", [(o.E5M2, o.E4M3, f8.TENSORWISE), (o.E4M3, o.E5M2, f8.ROWWISE)])
 @pytest.mark.parametrize("M,N,K", [(1040, 1104, 144), (1040, 1104, 400), (1040, 1104, 512), (2064, 3600, 272), (4368, 4112, 272)])
