@@ -771,7 +771,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     };
     using C16 = std::integral_constant<int, 16>;
     using C32 = std::integral_constant<int, 32>;
-    // Queries at or beyond S read as zero rows with lse = delta = 0: they add nothing.  MASKED: the diagonal's pair.
+    // MASKED: the diagonal's pair, and the first one if it reaches past S (its queries there are zero rows with
+    // lse = delta = 0, but their P is 1, or not a number for a key that is not finite).
     auto grad_scores = [&](int t, auto MASKED) {
         const float* st = sStat[t & 3];
 #pragma unroll
@@ -787,7 +788,8 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
                     const int r = 8 * u + 4 * j + i;
                     float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - lv[i] * 1.4426950408889634074f);
                     if constexpr (decltype(MASKED)::value) {
-                        if (key_pos > q0(t) + ql + i) p = 0.0f;
+                        // queries key_pos .. S - 1 (a key at or past S is not stored, whatever it gets)
+                        if ((unsigned)(q0(t) + ql + i - key_pos) >= (unsigned)(S - key_pos)) p = 0.0f;
                     }
                     sc[r] = p;
                     ds8[4 * j + i] = p * (dp[r] - dv[i]);
@@ -820,9 +822,14 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
 #pragma unroll
     for (int j = 0; j < 16; ++j) score_product(j, score_operands(0, j));
     const int t_inside = min(t_last - 2, steps - 3);
-    while (t < t_inside) step(std::false_type{}, std::false_type{});
-    while (t < t_last - 2) step(std::true_type{}, std::false_type{});
-    step(std::true_type{}, std::true_type{});  // scores of t_last - 1
+    const int t_whole = S % (2 * kDkvQ) ? 1 : -1;  // from this t on step(t) forms scores of whole pairs
+    do {
+        if (t >= t_whole) {
+            while (t < t_inside) step(std::false_type{}, std::false_type{});
+            while (t < t_last - 2) step(std::true_type{}, std::false_type{});
+        }
+        step(std::true_type{}, std::true_type{});  // scores of the first pair, or of t_last - 1
+    } while (t < t_last - 1);
     for (; t < steps; ++t) {
         end_of_m();
         if (t == t_last - 1) {

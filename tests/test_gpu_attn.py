@@ -253,6 +253,29 @@ def test_sdpa_reads_nothing_of_the_next_sequence(S):
         assert torch.equal(x.view(torch.int16), y[:S].view(torch.int16))
 
 
+@pytest.mark.parametrize("S", [8, 72, 136, 328])
+def test_sdpa_backward_infinite_key_of_probability_zero(S):
+    """A key with an element of +inf where every query has a negative one gets the score -inf and the probability 0 of
+    every query: its dK and dV are 0, every other key's are what they are without it.  The tiles' queries past the end
+    (S is no multiple of 64) are zero rows, whose score with that key is not a number."""
+    j, e = S // 2, 5
+    a = Attn(1, S, 1, 1, seed=S)
+    q = a.q.contiguous()
+    q[:, e] = -q[:, e].abs() - 0.5
+    k, do_t = a.k.contiguous(), gen((S, HD), S + 1, 1e-2)
+    k[j, e] = float("inf")
+    a.q, a.k = q, k
+    a.forward()
+    assert bool(torch.isfinite(a.o).all() and torch.isfinite(a.lse).all())
+    grads = run_backward(a, do_t)[0][:, HD:]
+    assert bool((grads[j] == 0).all())
+    k[j] = 0
+    k[j, e] = 1e6  # the same probabilities without the infinity
+    a.forward()
+    want = run_backward(a, do_t)[0][:, HD:]
+    assert torch.equal(grads.view(torch.int16), want.view(torch.int16))
+
+
 def test_sdpa_rows_far_apart():
     """Pitches whose tile spans more than 4 GiB take 64-bit lane offsets: the same bits."""
     S, pitch = 72, (1 << 25) + 8
