@@ -279,9 +279,8 @@ __global__ __launch_bounds__(kThreads) void scale_kernel(const float* __restrict
 //   next_scale / next_inv (nullable inv): FMAX / max(max(history), eps) for the next step.
 // used_scale and next_scale may be the same address: it is read before it is written.
 __global__ __launch_bounds__(kThreads) void history_push_kernel(
-    const uint32_t* __restrict__ partial, int npartial, const float* __restrict__ amax_in,
-    float* __restrict__ history, int len, float fm, float* __restrict__ amax_out,
-    const float* used_scale, float* __restrict__ saved_scale, float* __restrict__ saved_inv,
+    const uint32_t* __restrict__ partial, int npartial, const float* amax_in, float* history, int len, float fm,
+    float* __restrict__ amax_out, const float* used_scale, float* __restrict__ saved_scale, float* __restrict__ saved_inv,
     float* next_scale, float* __restrict__ next_inv)
 {
     // The history in registers, thread t has entries t, t + 256, ...: requested with the partial maxima instead of
@@ -296,14 +295,13 @@ __global__ __launch_bounds__(kThreads) void history_push_kernel(
         const int i = k * kThreads + (int)threadIdx.x;
         h[k] = i < len - 1 ? history[i] : 0.0f;
     }
-    float used = 0.0f;
+    float used = 0.0f, a = 0.0f;
     if (threadIdx.x == 0 && used_scale) used = used_scale[0];
+    if (!partial) a = amax_in[0];  // (before the history moves: it may be one of its entries)
 #pragma unroll
     for (int k = 0; k < PER_THREAD; ++k) hm = h[k] > __uint_as_float(hm) ? __float_as_uint(h[k]) : hm;
     hm = block_max_u32<kWaves>(hm, red);  // (its barriers also end every thread's reads of the history)
-    float a;
     if (partial) a = mag_to_float(reduce_partials(partial, npartial, red));
-    else a = amax_in[0];
 #pragma unroll
     for (int k = 0; k < PER_THREAD; ++k) {
         const int i = k * kThreads + (int)threadIdx.x;

@@ -262,3 +262,13 @@ def test_history_push_lengths(n):
         want = np.concatenate((np.float32([0.25]), want[:-1]))
         assert np.array_equal(dev.cpu().numpy(), want)
         assert scale.item() == np.float32(448.0) / want.max() and inv.item() == np.float32(1.0) / np.float32(scale.item())
+
+
+@pytest.mark.parametrize("n,j", [(1, 0), (16, 3), (256, 255), (1024, 0), (1024, 64), (1024, 700)])
+def test_history_push_of_an_entry_of_the_history(n, j):
+    """The new amax may be an entry of the history itself: it is read before any entry moves."""
+    hist = np.random.default_rng(n + j).uniform(0.5, 2.0, n).astype(np.float32)
+    dev, scale = torch.from_numpy(hist).cuda(), torch.zeros(1, device="cuda")
+    f8.amax_history_push(dev, dev[j:j + 1], f8.E4M3, scale)
+    want = np.concatenate((hist[j:j + 1], hist[:-1]))
+    assert np.array_equal(dev.cpu().numpy(), want) and scale.item() == np.float32(448.0) / want.max()
