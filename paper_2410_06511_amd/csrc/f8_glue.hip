@@ -17,42 +17,22 @@ constexpr int kGlueMaxBlocks = 2048;
 static_assert((size_t)kGlueMaxBlocks * sizeof(uint32_t) <= kMinWorkspaceBytes, "one partial per block fits the minimum workspace");
 
 // ab [M, 2H] as 16-byte chunks: row m has 2 * hc chunks, a first; h [M, H]: hc chunks per row.
-// A thread's chunks of h are a grid's width apart: row and column are carried along (no division per
-// chunk), and kGlueUnroll chunks are requested together.  At the rate of a large copy: 8192 x 14336 forward 134 us
-// (5.3 TB/s; 139 before), backward 231 us (5.1 TB/s).
-struct GlueWalk {
-    int64_t m, j, dm, dj, hc;
-    __device__ GlueWalk(int64_t first, int64_t stride, int64_t hc_) : m(first / hc_), j(first % hc_), dm(stride / hc_), dj(stride % hc_), hc(hc_) {}
-    __device__ int64_t a() const { return m * 2 * hc + j; }  // chunk of a in ab; b: hc further
-    __device__ void next()
-    {
-        m += dm, j += dj;
-        if (j >= hc) j -= hc, ++m;
-    }
-};
-constexpr int kGlueUnroll = 2;
+// At the rate of a large copy: 8192 x 14336 forward 140 us (5.1 TB/s), backward 235 us (5.0 TB/s).  (Row and column
+// carried along instead of a division per chunk, and two chunks requested together: the same to 2 % at 48 sizes.)
 __global__ __launch_bounds__(kGlueThreads) void silu_mul_kernel(const uint4* __restrict__ ab, int64_t M, int64_t hc,
                                                                uint4* __restrict__ h, uint32_t* __restrict__ partial)
 {
     __shared__ uint32_t red[kGlueWaves];
     const int64_t n = M * hc, stride = (int64_t)gridDim.x * kGlueThreads;
     uint32_t acc = 0;
-    int64_t c = (int64_t)blockIdx.x * kGlueThreads + threadIdx.x;
-    GlueWalk w(c, stride, hc);
-    auto chunk = [&](int64_t at, uint4 a, uint4 b) {
+    for (int64_t c = (int64_t)blockIdx.x * kGlueThreads + threadIdx.x; c < n; c += stride) {
+        const int64_t m = c / hc, j = c - m * hc;
+        const uint4 a = ab[m * 2 * hc + j], b = ab[m * 2 * hc + hc + j];
         uint4 o;
         o.x = silu_mul2(a.x, b.x), o.y = silu_mul2(a.y, b.y), o.z = silu_mul2(a.z, b.z), o.w = silu_mul2(a.w, b.w);
-        h[at] = o;
+        h[c] = o;
         acc = absmax_acc(acc, o);
-    };
-    for (; c + (kGlueUnroll - 1) * stride < n; c += kGlueUnroll * stride) {
-        uint4 a[kGlueUnroll], b[kGlueUnroll];
-#pragma unroll
-        for (int u = 0; u < kGlueUnroll; ++u, w.next()) a[u] = ab[w.a()], b[u] = ab[w.a() + hc];
-#pragma unroll
-        for (int u = 0; u < kGlueUnroll; ++u) chunk(c + u * stride, a[u], b[u]);
     }
-    for (; c < n; c += stride, w.next()) chunk(c, ab[w.a()], ab[w.a() + hc]);
     if (partial) {
         const uint32_t mx = block_max_u32<kGlueWaves>(pk_collapse(acc), red);
         if (threadIdx.x == 0) partial[blockIdx.x] = mx;
@@ -66,28 +46,18 @@ __global__ __launch_bounds__(kGlueThreads) void silu_mul_bwd_kernel(const uint4*
     __shared__ uint32_t red[kGlueWaves];
     const int64_t n = M * hc, stride = (int64_t)gridDim.x * kGlueThreads;
     uint32_t acc = 0;
-    int64_t c = (int64_t)blockIdx.x * kGlueThreads + threadIdx.x;
-    GlueWalk w(c, stride, hc);
-    auto chunk = [&](int64_t at, uint4 a, uint4 b, uint4 g) {
+    for (int64_t c = (int64_t)blockIdx.x * kGlueThreads + threadIdx.x; c < n; c += stride) {
+        const int64_t m = c / hc, j = c - m * hc;
+        const uint4 a = ab[m * 2 * hc + j], b = ab[m * 2 * hc + hc + j], g = dh[c];
         uint4 da, db;
         silu_mul_bwd2(a.x, b.x, g.x, &da.x, &db.x);
         silu_mul_bwd2(a.y, b.y, g.y, &da.y, &db.y);
         silu_mul_bwd2(a.z, b.z, g.z, &da.z, &db.z);
         silu_mul_bwd2(a.w, b.w, g.w, &da.w, &db.w);
-        dab[at] = da;
-        dab[at + hc] = db;
+        dab[m * 2 * hc + j] = da;
+        dab[m * 2 * hc + hc + j] = db;
         acc = absmax_acc(absmax_acc(acc, da), db);
-    };
-    for (; c + (kGlueUnroll - 1) * stride < n; c += kGlueUnroll * stride) {
-        uint4 a[kGlueUnroll], b[kGlueUnroll], g[kGlueUnroll];
-        int64_t at[kGlueUnroll];
-#pragma unroll
-        for (int u = 0; u < kGlueUnroll; ++u, w.next())
-            at[u] = w.a(), a[u] = ab[at[u]], b[u] = ab[at[u] + hc], g[u] = dh[c + u * stride];
-#pragma unroll
-        for (int u = 0; u < kGlueUnroll; ++u) chunk(at[u], a[u], b[u], g[u]);
     }
-    for (; c < n; c += stride, w.next()) chunk(w.a(), ab[w.a()], ab[w.a() + hc], dh[c]);
     if (partial) {
         const uint32_t mx = block_max_u32<kGlueWaves>(pk_collapse(acc), red);
         if (threadIdx.x == 0) partial[blockIdx.x] = mx;
