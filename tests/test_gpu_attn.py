@@ -287,3 +287,33 @@ def test_sdpa_rows_far_apart():
     a.k = buf[:, :HD]
     a.forward()
     assert torch.equal(want.view(torch.int16), a.o.view(torch.int16))
+
+
+def test_sdpa_backward_rows_far_apart():
+    """The backward kernels' 64-bit lane offsets: K rows 2^25 elements apart take them in dQ (64 rows to a tile), Q and dO
+    rows 2^26 apart and V rows 2^23 apart in dK/dV (32 and 256 rows), whose streams also step back.  Bits of the packed
+    tensors, each tensor far apart on its own and all together."""
+    S = 136
+    a = Attn(1, S, 1, 1, seed=4)
+    a.forward()
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    packed = dict(q=a.q.contiguous(), k=a.k.contiguous(), v=a.v.contiguous(), do=gen((S, HD), 5, 1e-2).cuda())
+    t = {n: torch.empty((HD, S), **bf) for n in packed}
+    for n in packed:
+        f8.transpose_bf16(packed[n], t[n])
+
+    def backward(x):
+        d, delta = torch.zeros((S, 3 * HD), **bf), torch.empty((1, S), device="cuda")
+        f8.sdpa_bwd(x["q"], t["q"], x["k"], t["k"], x["v"], a.o, x["do"], t["do"], a.lse, 1, S, 1, 1, HD, d[:, :HD], d[:, HD:2 * HD],
+                    d[:, 2 * HD:], delta)
+        return d.view(torch.int16), delta
+
+    want, want_delta = backward(packed)
+    far = {}
+    for n, pitch in (("q", (1 << 26) + 8), ("k", (1 << 25) + 8), ("v", (1 << 23) + 8), ("do", (1 << 26) + 8)):
+        far[n] = torch.empty(S * pitch, **bf).view(S, pitch)[:, :HD]
+        far[n].copy_(packed[n])
+        got, delta = backward({**packed, n: far[n]})
+        assert torch.equal(want, got) and torch.equal(want_delta, delta), n
+    got, delta = backward(far)
+    assert torch.equal(want, got) and torch.equal(want_delta, delta)

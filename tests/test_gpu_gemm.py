@@ -50,9 +50,8 @@ def run_gemm(layout, M, N, K, A, fa, B, fb, isa, isb, g, workspace=None):
     return bits(D)
 
 
-# (M, N, K): single tile; several 64- and 256-tiles with ragged M and N; K not a multiple of
-# 64 (generic kernel even for NT); K a multiple of 64 but not 256 (tail steps of the fast
-# kernel); a shape that takes the 256x256 tiles with ragged edges.
+# (M, N, K): single tile; several 64-tiles with ragged M and N; K not a multiple of 64, K a multiple of 64 but not
+# 256.  All of these are small products (64x64 tiles); the larger tiles are compared in full below.
 SMALL = [(16, 16, 16), (64, 64, 64), (80, 144, 208), (272, 400, 192), (144, 80, 576), (528, 784, 256)]
 
 
@@ -158,7 +157,8 @@ def test_gemm_exact_arithmetic_long_contraction():
 @pytest.mark.parametrize("M,N,K", [(512, 1024, 4096), (272, 400, 2048), (2048, 4096, 8192)])
 def test_gemm_split_contraction_exact_arithmetic(layout, g, M, N, K):
     """f8_gemm_ws on products with few output tiles and a long contraction (8, 4 and 128 tiles of
-    256 x 256): computed in contraction ranges whose fp32 sums a second kernel adds.  On the
+    256 x 256): the last is computed in contraction ranges whose fp32 sums a second kernel adds (the others have
+    one 64 x 64 tile per compute unit and are not split; see the tests of products that are).  On the
     exact-arithmetic grid every partial sum is exact, so the result is bit for bit the fp64
     product rounded once to bf16 - and equal to the unsplit f8_gemm."""
     rng = np.random.default_rng(13 + layout + M)
@@ -184,9 +184,8 @@ def test_gemm_split_contraction_exact_arithmetic(layout, g, M, N, K):
 
 @pytest.mark.parametrize("layout,fa,fb", [(o.TN, o.E5M2, o.E4M3), (o.NT, o.E4M3, o.E4M3), (o.NN, o.E4M3, o.E5M2)])
 def test_gemm_split_contraction_random_codes(layout, fa, fb):
-    """Random codes: the split product against the oracle and the fp64 bound element by element,
-    deterministic over repeated calls, and a workspace too small for the partial sums gives the
-    unsplit product's bits."""
+    """Random codes, with a workspace but few tiles (64 x 64, not split): against the oracle and the fp64 bound element
+    by element, deterministic over repeated calls, and with a workspace too small for partial sums the same bits."""
     M, N, K = 1024, 528, 4096
     rng = np.random.default_rng(layout + 400)
     sa, sb = shapes_of(layout, M, N, K)

@@ -20,8 +20,8 @@ def _codes(rng, shape):
 
 @pytest.mark.parametrize("M,N,K", [(16, 16, BIG), (BIG16, 16, 16), (16, BIG16, 16), (BIG16, 16, 256)])
 def test_gemm_at_the_size_limits(M, N, K):
-    """Longest contraction (fast kernel, 65534 K steps on one tile), most rows and most columns
-    (generic kernel: one block per 64x64 tile in a one-dimensional grid; fast kernel for K = 256)."""
+    """Longest contraction (65534 K steps on one 64x64 tile), most rows and most columns (larger tiles, a contraction
+    that fills part of a pair of K steps, or one pair)."""
     rng = np.random.default_rng(K % 1000 + M % 7)
     A, B = _codes(rng, (M, K)), _codes(rng, (N, K))
     isa = isb = np.float32(2.0 ** -4)
