@@ -67,9 +67,9 @@ typedef enum { F8_TENSORWISE = 0, F8_ROWWISE = 1, F8_COLWISE = 2 } f8_granularit
  *   F8_NT: A[M,K], B[N,K]   (both contraction-contiguous)
  *   F8_NN: A[M,K], B[K,N]
  *   F8_TN: A[K,M], B[K,N]
- * All three run on the same tiled kernel (operands whose contraction index is
- * the slow one are turned inside the kernel), with any K: a K that is not a
- * multiple of 256 costs what the next multiple does. */
+ * All three run on the same kernels (a tiled one, and one for small products;
+ * operands whose contraction index is the slow one are turned inside), with any
+ * K: a K that is not a multiple of 256 costs what the next multiple does. */
 typedef enum { F8_NT = 0, F8_NN = 1, F8_TN = 2 } f8_layout;
 
 /* Bytes of device workspace that is enough for any call of this library on
@@ -157,7 +157,8 @@ f8_status f8_cast_amax(const void* x_bf16, int64_t rows, int64_t cols, int64_t l
 /*
  * Delayed scaling's amax history: history[0] is the newest entry,
  * history[len-1] the oldest, 1 <= len <= F8_MAX_HISTORY.  The call drops the
- * oldest entry, shifts the rest by one, stores amax_new[0] at history[0], then
+ * oldest entry, shifts the rest by one, stores amax_new[0] (read before any entry
+ * moves) at history[0], then
  * writes scale_out[0] = FMAX(fmt) / max(max(history), 1e-12f) and
  * inv_scale_out[0] = 1 / scale_out[0] (inv_scale_out may be NULL).  A fresh
  * history is all zeros; an all-zero history gives the scale of an all-zero
@@ -468,10 +469,10 @@ f8_status f8_linear_bwd_dyq(const f8_linear_desc* d, f8_saved* saved, void* dX, 
  * the adjacent pair (x[2i], x[2i+1]) is turned by the angle
  * pos * theta^(-2i/hd) (by its negative when inverse != 0: the backward).
  * out (nullable) [M, n_heads * hd], row pitch ldo; out_t (nullable) the same
- * values transposed, [n_heads * hd, M] packed: the copy that the attention
- * backward contracts over tokens.  Angle and its reduction in fp64, sine and
- * cosine and the rotation in fp32, one rounding to bf16.  hd a multiple of 8
- * and <= 256, M and the pitches multiples of 8.
+ * values transposed, [n_heads * hd, M] packed (f8_sdpa_bwd asks for these
+ * copies of q and k, but reads the token-major ones).  Angle and its reduction
+ * in fp64, sine and cosine and the rotation in fp32, one rounding to bf16.  hd a
+ * multiple of 8 and <= 256, M and the pitches multiples of 8.
  *
  * amax_inout (nullable, 1 float, also in f8_rmsnorm_bwd_add and f8_sdpa_bwd):
  * raised to the maximum magnitude of the bf16 values this call writes if that is

@@ -210,8 +210,9 @@ class TransformerBlock:
         histories alone).
         "selective": keep the outputs of the matrix products and of the attention (and the fp8
         codes saved by the linears) and run again only the cheap operations whose results the
-        backward reads: the normalisation statistics, the rotated q and k with their transposed
-        copies, and the first residual sum."""
+        backward reads: the normalisation statistics, the rotated q and k (the call writes their
+        transposed copies too, which f8_sdpa_bwd asks for but does not read), and the first
+        residual sum."""
         if recompute == "selective":
             for name, call, _, _ in self.forward_stages(x, w, stream):
                 if name in self.SELECTIVE:

@@ -1,7 +1,6 @@
 // The bf16 operations that join the Float8 linears of one transformer block (Section 2.2.4
 // applies Float8 to the linear layers only; everything between them stays in bf16): rotary
-// position embedding (also writing the transposed copy that the attention backward contracts
-// over tokens), a plain bf16 transposition, the residual addition and the backward of RMSNorm.
+// position embedding (if asked, with a transposed copy), a plain bf16 transposition, the residual addition and the backward of RMSNorm.
 // All HBM-bound: 16-byte accesses, fp32 arithmetic, one rounding to bf16.
 #include "f8_device.hpp"
 #include "f8_host.hpp"
