@@ -3,7 +3,7 @@
 // f8_gemm_inst.hip is compiled once per operand-format pair and layout, in parallel).
 //
 // gemm_tile_kernel serves all three layouts and every shape (multiples of 16) but the smallest,
-// which gemm_small_kernel takes (at most one 64 x 64 tile per compute unit, or three with a contraction of at most 256):
+// which gemm_small_kernel takes (at most one 64 x 64 tile per compute unit, or two to three with a contraction of at most 256):
 // persistent workgroups, global -> LDS direct loads (no VGPR staging), two LDS stages,
 // v_mfma_f32_16x16x128_f8f6f4, scales folded into the fp32 epilogue, bf16 stores staged
 // through LDS.  An operand whose contraction index is the fast one in memory
@@ -774,12 +774,11 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
         }
     };
 
-    // the scales, requested before the operands: after the products their latency would be in the open
+    // Scales per row and column are requested before the operands: after the products their latency would be in the open.
+    // (The tensors' two come afterwards: held over the loop they cost 2 % of it, by the order of its LDS reads.)
     float s_tensor = 0.f, sa[2];
     float4 sb[2];
-    if constexpr (GRAN == F8_TENSORWISE) {
-        s_tensor = isa[0] * isb[0];
-    } else {
+    if constexpr (GRAN != F8_TENSORWISE) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int m = m0 + 32 * wm + 16 * i + fr, n = n0 + 32 * wn + 16 * i + 4 * fg;
@@ -823,6 +822,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
     }
     // no load may still be writing LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (GRAN == F8_TENSORWISE) s_tensor = isa[0] * isb[0];
     uint32_t amax_acc = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -999,9 +999,10 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
         return;
     }
     if constexpr (RAGGED) {
-        // One pair of K steps, and so few tiles that all of them are resident at once: without the ring (32 KB of LDS)
-        // (9328 x 160 x 128 5.8 / 4.5 us, 2816 x 1024 x 64 6.3 / 5.4; 1024 x 4096 x 240, four tiles per unit, 7.2 / 7.4).
-        if (one_pair && small_tiles <= 3 * cus) {
+        // One pair of K steps, and so few tiles that all of them are resident at once: without the ring (32 KB of LDS).
+        // Tile kernel / this in us: 9328 x 160 x 128 5.8 / 4.5, x 240 5.9 / 4.6, 2816 x 1024 x 64 6.3 / 5.4; with both K
+        // steps of the pair used and three tiles per unit no longer (256 x 11264 x 224 k-major 6.3 / 6.8, not in the L2).
+        if (one_pair && small_tiles <= (K <= kBK ? 3 : 2) * cus) {
             gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 1><<<(unsigned)small_tiles, 256, 0, st>>>(
                 A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (M + kSm - 1) / kSm, (N + kSm - 1) / kSm, amax_bits);
             return;

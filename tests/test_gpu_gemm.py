@@ -388,8 +388,9 @@ RAGGED = [(272, 400, k, False) for k in (16, 112, 128, 144, 240, 272, 400, 528, 
     (4112, 4144, 304, False), (8192, 1040, 1040, False), (4368, 4112, 272, False),
     (1008, 1552, 272, False), (1040, 1040, 16, False), (1040, 1040, 528, False),
     (512, 1024, 4112, True), (272, 400, 2080, True), (512, 512, 16400, True), (2048, 4096, 8208, True),
-    # one pair of K steps and up to three 64x64 tiles per compute unit, then one tile row more
-    (1040, 1104, 112, False), (1040, 1104, 144, False), (2064, 1456, 240, False), (2064, 1488, 240, False),
+    # one pair of K steps and up to three (one step: 256 units) or two 64x64 tiles per compute unit, then more
+    (1040, 1104, 112, False), (1040, 1104, 144, False), (2064, 1456, 128, False), (2064, 1488, 128, False),
+    (2064, 976, 240, False), (2064, 1040, 240, False),
     # more than one 64x64 tile per compute unit: these split (the first two above have fewer, and do not)
     (1040, 1104, 4112, True), (2064, 528, 2320, True)]
 
