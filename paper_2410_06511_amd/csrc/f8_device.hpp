@@ -126,6 +126,17 @@ __device__ inline uint2 cast8v(uint4 v, const float* s)
     return o;
 }
 
+// ---- streams ------------------------------------------------------------------
+// Loads and stores of data that this library does not touch again soon (non-temporal).
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ inline uint4 load_once(const uint4* p)
+{
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
+__device__ inline void store_stream(uint4* p, uint4 v) { __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p)); }
+__device__ inline void store_stream(uint2* p, uint2 v) { __builtin_nontemporal_store(__builtin_bit_cast(u32x2, v), reinterpret_cast<u32x2*>(p)); }
+
 // ---- abs-max on bf16 bit patterns --------------------------------------------
 
 // For finite bf16 the magnitude order is the integer order of the low 15 bits,

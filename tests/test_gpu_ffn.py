@@ -57,6 +57,24 @@ def test_silu_mul_forward_and_backward(M, H):
     assert torch.equal(h.view(torch.int16), h2.view(torch.int16))
 
 
+@pytest.mark.parametrize("M,H", [(16, 256), (16, 272), (1024, 4096), (1040, 4112)])
+def test_silu_mul_at_the_edges_of_a_block(M, H):
+    """A block takes 512 chunks of 16 bytes at a time, 1024 blocks make one round: one whole block, a block and a
+    remainder, one whole round, a round and a remainder.  In place too: a chunk is read and written by one thread."""
+    g = torch.Generator("cpu")
+    g.manual_seed(M + H)
+    ab, dh = wl.randn_bf16((M, 2 * H), 2.0, 0, generator=g), wl.randn_bf16((M, H), 1e-3, 0, generator=g)
+    ws = f8.new_workspace(M, 2 * H)
+    h, dab = torch.empty((M, H), dtype=torch.bfloat16, device="cuda"), ab.cuda()
+    a_h, a_d = torch.full((1,), -1.0, device="cuda"), torch.full((1,), -1.0, device="cuda")
+    f8.silu_mul(ab.cuda(), h, a_h, ws)
+    f8.silu_mul_bwd(dab, dh.cuda(), dab, a_d, ws)
+    torch.cuda.synchronize()
+    assert_bf16_close(bits(h), o.silu_mul(bits(ab))[0], "h")
+    assert_bf16_close(bits(dab), o.silu_mul_bwd(bits(ab), bits(dh))[0], "dab")
+    assert a_h.item() == o.amax(bits(h))[0] and a_d.item() == o.amax(bits(dab))[0]
+
+
 def test_glue_argument_errors():
     t = torch.zeros((16, 32), dtype=torch.bfloat16, device="cuda")
     h = torch.zeros((16, 16), dtype=torch.bfloat16, device="cuda")
