@@ -196,11 +196,10 @@ __global__ __launch_bounds__(kBlkThreads) void rmsnorm_dx_kernel(const uint4* __
     }
 }
 
-// dx and dg from one read of x and dy (D up to 4096): a wave walks rows and keeps, beside the row, the sums of
+// dx and dg from one read of x and dy (D up to 1024): a wave walks rows and keeps, beside the row, the sums of
 // dy * x * rstd of its own rows for its columns in registers; the block's four sets meet in LDS and leave one
 // partial row, partial[block][D].  NC: 16-byte chunks of a row per lane, so that a short row pays for no more
 // registers, LDS and chunks than it has (2048 x 512 with eight always 10.5 us, as two passes 9.2, so 8.1).
-// 8192 x 4096 with the residual: 94 us with the final sum, 105 as two passes.
 template <int NC>
 __global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const uint4* __restrict__ x, const uint4* __restrict__ g,
                                                                            const float* __restrict__ rstd, const uint4* __restrict__ dy,
@@ -283,6 +282,115 @@ __global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const
     if (amax_bits) {
         const uint32_t m = wave_max_u32(pk_collapse(mag)) << 16;
         if (lane == 0 && m > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, m);
+    }
+}
+
+// The same for rows of 1040 to 8192 elements, a row per block: thread t has chunks t, t + 256, ... of it (U of them).
+// Bound by memory.  With a row per wave a lane holds eight chunks of x and dy and 64 sums, which leaves no registers to
+// request the next row with, and all waves load, then compute, then store: 8192 x 4096 with the residual 82 us (268 MB).
+// A quarter of that per lane lets the next row be on its way while this one is worked on: 52 us; 1008 x 4096 20.8 -> 12.7,
+// 1008 x 2048 11.7 -> 10.0, 8192 x 6144 (two passes before) 144 -> 89.  Shorter rows would leave threads without a chunk.
+// The sum over a row is formed by every wave from the chunks' terms in LDS, in the order in which a lane of the kernel
+// above adds them, and the block takes that kernel's rows wave by wave: the same bits, of dx and of dg.
+template <int U>
+__global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_row_kernel(const uint4* __restrict__ x, const uint4* __restrict__ g,
+                                                                      const float* __restrict__ rstd, const uint4* __restrict__ dy,
+                                                                      int64_t M, int dc, float inv_d, uint4* __restrict__ dx,
+                                                                      const uint4* __restrict__ res /* nullable: added to dx */,
+                                                                      float* __restrict__ partial,
+                                                                      uint32_t* __restrict__ amax_bits /* nullable: max-updated */)
+{
+    __shared__ float terms[2][kBlkWaves * U][kWave];  // of x . g . dy, by chunk / 64 and chunk % 64; of this row and the next
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t step = (int64_t)gridDim.x * kBlkWaves;
+    uint32_t mag = 0;
+    float acc[U][8] = {}, sum[U][8] = {};
+    uint4 gw[U];
+    bool in[U];
+    struct Row {
+        uint4 x[U], d[U], a[U];
+        float r;
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int c = (int)threadIdx.x + kBlkThreads * u;
+        in[u] = c < dc;
+        gw[u] = in[u] ? g[c] : make_uint4(0, 0, 0, 0);
+    }
+    auto request = [&](int64_t m) {
+        Row row;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = m * dc + threadIdx.x + kBlkThreads * u;
+            row.x[u] = row.d[u] = row.a[u] = make_uint4(0, 0, 0, 0);
+            if (in[u]) {
+                row.x[u] = load_once(x + at), row.d[u] = load_once(dy + at);
+                if (res) row.a[u] = load_once(res + at);
+            }
+        }
+        row.r = rstd[m];
+        return row;
+    };
+    int w = 0, buf = 0;
+    int64_t m = (int64_t)blockIdx.x * kBlkWaves;
+    Row row = request(m);
+    while (true) {
+        // the row after this one: of wave w of the kernel above, then of the next wave
+        int nw = w;
+        int64_t nm = m + step;
+        if (nm >= M) nw = w + 1, nm = (int64_t)blockIdx.x * kBlkWaves + nw;
+        const bool more = nw < kBlkWaves && nm < M;
+        Row next = row;
+        if (more) next = request(nm);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint4 v = row.x[u], k = gw[u], d = row.d[u];
+            terms[buf][wave + kBlkWaves * u][lane] =
+                (xgd_word(v.x, k.x, d.x) + xgd_word(v.y, k.y, d.y)) + (xgd_word(v.z, k.z, d.z) + xgd_word(v.w, k.w, d.w));
+        }
+        __syncthreads();
+        float t = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kBlkWaves * U; ++i) t += terms[buf][i][lane];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, kWave);
+        const float r = row.r, k = ((r * r) * r) * (t * inv_d);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint4 v = row.x[u], wg = gw[u], d = row.d[u], a = row.a[u];
+            const uint32_t vw[4] = {v.x, v.y, v.z, v.w}, dw[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[u][2 * j] += bf16_lo(dw[j]) * (bf16_lo(vw[j]) * r);
+                acc[u][2 * j + 1] += bf16_hi(dw[j]) * (bf16_hi(vw[j]) * r);
+            }
+            uint4 o = make_uint4(dx_word(v.x, wg.x, d.x, r, k), dx_word(v.y, wg.y, d.y, r, k), dx_word(v.z, wg.z, d.z, r, k),
+                                 dx_word(v.w, wg.w, d.w, r, k));
+            if (res) o = make_uint4(add_word(a.x, o.x), add_word(a.y, o.y), add_word(a.z, o.z), add_word(a.w, o.w));
+            if (in[u]) {
+                store_stream(dx + m * dc + threadIdx.x + kBlkThreads * u, o);
+                mag = absmax_acc(mag, o);
+            }
+        }
+        if (nw != w || !more) {  // the waves' sums in wave order
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) sum[u][j] = w == 0 ? acc[u][j] : sum[u][j] + acc[u][j], acc[u][j] = 0.0f;
+        }
+        if (!more) break;
+        m = nm, w = nw, row = next, buf ^= 1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (!in[u]) continue;
+        float4* out = reinterpret_cast<float4*>(partial + ((int64_t)blockIdx.x * dc + threadIdx.x + kBlkThreads * u) * 8);
+        out[0] = make_float4(sum[u][0], sum[u][1], sum[u][2], sum[u][3]);
+        out[1] = make_float4(sum[u][4], sum[u][5], sum[u][6], sum[u][7]);
+    }
+    if (amax_bits) {
+        const uint32_t mx = wave_max_u32(pk_collapse(mag)) << 16;
+        if (lane == 0 && mx > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, mx);
     }
 }
 
@@ -489,17 +597,19 @@ static f8_status rmsnorm_bwd(const void* x_bf16, const void* g_bf16, const float
     if (dg && (!workspace || workspace_bytes_ < (size_t)(strips * D) * sizeof(float))) return F8_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (D == 0) return F8_OK;
-    // One pass where a row fits the registers and the workspace holds a partial row of every block (two per
+    // One pass where a row fits the registers of a block and the workspace holds a partial row of every block (two per
     // compute unit; f8_workspace_bytes always does from 16 rows on, a caller's smaller one may not).
     const int64_t blocks = (M + kBlkWaves - 1) / kBlkWaves < kRowBlocks ? (M + kBlkWaves - 1) / kBlkWaves : kRowBlocks;
-    if (dg && M && D <= 8 * kWave * 8 && aligned16(workspace) && workspace_bytes_ >= (size_t)(blocks * D) * sizeof(float)) {
+    if (dg && M && D <= 8 * kBlkThreads * 4 && aligned16(workspace) && workspace_bytes_ >= (size_t)(blocks * D) * sizeof(float)) {
         const int dc = (int)(D / 8), chunks = (dc + kWave - 1) / kWave;  // 16-byte chunks of a row, in all and per lane
         int strips = (int)blocks;
         if (dx_bf16) {
             const auto kernel = chunks == 1   ? rmsnorm_bwd_fused_kernel<1>
                                 : chunks == 2 ? rmsnorm_bwd_fused_kernel<2>
-                                : chunks <= 4 ? rmsnorm_bwd_fused_kernel<4>
-                                              : rmsnorm_bwd_fused_kernel<8>;
+                                : chunks <= 4 ? rmsnorm_bwd_row_kernel<1>
+                                : chunks <= 8 ? rmsnorm_bwd_row_kernel<2>
+                                : chunks <= 12 ? rmsnorm_bwd_row_kernel<3>
+                                              : rmsnorm_bwd_row_kernel<4>;
             kernel<<<(unsigned)blocks, kBlkThreads, 0, st>>>((const uint4*)x_bf16, (const uint4*)g_bf16, rstd, (const uint4*)dy_bf16, M, dc,
                                                              1.0f / (float)D, (uint4*)dx_bf16, (const uint4*)add_bf16,
                                                              (float*)workspace, reinterpret_cast<uint32_t*>(amax_dx));

@@ -219,3 +219,23 @@ def test_rope_angles_of_every_quadrant(S):
         # bf16 keeps seven bits after the leading one: half a unit is at most 2^-8 of the value (1 % more where the
         # fp32 value falls the other way); and the fp32 of sine and cosine (absolute, near their zeros)
         assert bool(((c - ref).abs() <= 2.0 ** -8 * ref.abs() * 1.01 + 2.0 ** -23).all())
+
+
+@pytest.mark.parametrize("M", [16, 2032, 2048, 4112])
+@pytest.mark.parametrize("D", [1024, 1040, 2048, 2064, 4096, 4112, 6144, 6160, 8192, 8208])
+def test_rmsnorm_backward_a_row_per_block(M, D):
+    """Rows of 1040 to 8192 elements are taken by a block each, one to four chunks per thread; shorter ones by a wave,
+    longer ones in two passes.  At the edges of each, and of one row block per block (2048 rows): dx has the bits of dx
+    alone with the residual added after, dg is the fp64 sum."""
+    x, g, dy, res = gen((M, D), M).cuda(), gen((D,), D, 0.5).cuda(), gen((M, D), M + D, 1e-2).cuda(), gen((M, D), 7, 1e-2).cuda()
+    rstd = 1.0 / torch.sqrt(x.float().square().mean(1) + 1e-5)
+    ws = f8.new_workspace(M, D)
+    dx, dx2, summed = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+    dg, cell = torch.empty(D, device="cuda"), torch.zeros(1, device="cuda")
+    f8.rmsnorm_bwd_add(x, g, rstd, dy, res, dx, dg, ws, amax_dx_inout=cell)
+    f8.rmsnorm_bwd(x, g, rstd, dy, dx2, None)
+    f8.add(res, dx2, summed)
+    assert torch.equal(dx.view(torch.int16), summed.view(torch.int16)) and cell.item() == dx.float().abs().max().item()
+    # as above: below 1e-5 of the terms' sum
+    terms = dy.double() * x.double() * rstd.double()[:, None]
+    assert bool(((dg.double() - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0) + 1e-30).all())

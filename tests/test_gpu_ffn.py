@@ -239,6 +239,21 @@ def test_rmsnorm_forward(M, D):
     assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
 
 
+@pytest.mark.parametrize("M,D", [(4096, 4096), (4112, 4080), (2064, 8192)])
+def test_rmsnorm_of_large_tensors(M, D):
+    """Tensors of 16 M elements and more go past the caches: the bits of the call on pieces of the rows, which do not."""
+    x = torch.randn((M, D), device="cuda").to(torch.bfloat16)
+    gw = (1.0 + 0.1 * torch.randn(D, device="cuda")).to(torch.bfloat16)
+    ws, a, b = f8.new_workspace(M, D), torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    y, y2, r, r2 = torch.empty_like(x), torch.empty_like(x), torch.empty(M, device="cuda"), torch.empty(M, device="cuda")
+    f8.rmsnorm(x, gw, 1e-5, y, r, a, ws)
+    top = 0.0
+    for i in range(0, M, 1024):
+        f8.rmsnorm(x[i:i + 1024], gw, 1e-5, y2[i:i + 1024], r2[i:i + 1024], b, ws)
+        top = max(top, b.item())
+    assert torch.equal(y.view(torch.int16), y2.view(torch.int16)) and torch.equal(r, r2) and a.item() == top
+
+
 def test_norm_then_feed_forward_chain():
     """rmsnorm -> w1|w3 -> silu(a) * b -> w2 with every amax handed over: identical to the same
     sequence with each linear taking its own amax."""
