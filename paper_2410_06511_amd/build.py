@@ -22,6 +22,7 @@ FLAGS = [
 
 
 GEMM_INST = "f8_gemm_inst.hip"   # compiled once per (format of A, format of B, layout)
+GEMM_PAIR = "f8_gemm_pair.hip"   # compiled once per (format of dY, granularity)
 
 
 def sources():
@@ -35,10 +36,14 @@ def sources():
                     for layout in (0, 1, 2):
                         units.append((src, [f"-DF8_INST_FA={fa}", f"-DF8_INST_FB={fb}", f"-DF8_INST_LAYOUT={layout}"],
                                       f"f8_gemm_inst_{fa}{fb}{layout}.o"))
+        elif name == GEMM_PAIR:
+            for fa in (0, 1):
+                for g in (0, 1):
+                    units.append((src, [f"-DF8_PAIR_FA={fa}", f"-DF8_PAIR_GRAN={g}"], f"f8_gemm_pair_{fa}{g}.o"))
         else:
             units.append((src, [], name + ".o"))
     # the GEMM instances take longest: start them first
-    return sorted(units, key=lambda u: os.path.basename(u[0]) != GEMM_INST)
+    return sorted(units, key=lambda u: os.path.basename(u[0]) not in (GEMM_INST, GEMM_PAIR))
 
 
 def build(extra=(), verbose=False) -> str:

@@ -57,16 +57,16 @@ __device__ inline void amax_publish(uint32_t acc, uint32_t* amax_bits, uint32_t*
 // Tile order: consecutive workgroup ids go round-robin to the 8 XCDs, each with
 // its own L2.  Give every XCD one contiguous run of logical tile ids, and walk
 // the tiles in bands of kGroupM tile-rows so that the 32 CUs of an XCD share A
-// rows and B rows.
+// rows and B rows.  `xcds`: how many of them share the product (pid counts the workgroups on those).
 // ---------------------------------------------------------------------------
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 
-__device__ inline void tile_coords(int pid, int tiles_m, int tiles_n, int* tm, int* tn)
+__device__ inline void tile_coords(int pid, int tiles_m, int tiles_n, int* tm, int* tn, int xcds = kXcds)
 {
     const int total = tiles_m * tiles_n;
-    const int q = total / kXcds, r = total % kXcds;
-    const int xcd = pid % kXcds, idx = pid / kXcds;
+    const int q = total / xcds, r = total % xcds;
+    const int xcd = pid % xcds, idx = pid / xcds;
     const int logical = xcd * q + (xcd < r ? xcd : r) + idx;
     const int band = kGroupM * tiles_n;
     const int g = logical / band;
@@ -165,19 +165,30 @@ constexpr int kWaitAllVmLgkm = 0x0070;
 // everywhere the large products were 0.5 to 1 % slower (16384 x 14336 x 4096, forward and backward:
 // 2.219 ms against 2.206), while a separate 64x64-tile kernel for ragged lengths, which this
 // replaces, took 300 us for a 4096 x 4096 weight gradient over 2000 tokens (now 30).
+// The work is a device function: gemm_tile_kernel gives a launch to one product, gemm_pair_kernel (f8_gemm_pair.hip) to
+// two.  `first`, `stride`: this workgroup's work items; `xcds`: see tile_coords.
+// LDS of a workgroup.  One array per stage: the compiler then knows that a load into one stage does
+// not alias LDS reads of the other and does not serialise them.
+template <int BM, int BN>
+struct TileLds {
+    static constexpr int kEpw = BN / 2 / 16 >= 8 ? 8 : 4, kEpr = 8 / kEpw;  // of an epilogue pass, see below
+    static constexpr int kStage = (BM + BN) * kBK, kEpilogue = 4 * 16 * kEpr * (16 * kEpw * 2 + 16);
+};
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, int GRAN, bool AMAX, bool AKM, bool BKM,
-          bool SPLITK = false, bool RAGGED = false>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
+          bool SPLITK, bool RAGGED>
+__device__ __forceinline__ void gemm_tile_work(
     const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ D, int M,
     int N, int K, int64_t lda, int64_t ldb, int64_t ldd, const float* __restrict__ isa,
     const float* __restrict__ isb, int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits,
-    int ksteps /* K steps per work item, even */, int splits = 1, float* __restrict__ partial = nullptr, int64_t ldp = 0)
+    int ksteps /* K steps per work item, even */, int splits, float* __restrict__ partial, int64_t ldp,
+    int first, int stride, int xcds, uint8_t* st0, uint8_t* st1, uint8_t* epb)
 {
     static_assert(!(SPLITK && AMAX), "the output amax is taken by the kernel that writes D");
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
     constexpr int TM = WM / 16, TN = WN / 16;            // MFMA tiles (fragments) per wave
-    constexpr int A_BYTES = BM * kBK, STAGE = (BM + BN) * kBK;
+    constexpr int A_BYTES = BM * kBK;
     constexpr int A_LOADS = BM / 8 / NW, B_LOADS = BN / 8 / NW;  // 1 KB (8 rows) per wave load
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile rows must split over the waves");
     static_assert(NW == 4, "four waves");
@@ -186,15 +197,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     // An epilogue pass stages 8 MFMA tiles: EPW of them side by side (the whole width of the wave's
     // tile if that is 128 columns: a store instruction then covers 4 rows x 256 bytes, measured
     // 1 % faster on the products than 8 rows x 128 bytes), 8 / EPW below each other
-    constexpr int EPW = TN >= 8 ? 8 : 4, EPR = 8 / EPW;
+    constexpr int EPW = TileLds<BM, BN>::kEpw, EPR = TileLds<BM, BN>::kEpr;
     constexpr int EP_STRIDE = 16 * EPW * 2 + 16;    // bytes per staged epilogue row: the bf16 of a row + padding
     static_assert(TM % EPR == 0 && TN % EPW == 0, "the wave tile is a whole number of epilogue passes");
-
-    // One array per stage: the compiler then knows that a load into one stage does not alias
-    // LDS reads of the other and does not serialise them.
-    __shared__ __attribute__((aligned(1024))) uint8_t st0[STAGE];
-    __shared__ __attribute__((aligned(1024))) uint8_t st1[STAGE];
-    __shared__ __attribute__((aligned(16))) uint8_t epb[NW * 16 * EPR * EP_STRIDE];
+    static_assert(NW * 16 * EPR * EP_STRIDE == TileLds<BM, BN>::kEpilogue, "the caller's arrays");
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -215,7 +221,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     // M0, one instruction with a per-load lane offset (kept in a register, rebuilt per tile) and a
     // scalar base that moves with the K step.  Anything more per load would not fit between two
     // matrix instructions (32 cycles), and the matrix pipe would wait for the instruction stream.
-    int ld_tile = blockIdx.x;
+    int ld_tile = first;
     // row-major operand: the lane's row of piece 0 in the tile decides its chunk terms (the
     // swizzle looks at bits 1 and 2 of the row only, so every 8-row piece has the same)
     const int a_row = wave * (BM / NW) + (lane >> 3);
@@ -253,7 +259,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     int k_left = K;  // contraction length from the item's first k to the end of the operands
     auto load_context = [&](int item) {
         int tm, tn;
-        tile_coords(SPLITK ? item % tiles_mn : item, tiles_m, tiles_n, &tm, &tn);
+        tile_coords(SPLITK ? item % tiles_mn : item, tiles_m, tiles_n, &tm, &tn, xcds);
         const int64_t koff = SPLITK ? (int64_t)(item / tiles_mn) * KT * kBK : 0;  // first k of the item's range
         if constexpr (SPLITK) k_left = K - (int)koff;
         if constexpr (AKM) {
@@ -347,7 +353,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     // stays where it is: the same K steps are fetched again into stages nobody reads, so that
     // every K step issues the same number of loads and the wait counts below hold throughout.
     auto next_load_tile = [&]() {
-        ld_tile += gridDim.x;
+        ld_tile += stride;
         if (ld_tile < total_tiles) load_context(ld_tile);
     };
 
@@ -441,7 +447,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     // covers whole row segments of 32 EPW bytes (a multiple of the 128-byte line).
     auto epilogue = [&](int item) {
         int tm, tn;
-        tile_coords(SPLITK ? item % tiles_mn : item, tiles_m, tiles_n, &tm, &tn);
+        tile_coords(SPLITK ? item % tiles_mn : item, tiles_m, tiles_n, &tm, &tn, xcds);
         const int m0 = tm * BM + wm * WM, n0 = tn * BN + wn * WN;  // of this wave's tile
         if constexpr (SPLITK) {
             // the unscaled sums of this range, as 16-byte pieces (four consecutive n of one m per lane)
@@ -561,7 +567,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     };
 
     // ---- prologue: two stages in flight, the first K step's starting fragments into registers
-    load_context(ld_tile);  // the grid never exceeds the tile count
+    load_context(ld_tile);  // the caller has seen to it that there is one
     cut_loads(0);
     issue_all(0, I0{});
     cut_loads(1);
@@ -654,7 +660,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     // ---- main loop over this workgroup's tiles.  KT is even, so every tile starts in stage 0.
     // The step computed at kt fetches step kt + 2; the last two steps of a tile fetch the first
     // two of the next tile.
-    for (int tile = blockIdx.x; tile < total_tiles; tile += gridDim.x) {
+    for (int tile = first; tile < total_tiles; tile += stride) {
         // Retire every earlier vector-memory operation (the previous tile's stores, register
         // spills) once per tile.  Otherwise the compiler, which must protect the data
         // registers of pending stores, places its own full wait inside the K loop, where it
@@ -686,6 +692,22 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
     }
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, int GRAN, bool AMAX, bool AKM, bool BKM,
+          bool SPLITK = false, bool RAGGED = false>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
+    const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, uint16_t* __restrict__ D, int M,
+    int N, int K, int64_t lda, int64_t ldb, int64_t ldd, const float* __restrict__ isa,
+    const float* __restrict__ isb, int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits,
+    int ksteps, int splits = 1, float* __restrict__ partial = nullptr, int64_t ldp = 0)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t st0[TileLds<BM, BN>::kStage];
+    __shared__ __attribute__((aligned(1024))) uint8_t st1[TileLds<BM, BN>::kStage];
+    __shared__ __attribute__((aligned(16))) uint8_t epb[TileLds<BM, BN>::kEpilogue];
+    gemm_tile_work<BM, BN, WAVES_M, WAVES_N, FA, FB, GRAN, AMAX, AKM, BKM, SPLITK, RAGGED>(  // the grid never exceeds the item count
+        A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, amax_bits, ksteps, splits, partial, ldp,
+        (int)blockIdx.x, (int)gridDim.x, kXcds, st0, st1, epb);
+}
+
 // ---------------------------------------------------------------------------
 // small products: 64 x 64 tiles, one per workgroup, a deep load queue
 // ---------------------------------------------------------------------------
@@ -701,18 +723,21 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_tile_kernel(
 constexpr int kSm = 64;
 __device__ inline int kswz_small(int krow) { return ((krow >> 2) & 1) | (((krow >> 5) & 1) << 1); }  // four chunks per k-row
 
+constexpr int kSmOp = kSm * kBK;  // bytes of an operand's K step
+
+// `pid`: the workgroup's tile; st: [PAIRS][2][2 * kSmOp] bytes of LDS
 template <int FA, int FB, int GRAN, bool AKM, bool BKM, int PAIRS>
-__global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
-                                                         uint16_t* __restrict__ D, int M, int N, int K, int64_t lda, int64_t ldb,
-                                                         int64_t ldd, const float* __restrict__ isa, const float* __restrict__ isb,
-                                                         int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits /* nullable */)
+__device__ __forceinline__ void gemm_small_work(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
+                                                uint16_t* __restrict__ D, int M, int N, int K, int64_t lda, int64_t ldb,
+                                                int64_t ldd, const float* __restrict__ isa, const float* __restrict__ isb,
+                                                int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits /* nullable */,
+                                                int pid, uint8_t (&st)[PAIRS][2][2 * kSmOp])
 {
-    constexpr int OP = kSm * kBK;  // bytes of an operand's K step
-    __shared__ __attribute__((aligned(1024))) uint8_t st[PAIRS][2][2 * OP];
+    constexpr int OP = kSmOp;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, fr = lane & 15, fg = lane >> 4;
     int tm, tn;
-    tile_coords((int)blockIdx.x, tiles_m, tiles_n, &tm, &tn);
+    tile_coords(pid, tiles_m, tiles_n, &tm, &tn);
     const int m0 = tm * kSm, n0 = tn * kSm;
 
     // this lane's 16 bytes of its wave's two 1 KB pieces of an operand's K step: offset from the step's base, k
@@ -852,6 +877,17 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restri
     }
 }
 
+template <int FA, int FB, int GRAN, bool AKM, bool BKM, int PAIRS>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B,
+                                                         uint16_t* __restrict__ D, int M, int N, int K, int64_t lda, int64_t ldb,
+                                                         int64_t ldd, const float* __restrict__ isa, const float* __restrict__ isb,
+                                                         int tiles_m, int tiles_n, uint32_t* __restrict__ amax_bits)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t st[PAIRS][2][2 * kSmOp];
+    gemm_small_work<FA, FB, GRAN, AKM, BKM, PAIRS>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, amax_bits,
+                                                   (int)blockIdx.x, st);
+}
+
 // ---------------------------------------------------------------------------
 // split-K: sum of the ranges' partial results, scales, bf16
 // ---------------------------------------------------------------------------
@@ -954,11 +990,18 @@ static int splitk_ranges(int M, int N, int K, int cus, double best_unsplit, size
     return best;
 }
 
-template <int FA, int FB, int GRAN, bool AKM, bool BKM, bool RAGGED>
-static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
-                          const float* isa, const float* isb, uint16_t* D, int64_t ldd, uint32_t* amax_bits,
-                          void* ws, size_t ws_bytes, hipStream_t st)
+// How one product is launched.
+struct TilePlan {
+    enum Kind { kSmall, kSmallOnePair, kSplit, kFull, kFullRows, kFullCols, kHalf, kQuarter } kind;
+    int ranges;  // kSplit
+    int tm, tn;  // 256 x 256 tiles
+    int whole;   // kFullRows, kFullCols: tiles in whole rounds, launched on their own
+};
+
+// may_split: there is a workspace of ws_bytes for partial sums.
+static TilePlan plan_product(int M, int N, int K, bool b_kmajor, bool takes_amax, bool may_split, size_t ws_bytes)
 {
+    const bool ragged = K % (2 * kBK) != 0 || K <= 0;  // as dispatch_layout has it
     // Tile configuration by estimated time, in units of one 256x256 tile's time on one compute
     // unit: T tiles on `cus` persistent workgroups take ceil(T / cus) rounds; a 256x128 tile costs
     // about 0.63 and a 128x128 tile about 0.58 of a 256x256 one (measured: their wave tiles need
@@ -977,14 +1020,13 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
     const bool split_cols = !split_rows && whole > 0 && rest > 0 && 2 * rest <= cus && whole % tm == 0;
     const double c_full = (split_rows || split_cols) ? (double)(whole / cus) + kHalfTile : rounds(T);
     // With one pair of K steps a tile is its epilogue, which costs what its area does.
-    const bool one_pair = RAGGED && K <= 2 * kBK;
+    const bool one_pair = ragged && K <= 2 * kBK;
     const double c_half = rounds(tiles(256, 128)) * (one_pair ? 0.5 : kHalfTile);
     const double c_quarter = rounds(tiles(128, 128)) * (one_pair ? 0.25 : kQuarterTile);
-    const bool rw = GRAN != F8_TENSORWISE;
-    const bool may_split = ws && !amax_bits;
     const double best = c_full < c_half ? (c_full < c_quarter ? c_full : c_quarter) : (c_half < c_quarter ? c_half : c_quarter);
-    const int ranges = may_split ? splitk_ranges(M, N, K, cus, best, ws_bytes) : 1;
+    const int ranges = may_split && !takes_amax ? splitk_ranges(M, N, K, cus, best, ws_bytes) : 1;
     const int64_t small_tiles = tiles(kSm, kSm);
+    auto plan = [&](TilePlan::Kind kind) { return TilePlan{kind, ranges, tm, tn, (int)whole}; };
     // At most one 64 x 64 tile per compute unit: the deep load queue wins (operands not in the L2, 128 x 128 or 256-wide
     // tiles / this in us: 64 x 4096 x 4096 20 / 10, 1008 x 1024 x 2816 15.0 / 8.8, 256 x 1024 x 512 5.6 / 4.1); with
     // two rounds of tiles it does not (512 x 4096 x 4096 15.4 / 20.0).
@@ -992,52 +1034,69 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
     // 8192 28 / 30; row-major 1024 x 1024 x 8192 28 / 17, but 64 x 4096 x 16384 28 / 35.
     // With an amax of the output, whose atomics then come from 200 blocks at once (1 to 2 us), a short product keeps the
     // larger tiles unless there are few (1024 x 1024 x 512, operands in the L2: 9.3 / 10.6; 2048 long, not in the L2: 16 / 14).
-    const int64_t most = amax_bits && !RAGGED && K < 2048 ? cus / 2 : cus;
-    if (small_tiles <= most && (ranges == 1 || K < (BKM ? 8192 : 16384))) {
-        gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 4><<<(unsigned)small_tiles, 256, 0, st>>>(
-            A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (M + kSm - 1) / kSm, (N + kSm - 1) / kSm, amax_bits);
+    const int64_t most = takes_amax && !ragged && K < 2048 ? cus / 2 : cus;
+    if (small_tiles <= most && (ranges == 1 || K < (b_kmajor ? 8192 : 16384))) return plan(TilePlan::kSmall);
+    // One pair of K steps, and so few tiles that all of them are resident at once: without the ring (32 KB of LDS).
+    // Tile kernel / this in us: 9328 x 160 x 128 5.8 / 4.5, x 240 5.9 / 4.6, 2816 x 1024 x 64 6.3 / 5.4; with both K
+    // steps of the pair used and three tiles per unit no longer (256 x 11264 x 224 k-major 6.3 / 6.8, not in the L2).
+    if (one_pair && small_tiles <= (K <= kBK ? 3 : 2) * cus) return plan(TilePlan::kSmallOnePair);
+    if (ranges > 1) return plan(TilePlan::kSplit);
+    if (c_full <= c_half && c_full <= c_quarter)
+        return plan(split_rows ? TilePlan::kFullRows : split_cols ? TilePlan::kFullCols : TilePlan::kFull);
+    return plan(c_half <= c_quarter ? TilePlan::kHalf : TilePlan::kQuarter);
+}
+
+template <int FA, int FB, int GRAN, bool AKM, bool BKM, bool RAGGED>
+static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
+                          const float* isa, const float* isb, uint16_t* D, int64_t ldd, uint32_t* amax_bits,
+                          void* ws, size_t ws_bytes, hipStream_t st)
+{
+    const int cus = cu_count();
+    const TilePlan plan = plan_product(M, N, K, BKM, amax_bits != nullptr, ws != nullptr, ws_bytes);
+    const bool rw = GRAN != F8_TENSORWISE;
+    const int tm = plan.tm, tn = plan.tn;
+    const int sm = (M + kSm - 1) / kSm, sn = (N + kSm - 1) / kSm;
+    if (plan.kind == TilePlan::kSmall) {
+        gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 4><<<(unsigned)(sm * sn), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb,
+                                                                                          sm, sn, amax_bits);
         return;
     }
     if constexpr (RAGGED) {
-        // One pair of K steps, and so few tiles that all of them are resident at once: without the ring (32 KB of LDS).
-        // Tile kernel / this in us: 9328 x 160 x 128 5.8 / 4.5, x 240 5.9 / 4.6, 2816 x 1024 x 64 6.3 / 5.4; with both K
-        // steps of the pair used and three tiles per unit no longer (256 x 11264 x 224 k-major 6.3 / 6.8, not in the L2).
-        if (one_pair && small_tiles <= (K <= kBK ? 3 : 2) * cus) {
-            gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 1><<<(unsigned)small_tiles, 256, 0, st>>>(
-                A, B, D, M, N, K, lda, ldb, ldd, isa, isb, (M + kSm - 1) / kSm, (N + kSm - 1) / kSm, amax_bits);
+        if (plan.kind == TilePlan::kSmallOnePair) {
+            gemm_small_kernel<FA, FB, GRAN, AKM, BKM, 1><<<(unsigned)(sm * sn), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa,
+                                                                                              isb, sm, sn, amax_bits);
             return;
         }
     }
-    if (ranges > 1) {
+    if (plan.kind == TilePlan::kSplit) {
+        const int ranges = plan.ranges;
         float* partial = static_cast<float*>(ws);
         const bool whole_ranges = !RAGGED && K % (ranges * 2 * kBK) == 0;
         const auto kernel = whole_ranges ? gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, false>
                                          : gemm_tile_kernel<256, 256, 2, 2, FA, FB, GRAN, false, AKM, BKM, true, true>;
-        kernel<<<(unsigned)(T * ranges), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tm, tn, nullptr,
-                                                       ksteps_of(K, ranges), ranges, partial, (int64_t)N);
+        kernel<<<(unsigned)(tm * tn * ranges), 256, 0, st>>>(A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tm, tn, nullptr,
+                                                             ksteps_of(K, ranges), ranges, partial, (int64_t)N);
         const int64_t threads = (int64_t)M * (N / 8);
         splitk_reduce_kernel<GRAN><<<(unsigned)((threads + 255) / 256), 256, 0, st>>>(partial, ranges, M, N, (int64_t)N,
                                                                                      isa, isb, D, ldd);
         return;
     }
 #define F8_TILE(BM_, BN_) launch_tile<BM_, BN_, 2, 2, FA, FB, GRAN, AKM, BKM, RAGGED>
-    if (c_full <= c_half && c_full <= c_quarter) {
-        if (split_rows) {
-            const int m1 = (int)(whole / tn) * 256;
-            // rows m1 .. M-1 of A: m1 rows down (row-major) or m1 bytes along each k-row (k-major)
-            const uint8_t* A2 = AKM ? A + m1 : A + (int64_t)m1 * lda;
-            F8_TILE(256, 256)(m1, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
-            F8_TILE(256, 128)(M - m1, N, K, A2, lda, B, ldb, rw ? isa + m1 : isa, isb, D + (int64_t)m1 * ldd, ldd,
-                              amax_bits, cus, st);
-        } else if (split_cols) {
-            const int n1 = (int)(whole / tm) * 256;
-            const uint8_t* B2 = BKM ? B + n1 : B + (int64_t)n1 * ldb;
-            F8_TILE(256, 256)(M, n1, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
-            F8_TILE(256, 128)(M, N - n1, K, A, lda, B2, ldb, isa, rw ? isb + n1 : isb, D + n1, ldd, amax_bits, cus, st);
-        } else {
-            F8_TILE(256, 256)(M, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
-        }
-    } else if (c_half <= c_quarter) {
+    if (plan.kind == TilePlan::kFullRows) {
+        const int m1 = plan.whole / tn * 256;
+        // rows m1 .. M-1 of A: m1 rows down (row-major) or m1 bytes along each k-row (k-major)
+        const uint8_t* A2 = AKM ? A + m1 : A + (int64_t)m1 * lda;
+        F8_TILE(256, 256)(m1, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
+        F8_TILE(256, 128)(M - m1, N, K, A2, lda, B, ldb, rw ? isa + m1 : isa, isb, D + (int64_t)m1 * ldd, ldd,
+                          amax_bits, cus, st);
+    } else if (plan.kind == TilePlan::kFullCols) {
+        const int n1 = plan.whole / tm * 256;
+        const uint8_t* B2 = BKM ? B + n1 : B + (int64_t)n1 * ldb;
+        F8_TILE(256, 256)(M, n1, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
+        F8_TILE(256, 128)(M, N - n1, K, A, lda, B2, ldb, isa, rw ? isb + n1 : isb, D + n1, ldd, amax_bits, cus, st);
+    } else if (plan.kind == TilePlan::kFull) {
+        F8_TILE(256, 256)(M, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
+    } else if (plan.kind == TilePlan::kHalf) {
         F8_TILE(256, 128)(M, N, K, A, lda, B, ldb, isa, isb, D, ldd, amax_bits, cus, st);
     } else {
         // LDS allows two 128x128 workgroups per compute unit

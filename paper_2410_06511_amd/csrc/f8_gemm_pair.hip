@@ -1,0 +1,177 @@
+// Both products of a linear's backward in ONE launch: dX [M,K] = dY . W and dW [N,K] = dY^T . X.  The build compiles this
+// file once per format of dY and granularity (-DF8_PAIR_FA=<0|1>, -DF8_PAIR_GRAN=<F8_TENSORWISE | F8_ROWWISE>).
+#if !defined(F8_PAIR_FA) || !defined(F8_PAIR_GRAN)
+#error "compile with -DF8_PAIR_FA=, -DF8_PAIR_GRAN= (see build.py)"
+#endif
+#include "f8_gemm_kernels.hpp"
+
+namespace f8 {
+
+// One product as its kernel takes it
+struct PairSide {
+    const uint8_t *A, *B;
+    uint16_t* D;
+    int M, N, K;
+    int64_t lda, ldb, ldd;
+    const float *isa, *isb;
+    int tiles_m, tiles_n, ksteps;
+};
+
+// The XCDs share the products: those below x_xcds work on dX, the others on dW, each XCD as it would in a launch of its
+// own (one product's tiles in its L2).  Rowwise codes are read row-major in both products, tensorwise ones where they lie.
+template <int BM, int BN, int FA, int GRAN, bool RAGGED>
+__global__ __launch_bounds__(256) void gemm_pair_kernel(const PairSide x, const PairSide w, int x_xcds)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t st0[TileLds<BM, BN>::kStage];
+    __shared__ __attribute__((aligned(1024))) uint8_t st1[TileLds<BM, BN>::kStage];
+    __shared__ __attribute__((aligned(16))) uint8_t epb[TileLds<BM, BN>::kEpilogue];
+    constexpr bool KM = GRAN == F8_TENSORWISE;
+    const int xcd = (int)blockIdx.x % kXcds, idx = (int)blockIdx.x / kXcds, per_xcd = (int)gridDim.x / kXcds;
+    if (xcd < x_xcds) {
+        const int first = idx * x_xcds + xcd;
+        if (first >= x.tiles_m * x.tiles_n) return;
+        gemm_tile_work<BM, BN, 2, 2, FA, F8_E4M3, GRAN, false, false, KM, false, RAGGED>(
+            x.A, x.B, x.D, x.M, x.N, x.K, x.lda, x.ldb, x.ldd, x.isa, x.isb, x.tiles_m, x.tiles_n, nullptr, x.ksteps, 1,
+            nullptr, 0, first, per_xcd * x_xcds, x_xcds, st0, st1, epb);
+    } else {
+        const int xcds = kXcds - x_xcds, first = idx * xcds + (xcd - x_xcds);
+        if (first >= w.tiles_m * w.tiles_n) return;
+        gemm_tile_work<BM, BN, 2, 2, FA, F8_E4M3, GRAN, false, KM, KM, false, RAGGED>(
+            w.A, w.B, w.D, w.M, w.N, w.K, w.lda, w.ldb, w.ldd, w.isa, w.isb, w.tiles_m, w.tiles_n, nullptr, w.ksteps, 1,
+            nullptr, 0, first, per_xcd * xcds, xcds, st0, st1, epb);
+    }
+}
+
+template <int FA, int GRAN>
+__global__ __launch_bounds__(256) void gemm_small_pair_kernel(const PairSide x, const PairSide w)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t st[4][2][2 * kSmOp];
+    constexpr bool KM = GRAN == F8_TENSORWISE;
+    const int nx = x.tiles_m * x.tiles_n;
+    if ((int)blockIdx.x < nx)
+        gemm_small_work<FA, F8_E4M3, GRAN, false, KM, 4>(x.A, x.B, x.D, x.M, x.N, x.K, x.lda, x.ldb, x.ldd, x.isa, x.isb,
+                                                         x.tiles_m, x.tiles_n, nullptr, (int)blockIdx.x, st);
+    else
+        gemm_small_work<FA, F8_E4M3, GRAN, KM, KM, 4>(w.A, w.B, w.D, w.M, w.N, w.K, w.lda, w.ldb, w.ldd, w.isa, w.isb,
+                                                      w.tiles_m, w.tiles_n, nullptr, (int)blockIdx.x - nx, st);
+}
+
+template <int BM, int BN, int FA, int GRAN>
+static void launch_pair(PairSide x, PairSide w, int x_xcds, int cus, hipStream_t st)
+{
+    for (PairSide* s : {&x, &w}) s->tiles_m = (s->M + BM - 1) / BM, s->tiles_n = (s->N + BN - 1) / BN, s->ksteps = ksteps_of(s->K, 1);
+    const bool ragged = x.K % (2 * kBK) != 0 || w.K % (2 * kBK) != 0;
+    const unsigned grid = (unsigned)(BM * BN == 128 * 128 ? 2 * cus : cus);  // two workgroups of 128 x 128 tiles fit a compute unit
+    const auto kernel = ragged ? gemm_pair_kernel<BM, BN, FA, GRAN, true> : gemm_pair_kernel<BM, BN, FA, GRAN, false>;
+    kernel<<<grid, 256, 0, st>>>(x, w, x_xcds);
+}
+
+// ---------------------------------------------------------------------------
+// one launch or two
+// ---------------------------------------------------------------------------
+// Estimates in us, fitted to 236 backward passes of random linears (128 .. 16384 tokens, both granularities), each in one
+// launch in every way below and in two, and good to about 10 % each: a launch, its rounds of tiles, and per tile its K
+// steps and its epilogue.
+struct TileTime {
+    double step, epilogue;
+    double tile(int k) const { return ksteps_of(k, 1) * step + epilogue; }
+};
+constexpr TileTime kFullTime{1.04, 7.9}, kHalfTime{0.70, 2.95}, kSmallTime{0.256, 1.9};
+
+// 128 x 128 tiles, two on a compute unit at once where it has more than one
+static double quarter_us(int64_t per_cu, int k, double alone, double two, double epilogue)
+{
+    const int steps = ksteps_of(k, 1);
+    return (double)(per_cu / 2) * (steps * two + epilogue) + (double)(per_cu % 2) * (steps * alone + epilogue);
+}
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+static int64_t tile_count(const PairSide& s, int bm, int bn) { return ceil_div(s.M, bm) * ceil_div(s.N, bn); }
+
+static double alone_us(const PairSide& s, bool b_kmajor, bool may_split, size_t ws_bytes, int cus, double launch)
+{
+    const TilePlan p = plan_product(s.M, s.N, s.K, b_kmajor, false, may_split, ws_bytes);
+    switch (p.kind) {
+        case TilePlan::kSmall: return 4.65 + ksteps_of(s.K, 1) * 0.244;
+        case TilePlan::kSmallOnePair: return 4.65;
+        case TilePlan::kSplit:  // and the pass that adds the ranges
+            return 2 * launch + ksteps_of(s.K, p.ranges) * kFullTime.step + kFullTime.epilogue + (p.ranges + 0.5) * s.M * s.N * 4.0 / 5.0e6;
+        case TilePlan::kFull: return launch + ceil_div((int64_t)p.tm * p.tn, cus) * kFullTime.tile(s.K);
+        case TilePlan::kFullRows:
+        case TilePlan::kFullCols: return 2 * launch + p.whole / cus * kFullTime.tile(s.K) + kHalfTime.tile(s.K);
+        case TilePlan::kHalf: return launch + ceil_div(tile_count(s, 256, 128), cus) * kHalfTime.tile(s.K);
+        case TilePlan::kQuarter: break;
+    }
+    return launch + quarter_us(ceil_div(tile_count(s, 128, 128), cus), s.K, 0.49, 2.5, 0.6);
+}
+
+#define F8_PAIR_NAME_(fa, g) gemm_pair_##fa##_##g
+#define F8_PAIR_NAME(fa, g) F8_PAIR_NAME_(fa, g)
+
+// One launch where it is estimated to be enough faster than the separate ones.  dX and dW have the same number of
+// operations, so an even division of the XCDs is mostly right (others are taken only for 3 % more); it is the rounds of
+// tiles that decide: 896 tiles are 3.5 rounds of a whole chip, but 7 of half of it, and the two products' epilogues
+// (67 MB of dX in 14 us for 8192 x 4096) overlap with each other's arithmetic.  Over those 236 passes this rule gave 1.13
+// in the mean (the best choice at hand each time: 1.157).  us of a backward, two launches / one: 256 x 512 x 1024 (tokens,
+// inputs, outputs) 15.4 / 12.7, 8192 x 4096 x 1024 101 / 78, 2000 x 4096 x 4096 72 / 67, 8192 x 4096 x 6144 354 / 322,
+// 16384 x 4096 x 14336 1459 / 1441.  The margin is 0.985 for the tiles that large separate launches have too, 0.95 for the
+// others (with less, 192 x 2176 x 11648 takes 1.09 times as long).  Where no round is saved there is nothing to gain: within
+// a whole step 8192 x 3584 x 8192 would be 1 % and rowwise 8192 x 16384 x 2048 3 % slower.
+bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& gw, void* ws, size_t ws_bytes, hipStream_t st)
+{
+    constexpr int FA = F8_PAIR_FA, GRAN = F8_PAIR_GRAN;
+    auto side = [](const GemmArgs& a) {
+        return PairSide{a.A, a.B, a.D, a.M, a.N, a.K, a.lda, a.ldb, a.ldd, a.isa, a.isb, 0, 0, 0};
+    };
+    const PairSide x = side(gx), w = side(gw);
+    const int cus = cu_count(), per_xcd = cus / kXcds;
+    constexpr bool KM = GRAN == F8_TENSORWISE;
+    auto separately = [&](double launch) {
+        return alone_us(x, KM, false, 0, cus, launch) + alone_us(w, KM, ws != nullptr, ws_bytes, cus, launch);
+    };
+    // Where the products take long, a launch hides behind the one before it and saves nothing by itself.
+    double apart = separately(4.5);
+    const bool hidden = apart > 200.0;
+    if (hidden) apart = separately(0.0);
+    // Smaller tiles than 256 x 256 need more of the L2 per product: not with more than two rounds of work.
+    const bool few = tile_count(x, 256, 256) + tile_count(w, 256, 256) <= 2 * cus;
+
+    double best = apart;
+    int tile = 0, x_xcds = 0;
+    // 64 x 64 tiles, several rounds of them if need be: the other tiles' larger areas leave more of the chip idle.
+    const int64_t small = tile_count(x, kSm, kSm) + tile_count(w, kSm, kSm);
+    if (small <= 4 * cus) {
+        const double tx = kSmallTime.tile(x.K), tw = kSmallTime.tile(w.K), longest = tx > tw ? tx : tw;
+        const double work = (tile_count(x, kSm, kSm) * tx + tile_count(w, kSm, kSm) * tw) / cus + 0.22 * longest;
+        const double us = 4.8 + (work > longest ? work : longest);
+        if (us < 0.95 * best) best = us / 0.95, tile = kSm;
+    }
+    for (int xc : {4, 3, 5}) {
+        auto side_us = [&](const PairSide& s, int xcds, int t) {
+            const int64_t units = (int64_t)per_xcd * xcds;
+            if (t == 256) return ceil_div(tile_count(s, 256, 256), units) * kFullTime.tile(s.K);
+            if (t == 192) return ceil_div(tile_count(s, 256, 128), units) * kHalfTime.tile(s.K);
+            return quarter_us(ceil_div(tile_count(s, 128, 128), units), s.K, 0.46, 1.13, 2.8);
+        };
+        for (int t : {256, 192, 128}) {  // 192: 256 x 128
+            if (t != 256 && !few) continue;
+            const double tx = side_us(x, xc, t), tw = side_us(w, kXcds - xc, t), launch = hidden ? 0.0 : t == 256 ? 2.5 : t == 192 ? 3.5 : 3.9;
+            const double margin = (t == 256 ? 0.985 : 0.95) / (xc == 4 ? 1.0 : 1.03);
+            const double us = (launch + (tx > tw ? tx : tw)) / margin;
+            if (us < best) best = us, tile = t, x_xcds = xc;
+        }
+    }
+    switch (tile) {
+        case kSm: {
+            PairSide a = x, b = w;
+            for (PairSide* s : {&a, &b}) s->tiles_m = (s->M + kSm - 1) / kSm, s->tiles_n = (s->N + kSm - 1) / kSm;
+            gemm_small_pair_kernel<FA, GRAN><<<(unsigned)small, 256, 0, st>>>(a, b);
+            return true;
+        }
+        case 128: launch_pair<128, 128, FA, GRAN>(x, w, x_xcds, cus, st); return true;
+        case 192: launch_pair<256, 128, FA, GRAN>(x, w, x_xcds, cus, st); return true;
+        case 256: launch_pair<256, 256, FA, GRAN>(x, w, x_xcds, cus, st); return true;
+    }
+    return false;
+}
+
+}  // namespace f8

@@ -67,6 +67,18 @@ f8_status quantise_known_amax(const void* x, int64_t rows, int64_t cols, int64_t
 f8_status gemm(int layout, int64_t M, int64_t N, int64_t K, const uint8_t* A, int fa, int64_t lda,
                const uint8_t* B, int fb, int64_t ldb, const float* isa, const float* isb, int g,
                void* D, int64_t ldd, float* amax_d, hipStream_t st, void* ws = nullptr, size_t ws_bytes = 0);
+// The two products of a linear's backward (dX, dW) in one launch, where that is the faster way: true if they have been
+// enqueued.  Validated operands; both outputs and contractions are non-empty.  Tensorwise: dX as F8_NN, dW as F8_TN;
+// rowwise: both as F8_NT.  ws as in gemm.
+struct GemmArgs {
+    int M, N, K;
+    const uint8_t *A, *B;
+    int64_t lda, ldb;
+    const float *isa, *isb;
+    uint16_t* D;
+    int64_t ldd;
+};
+bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, void* ws, size_t ws_bytes, hipStream_t st);
 // Largest scratch a split product can use (ranges x output elements x 4 bytes, with ranges x tiles
 // at most one per compute unit): part of what workspace_bytes returns.
 constexpr size_t kSplitKMaxBytes = (size_t)256 * 256 * 256 * sizeof(float);

@@ -314,3 +314,30 @@ def test_split_contraction_against_oracle(rowwise, transposed):
     # per-line criterion too, so that a wrong range of rows cannot hide behind the global maximum
     gf, rf = o.bf16_to_f32(bits(dW)).astype(np.float64), o.bf16_to_f32(rdW).astype(np.float64)
     assert (np.abs(gf - rf).max(axis=1) <= 1e-2 * np.abs(rf).max()).all()
+
+
+# One launch for both products of the backward: 64x64 tiles (one ragged, one with a single pair of K steps, one of several
+# rounds), 128x128, 256x128 (the XCDs divided 4 : 4 and 3 : 5) and 256x256 tiles (several per workgroup), ragged
+# contractions, per-row scales, XCDs with more workgroups than tiles.
+PAIRS = [(16, 16, 16), (256, 512, 1024), (272, 336, 208), (1328, 256, 13312), (480, 1376, 512), (1008, 1024, 1536),
+         (2048, 2048, 2048), (2064, 2064, 1552), (1040, 2064, 2064), (2000, 4096, 4096), (8192, 4096, 1024)]
+
+
+@pytest.mark.parametrize("rowwise", (False, True))
+@pytest.mark.parametrize("M,K,N", PAIRS)
+def test_backward_in_one_launch_has_the_bits_of_two(M, K, N, rowwise):
+    """Same instructions and the same order of each contraction as separate (unsplit) f8_gemm calls on the same codes."""
+    g = torch.Generator("cuda")
+    g.manual_seed(M + K + N)
+    R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    for gf in (f8.E4M3, f8.E5M2):
+        _, dX, dW, sv = run_linear(R(1.0, M, K), R(0.02, N, K), R(1e-3, M, N), rowwise, gf)
+        rX, rW = torch.full_like(dX, float("nan")), torch.full_like(dW, float("nan"))
+        if rowwise:
+            f8.gemm(f8.NT, M, K, N, sv.dy.q, gf, sv.w.q_t, f8.E4M3, sv.dy.inv_scale, sv.w.inv_scale_t, f8.ROWWISE, rX)
+            f8.gemm(f8.NT, N, K, M, sv.dy.q_t, gf, sv.x.q_t, f8.E4M3, sv.dy.inv_scale_t, sv.x.inv_scale_t, f8.ROWWISE, rW)
+        else:
+            f8.gemm(f8.NN, M, K, N, sv.dy.q, gf, sv.w.q, f8.E4M3, sv.dy.inv_scale, sv.w.inv_scale, f8.TENSORWISE, rX)
+            f8.gemm(f8.TN, N, K, M, sv.dy.q, gf, sv.x.q, f8.E4M3, sv.dy.inv_scale, sv.x.inv_scale, f8.TENSORWISE, rW)
+        assert torch.equal(dX.view(torch.int16), rX.view(torch.int16))
+        assert torch.equal(dW.view(torch.int16), rW.view(torch.int16))
