@@ -39,13 +39,14 @@ bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, void* ws, si
 }
 
 __global__ void zero_word_kernel(uint32_t* p) { p[0] = 0; }
+void zero_word(uint32_t* p, hipStream_t st) { zero_word_kernel<<<1, 1, 0, st>>>(p); }
 
 f8_status gemm(int layout, int64_t M, int64_t N, int64_t K, const uint8_t* A, int fa, int64_t lda,
                const uint8_t* B, int fb, int64_t ldb, const float* isa, const float* isb, int g, void* D,
                int64_t ldd, float* amax_d, hipStream_t st, void* ws, size_t ws_bytes)
 {
     uint32_t* amax_bits = reinterpret_cast<uint32_t*>(amax_d);
-    if (amax_bits) zero_word_kernel<<<1, 1, 0, st>>>(amax_bits);
+    if (amax_bits) zero_word(amax_bits, st);
     if (M == 0 || N == 0) return last_launch_status();
     uint16_t* d = static_cast<uint16_t*>(D);
     const int m = (int)M, n = (int)N, k = (int)K;

@@ -79,6 +79,11 @@ struct GemmArgs {
     int64_t ldd;
 };
 bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, void* ws, size_t ws_bytes, hipStream_t st);
+// F8_NT product of few rows (contiguous e4m3 operands), where a kernel of its own is faster: true if it has been enqueued.
+// It adds the contraction in another order than gemm.
+bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, const float* isa, const float* isb, uint16_t* D,
+               uint32_t* amax_bits, hipStream_t st);
+void zero_word(uint32_t* p, hipStream_t st);  // not a memset: the call may be captured
 // Largest scratch a split product can use (ranges x output elements x 4 bytes, with ranges x tiles
 // at most one per compute unit): part of what workspace_bytes returns.
 constexpr size_t kSplitKMaxBytes = (size_t)256 * 256 * 256 * sizeof(float);

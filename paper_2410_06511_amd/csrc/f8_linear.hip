@@ -151,6 +151,9 @@ static f8_status check_bwd(const f8_linear_desc* d, bool tensorwise_only, const 
 // Y [M,N] = X8 [M,K] . (W8 [N,K])^T, scales in the epilogue; y_amax may be null.
 static f8_status gemm_fwd(const f8_linear_desc* d, const f8_saved* sv, void* Y, float* y_amax, hipStream_t st)
 {
+    if (gemm_rows(d->granularity, (int)d->M, (int)d->N, (int)d->K, sv->x.q, sv->w.q, sv->x.inv_scale, sv->w.inv_scale,
+                  static_cast<uint16_t*>(Y), reinterpret_cast<uint32_t*>(y_amax), st))
+        return last_launch_status();
     return gemm(F8_NT, d->M, d->N, d->K, sv->x.q, F8_E4M3, d->K, sv->w.q, F8_E4M3, d->K, sv->x.inv_scale,
                 sv->w.inv_scale, d->granularity, Y, d->N, y_amax, st);
 }

@@ -6,7 +6,7 @@ import torch
 import oracle as o
 from paper_2410_06511_amd import f8
 from paper_2410_06511_amd import workloads as wl
-from helpers import bits, u8, f32, assert_gemm_close, sampled_check, qt_matches
+from helpers import bits, u8, f32, assert_gemm_close, assert_gemm_tight, group_max_sum, sampled_check, qt_matches
 
 pytestmark = pytest.mark.gpu
 
@@ -341,3 +341,27 @@ def test_backward_in_one_launch_has_the_bits_of_two(M, K, N, rowwise):
             f8.gemm(f8.TN, N, K, M, sv.dy.q, gf, sv.x.q, f8.E4M3, sv.dy.inv_scale, sv.x.inv_scale, f8.TENSORWISE, rW)
         assert torch.equal(dX.view(torch.int16), rX.view(torch.int16))
         assert torch.equal(dW.view(torch.int16), rW.view(torch.int16))
+
+
+# Forwards of few tokens, one of every tile shape of their kernel (16 x 16, 16 x 32, 32 x 32, 64 x 32, 64 x 64), with rows,
+# columns and contractions that end inside a tile or a K step, waves with one K step more than others, and two rounds.
+@pytest.mark.parametrize("rowwise", (False, True))
+@pytest.mark.parametrize("M,K,N", [(16, 512, 1024), (48, 528, 1040), (16, 4096, 4096), (32, 2048, 8208), (64, 4096, 4096),
+                                   (80, 4112, 2064), (112, 3856, 2304), (512, 2064, 1840), (304, 6400, 1280)])
+def test_forward_of_few_tokens(M, K, N, rowwise):
+    """Against the fp64 product of the codes, with the bound that holds for the matrix instruction and fp32 sums."""
+    g = torch.Generator("cuda")
+    g.manual_seed(M + K + N)
+    R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    X, W = R(1.0, M, K), R(0.02, N, K)
+    desc, sv, ws = f8.linear_desc(M, K, N, rowwise), f8.Saved(M, K, N, rowwise), f8.new_workspace(max(M, K, N), max(M, K, N))
+    Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    f8.linear_fwd(desc, X, W, Y, sv, ws)
+    isa, isb = f32(sv.x.inv_scale), f32(sv.w.inv_scale)
+    op = (o.NT, u8(sv.x.q), o.E4M3, u8(sv.w.q), o.E4M3) + ((isa, isb) if rowwise else (isa[0], isb[0]))
+    d64, dabs = o.gemm_f64(*op, f8.ROWWISE if rowwise else f8.TENSORWISE)
+    assert_gemm_tight(bits(Y), d64, dabs, K, (M, K, N, rowwise), group_max_sum(*op, rowwise) if M * K * N < 1e8 else None)
+    if not rowwise:  # the output's amax, and the same bits with it
+        Y2, amax = torch.empty_like(Y), torch.full((1,), 7e7, device="cuda")
+        f8.linear_fwd_chained(desc, X, None, W, Y2, amax, sv, ws)
+        assert torch.equal(Y2.view(torch.int16), Y.view(torch.int16)) and amax.item() == Y.float().abs().max().item()
