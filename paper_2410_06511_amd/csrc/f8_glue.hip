@@ -6,6 +6,8 @@
 // Both are elementwise and HBM-bound.  Each also leaves the amax of what it wrote, taken while
 // the values are in registers, so that the Float8 linear that consumes the result casts it in
 // one pass (f8_linear_fwd_chained / f8_linear_bwd_chained) instead of reading it twice.
+#include <type_traits>
+
 #include "f8_device.hpp"
 #include "f8_host.hpp"
 
@@ -17,34 +19,51 @@ constexpr int kGlueMaxBlocks = 2048;
 static_assert((size_t)kGlueMaxBlocks * sizeof(uint32_t) <= kMinWorkspaceBytes, "one partial per block fits the minimum workspace");
 
 // ab [M, 2H] as 16-byte chunks: row m has 2 * hc chunks, a first; h [M, H]: hc chunks per row.
-// Bound by memory.  A block takes kGateChunks chunks per thread that lie side by side, then as many a grid further on:
-// one front moves through each tensor.  (Chunks of one thread a grid apart are streams some MB apart that meet in the
-// same memory channels.)  Loads and stores stream past the caches: of tensors of this size they would keep little.
-// 8192 x 14336: forward 134 -> 117 us (6.0 TB/s), backward 227 -> 200 us (5.9 TB/s); 2048 x 4096 15.8 -> 12.8 and 21.3 -> 18.1.
-constexpr int kGateChunks = 2;
-constexpr int kGateTile = kGateChunks * kGlueThreads;
-constexpr int kGateMaxBlocks = 1024;  // (2048: 0.5 to 1.5 % slower)
+// Bound by memory.  A block takes CHUNKS chunks per thread that lie side by side, then as many a grid further on: one front
+// moves through each tensor.  (Chunks of one thread a grid apart are streams some MB apart that meet in the same memory
+// channels.)  Two chunks a thread, except where one each still fits the most blocks: the loads of few blocks then start at
+// once (608 x 6496 backward 8.5 us with two, 7.7 with one).
+// STREAM: loads and stores past the caches, for tensors of which they would keep little until they are read again.  us plain
+// / past them, with other data in between: 8192 x 14336 forward 130 / 118 (6.0 TB/s), backward 223 / 204, 2048 x 14336
+// 33.1 / 30.0 and 54.5 / 49.5, 2048 x 4096 11.3 / 10.0 and 17.2 / 15.4; where the operands are still in the caches that is
+// 8 % slower up to 2048 x 14336, so the line lies where a pass of their own (6 to 10 bytes an element) turns most of them over.
+constexpr int kGateMaxBlocks = 1024;  // of many tiles (2048: 0.5 to 1.5 % slower)
+constexpr int64_t kGateStreamChunks = (int64_t)1 << 20;  // 8 M elements of h
 
+template <bool STREAM>
+__device__ inline uint4 gate_load(const uint4* p)
+{
+    if constexpr (STREAM) return load_once(p);
+    else return *p;
+}
+template <bool STREAM>
+__device__ inline void gate_store(uint4* p, uint4 v)
+{
+    if constexpr (STREAM) store_stream(p, v);
+    else *p = v;
+}
+
+template <bool STREAM, int CHUNKS>
 __global__ __launch_bounds__(kGlueThreads) void silu_mul_kernel(const uint4* __restrict__ ab, int64_t M, int64_t hc,
                                                                uint4* __restrict__ h, uint32_t* __restrict__ partial)
 {
     __shared__ uint32_t red[kGlueWaves];
     const int64_t n = M * hc;
     uint32_t acc = 0;
-    for (int64_t c0 = (int64_t)blockIdx.x * kGateTile + threadIdx.x; c0 < n; c0 += (int64_t)gridDim.x * kGateTile) {
-        uint4 a[kGateChunks], b[kGateChunks];
+    for (int64_t c0 = (int64_t)blockIdx.x * (CHUNKS * kGlueThreads) + threadIdx.x; c0 < n; c0 += (int64_t)gridDim.x * (CHUNKS * kGlueThreads)) {
+        uint4 a[CHUNKS], b[CHUNKS];
 #pragma unroll
-        for (int u = 0; u < kGateChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             const int64_t c = c0 + u * kGlueThreads < n ? c0 + u * kGlueThreads : c0, at = c + c / hc * hc;
-            a[u] = load_once(ab + at), b[u] = load_once(ab + at + hc);
+            a[u] = gate_load<STREAM>(ab + at), b[u] = gate_load<STREAM>(ab + at + hc);
         }
 #pragma unroll
-        for (int u = 0; u < kGateChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             if (c0 + u * kGlueThreads >= n) break;
             uint4 o;
             o.x = silu_mul2(a[u].x, b[u].x), o.y = silu_mul2(a[u].y, b[u].y);
             o.z = silu_mul2(a[u].z, b[u].z), o.w = silu_mul2(a[u].w, b[u].w);
-            store_stream(h + c0 + u * kGlueThreads, o);
+            gate_store<STREAM>(h + c0 + u * kGlueThreads, o);
             acc = absmax_acc(acc, o);
         }
     }
@@ -54,6 +73,7 @@ __global__ __launch_bounds__(kGlueThreads) void silu_mul_kernel(const uint4* __r
     }
 }
 
+template <bool STREAM, int CHUNKS>
 __global__ __launch_bounds__(kGlueThreads) void silu_mul_bwd_kernel(const uint4* __restrict__ ab, const uint4* __restrict__ dh,
                                                                    int64_t M, int64_t hc, uint4* __restrict__ dab,
                                                                    uint32_t* __restrict__ partial)
@@ -61,25 +81,25 @@ __global__ __launch_bounds__(kGlueThreads) void silu_mul_bwd_kernel(const uint4*
     __shared__ uint32_t red[kGlueWaves];
     const int64_t n = M * hc;
     uint32_t acc = 0;
-    for (int64_t c0 = (int64_t)blockIdx.x * kGateTile + threadIdx.x; c0 < n; c0 += (int64_t)gridDim.x * kGateTile) {
-        uint4 a[kGateChunks], b[kGateChunks], g[kGateChunks];
-        int64_t at[kGateChunks];
+    for (int64_t c0 = (int64_t)blockIdx.x * (CHUNKS * kGlueThreads) + threadIdx.x; c0 < n; c0 += (int64_t)gridDim.x * (CHUNKS * kGlueThreads)) {
+        uint4 a[CHUNKS], b[CHUNKS], g[CHUNKS];
+        int64_t at[CHUNKS];
 #pragma unroll
-        for (int u = 0; u < kGateChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             const int64_t c = c0 + u * kGlueThreads < n ? c0 + u * kGlueThreads : c0;
             at[u] = c + c / hc * hc;
-            a[u] = load_once(ab + at[u]), b[u] = load_once(ab + at[u] + hc), g[u] = load_once(dh + c);
+            a[u] = gate_load<STREAM>(ab + at[u]), b[u] = gate_load<STREAM>(ab + at[u] + hc), g[u] = gate_load<STREAM>(dh + c);
         }
 #pragma unroll
-        for (int u = 0; u < kGateChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             if (c0 + u * kGlueThreads >= n) break;
             uint4 da, db;
             silu_mul_bwd2(a[u].x, b[u].x, g[u].x, &da.x, &db.x);
             silu_mul_bwd2(a[u].y, b[u].y, g[u].y, &da.y, &db.y);
             silu_mul_bwd2(a[u].z, b[u].z, g[u].z, &da.z, &db.z);
             silu_mul_bwd2(a[u].w, b[u].w, g[u].w, &da.w, &db.w);
-            store_stream(dab + at[u], da);
-            store_stream(dab + at[u] + hc, db);
+            gate_store<STREAM>(dab + at[u], da);
+            gate_store<STREAM>(dab + at[u] + hc, db);
             acc = absmax_acc(absmax_acc(acc, da), db);
         }
     }
@@ -172,10 +192,16 @@ __global__ __launch_bounds__(kGlueThreads) void rmsnorm_kernel(const uint4* __re
     }
 }
 
-static int gate_blocks(int64_t chunks)
+// f(which instance of a gate kernel, its blocks)
+template <class F>
+static int launch_gate(int64_t chunks, F&& f)
 {
-    const int64_t b = (chunks + kGateTile - 1) / kGateTile;
-    return (int)(b < kGateMaxBlocks ? b : kGateMaxBlocks);
+    const int64_t one = (chunks + kGlueThreads - 1) / kGlueThreads, two = (one + 1) / 2;
+    if (one <= kGlueMaxBlocks) return f(std::false_type{}, std::integral_constant<int, 1>{}, (int)one), (int)one;
+    const int nb = (int)(two <= kGlueMaxBlocks ? two : kGateMaxBlocks);
+    if (chunks >= kGateStreamChunks) f(std::true_type{}, std::integral_constant<int, 2>{}, nb);
+    else f(std::false_type{}, std::integral_constant<int, 2>{}, nb);
+    return nb;
 }
 
 static f8_status check_glue(const void* ab, const void* other, void* out, int64_t M, int64_t H, const float* amax,
@@ -203,9 +229,10 @@ f8_status f8_silu_mul(const void* ab_bf16, int64_t M, int64_t H, void* h_bf16, f
     const int64_t hc = H / 8;
     int nb = 0;
     if (M > 0 && H > 0) {
-        nb = gate_blocks(M * hc);
-        silu_mul_kernel<<<nb, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, M, hc, (uint4*)h_bf16,
-                                                     amax_h ? (uint32_t*)workspace : nullptr);
+        nb = launch_gate(M * hc, [&](auto STREAM, auto CHUNKS, int blocks) {
+            silu_mul_kernel<STREAM(), CHUNKS()><<<blocks, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, M, hc, (uint4*)h_bf16,
+                                                                                amax_h ? (uint32_t*)workspace : nullptr);
+        });
     }
     if (amax_h) glue_amax_final_kernel<<<1, kGlueThreads, 0, st>>>((const uint32_t*)workspace, nb, amax_h);
     return last_launch_status();
@@ -220,9 +247,10 @@ f8_status f8_silu_mul_bwd(const void* ab_bf16, const void* dh_bf16, int64_t M, i
     const int64_t hc = H / 8;
     int nb = 0;
     if (M > 0 && H > 0) {
-        nb = gate_blocks(M * hc);
-        silu_mul_bwd_kernel<<<nb, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, (const uint4*)dh_bf16, M, hc,
-                                                         (uint4*)dab_bf16, amax_dab ? (uint32_t*)workspace : nullptr);
+        nb = launch_gate(M * hc, [&](auto STREAM, auto CHUNKS, int blocks) {
+            silu_mul_bwd_kernel<STREAM(), CHUNKS()><<<blocks, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, (const uint4*)dh_bf16, M, hc,
+                                                                                    (uint4*)dab_bf16, amax_dab ? (uint32_t*)workspace : nullptr);
+        });
     }
     if (amax_dab) glue_amax_final_kernel<<<1, kGlueThreads, 0, st>>>((const uint32_t*)workspace, nb, amax_dab);
     return last_launch_status();
