@@ -42,6 +42,16 @@ f8_status cast_measure(const void* x, int64_t rows, int64_t cols, int64_t ld, co
 f8_status history_push(const void* partial, int npartial, const float* amax_in, float* history, int64_t len,
                        int fmt, float* amax_out, const float* used_scale, float* saved_scale,
                        float* saved_inv, float* next_scale, float* next_inv, hipStream_t st);
+// A forward's X and W under delayed scaling, the casts in one launch and the histories in another: true if that has been
+// enqueued (contiguous, no transposed copies, no state or scale cell that the two share, partial maxima that fit ws).
+struct DelayedTensor {
+    const void* x;
+    int64_t rows, cols;
+    float *history, *scale;  // of the state
+    const f8_qtensor* q;
+};
+bool quantise_delayed_pair(const DelayedTensor& a, const DelayedTensor& b, int64_t len, int fmt, void* ws, size_t ws_bytes,
+                           hipStream_t st);
 f8_status publish_scale(const float* s_in, float* s_out, float* inv_out, hipStream_t st);
 f8_status cast_given(const void* x, int64_t rows, int64_t cols, int64_t ld, const float* scale, int fmt,
                      uint8_t* out, int64_t ld_out, uint8_t* out_t, int64_t ld_out_t, hipStream_t st);

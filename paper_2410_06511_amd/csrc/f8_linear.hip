@@ -330,6 +330,13 @@ f8_status f8_linear_fwd_scaled(const f8_linear_desc* d, const f8_scaling_state* 
     if (state->mode == F8_DYNAMIC) return f8_linear_fwd(d, X, W, Y, saved, workspace, workspace_bytes_, stream);
     if ((s = check_fwd(d, true, X, W, Y, saved, workspace, workspace_bytes_)) != F8_OK) return s;
     hipStream_t st = (hipStream_t)stream;
+    if (state->mode == F8_DELAYED &&
+        quantise_delayed_pair({X, d->M, d->K, state->hist_x, state->scale_x, &saved->x},
+                              {W, d->N, d->K, state->hist_w, state->scale_w, &saved->w}, state->history_len, F8_E4M3, workspace,
+                              workspace_bytes_, st)) {
+        if ((s = last_launch_status()) != F8_OK) return s;
+        return gemm_fwd(d, saved, Y, nullptr, st);
+    }
     if ((s = quantise_scaled(X, d->M, d->K, F8_E4M3, state->mode, state->history_len, state->hist_x, state->scale_x,
                              &saved->x, workspace, workspace_bytes_, st)) != F8_OK)
         return s;

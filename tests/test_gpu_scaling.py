@@ -272,3 +272,27 @@ def test_history_push_of_an_entry_of_the_history(n, j):
     f8.amax_history_push(dev, dev[j:j + 1], f8.E4M3, scale)
     want = np.concatenate((hist[j:j + 1], hist[:-1]))
     assert np.array_equal(dev.cpu().numpy(), want) and scale.item() == np.float32(448.0) / want.max()
+
+
+@pytest.mark.parametrize("shared", (False, True))
+@pytest.mark.parametrize("M,K,N", [(16, 16, 16), (272, 336, 2064), (2064, 4112, 528), (512, 768, 512)])
+def test_delayed_forward_quantises_both_tensors_as_one_after_the_other(M, K, N, shared):
+    """X and W share their launches; with a scale and a history that the state shares (W's cast then uses the scale that
+    X left) they must not.  Codes, scales and histories are those of separate calls."""
+    g = torch.Generator("cuda")
+    g.manual_seed(M + N)
+    X, W = ((torch.randn(s, generator=g, device="cuda") * f).to(torch.bfloat16) for s, f in (((M, K), 3.0), ((N, K), 0.02)))
+    st = f8.ScalingState(f8.DELAYED, 5)
+    if shared:
+        st._struct.hist_w, st._struct.scale_w = st._struct.hist_x, st._struct.scale_x
+    hx, sx = st.hist_x.clone(), st.scale_x.clone()
+    hw, sw = (hx, sx) if shared else (st.hist_w.clone(), st.scale_w.clone())
+    sv, ws = f8.Saved(M, K, N), f8.new_workspace(max(M, K, N), max(M, K, N))
+    f8.linear_fwd_scaled(f8.linear_desc(M, K, N), st, X, W, torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), sv, ws)
+    for t, h, s, q in ((X, hx, sx, sv.x), (W, hw, sw, sv.w)):
+        out, a, used = torch.empty(t.shape, dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda"), s.clone()
+        f8.cast_amax(t, s, f8.E4M3, a, out, workspace=ws)
+        f8.amax_history_push(h, a, f8.E4M3, s)
+        assert torch.equal(q.q, out) and torch.equal(q.scale, used) and torch.equal(q.amax, a) and torch.equal(q.inv_scale, 1.0 / used)
+    assert torch.equal(st.hist_x, hx) and torch.equal(st.scale_x, sx)
+    assert shared or (torch.equal(st.hist_w, hw) and torch.equal(st.scale_w, sw))
