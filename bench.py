@@ -231,7 +231,8 @@ def run_linear_workload(f8, wl, torch, args, w, gran, gfmt, steps, warmup, input
     # An instrumented pass issues the step's own sequence of library calls (every tensor's
     # amax+cast and every GEMM, forward in model order, backward in reverse, through the same
     # C entry points the linear composes), each call between two events.  Same kernels, same
-    # order and therefore the same cache state as in the timed steps.
+    # order and therefore the same cache state as in the timed steps.  (A backward whose two
+    # products share a launch in the steps has them here one after the other.)
     g = f8.ROWWISE if rowwise else f8.TENSORWISE
     reps = max(3, min(steps, 10))
 

@@ -274,7 +274,8 @@ f8_status f8_linear_fwd(const f8_linear_desc* d, const void* X, const void* W, v
  * as f8_linear_fwd does and with the same launches - tensorwise without
  * transposed copies, ONE amax launch and ONE cast launch serve both tensors
  * (the grid is split between them by size).  f8_linear_fwd is this call
- * followed by f8_gemm(F8_NT) on the codes.  Same arguments, checks and
+ * followed by f8_gemm(F8_NT) on the codes (up to 512 tokens by a kernel of its
+ * own, whose fp32 sums are in another order).  Same arguments, checks and
  * workspace as f8_linear_fwd, minus Y.
  */
 f8_status f8_linear_fwd_quantise(const f8_linear_desc* d, const void* X, const void* W, f8_saved* saved,

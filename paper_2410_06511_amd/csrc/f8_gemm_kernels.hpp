@@ -3,7 +3,9 @@
 // f8_gemm_inst.hip is compiled once per operand-format pair and layout, in parallel).
 //
 // gemm_tile_kernel serves all three layouts and every shape (multiples of 16) but the smallest,
-// which gemm_small_kernel takes (at most one 64 x 64 tile per compute unit, or two to three with a contraction of at most 256):
+// which gemm_small_kernel takes (at most one 64 x 64 tile per compute unit, or two to three with a contraction of at most 256).
+// The forward of few tokens has a kernel of its own (f8_gemm_rows.hip), and a linear's backward may run both of its
+// products in one launch of the two kernels' device functions (f8_gemm_pair.hip):
 // persistent workgroups, global -> LDS direct loads (no VGPR staging), two LDS stages,
 // v_mfma_f32_16x16x128_f8f6f4, scales folded into the fp32 epilogue, bf16 stores staged
 // through LDS.  An operand whose contraction index is the fast one in memory
