@@ -174,7 +174,11 @@ constexpr int kWaitAllVmLgkm = 0x0070;
 template <int BM, int BN>
 struct TileLds {
     static constexpr int kEpw = BN / 2 / 16 >= 8 ? 8 : 4, kEpr = 8 / kEpw;  // of an epilogue pass, see below
-    static constexpr int kStage = (BM + BN) * kBK, kEpilogue = 4 * 16 * kEpr * (16 * kEpw * 2 + 16);
+    // Bytes of a staged epilogue row.  Rows of 256 bytes are padded; rows of 128 have their 16-byte chunks permuted instead:
+    // with padding a workgroup of 128 x 128 tiles takes 82 KB, and a second one does not fit the compute unit (padded /
+    // permuted in us: 1008 x 1536 x 1024 9.0 / 8.6, 1008 x 2816 x 1024 k-major 8.8 / 8.6, 4096 x 1024 x 2048 12.6 / 12.4).
+    static constexpr int kEpStride = kEpw == 4 ? 128 : 16 * kEpw * 2 + 16;
+    static constexpr int kStage = (BM + BN) * kBK, kEpilogue = 4 * 16 * kEpr * kEpStride;
 };
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, int GRAN, bool AMAX, bool AKM, bool BKM,
@@ -200,7 +204,7 @@ __device__ __forceinline__ void gemm_tile_work(
     // tile if that is 128 columns: a store instruction then covers 4 rows x 256 bytes, measured
     // 1 % faster on the products than 8 rows x 128 bytes), 8 / EPW below each other
     constexpr int EPW = TileLds<BM, BN>::kEpw, EPR = TileLds<BM, BN>::kEpr;
-    constexpr int EP_STRIDE = 16 * EPW * 2 + 16;    // bytes per staged epilogue row: the bf16 of a row + padding
+    constexpr int EP_STRIDE = TileLds<BM, BN>::kEpStride;
     static_assert(TM % EPR == 0 && TN % EPW == 0, "the wave tile is a whole number of epilogue passes");
     static_assert(NW * 16 * EPR * EP_STRIDE == TileLds<BM, BN>::kEpilogue, "the caller's arrays");
 
@@ -533,14 +537,18 @@ __device__ __forceinline__ void gemm_tile_work(
                                 counted = m0 + 16 * i + fr < M && n0 + 16 * EPW * jp + nl < N;
                             if (counted) amax_acc = amax_pair(amax_acc, o);
                         }
-                        *reinterpret_cast<uint2*>(ep + (16 * ii + fr) * EP_STRIDE + nl * 2) = o;
+                        if constexpr (EPW == 4)
+                            *reinterpret_cast<uint2*>(ep + (16 * ii + fr) * EP_STRIDE + 16 * ((2 * jj + (fg >> 1)) ^ (fr & 7)) + 8 * (fg & 1)) = o;
+                        else
+                            *reinterpret_cast<uint2*>(ep + (16 * ii + fr) * EP_STRIDE + nl * 2) = o;
                     }
                 }
                 uint8_t* pbase = dbase + ((int64_t)(16 * EPR * ip) * ldd + 16 * EPW * jp) * 2;  // uniform
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int idx = t * 64 + lane;
-                    const uint4 v = *reinterpret_cast<const uint4*>(ep + (idx / LPR) * EP_STRIDE + (idx % LPR) * 16);
+                    const int chunk = EPW == 4 ? (idx % LPR) ^ ((idx / LPR) & 7) : idx % LPR;
+                    const uint4 v = *reinterpret_cast<const uint4*>(ep + (idx / LPR) * EP_STRIDE + chunk * 16);
                     bool ok = true;
                     if constexpr (!decltype(INTERIOR)::value)
                         ok = m0 + 16 * EPR * ip + idx / LPR < M && n0 + 16 * EPW * jp + (idx % LPR) * 8 < N;
