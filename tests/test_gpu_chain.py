@@ -128,6 +128,27 @@ def test_chained_full_size_pair_is_identical():
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
+def _spread(seed):
+    """Normal variates whose magnitudes are spread over most of e4m3's exponents: with one magnitude the fp32 sums are
+    mostly exact, and their order shows in no bit of the result."""
+    g = torch.Generator("cuda")
+    g.manual_seed(seed)
+    return lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std
+                            * torch.exp2(-10.0 * torch.rand(s, generator=g, device="cuda"))).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("M,K,N", [(64, 4096, 4096), (256, 1024, 4096), (512, 1024, 2048), (384, 768, 2304), (512, 4096, 4096)])
+def test_output_amax_does_not_change_the_forward(M, K, N):
+    """Up to 512 tokens the product may run on the kernel of few tokens, whose sums are in another order than the others':
+    with 129 to 256 tiles of 64x64 and a contraction below 2048 the general rule looks at whether an amax is taken."""
+    R = _spread(M + K + N)
+    X, W = R(1.0, M, K), R(0.02, N, K)
+    d, ws, Y, Y2, a = f8.linear_desc(M, K, N), f8.new_workspace(4096, 4096), _bf((M, N)), _bf((M, N)), torch.full((1,), -1.0, device="cuda")
+    f8.linear_fwd(d, X, W, Y, f8.Saved(M, K, N), ws)
+    f8.linear_fwd_chained(d, X, None, W, Y2, a, f8.Saved(M, K, N), ws)
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16)) and a.item() == Y.float().abs().max().item()
+
+
 def test_chained_argument_errors():
     t = torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda")
     ws = f8.new_workspace(64, 64)
