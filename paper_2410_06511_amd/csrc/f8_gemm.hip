@@ -26,16 +26,16 @@ static const gemm_fn kGemmTable[2][2][3] = {{F8_ROW(0, 0), F8_ROW(0, 1)}, {F8_RO
 #undef F8_ROW
 
 // gemm_pair_<format of dY>_<granularity>: one object file each (f8_gemm_pair.hip)
-#define F8_DECLARE_PAIR(fa, g) bool gemm_pair_##fa##_##g(const GemmArgs& x, const GemmArgs& w, void* ws, size_t ws_bytes, hipStream_t st);
+#define F8_DECLARE_PAIR(fa, g) bool gemm_pair_##fa##_##g(const GemmArgs& x, const GemmArgs& w, uint32_t* amax_bits, void* ws, size_t ws_bytes, hipStream_t st);
 F8_DECLARE_PAIR(0, 0) F8_DECLARE_PAIR(0, 1) F8_DECLARE_PAIR(1, 0) F8_DECLARE_PAIR(1, 1)
 #undef F8_DECLARE_PAIR
 static_assert(F8_TENSORWISE == 0 && F8_ROWWISE == 1, "table order below");
 
-bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, void* ws, size_t ws_bytes, hipStream_t st)
+bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, float* amax_x, void* ws, size_t ws_bytes, hipStream_t st)
 {
-    static bool (*const table[2][2])(const GemmArgs&, const GemmArgs&, void*, size_t, hipStream_t) = {
+    static bool (*const table[2][2])(const GemmArgs&, const GemmArgs&, uint32_t*, void*, size_t, hipStream_t) = {
         {gemm_pair_0_0, gemm_pair_0_1}, {gemm_pair_1_0, gemm_pair_1_1}};
-    return table[fa][g](x, w, ws, ws_bytes, st);
+    return table[fa][g](x, w, reinterpret_cast<uint32_t*>(amax_x), ws, ws_bytes, st);
 }
 
 __global__ void zero_word_kernel(uint32_t* p) { p[0] = 0; }

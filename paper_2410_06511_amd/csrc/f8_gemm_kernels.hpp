@@ -531,9 +531,11 @@ __device__ __forceinline__ void gemm_tile_work(
                         o.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2));
                         o.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2));
                         if constexpr (AMAX) {
-                            // edge tiles hold results of re-read rows past M / N: not output
+                            // Edge tiles hold results of re-read rows past M / N: not output.  With one scale they are
+                            // copies of outputs of the same tile and may be counted (the 64 conditions cost the edge
+                            // tiles of the 256 x 256 instances 10 us each, in spilled registers).
                             bool counted = true;
-                            if constexpr (!decltype(INTERIOR)::value)
+                            if constexpr (!decltype(INTERIOR)::value && GRAN != F8_TENSORWISE)
                                 counted = m0 + 16 * i + fr < M && n0 + 16 * EPW * jp + nl < N;
                             if (counted) amax_acc = amax_pair(amax_acc, o);
                         }

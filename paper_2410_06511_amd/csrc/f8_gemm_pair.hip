@@ -19,8 +19,9 @@ struct PairSide {
 
 // The XCDs share the products: those below x_xcds work on dX, the others on dW, each XCD as it would in a launch of its
 // own (one product's tiles in its L2).  Rowwise codes are read row-major in both products, tensorwise ones where they lie.
-template <int BM, int BN, int FA, int GRAN, bool RAGGED>
-__global__ __launch_bounds__(256) void gemm_pair_kernel(const PairSide x, const PairSide w, int x_xcds)
+template <int BM, int BN, int FA, int GRAN, bool RAGGED, bool AMAX>
+__global__ __launch_bounds__(256) void gemm_pair_kernel(const PairSide x, const PairSide w, int x_xcds,
+                                                        uint32_t* __restrict__ amax_bits /* AMAX: of dX */)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t st0[TileLds<BM, BN>::kStage];
     __shared__ __attribute__((aligned(1024))) uint8_t st1[TileLds<BM, BN>::kStage];
@@ -30,8 +31,8 @@ __global__ __launch_bounds__(256) void gemm_pair_kernel(const PairSide x, const 
     if (xcd < x_xcds) {
         const int first = idx * x_xcds + xcd;
         if (first >= x.tiles_m * x.tiles_n) return;
-        gemm_tile_work<BM, BN, 2, 2, FA, F8_E4M3, GRAN, false, false, KM, false, RAGGED>(
-            x.A, x.B, x.D, x.M, x.N, x.K, x.lda, x.ldb, x.ldd, x.isa, x.isb, x.tiles_m, x.tiles_n, nullptr, x.ksteps, 1,
+        gemm_tile_work<BM, BN, 2, 2, FA, F8_E4M3, GRAN, AMAX, false, KM, false, RAGGED>(
+            x.A, x.B, x.D, x.M, x.N, x.K, x.lda, x.ldb, x.ldd, x.isa, x.isb, x.tiles_m, x.tiles_n, amax_bits, x.ksteps, 1,
             nullptr, 0, first, per_xcd * x_xcds, x_xcds, st0, st1, epb);
     } else {
         const int xcds = kXcds - x_xcds, first = idx * xcds + (xcd - x_xcds);
@@ -43,27 +44,30 @@ __global__ __launch_bounds__(256) void gemm_pair_kernel(const PairSide x, const 
 }
 
 template <int FA, int GRAN>
-__global__ __launch_bounds__(256) void gemm_small_pair_kernel(const PairSide x, const PairSide w)
+__global__ __launch_bounds__(256) void gemm_small_pair_kernel(const PairSide x, const PairSide w,
+                                                              uint32_t* __restrict__ amax_bits /* nullable: of dX */)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t st[4][2][2 * kSmOp];
     constexpr bool KM = GRAN == F8_TENSORWISE;
     const int nx = x.tiles_m * x.tiles_n;
     if ((int)blockIdx.x < nx)
         gemm_small_work<FA, F8_E4M3, GRAN, false, KM, 4>(x.A, x.B, x.D, x.M, x.N, x.K, x.lda, x.ldb, x.ldd, x.isa, x.isb,
-                                                         x.tiles_m, x.tiles_n, nullptr, (int)blockIdx.x, st);
+                                                         x.tiles_m, x.tiles_n, amax_bits, (int)blockIdx.x, st);
     else
         gemm_small_work<FA, F8_E4M3, GRAN, KM, KM, 4>(w.A, w.B, w.D, w.M, w.N, w.K, w.lda, w.ldb, w.ldd, w.isa, w.isb,
                                                       w.tiles_m, w.tiles_n, nullptr, (int)blockIdx.x - nx, st);
 }
 
 template <int BM, int BN, int FA, int GRAN>
-static void launch_pair(PairSide x, PairSide w, int x_xcds, int cus, hipStream_t st)
+static void launch_pair(PairSide x, PairSide w, int x_xcds, uint32_t* amax_bits, int cus, hipStream_t st)
 {
     for (PairSide* s : {&x, &w}) s->tiles_m = (s->M + BM - 1) / BM, s->tiles_n = (s->N + BN - 1) / BN, s->ksteps = ksteps_of(s->K, 1);
     const bool ragged = x.K % (2 * kBK) != 0 || w.K % (2 * kBK) != 0;
     const unsigned grid = (unsigned)(BM * BN == 128 * 128 ? 2 * cus : cus);  // two workgroups of 128 x 128 tiles fit a compute unit
-    const auto kernel = ragged ? gemm_pair_kernel<BM, BN, FA, GRAN, true> : gemm_pair_kernel<BM, BN, FA, GRAN, false>;
-    kernel<<<grid, 256, 0, st>>>(x, w, x_xcds);
+    auto kernel = ragged ? gemm_pair_kernel<BM, BN, FA, GRAN, true, false> : gemm_pair_kernel<BM, BN, FA, GRAN, false, false>;
+    if constexpr (GRAN == F8_TENSORWISE)
+        if (amax_bits) kernel = ragged ? gemm_pair_kernel<BM, BN, FA, GRAN, true, true> : gemm_pair_kernel<BM, BN, FA, GRAN, false, true>;
+    kernel<<<grid, 256, 0, st>>>(x, w, x_xcds, amax_bits);
 }
 
 // ---------------------------------------------------------------------------
@@ -116,9 +120,13 @@ static double alone_us(const PairSide& s, bool b_kmajor, bool may_split, size_t 
 // 16384 x 4096 x 14336 1459 / 1441.  The margin is 0.985 for the tiles that large separate launches have too, 0.95 for the
 // others (with less, 192 x 2176 x 11648 takes 1.09 times as long).  Where no round is saved there is nothing to gain: within
 // a whole step 8192 x 3584 x 8192 would be 1 % and rowwise 8192 x 16384 x 2048 3 % slower.
-bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& gw, void* ws, size_t ws_bytes, hipStream_t st)
+// An amax of dX (tensorwise scaling only) changes nothing in the rule: separately dW may be split, and its sums are then in
+// another order.
+bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& gw, uint32_t* amax_bits, void* ws, size_t ws_bytes,
+                                            hipStream_t st)
 {
     constexpr int FA = F8_PAIR_FA, GRAN = F8_PAIR_GRAN;
+    if (GRAN != F8_TENSORWISE && amax_bits) return false;  // no call asks for it
     auto side = [](const GemmArgs& a) {
         return PairSide{a.A, a.B, a.D, a.M, a.N, a.K, a.lda, a.ldb, a.ldd, a.isa, a.isb, 0, 0, 0};
     };
@@ -160,16 +168,17 @@ bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& 
             if (us < best) best = us, tile = t, x_xcds = xc;
         }
     }
+    if (tile && amax_bits) zero_word(amax_bits, st);
     switch (tile) {
         case kSm: {
             PairSide a = x, b = w;
             for (PairSide* s : {&a, &b}) s->tiles_m = (s->M + kSm - 1) / kSm, s->tiles_n = (s->N + kSm - 1) / kSm;
-            gemm_small_pair_kernel<FA, GRAN><<<(unsigned)small, 256, 0, st>>>(a, b);
+            gemm_small_pair_kernel<FA, GRAN><<<(unsigned)small, 256, 0, st>>>(a, b, amax_bits);
             return true;
         }
-        case 128: launch_pair<128, 128, FA, GRAN>(x, w, x_xcds, cus, st); return true;
-        case 192: launch_pair<256, 128, FA, GRAN>(x, w, x_xcds, cus, st); return true;
-        case 256: launch_pair<256, 256, FA, GRAN>(x, w, x_xcds, cus, st); return true;
+        case 128: launch_pair<128, 128, FA, GRAN>(x, w, x_xcds, amax_bits, cus, st); return true;
+        case 192: launch_pair<256, 128, FA, GRAN>(x, w, x_xcds, amax_bits, cus, st); return true;
+        case 256: launch_pair<256, 256, FA, GRAN>(x, w, x_xcds, amax_bits, cus, st); return true;
     }
     return false;
 }

@@ -79,7 +79,7 @@ f8_status gemm(int layout, int64_t M, int64_t N, int64_t K, const uint8_t* A, in
                void* D, int64_t ldd, float* amax_d, hipStream_t st, void* ws = nullptr, size_t ws_bytes = 0);
 // The two products of a linear's backward (dX, dW) in one launch, where that is the faster way: true if they have been
 // enqueued.  Validated operands; both outputs and contractions are non-empty.  Tensorwise: dX as F8_NN, dW as F8_TN;
-// rowwise: both as F8_NT.  ws as in gemm.
+// rowwise: both as F8_NT.  amax_x (nullable): receives max |dX|.  ws as in gemm.
 struct GemmArgs {
     int M, N, K;
     const uint8_t *A, *B;
@@ -88,7 +88,7 @@ struct GemmArgs {
     uint16_t* D;
     int64_t ldd;
 };
-bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, void* ws, size_t ws_bytes, hipStream_t st);
+bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, float* amax_x, void* ws, size_t ws_bytes, hipStream_t st);
 // F8_NT product of few rows (contiguous e4m3 operands), where a kernel of its own is faster: true if it has been enqueued.
 // It adds the contraction in another order than gemm.
 bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, const float* isa, const float* isb, uint16_t* D,

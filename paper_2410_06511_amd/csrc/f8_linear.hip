@@ -171,14 +171,14 @@ static f8_status gemms_bwd(const f8_linear_desc* d, const f8_saved* sv, void* dX
     f8_status s;
     // Both in one launch, with the operands that the separate calls below would read.  (Transposed copies of
     // tensorwise codes keep them separate.)
-    if (!dx_amax && M > 0 && K > 0 && N > 0 && (rw || (!sv->w.q_t && !(sv->dy.q_t && sv->x.q_t)))) {
+    if (M > 0 && K > 0 && N > 0 && (rw || (!sv->w.q_t && !(sv->dy.q_t && sv->x.q_t)))) {
         const int m = (int)M, k = (int)K, n = (int)N;
         uint16_t *dx = static_cast<uint16_t*>(dX), *dw = static_cast<uint16_t*>(dW);
         const GemmArgs x = rw ? GemmArgs{m, k, n, sv->dy.q, sv->w.q_t, N, N, sv->dy.inv_scale, sv->w.inv_scale_t, dx, K}
                               : GemmArgs{m, k, n, sv->dy.q, sv->w.q, N, K, sv->dy.inv_scale, sv->w.inv_scale, dx, K};
         const GemmArgs w = rw ? GemmArgs{n, k, m, sv->dy.q_t, sv->x.q_t, M, M, sv->dy.inv_scale_t, sv->x.inv_scale_t, dw, K}
                               : GemmArgs{n, k, m, sv->dy.q, sv->x.q, N, K, sv->dy.inv_scale, sv->x.inv_scale, dw, K};
-        if (gemm_pair(gf, d->granularity, x, w, ws, ws_bytes, st)) return last_launch_status();
+        if (gemm_pair(gf, d->granularity, x, w, dx_amax, ws, ws_bytes, st)) return last_launch_status();
     }
     if (sv->w.q_t)
         s = gemm(F8_NT, M, K, N, sv->dy.q, gf, N, sv->w.q_t, F8_E4M3, N, sv->dy.inv_scale,

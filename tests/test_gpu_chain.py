@@ -149,6 +149,24 @@ def test_output_amax_does_not_change_the_forward(M, K, N):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16)) and a.item() == Y.float().abs().max().item()
 
 
+# Backwards in one launch with 64x64, 128x128, 256x128 and 256x256 tiles, whole and ragged; in the last three dW would be
+# split by itself.
+@pytest.mark.parametrize("gfmt", [f8.E4M3, f8.E5M2])
+@pytest.mark.parametrize("M,K,N", [(256, 512, 1024), (272, 336, 208), (480, 1376, 512), (1008, 1024, 1536), (1024, 1024, 2048),
+                                   (2048, 2048, 2048), (1040, 2064, 2064), (2064, 2064, 1552), (2000, 4096, 4096),
+                                   (8192, 4096, 1024), (8192, 2048, 2048), (16384, 1024, 4096)])
+def test_output_amax_does_not_change_the_backward(M, K, N, gfmt):
+    R = _spread(M + K + N)
+    X, W, dY = R(1.0, M, K), R(0.02, N, K), R(1e-3, M, N)
+    d, sv, ws = f8.linear_desc(M, K, N, False, gfmt), f8.Saved(M, K, N), f8.new_workspace(max(M, K, N), max(M, K, N))
+    f8.linear_fwd(d, X, W, _bf((M, N)), sv, ws)
+    dX, dW, dX2, dW2, a = _bf((M, K)), _bf((N, K)), _bf((M, K)), _bf((N, K)), torch.full((1,), -1.0, device="cuda")
+    f8.linear_bwd(d, dY, sv, dX, dW, ws)
+    f8.linear_bwd_chained(d, dY, None, sv, dX2, a, dW2, ws)
+    assert torch.equal(dX.view(torch.int16), dX2.view(torch.int16)) and a.item() == dX.float().abs().max().item()
+    assert torch.equal(dW.view(torch.int16), dW2.view(torch.int16))
+
+
 def test_chained_argument_errors():
     t = torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda")
     ws = f8.new_workspace(64, 64)
