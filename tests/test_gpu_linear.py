@@ -343,6 +343,31 @@ def test_backward_in_one_launch_has_the_bits_of_two(M, K, N, rowwise):
         assert torch.equal(dW.view(torch.int16), rW.view(torch.int16))
 
 
+# one launch with 64x64, 128x128, 256x128 and 256x256 tiles
+@pytest.mark.parametrize("rowwise", (False, True))
+@pytest.mark.parametrize("M,K,N", [(256, 512, 1024), (1008, 1024, 1536), (1040, 2064, 2064), (2000, 4096, 4096)])
+def test_weight_gradient_in_memory_that_the_input_gradient_reads(M, K, N, rowwise):
+    """dX is formed before dW: dW may lie over the weight's codes, or over dX.  (None of these contractions is split.)"""
+    g = torch.Generator("cuda")
+    g.manual_seed(M + K + N)
+    R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    X, W, dY = R(1.0, M, K), R(0.02, N, K), R(1e-3, M, N)
+    _, dX, dW, sv = run_linear(X, W, dY, rowwise)
+    desc, ws = f8.linear_desc(M, K, N, rowwise), f8.new_workspace(max(M, K, N), max(M, K, N))
+    lent, dX2 = torch.empty((N, K), dtype=torch.bfloat16, device="cuda"), torch.empty_like(dX)
+    codes = lent.view(torch.uint8).view(-1)[:N * K].view(sv.w.q_t.shape if rowwise else (N, K))
+    codes.copy_(sv.w.q_t if rowwise else sv.w.q)
+    over = f8.SavedStruct(sv.x.struct(), sv.w.struct(), sv.dy.struct())
+    setattr(over.w, "q_t" if rowwise else "q", codes.data_ptr())
+    sv._struct = over
+    f8.linear_bwd(desc, dY, sv, dX2, lent, ws)
+    assert torch.equal(dX2.view(torch.int16), dX.view(torch.int16)) and torch.equal(lent.view(torch.int16), dW.view(torch.int16))
+    sv._struct = f8.SavedStruct(sv.x.struct(), sv.w.struct(), sv.dy.struct())
+    both = torch.empty(max(M, N) * K, dtype=torch.bfloat16, device="cuda")
+    f8.linear_bwd(desc, dY, sv, both[:M * K].view(M, K), both[:N * K].view(N, K), ws)
+    assert torch.equal(both[:N * K].view(torch.int16), dW.view(-1).view(torch.int16))
+
+
 # Forwards of few tokens, one of every tile shape of their kernel (16 x 16, 16 x 32, 32 x 32, 64 x 32, 64 x 64), with rows,
 # columns and contractions that end inside a tile or a K step, waves with one K step more than others, and two rounds.
 @pytest.mark.parametrize("rowwise", (False, True))
