@@ -1038,7 +1038,15 @@ static void launch_measure(const MeasureJobs& jobs, int fmt, hipStream_t st)
     if (fmt == F8_E4M3) cast_measure_stream_kernel<F8_E4M3><<<blocks, kThreads, 0, st>>>(jobs);
     else cast_measure_stream_kernel<F8_E5M2><<<blocks, kThreads, 0, st>>>(jobs);
 }
-static bool apart(const float* a, int64_t na, const float* b, int64_t nb) { return a + na <= b || b + nb <= a; }
+struct Span {
+    const void* p;
+    int64_t bytes;
+};
+static bool apart(const Span& a, const Span& b)
+{
+    const uintptr_t p = (uintptr_t)a.p, q = (uintptr_t)b.p;
+    return p + (uintptr_t)a.bytes <= q || q + (uintptr_t)b.bytes <= p;
+}
 
 // Two tensors in two launches instead of four: of small ones each costs its launch (a linear of 208 x 2112 x 1184, forward
 // and backward, 38.2 -> 30.7 us; a block of 1008 tokens 337 -> 314; 8192 x 3584 x 8192 1 %).
@@ -1047,12 +1055,19 @@ bool quantise_delayed_pair(const DelayedTensor& a, const DelayedTensor& b, int64
 {
     if (!streamable(a.rows, a.cols, a.cols, a.cols, a.q->q, a.q->q_t) || !streamable(b.rows, b.cols, b.cols, b.cols, b.q->q, b.q->q_t))
         return false;
-    // Cells that the two share would be read and written in an order that is not defined.
-    const struct { const float* p; int64_t n; } mine[] = {{a.history, len}, {a.scale, 1}, {a.q->amax, 1}, {a.q->scale, 1}, {a.q->inv_scale, 1}},
-                                                theirs[] = {{b.history, len}, {b.scale, 1}, {b.q->amax, 1}, {b.q->scale, 1}, {b.q->inv_scale, 1}};
-    for (const auto& m : mine)
-        for (const auto& t : theirs)
-            if (!apart(m.p, m.n, t.p, t.n)) return false;
+    // What one tensor writes and the other one uses would be read and written in an order that is not defined: shared
+    // cells of the state, or the weight's codes over an X that is of no use any more.
+    constexpr int kSpans = 7;
+    auto spans = [&](const DelayedTensor& t, Span(&to)[kSpans]) {  // the tensor itself first: it is only read
+        const Span all[kSpans] = {{t.x, t.rows * t.cols * 2}, {t.q->q, t.rows * t.cols}, {t.history, len * 4}, {t.scale, 4},
+                                  {t.q->amax, 4}, {t.q->scale, 4}, {t.q->inv_scale, 4}};
+        for (int i = 0; i < kSpans; ++i) to[i] = all[i];
+    };
+    Span of_a[kSpans], of_b[kSpans];
+    spans(a, of_a), spans(b, of_b);
+    for (int i = 0; i < kSpans; ++i)
+        for (int j = 0; j < kSpans; ++j)
+            if ((i || j) && !apart(of_a[i], of_b[j])) return false;
     const bool swap = a.rows * a.cols < b.rows * b.cols;  // the larger tensor's blocks first, the smaller one's fill the tail
     const DelayedTensor* t[2] = {swap ? &b : &a, swap ? &a : &b};
     MeasureJobs jobs;

@@ -43,7 +43,7 @@ f8_status history_push(const void* partial, int npartial, const float* amax_in, 
                        int fmt, float* amax_out, const float* used_scale, float* saved_scale,
                        float* saved_inv, float* next_scale, float* next_inv, hipStream_t st);
 // A forward's X and W under delayed scaling, the casts in one launch and the histories in another: true if that has been
-// enqueued (contiguous, no transposed copies, no state or scale cell that the two share, partial maxima that fit ws).
+// enqueued (contiguous, no transposed copies, nothing that one writes and the other uses, partial maxima that fit ws).
 struct DelayedTensor {
     const void* x;
     int64_t rows, cols;

@@ -296,3 +296,21 @@ def test_delayed_forward_quantises_both_tensors_as_one_after_the_other(M, K, N, 
         assert torch.equal(q.q, out) and torch.equal(q.scale, used) and torch.equal(q.amax, a) and torch.equal(q.inv_scale, 1.0 / used)
     assert torch.equal(st.hist_x, hx) and torch.equal(st.scale_x, sx)
     assert shared or (torch.equal(st.hist_w, hw) and torch.equal(st.scale_w, sw))
+
+
+@pytest.mark.parametrize("M,K,N", [(512, 768, 512), (272, 336, 208), (2064, 4112, 528)])
+def test_delayed_forward_with_the_weight_codes_over_the_input(M, K, N):
+    """X is cast before W: W's codes may lie over an X that is of no use any more."""
+    g = torch.Generator("cuda")
+    g.manual_seed(M + N)
+    X, W = ((torch.randn(s, generator=g, device="cuda") * f).to(torch.bfloat16) for s, f in (((M, K), 3.0), ((N, K), 0.02)))
+    ws, desc, outs = f8.new_workspace(max(M, K, N), max(M, K, N)), f8.linear_desc(M, K, N), []
+    for over in (False, True):
+        st, sv, Y, Xc = f8.ScalingState(f8.DELAYED, 5), f8.Saved(M, K, N), torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), X.clone()
+        if over:
+            sv.w.q = Xc.view(torch.uint8).view(-1)[:N * K].view(N, K)
+            sv._struct = f8.SavedStruct(sv.x.struct(), sv.w.struct(), sv.dy.struct())
+        f8.linear_fwd_scaled(desc, st, Xc, W, Y, sv, ws)
+        outs.append((Y.view(torch.int16), sv.x.q, sv.w.q, sv.x.amax, sv.w.amax, st.hist_x, st.hist_w, st.scale_x, st.scale_w))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
