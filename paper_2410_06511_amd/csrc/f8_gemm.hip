@@ -1,6 +1,8 @@
 // The f8_gemm entry point (steps 4-6 of the Float8 linear: Y = X W^T, dX = dY W, dW = dY^T X).
 // The kernels live in f8_gemm_kernels.hpp and are instantiated per operand-format pair and layout
 // by f8_gemm_inst.hip.
+#include <atomic>
+
 #include "f8_host.hpp"
 
 namespace f8 {
@@ -36,6 +38,21 @@ bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, float* amax_
     static bool (*const table[2][2])(const GemmArgs&, const GemmArgs&, uint32_t*, void*, size_t, hipStream_t) = {
         {gemm_pair_0_0, gemm_pair_0_1}, {gemm_pair_1_0, gemm_pair_1_1}};
     return table[fa][g](x, w, reinterpret_cast<uint32_t*>(amax_x), ws, ws_bytes, st);
+}
+
+// Compute units of the current device, a multiple of the XCD count (the persistent tile order assumes that).  Kept per
+// device: a backward asks several times, at about 0.2 us of host time each for the attribute.
+int cu_count()
+{
+    constexpr int kDevices = 64;
+    static std::atomic<int> kept[kDevices];
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (dev >= 0 && dev < kDevices && (n = kept[dev].load(std::memory_order_relaxed)) > 0) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+    n -= n % 8;
+    if (dev >= 0 && dev < kDevices) kept[dev].store(n, std::memory_order_relaxed);
+    return n;
 }
 
 __global__ void zero_word_kernel(uint32_t* p) { p[0] = 0; }

@@ -969,14 +969,6 @@ static void launch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, cons
             A, B, D, M, N, K, lda, ldb, ldd, isa, isb, tiles_m, tiles_n, nullptr, ksteps_of(K, 1));
 }
 
-static int cu_count()
-{
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-        n = 256;
-    return n - n % kXcds;  // the persistent tile order assumes a multiple of the XCD count
-}
-
 // Number of contraction ranges for a product whose 256x256 tiles would occupy at most half of
 // the compute units, or 1.  A range must be a multiple of 256 (two LDS stages) and at least 1024
 // long, ranges x tiles must fit the compute units (one work item each), and the partial results
@@ -1010,15 +1002,14 @@ struct TilePlan {
     int whole;   // kFullRows, kFullCols: tiles in whole rounds, launched on their own
 };
 
-// may_split: there is a workspace of ws_bytes for partial sums.
-static TilePlan plan_product(int M, int N, int K, bool b_kmajor, bool takes_amax, bool may_split, size_t ws_bytes)
+// may_split: there is a workspace of ws_bytes for partial sums.  cus: cu_count().
+static TilePlan plan_product(int M, int N, int K, bool b_kmajor, bool takes_amax, bool may_split, size_t ws_bytes, int cus)
 {
     const bool ragged = K % (2 * kBK) != 0 || K <= 0;  // as dispatch_layout has it
     // Tile configuration by estimated time, in units of one 256x256 tile's time on one compute
     // unit: T tiles on `cus` persistent workgroups take ceil(T / cus) rounds; a 256x128 tile costs
     // about 0.63 and a 128x128 tile about 0.58 of a 256x256 one (measured: their wave tiles need
     // more LDS bytes per MFMA).  Ties go to the larger tile.
-    const int cus = cu_count();
     auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     auto rounds = [&](int64_t t) { return (double)((t + cus - 1) / cus); };
     constexpr double kHalfTile = 0.63, kQuarterTile = 0.58;
@@ -1064,7 +1055,7 @@ static void dispatch_tile(int M, int N, int K, const uint8_t* A, int64_t lda, co
                           void* ws, size_t ws_bytes, hipStream_t st)
 {
     const int cus = cu_count();
-    const TilePlan plan = plan_product(M, N, K, BKM, amax_bits != nullptr, ws != nullptr, ws_bytes);
+    const TilePlan plan = plan_product(M, N, K, BKM, amax_bits != nullptr, ws != nullptr, ws_bytes, cus);
     const bool rw = GRAN != F8_TENSORWISE;
     const int tm = plan.tm, tn = plan.tn;
     const int sm = (M + kSm - 1) / kSm, sn = (N + kSm - 1) / kSm;

@@ -93,7 +93,7 @@ static int64_t tile_count(const PairSide& s, int bm, int bn) { return ceil_div(s
 
 static double alone_us(const PairSide& s, bool b_kmajor, bool may_split, size_t ws_bytes, int cus, double launch)
 {
-    const TilePlan p = plan_product(s.M, s.N, s.K, b_kmajor, false, may_split, ws_bytes);
+    const TilePlan p = plan_product(s.M, s.N, s.K, b_kmajor, false, may_split, ws_bytes, cus);
     switch (p.kind) {
         case TilePlan::kSmall: return 4.65 + ksteps_of(s.K, 1) * 0.244;
         case TilePlan::kSmallOnePair: return 4.65;

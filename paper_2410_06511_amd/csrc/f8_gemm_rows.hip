@@ -154,7 +154,7 @@ bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, c
     auto kilobytes = [&](int rows, int cols) { return ((M < rows ? M : rows) + (N < cols ? N : cols)) * (double)K / 1024.0; };
     auto tiles = [&](int rows, int cols) { return (int64_t)((M + rows - 1) / rows) * ((N + cols - 1) / cols); };
     // (as without an output amax, whatever the call: these sums are in another order, and the amax is not to change Y)
-    const TilePlan plan = plan_product(M, N, K, false, false, false, 0);
+    const TilePlan plan = plan_product(M, N, K, false, false, false, 0, cus);
     double best;
     if (plan.kind == TilePlan::kSmall)
         best = 3.1 + 0.0222 * kilobytes(kSm, kSm);

@@ -93,6 +93,7 @@ bool gemm_pair(int fa, int g, const GemmArgs& x, const GemmArgs& w, float* amax_
 // It adds the contraction in another order than gemm.
 bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, const float* isa, const float* isb, uint16_t* D,
                uint32_t* amax_bits, hipStream_t st);
+int cu_count();  // of the current device
 void zero_word(uint32_t* p, hipStream_t st);  // not a memset: the call may be captured
 // Largest scratch a split product can use (ranges x output elements x 4 bytes, with ranges x tiles
 // at most one per compute unit): part of what workspace_bytes returns.
