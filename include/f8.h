@@ -29,7 +29,8 @@
  *     error return nothing has been enqueued or written.  A failed launch
  *     returns F8_ERR_LAUNCH.  No exception or abort crosses this boundary.
  *   - No global mutable state (f8_linear_fwd_noalloc is the one exception, see
- *     there): calls on different streams with disjoint buffers (including
+ *     there; each device's number of compute units is kept once it has been
+ *     asked for): calls on different streams with disjoint buffers (including
  *     disjoint workspaces) may run concurrently.
  *   - Inputs are expected to be finite.  With a caller-given finite scale,
  *     f8_cast maps NaN to one of the format's NaN codes and +-Inf to the

@@ -108,8 +108,13 @@ static double alone_us(const PairSide& s, bool b_kmajor, bool may_split, size_t 
     return launch + quarter_us(ceil_div(tile_count(s, 128, 128), cus), s.K, 0.49, 2.5, 0.6);
 }
 
-#define F8_PAIR_NAME_(fa, g) gemm_pair_##fa##_##g
-#define F8_PAIR_NAME(fa, g) F8_PAIR_NAME_(fa, g)
+#define F8_PAIR_NAME_(what, fa, g) gemm_pair_##what##fa##_##g
+#define F8_PAIR_NAME(what, fa, g) F8_PAIR_NAME_(what, fa, g)
+
+struct PairChoice {
+    int tile;    // 64, 128, 192 (256 x 128) or 256; 0: two launches
+    int x_xcds;  // XCDs that work on dX (not with 64)
+};
 
 // One launch where it is estimated to be enough faster than the separate ones.  dX and dW have the same number of
 // operations, so an even division of the XCDs is mostly right (others are taken only for 3 % more); it is the rounds of
@@ -122,19 +127,14 @@ static double alone_us(const PairSide& s, bool b_kmajor, bool may_split, size_t 
 // a whole step 8192 x 3584 x 8192 would be 1 % and rowwise 8192 x 16384 x 2048 3 % slower.
 // An amax of dX (tensorwise scaling only) changes nothing in the rule: separately dW may be split, and its sums are then in
 // another order.
-bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& gw, uint32_t* amax_bits, void* ws, size_t ws_bytes,
-                                            hipStream_t st)
+PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, bool may_split, size_t ws_bytes, int cus)
 {
-    constexpr int FA = F8_PAIR_FA, GRAN = F8_PAIR_GRAN;
-    if (GRAN != F8_TENSORWISE && amax_bits) return false;  // no call asks for it
-    auto side = [](const GemmArgs& a) {
-        return PairSide{a.A, a.B, a.D, a.M, a.N, a.K, a.lda, a.ldb, a.ldd, a.isa, a.isb, 0, 0, 0};
-    };
-    const PairSide x = side(gx), w = side(gw);
-    const int cus = cu_count(), per_xcd = cus / kXcds;
-    constexpr bool KM = GRAN == F8_TENSORWISE;
+    PairSide x{}, w{};
+    x.M = M, x.N = K, x.K = N, w.M = N, w.N = K, w.K = M;
+    const int per_xcd = cus / kXcds;
+    constexpr bool KM = F8_PAIR_GRAN == F8_TENSORWISE;
     auto separately = [&](double launch) {
-        return alone_us(x, KM, false, 0, cus, launch) + alone_us(w, KM, ws != nullptr, ws_bytes, cus, launch);
+        return alone_us(x, KM, false, 0, cus, launch) + alone_us(w, KM, may_split, ws_bytes, cus, launch);
     };
     // Where the products take long, a launch hides behind the one before it and saves nothing by itself.
     double apart = separately(4.5);
@@ -144,14 +144,14 @@ bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& 
     const bool few = tile_count(x, 256, 256) + tile_count(w, 256, 256) <= 2 * cus;
 
     double best = apart;
-    int tile = 0, x_xcds = 0;
+    PairChoice c{0, 0};
     // 64 x 64 tiles, several rounds of them if need be: the other tiles' larger areas leave more of the chip idle.
     const int64_t small = tile_count(x, kSm, kSm) + tile_count(w, kSm, kSm);
     if (small <= 4 * cus) {
         const double tx = kSmallTime.tile(x.K), tw = kSmallTime.tile(w.K), longest = tx > tw ? tx : tw;
         const double work = (tile_count(x, kSm, kSm) * tx + tile_count(w, kSm, kSm) * tw) / cus + 0.22 * longest;
         const double us = 4.8 + (work > longest ? work : longest);
-        if (us < 0.95 * best) best = us / 0.95, tile = kSm;
+        if (us < 0.95 * best) best = us / 0.95, c.tile = kSm;
     }
     for (int xc : {4, 3, 5}) {
         auto side_us = [&](const PairSide& s, int xcds, int t) {
@@ -165,22 +165,37 @@ bool F8_PAIR_NAME(F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& 
             const double tx = side_us(x, xc, t), tw = side_us(w, kXcds - xc, t), launch = hidden ? 0.0 : t == 256 ? 2.5 : t == 192 ? 3.5 : 3.9;
             const double margin = (t == 256 ? 0.985 : 0.95) / (xc == 4 ? 1.0 : 1.03);
             const double us = (launch + (tx > tw ? tx : tw)) / margin;
-            if (us < best) best = us, tile = t, x_xcds = xc;
+            if (us < best) best = us, c = PairChoice{t, xc};
         }
     }
-    if (tile && amax_bits) zero_word(amax_bits, st);
-    switch (tile) {
+    return c;
+}
+
+bool F8_PAIR_NAME(, F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& gw, uint32_t* amax_bits, void* ws, size_t ws_bytes,
+                                              hipStream_t st)
+{
+    constexpr int FA = F8_PAIR_FA, GRAN = F8_PAIR_GRAN;
+    if (GRAN != F8_TENSORWISE && amax_bits) return false;  // no call asks for it
+    const int cus = cu_count();
+    const PairChoice c = F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(gx.M, gx.N, gx.K, ws != nullptr, ws_bytes, cus);
+    if (!c.tile) return false;
+    auto side = [](const GemmArgs& a) {
+        return PairSide{a.A, a.B, a.D, a.M, a.N, a.K, a.lda, a.ldb, a.ldd, a.isa, a.isb, 0, 0, 0};
+    };
+    const PairSide x = side(gx), w = side(gw);
+    if (amax_bits) zero_word(amax_bits, st);
+    switch (c.tile) {
         case kSm: {
             PairSide a = x, b = w;
             for (PairSide* s : {&a, &b}) s->tiles_m = (s->M + kSm - 1) / kSm, s->tiles_n = (s->N + kSm - 1) / kSm;
-            gemm_small_pair_kernel<FA, GRAN><<<(unsigned)small, 256, 0, st>>>(a, b, amax_bits);
-            return true;
+            gemm_small_pair_kernel<FA, GRAN><<<(unsigned)(a.tiles_m * a.tiles_n + b.tiles_m * b.tiles_n), 256, 0, st>>>(a, b, amax_bits);
+            break;
         }
-        case 128: launch_pair<128, 128, FA, GRAN>(x, w, x_xcds, amax_bits, cus, st); return true;
-        case 192: launch_pair<256, 128, FA, GRAN>(x, w, x_xcds, amax_bits, cus, st); return true;
-        case 256: launch_pair<256, 256, FA, GRAN>(x, w, x_xcds, amax_bits, cus, st); return true;
+        case 128: launch_pair<128, 128, FA, GRAN>(x, w, c.x_xcds, amax_bits, cus, st); break;
+        case 192: launch_pair<256, 128, FA, GRAN>(x, w, c.x_xcds, amax_bits, cus, st); break;
+        default: launch_pair<256, 256, FA, GRAN>(x, w, c.x_xcds, amax_bits, cus, st);
     }
-    return false;
+    return true;
 }
 
 }  // namespace f8

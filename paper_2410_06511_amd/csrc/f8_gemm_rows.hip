@@ -143,14 +143,12 @@ void launch_rows(const RowsArgs& a, hipStream_t st)
 
 }  // namespace
 
-// Contiguous, validated operands; amax_bits nullable.  true: the product has been enqueued.
-bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, const float* isa, const float* isb, uint16_t* D,
-               uint32_t* amax_bits, hipStream_t st)
+// The tile that a forward of few tokens takes here, as 10 TM + TN, or 0: another kernel is faster.
+int rows_tile(int M, int N, int K, int cus)
 {
     // Estimates in us, from 75 sizes of 16 to 512 tokens and good to 10 %: a round of tiles takes a little and the bytes
     // that a tile loads, in any shape.  A wave needs a K step or more to be worth its share of the sums.
-    if (M <= 0 || M > 512 || N <= 0 || K < 4 * kBK) return false;
-    const int cus = cu_count();
+    if (M <= 0 || M > 512 || N <= 0 || K < 4 * kBK) return 0;
     auto kilobytes = [&](int rows, int cols) { return ((M < rows ? M : rows) + (N < cols ? N : cols)) * (double)K / 1024.0; };
     auto tiles = [&](int rows, int cols) { return (int64_t)((M + rows - 1) / rows) * ((N + cols - 1) / cols); };
     // (as without an output amax, whatever the call: these sums are in another order, and the amax is not to change Y)
@@ -161,7 +159,7 @@ bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, c
     else if (plan.kind == TilePlan::kQuarter && tiles(128, 128) <= cus)
         best = 2.5 + 0.75 * ksteps_of(K, 1);  // (0.75 to 1.0 a step)
     else
-        return false;
+        return 0;
     best *= 0.93;
     int choice = 0;
     constexpr int kShapes[][2] = {{4, 4}, {4, 2}, {2, 2}, {1, 2}, {1, 1}};
@@ -170,10 +168,18 @@ bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, c
         const double us = 2.2 + (double)rounds * (0.9 + 0.0205 * kilobytes(16 * tm, 16 * tn));
         if (rounds <= 2 && us < best) best = us, choice = 10 * tm + tn;
     }
-    if (!choice) return false;
+    return choice;
+}
+
+// Contiguous, validated operands; amax_bits nullable.  true: the product has been enqueued.
+bool gemm_rows(int g, int M, int N, int K, const uint8_t* A, const uint8_t* B, const float* isa, const float* isb, uint16_t* D,
+               uint32_t* amax_bits, hipStream_t st)
+{
+    const int tile = rows_tile(M, N, K, cu_count());
+    if (!tile) return false;
     if (amax_bits) zero_word(amax_bits, st);
     const RowsArgs a{g, M, N, K, A, B, isa, isb, D, amax_bits};
-    switch (choice) {
+    switch (tile) {
         case 44: launch_rows<4, 4, 2>(a, st); return true;
         case 42: launch_rows<4, 2, 3>(a, st); return true;
         case 22: launch_rows<2, 2, 4>(a, st); return true;

@@ -164,9 +164,10 @@ def test_block_glue_argument_errors():
     assert e.value.code == 5
 
 
-@pytest.mark.parametrize("M,D,small_ws", [(48, 4096, False), (2064, 4112, False), (4112, 1024, True)])
+@pytest.mark.parametrize("M,D,small_ws", [(48, 4096, False), (2064, 4112, False), (2064, 8208, False), (4112, 1024, True),
+                                          (4112, 4096, True), (1040, 6160, True)])
 def test_rmsnorm_backward_one_pass_and_two(M, D, small_ws):
-    """Rows up to 4096 elements go through one kernel for dx and dg, longer ones (and callers with room for fewer
+    """Rows up to 8192 elements go through one kernel for dx and dg, longer ones (and callers with room for fewer
     partial rows than blocks) through two: dx has the same bits either way, dg is the fp64 sum to 1e-5 of its terms."""
     x, g, dy = gen((M, D), M).cuda(), gen((D,), D, 0.5).cuda(), gen((M, D), M + D, 1e-2).cuda()
     rstd = 1.0 / torch.sqrt(x.float().square().mean(1) + 1e-5)
@@ -180,10 +181,11 @@ def test_rmsnorm_backward_one_pass_and_two(M, D, small_ws):
 
 
 @pytest.mark.parametrize("M", [16, 64, 80, 2048, 2064])
-@pytest.mark.parametrize("D", [48, 512, 528, 1024, 1040, 2048, 2064, 4096])
+@pytest.mark.parametrize("D", [48, 512, 528, 1024, 1040, 2048, 2064, 4096, 4112, 6160, 8192])
 def test_rmsnorm_backward_dg_alone(M, D):
     """dg alone comes from a kernel of its own (column pieces, sixteen partial rows): the bits of the call with dx, at
-    the edges of both kernels' chunks (512, 1024, 2048 columns; 64 per piece) and row blocks (16, 512 of four rows)."""
+    the edges of the kernels' chunks (512, 1024, 2048, 4096, 6144 columns; 64 per piece) and row blocks (16, 512 of four
+    rows)."""
     x, g, dy = gen((M, D), M).cuda(), gen((D,), D, 0.5).cuda(), gen((M, D), M + D, 1e-2).cuda()
     rstd = 1.0 / torch.sqrt(x.float().square().mean(1) + 1e-5)
     ws = f8.new_workspace(M, D)

@@ -57,10 +57,12 @@ def test_silu_mul_forward_and_backward(M, H):
     assert torch.equal(h.view(torch.int16), h2.view(torch.int16))
 
 
-@pytest.mark.parametrize("M,H", [(16, 256), (16, 272), (1024, 4096), (1040, 4112)])
+@pytest.mark.parametrize("M,H", [(16, 128), (16, 272), (1024, 4096), (1040, 4112), (2048, 4080), (2048, 4096), (2064, 4112)])
 def test_silu_mul_at_the_edges_of_a_block(M, H):
-    """A block takes 512 chunks of 16 bytes at a time, 1024 blocks make one round: one whole block, a block and a
-    remainder, one whole round, a round and a remainder.  In place too: a chunk is read and written by one thread."""
+    """Up to 2048 blocks take one chunk of 16 bytes a thread: one whole block, two and a remainder, all of them.  Above that
+    two chunks a thread, in one round up to 2^20 chunks: with a remainder, whole blocks, all 2048 of them, which is the first
+    size past the caches; beyond, rounds of 1024 blocks, the last one with a remainder.  In place too: a chunk is read and
+    written by one thread."""
     g = torch.Generator("cpu")
     g.manual_seed(M + H)
     ab, dh = wl.randn_bf16((M, 2 * H), 2.0, 0, generator=g), wl.randn_bf16((M, H), 1e-3, 0, generator=g)

@@ -1,4 +1,6 @@
 """GPU parity of the whole Float8 linear (forward + backward) against the CPU oracle."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -9,6 +11,28 @@ from paper_2410_06511_amd import workloads as wl
 from helpers import bits, u8, f32, assert_gemm_close, assert_gemm_tight, group_max_sum, sampled_check, qt_matches
 
 pytestmark = pytest.mark.gpu
+
+
+class PairChoice(C.Structure):
+    _fields_ = [("tile", C.c_int), ("x_xcds", C.c_int)]
+
+
+def cus():
+    n = torch.cuda.get_device_properties(0).multi_processor_count
+    return n - n % 8
+
+
+def rows_tile(M, K, N):
+    """What f8::rows_tile decides (f8_gemm_rows.hip): the tile of the forward of few tokens, or 0."""
+    return f8.lib()._ZN2f89rows_tileEiiii(M, N, K, cus())
+
+
+def pair_choice(M, K, N, rowwise):
+    """What f8::gemm_pair_choice_0_<granularity> decides (f8_gemm_pair.hip) for a caller with a full workspace."""
+    rule = getattr(f8.lib(), f"_ZN2f820gemm_pair_choice_0_{int(rowwise)}Eiiibmi")
+    rule.restype, rule.argtypes = PairChoice, [C.c_int, C.c_int, C.c_int, C.c_bool, C.c_size_t, C.c_int]
+    c = rule(M, K, N, True, f8.workspace_bytes(max(M, K, N), max(M, K, N)), cus())
+    return c.tile, c.x_xcds
 
 
 def run_linear(X, W, dY, rowwise=False, grad_fmt=f8.E4M3, transposed=False):
@@ -296,17 +320,22 @@ def test_backward_with_split_contraction_is_deterministic():
 
 
 @pytest.mark.parametrize("rowwise,transposed", [(True, False), (False, True), (False, False)])
-def test_split_contraction_against_oracle(rowwise, transposed):
-    """A linear whose weight gradient takes the split-contraction path (dW [512, 1024] over 4096
-    tokens), with per-tensor and with per-row / per-column scales: everything against the oracle
-    in full."""
+@pytest.mark.parametrize("M,K,N,ranges", [(4096, 1024, 512, 1), (7440, 4128, 224, 4)])
+def test_split_contraction_against_oracle(M, K, N, ranges, rowwise, transposed):
+    """A linear whose weight gradient has few tiles and a long contraction (the tokens): small enough for 64x64 tiles, and
+    split into four ranges, the last one shorter; with per-tensor and with per-row / per-column scales, everything
+    against the oracle in full."""
     g = torch.Generator("cpu")
     g.manual_seed(4096)
-    M, K, N = 4096, 1024, 512
     X = wl.randn_bf16((M, K), 1.0, 0, generator=g)
     W = wl.randn_bf16((N, K), 0.02, 0, generator=g)
     dY = wl.randn_bf16((M, N), 1e-3, 0, generator=g)
     Y, dX, dW, saved = run_linear(X, W, dY, rowwise, f8.E5M2, transposed)
+    # the ranges' fp32 sums lie one after the other in the workspace, the last of them at the end
+    ws = f8.new_workspace(max(M, K, N), max(M, K, N)).fill_(0xA5)
+    f8.linear_bwd(f8.linear_desc(M, K, N, rowwise, f8.E5M2), dY.cuda(), saved, dX, dW, ws)
+    sums = ws[:4 * ranges * N * K].view(torch.int32)
+    assert bool((sums[-64:] != -0x5A5A5A5B).any()) == (ranges > 1) and bool((ws[4 * ranges * N * K:] == 0xA5).all())
     rY, xq, wq = o.linear_fwd(bits(X), bits(W), rowwise)
     rdX, rdW, dyq = o.linear_bwd(bits(dY), xq, wq, rowwise, o.E5M2)
     check_quantised(saved.dy, dyq, rowwise)
@@ -317,16 +346,20 @@ def test_split_contraction_against_oracle(rowwise, transposed):
 
 
 # One launch for both products of the backward: 64x64 tiles (one ragged, one with a single pair of K steps, one of several
-# rounds), 128x128, 256x128 (the XCDs divided 4 : 4 and 3 : 5) and 256x256 tiles (several per workgroup), ragged
-# contractions, per-row scales, XCDs with more workgroups than tiles.
-PAIRS = [(16, 16, 16), (256, 512, 1024), (272, 336, 208), (1328, 256, 13312), (480, 1376, 512), (1008, 1024, 1536),
-         (2048, 2048, 2048), (2064, 2064, 1552), (1040, 2064, 2064), (2000, 4096, 4096), (8192, 4096, 1024)]
+# rounds), 128x128, 256x128 (192 here) and 256x256 tiles (several per workgroup), each with 3, 4 and 5 of the XCDs on dX;
+# ragged contractions, per-row scales, XCDs with more workgroups than tiles.
+PAIRS = [(16, 16, 16, 64, 0), (256, 512, 1024, 64, 0), (272, 336, 208, 64, 0), (1328, 256, 13312, 64, 0),
+         (128, 4688, 464, 128, 3), (480, 1376, 512, 128, 4), (1008, 1024, 1536, 128, 4), (304, 5872, 128, 128, 5),
+         (1040, 2064, 2064, 192, 3), (2048, 2048, 2048, 192, 4), (336, 8208, 208, 192, 5),
+         (304, 8208, 912, 256, 3), (2064, 2064, 1552, 256, 4), (2000, 4096, 4096, 256, 4), (8192, 4096, 1024, 256, 4),
+         (1088, 7856, 400, 256, 5), (8192, 8192, 512, 256, 5)]
 
 
 @pytest.mark.parametrize("rowwise", (False, True))
-@pytest.mark.parametrize("M,K,N", PAIRS)
-def test_backward_in_one_launch_has_the_bits_of_two(M, K, N, rowwise):
+@pytest.mark.parametrize("M,K,N,tile,x_xcds", PAIRS)
+def test_backward_in_one_launch_has_the_bits_of_two(M, K, N, tile, x_xcds, rowwise):
     """Same instructions and the same order of each contraction as separate (unsplit) f8_gemm calls on the same codes."""
+    assert pair_choice(M, K, N, rowwise) == (tile, x_xcds)
     g = torch.Generator("cuda")
     g.manual_seed(M + K + N)
     R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
@@ -368,13 +401,18 @@ def test_weight_gradient_in_memory_that_the_input_gradient_reads(M, K, N, rowwis
     assert torch.equal(both[:N * K].view(torch.int16), dW.view(-1).view(torch.int16))
 
 
-# Forwards of few tokens, one of every tile shape of their kernel (16 x 16, 16 x 32, 32 x 32, 64 x 32, 64 x 64), with rows,
-# columns and contractions that end inside a tile or a K step, waves with one K step more than others, and two rounds.
+# Forwards of few tokens, some of every tile shape of their kernel (16 x 16, 16 x 32, 32 x 32, 64 x 32, 64 x 64: 44 stands
+# for 4 x 4 times 16; 0: they take another kernel), with rows, columns and contractions that end inside a tile or a K step,
+# waves with one K step more than others, and two rounds (352 x 1280 x 2720 and all of 64 x 64).
 @pytest.mark.parametrize("rowwise", (False, True))
-@pytest.mark.parametrize("M,K,N", [(16, 512, 1024), (48, 528, 1040), (16, 4096, 4096), (32, 2048, 8208), (64, 4096, 4096),
-                                   (80, 4112, 2064), (112, 3856, 2304), (512, 2064, 1840), (304, 6400, 1280)])
-def test_forward_of_few_tokens(M, K, N, rowwise):
+@pytest.mark.parametrize("M,K,N,tile", [(16, 512, 1024, 11), (48, 528, 1040, 11), (16, 4096, 4096, 11), (32, 512, 2112, 12),
+                                        (48, 1040, 2576, 12), (32, 1024, 4096, 12), (64, 4096, 4096, 22), (80, 4112, 2064, 22),
+                                        (112, 3856, 2304, 42), (304, 6400, 1280, 42), (352, 1280, 2720, 42),
+                                        (80, 2112, 8256, 44), (288, 1296, 3440, 44), (512, 6144, 4096, 44), (32, 2048, 8208, 0),
+                                        (512, 2064, 1840, 0)])
+def test_forward_of_few_tokens(M, K, N, tile, rowwise):
     """Against the fp64 product of the codes, with the bound that holds for the matrix instruction and fp32 sums."""
+    assert rows_tile(M, K, N) == tile
     g = torch.Generator("cuda")
     g.manual_seed(M + K + N)
     R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
