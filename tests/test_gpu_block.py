@@ -184,8 +184,8 @@ def test_rmsnorm_backward_one_pass_and_two(M, D, small_ws):
 @pytest.mark.parametrize("D", [48, 512, 528, 1024, 1040, 2048, 2064, 4096, 4112, 6160, 8192])
 def test_rmsnorm_backward_dg_alone(M, D):
     """dg alone comes from a kernel of its own (column pieces, sixteen partial rows): the bits of the call with dx, at
-    the edges of the kernels' chunks (512, 1024, 2048, 4096, 6144 columns; 64 per piece) and row blocks (16, 512 of four
-    rows)."""
+    the edges of both kernels' chunks (512, 1024, 2048 columns; 64 per piece) and row blocks (16, 512 of four rows).  Above
+    4096 columns from strips of rows, whose sums are in another order."""
     x, g, dy = gen((M, D), M).cuda(), gen((D,), D, 0.5).cuda(), gen((M, D), M + D, 1e-2).cuda()
     rstd = 1.0 / torch.sqrt(x.float().square().mean(1) + 1e-5)
     ws = f8.new_workspace(M, D)
@@ -194,10 +194,10 @@ def test_rmsnorm_backward_dg_alone(M, D):
     f8.rmsnorm_bwd(x, g, rstd, dy, dx, dg, ws)
     f8.rmsnorm_bwd(x, g, rstd, dy, dx2, None)
     f8.rmsnorm_bwd(x, g, rstd, dy, None, dg2, ws)
-    assert torch.equal(dx.view(torch.int16), dx2.view(torch.int16)) and torch.equal(dg, dg2)
+    assert torch.equal(dx.view(torch.int16), dx2.view(torch.int16)) and (D > 4096 or torch.equal(dg, dg2))
     # sums of M fp32 terms of three roundings each, at most M / 4 / 512 + 32 + 16 additions in a chain: below 1e-5 of the terms
     terms = dy.double() * x.double() * rstd.double()[:, None]
-    assert bool(((dg.double() - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0) + 1e-30).all())
+    assert all(bool(((t.double() - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0) + 1e-30).all()) for t in (dg, dg2))
 
 
 @pytest.mark.parametrize("S", [16, 4096, 1 << 20])
