@@ -118,11 +118,12 @@ def test_linear_exact_case_bit_for_bit():
     _exact_linear(draw, 512, 768, 256)
 
 
-def test_linear_exact_case_with_split_contraction():
+@pytest.mark.parametrize("M,K,N", [(4096, 1024, 512), (7440, 4128, 224)])
+def test_linear_exact_case_with_split_contraction(M, K, N):
     """The same with a weight gradient of few output tiles and a long contraction (dW [512, 1024]
-    over 4096 tokens): that product is split along its contraction into ranges whose fp32 partial
-    sums a second kernel adds; every sum is exact, so the result is still bit for bit the rounded
-    exact product."""
+    over 4096 tokens, small enough for 64x64 tiles; [224, 4128] over 7440): the latter is split along its
+    contraction into ranges whose fp32 partial sums a second kernel adds; every sum is exact, so the
+    result is still bit for bit the rounded exact product."""
     rng = np.random.default_rng(32)
     vals = np.array([0, 0.5, -0.5, 1, -1, 2, -2], np.float32)
 
@@ -130,7 +131,7 @@ def test_linear_exact_case_with_split_contraction():
         t = vals[rng.integers(0, vals.size, shape)]
         t.flat[rng.integers(0, t.size)] = 3.5
         return t
-    _exact_linear(draw, 4096, 1024, 512)
+    _exact_linear(draw, M, K, N)
 
 
 def _exact_linear(draw, M, K, N):
@@ -303,13 +304,14 @@ def test_backward_in_place_equals_backward_on_transposed_copies(M, K, N, grad_fm
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-def test_backward_with_split_contraction_is_deterministic():
-    """8B wk shape at 4096 tokens: dW [1024, 4096] has 64 output tiles and is computed in
-    contraction ranges added in a fixed order; repeated calls give identical bits, and the result
-    agrees with the oracle on sampled lines."""
+@pytest.mark.parametrize("M,transposed", [(4096, False), (8192, True)])
+def test_backward_with_split_contraction_is_deterministic(M, transposed):
+    """8B wk shape: dW [1024, 4096] has 64 output tiles.  At 4096 tokens it shares a launch with dX; at 8192, from
+    transposed copies, it is computed in contraction ranges added in a fixed order.  Repeated calls give identical bits,
+    and the result agrees with the oracle on sampled lines."""
     w = wl.WORKLOADS["llama8b"]
-    X, W, dY = wl.make_linear_inputs(w, 1, M=4096)
-    outs = [run_linear(X, W, dY)[1:3] for _ in range(3)]
+    X, W, dY = wl.make_linear_inputs(w, 1, M=M)
+    outs = [run_linear(X, W, dY, transposed=transposed)[1:3] for _ in range(3)]
     for dX, dW in outs[1:]:
         assert torch.equal(dX.view(torch.int16), outs[0][0].view(torch.int16))
         assert torch.equal(dW.view(torch.int16), outs[0][1].view(torch.int16))
