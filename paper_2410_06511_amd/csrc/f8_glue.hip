@@ -19,16 +19,22 @@ constexpr int kGlueMaxBlocks = 2048;
 static_assert((size_t)kGlueMaxBlocks * sizeof(uint32_t) <= kMinWorkspaceBytes, "one partial per block fits the minimum workspace");
 
 // ab [M, 2H] as 16-byte chunks: row m has 2 * hc chunks, a first; h [M, H]: hc chunks per row.
-// Bound by memory.  A block takes CHUNKS chunks per thread that lie side by side, then as many a grid further on: one front
-// moves through each tensor.  (Chunks of one thread a grid apart are streams some MB apart that meet in the same memory
-// channels.)  Two chunks a thread, except where one each still fits the most blocks: the loads of few blocks then start at
-// once (608 x 6496 backward 8.5 us with two, 7.7 with one).
-// STREAM: loads and stores past the caches, for tensors of which they would keep little until they are read again.  us plain
-// / past them, with other data in between: 8192 x 14336 forward 130 / 118 (6.0 TB/s), backward 223 / 204, 2048 x 14336
-// 33.1 / 30.0 and 54.5 / 49.5, 2048 x 4096 11.3 / 10.0 and 17.2 / 15.4; where the operands are still in the caches that is
-// 8 % slower up to 2048 x 14336, so the line lies where a pass of their own (6 to 10 bytes an element) turns most of them over.
-constexpr int kGateMaxBlocks = 1024;  // of many tiles (2048: 0.5 to 1.5 % slower)
-constexpr int64_t kGateStreamChunks = (int64_t)1 << 20;  // 8 M elements of h
+// Bound by memory.  A block takes CHUNKS chunks per thread that lie side by side, then as many a grid further on.
+// STREAM (from 8 M elements of h on): loads and stores past the caches, which would keep little of the tensors until they are
+// read again, and two chunks side by side, so that one front moves through each tensor (chunks of one thread a grid apart are
+// streams some MB apart that meet in the same memory channels).  us plain / past the caches, with other data in between:
+// 8192 x 14336 forward 130 / 118 (6.0 TB/s), backward 223 / 204, 2048 x 14336 33.1 / 30.0 and 54.5 / 49.5.  With operands that
+// are still in the caches it is 8 % slower up to 2048 x 14336, and the cast that reads the result misses more (with an amax
+// after it 4096 x 4096 31.8 / 30.2, 2048 x 4096 19.4 / 21.1): in a whole block of the 8B model gate and casts take 758 / 745 us
+// at 8192 tokens, 429 / 438 at 4096.  Stores to the caches and only the loads past them: 428 there, but alone 8192 x 14336 134
+// and 229, and whole blocks of 2048 tokens lose 1 % in their products.
+// Smaller tensors: one chunk a thread, one or two of them in turn; a block of its own for every 256 chunks only while those
+// are at most one per compute unit.  us in turn / all at once: 256 x 1024 4.7 / 4.3, but 1008 x 4096
+// 8.9 / 9.8 and backward 10.7 / 11.7 (blocks that do little, and twice the partial maxima to read); two side by side 9.1 and
+// 11.7.
+constexpr int kGateMaxBlocks = 1024;  // of a streamed tensor (2048: 0.5 to 1.5 % slower)
+constexpr int kGateAtOnceBlocks = 256;
+constexpr int64_t kGateStreamChunks = (int64_t)1 << 20;
 
 template <bool STREAM>
 __device__ inline uint4 gate_load(const uint4* p)
@@ -43,7 +49,7 @@ __device__ inline void gate_store(uint4* p, uint4 v)
     else *p = v;
 }
 
-template <bool STREAM, int CHUNKS>
+template <bool STREAM, int CHUNKS = STREAM ? 2 : 1>
 __global__ __launch_bounds__(kGlueThreads) void silu_mul_kernel(const uint4* __restrict__ ab, int64_t M, int64_t hc,
                                                                uint4* __restrict__ h, uint32_t* __restrict__ partial)
 {
@@ -73,7 +79,7 @@ __global__ __launch_bounds__(kGlueThreads) void silu_mul_kernel(const uint4* __r
     }
 }
 
-template <bool STREAM, int CHUNKS>
+template <bool STREAM, int CHUNKS = STREAM ? 2 : 1>
 __global__ __launch_bounds__(kGlueThreads) void silu_mul_bwd_kernel(const uint4* __restrict__ ab, const uint4* __restrict__ dh,
                                                                    int64_t M, int64_t hc, uint4* __restrict__ dab,
                                                                    uint32_t* __restrict__ partial)
@@ -196,11 +202,10 @@ __global__ __launch_bounds__(kGlueThreads) void rmsnorm_kernel(const uint4* __re
 template <class F>
 static int launch_gate(int64_t chunks, F&& f)
 {
-    const int64_t one = (chunks + kGlueThreads - 1) / kGlueThreads, two = (one + 1) / 2;
-    if (one <= kGlueMaxBlocks) return f(std::false_type{}, std::integral_constant<int, 1>{}, (int)one), (int)one;
-    const int nb = (int)(two <= kGlueMaxBlocks ? two : kGateMaxBlocks);
-    if (chunks >= kGateStreamChunks) f(std::true_type{}, std::integral_constant<int, 2>{}, nb);
-    else f(std::false_type{}, std::integral_constant<int, 2>{}, nb);
+    if (chunks >= kGateStreamChunks) return f(std::true_type{}, kGateMaxBlocks), kGateMaxBlocks;
+    static_assert(kGateStreamChunks <= 2 * kGlueThreads * kGlueMaxBlocks && kGateMaxBlocks <= kGlueMaxBlocks, "one partial maximum per block");
+    const int one = (int)((chunks + kGlueThreads - 1) / kGlueThreads), nb = one <= kGateAtOnceBlocks ? one : (one + 1) / 2;
+    f(std::false_type{}, nb);
     return nb;
 }
 
@@ -229,8 +234,8 @@ f8_status f8_silu_mul(const void* ab_bf16, int64_t M, int64_t H, void* h_bf16, f
     const int64_t hc = H / 8;
     int nb = 0;
     if (M > 0 && H > 0) {
-        nb = launch_gate(M * hc, [&](auto STREAM, auto CHUNKS, int blocks) {
-            silu_mul_kernel<STREAM(), CHUNKS()><<<blocks, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, M, hc, (uint4*)h_bf16,
+        nb = launch_gate(M * hc, [&](auto STREAM, int blocks) {
+            silu_mul_kernel<STREAM()><<<blocks, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, M, hc, (uint4*)h_bf16,
                                                                                 amax_h ? (uint32_t*)workspace : nullptr);
         });
     }
@@ -247,8 +252,8 @@ f8_status f8_silu_mul_bwd(const void* ab_bf16, const void* dh_bf16, int64_t M, i
     const int64_t hc = H / 8;
     int nb = 0;
     if (M > 0 && H > 0) {
-        nb = launch_gate(M * hc, [&](auto STREAM, auto CHUNKS, int blocks) {
-            silu_mul_bwd_kernel<STREAM(), CHUNKS()><<<blocks, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, (const uint4*)dh_bf16, M, hc,
+        nb = launch_gate(M * hc, [&](auto STREAM, int blocks) {
+            silu_mul_bwd_kernel<STREAM()><<<blocks, kGlueThreads, 0, st>>>((const uint4*)ab_bf16, (const uint4*)dh_bf16, M, hc,
                                                                                     (uint4*)dab_bf16, amax_dab ? (uint32_t*)workspace : nullptr);
         });
     }

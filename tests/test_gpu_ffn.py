@@ -57,12 +57,13 @@ def test_silu_mul_forward_and_backward(M, H):
     assert torch.equal(h.view(torch.int16), h2.view(torch.int16))
 
 
-@pytest.mark.parametrize("M,H", [(16, 128), (16, 272), (1024, 4096), (1040, 4112), (2048, 4080), (2048, 4096), (2064, 4112)])
+@pytest.mark.parametrize("M,H", [(16, 128), (16, 272), (512, 1024), (528, 1024), (1040, 4112), (2048, 4080), (2048, 4096),
+                                 (2064, 4112)])
 def test_silu_mul_at_the_edges_of_a_block(M, H):
-    """Up to 2048 blocks take one chunk of 16 bytes a thread: one whole block, two and a remainder, all of them.  Above that
-    two chunks a thread, in one round up to 2^20 chunks: with a remainder, whole blocks, all 2048 of them, which is the first
-    size past the caches; beyond, rounds of 1024 blocks, the last one with a remainder.  In place too: a chunk is read and
-    written by one thread."""
+    """Up to 256 blocks take one chunk of 16 bytes a thread: one whole block, two and a remainder, all of them.  Above that
+    two in turn: some threads only one, a remainder, all of them.  From 2^20 chunks on, past the caches, 1024 blocks take two
+    chunks a thread side by side: two whole rounds, a third with a remainder.  In place too: a chunk is read and written by
+    one thread."""
     g = torch.Generator("cpu")
     g.manual_seed(M + H)
     ab, dh = wl.randn_bf16((M, 2 * H), 2.0, 0, generator=g), wl.randn_bf16((M, H), 1e-3, 0, generator=g)
