@@ -290,6 +290,8 @@ __global__ __launch_bounds__(kBlkThreads, 2) void rmsnorm_bwd_fused_kernel(const
 // request the next row with, and all waves load, then compute, then store: 8192 x 4096 with the residual 82 us (268 MB).
 // A quarter of that per lane lets the next row be on its way while this one is worked on: 52 us; 1008 x 4096 20.8 -> 12.7,
 // 1008 x 2048 11.7 -> 10.0, 8192 x 6144 (two passes before) 144 -> 89.  Shorter rows would leave threads without a chunk.
+// Loads and stores past the caches at every size: both calls of a transformer block together, past / through them, 36 / 47 us
+// for 2048 x 2048, 36 / 39 for 1008 x 2048, 65 / 68 for 4096 x 4096, 107 / 113 for 8192 x 4096, but 54 / 50 for 2048 x 4096.
 // The sum over a row is formed by every wave from the chunks' terms in LDS, in the order in which a lane of the kernel
 // above adds them, and the block takes that kernel's rows wave by wave: the same bits, of dx and of dg.
 template <int U>
