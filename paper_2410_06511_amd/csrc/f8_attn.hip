@@ -474,7 +474,11 @@ __global__ void zero_amax_kernel(uint32_t* p) { p[0] = 0; }
 // Two kernels, neither with atomics: dQ per query tile (loop over keys, S^T orientation, which
 // also produces delta), then dK and dV per key tile and query head (loop over queries, S
 // orientation: one key per lane); with grouped heads the shares of a group's query heads are
-// kept in fp32 and summed in head order by a small third kernel.
+// kept in fp32 and summed in head order by a small third kernel.  Where a launch of either is few blocks, both
+// run in one (sdpa_bwd_kernel).
+
+// two of the products of delta
+__device__ inline float delta_term(uint32_t d, uint32_t o) { return bf16_lo(d) * bf16_lo(o) + bf16_hi(d) * bf16_hi(o); }
 
 // dQ^T = K^T dS^T.  In two staggered halves like the forward (see there), per 64-key step:
 //   M_t: dQ += K_t^T dS_t (16 products), then S^T = K_t+1 Q^T and dP^T = V_t+1 dO^T (32 products)
@@ -482,20 +486,32 @@ __global__ void zero_amax_kernel(uint32_t* p) { p[0] = 0; }
 // Tiles t live in buffer t % 4: M_t reads K_t, K_t+1 and V_t+1; K_t+3 and V_t+3 are requested at the end of V_t.
 // K^T comes from the K tile itself, by transposing reads.  (All waves in step, three tiles through registers: 821 us for
 // 1 x 8192 tokens, 32/8 heads; this: 700.  Phase M is what it waits for: 48 products, 1536 cycles, in about 1900.)
-template <int NW, bool FAR>
-__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
-    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk,
-    const uint16_t* __restrict__ V, int64_t ldv, const uint16_t* __restrict__ O, int64_t ldo, const uint16_t* __restrict__ dO,
-    int64_t lddo, const float* __restrict__ lse, int64_t M, int S, int Hq, int group, float scale_log2e, float scale,
-    uint16_t* __restrict__ dQ, int64_t lddq, float* __restrict__ delta, int nqt)
+// The work of one block: query tile qt of (sequence, head) bh.  DELTA: delta is formed and stored here, else it is read.
+struct DqArgs {
+    const uint16_t *Q, *K, *V, *O, *dO;
+    int64_t ldq, ldk, ldv, ldo, lddo;
+    const float* lse;
+    int64_t M;
+    int S, Hq, group;
+    float scale_log2e, scale;
+    uint16_t* dQ;
+    int64_t lddq;
+    float* delta;
+};
+template <int NW, bool FAR, bool DELTA>
+__device__ __forceinline__ void sdpa_bwd_dq_work(const DqArgs& P, int qt, int bh, uint16_t (&sK)[4][kBk * kHd], uint16_t (&sV)[4][kBk * kHd])
 {
     static_assert(NW == 8, "two waves per SIMD in opposite phases");
     constexpr int QB = 32 * NW;  // queries per block
-    __shared__ __attribute__((aligned(1024))) uint16_t sK[4][kBk * kHd];
-    __shared__ __attribute__((aligned(1024))) uint16_t sV[4][kBk * kHd];
+    const uint16_t *__restrict__ Q = P.Q, *__restrict__ K = P.K, *__restrict__ V = P.V, *__restrict__ O = P.O, *__restrict__ dO = P.dO;
+    const int64_t ldq = P.ldq, ldk = P.ldk, ldv = P.ldv, ldo = P.ldo, lddo = P.lddo, M = P.M, lddq = P.lddq;
+    const float* __restrict__ lse = P.lse;
+    const int S = P.S, Hq = P.Hq, group = P.group;
+    const float scale_log2e = P.scale_log2e, scale = P.scale;
+    uint16_t* __restrict__ dQ = P.dQ;
+    float* __restrict__ delta = P.delta;
 
-    const int nbh = Hq * (int)(M / S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
-    const int bh = blockIdx.x % nbh, h = bh % Hq, b = bh / Hq, kvh = h / group;
+    const int h = bh % Hq, b = bh / Hq, kvh = h / group;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
     const bool late = wave >= NW / 2;
     const int q_first = qt * QB + wave * 32, q_pos = q_first + ln;
@@ -531,14 +547,20 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
         for (int s = 0; s < kHd / 16; ++s) {
             qf[s] = q_ok ? *reinterpret_cast<const uint4*>(qrow + 16 * s) : make_uint4(0, 0, 0, 0);
             dof[s] = q_ok ? *reinterpret_cast<const uint4*>(drow + 16 * s) : make_uint4(0, 0, 0, 0);
-            const uint4 ov = q_ok ? *reinterpret_cast<const uint4*>(orow + 16 * s) : make_uint4(0, 0, 0, 0);
-            const uint32_t dw[4] = {dof[s].x, dof[s].y, dof[s].z, dof[s].w}, ow[4] = {ov.x, ov.y, ov.z, ov.w};
+            if constexpr (DELTA) {
+                const uint4 ov = q_ok ? *reinterpret_cast<const uint4*>(orow + 16 * s) : make_uint4(0, 0, 0, 0);
+                const uint32_t dw[4] = {dof[s].x, dof[s].y, dof[s].z, dof[s].w}, ow[4] = {ov.x, ov.y, ov.z, ov.w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dl += bf16_lo(dw[j]) * bf16_lo(ow[j]) + bf16_hi(dw[j]) * bf16_hi(ow[j]);
+                for (int j = 0; j < 4; ++j) dl += delta_term(dw[j], ow[j]);
+            }
         }
     }
-    dl += __shfl_xor(dl, 32, kWave);
-    if (q_ok && g == 0) delta[(int64_t)h * M + tok] = dl;
+    if constexpr (DELTA) {
+        dl += __shfl_xor(dl, 32, kWave);
+        if (q_ok && g == 0) delta[(int64_t)h * M + tok] = dl;
+    } else {
+        dl = q_ok ? delta[(int64_t)h * M + tok] : 0.0f;
+    }
     const float lse2 = q_ok ? lse[(int64_t)h * M + tok] * 1.4426950408889634074f : 0.0f;
 
     f32x16 acc[kHd / 32], sc[2], dp[2];
@@ -643,6 +665,16 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
     }
 }
 
+template <int NW, bool FAR>
+__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(const DqArgs P, int nqt)
+{
+    __shared__ __attribute__((aligned(1024))) uint16_t sK[4][kBk * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sV[4][kBk * kHd];
+    // long (late) query tiles first, over all heads
+    const int nbh = P.Hq * (int)(P.M / P.S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
+    sdpa_bwd_dq_work<NW, FAR, true>(P, qt, blockIdx.x % nbh, sK, sV);
+}
+
 // dV^T = dO^T P and dK^T = Q^T dS in one pass over the scores.  One block: 8 waves, 32 keys each (one key per lane),
 // of one (sequence, query head); steps of 32 queries, in pairs from the end of the sequence down to the diagonal (the
 // lower half of a pair first), in two staggered halves like the forward (see there):
@@ -654,22 +686,37 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(
 // (dK and dV in a kernel each, 40 products a step instead of 32 and the exponentials twice, all waves in step: 1490 us for
 // 1 x 8192 tokens, 32/8 heads; this: 1010.)
 constexpr int kDkvQ = 32;  // queries per step
+struct DkvArgs {
+    const uint16_t *Q, *K, *V, *dO;
+    int64_t ldq, ldk, ldv, lddo;
+    const float *lse, *delta;
+    int64_t M;
+    int S, Hq, group;
+    float scale_log2e, scale;
+    uint16_t *dK, *dV;
+    int64_t lddk, lddv;
+    float *part_k, *part_v;
+};
+template <int NW>
+struct DkvLds {
+    uint16_t sQ[4][kDkvQ * kHd], sD[4][kDkvQ * kHd], sV[32 * NW * kHd];
+    float sStat[4][2 * kDkvQ];  // lse, then delta
+};
+// The work of one block: key tile kt of (sequence, query head) bh.
 template <int NW, bool FAR>
-__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
-    const uint16_t* __restrict__ Q, int64_t ldq, const uint16_t* __restrict__ K, int64_t ldk, const uint16_t* __restrict__ V,
-    int64_t ldv, const uint16_t* __restrict__ dO, int64_t lddo, const float* __restrict__ lse, const float* __restrict__ delta,
-    int64_t M, int S, int Hq, int group, float scale_log2e, float scale, uint16_t* __restrict__ dK, int64_t lddk,
-    uint16_t* __restrict__ dV, int64_t lddv, float* __restrict__ part_k, float* __restrict__ part_v)
+__device__ __forceinline__ void sdpa_bwd_dkv_work(const DkvArgs& P, int kt, int bh, uint16_t (&sQ)[4][kDkvQ * kHd], uint16_t (&sD)[4][kDkvQ * kHd],
+                                                  uint16_t (&sV)[32 * NW * kHd], float (&sStat)[4][2 * kDkvQ])
 {
     static_assert(NW == 8, "two waves per SIMD in opposite phases");
     constexpr int KB = 32 * NW;  // keys per block
-    __shared__ __attribute__((aligned(1024))) uint16_t sQ[4][kDkvQ * kHd];
-    __shared__ __attribute__((aligned(1024))) uint16_t sD[4][kDkvQ * kHd];
-    __shared__ __attribute__((aligned(1024))) uint16_t sV[KB * kHd];
-    __shared__ __attribute__((aligned(1024))) float sStat[4][2 * kDkvQ];  // lse, then delta
+    const uint16_t *__restrict__ Q = P.Q, *__restrict__ K = P.K, *__restrict__ V = P.V, *__restrict__ dO = P.dO;
+    const int64_t ldq = P.ldq, ldk = P.ldk, ldv = P.ldv, lddo = P.lddo, M = P.M, lddk = P.lddk, lddv = P.lddv;
+    const float *__restrict__ lse = P.lse, *__restrict__ delta = P.delta;
+    const int S = P.S, Hq = P.Hq, group = P.group;
+    const float scale_log2e = P.scale_log2e, scale = P.scale;
+    uint16_t *__restrict__ dK = P.dK, *__restrict__ dV = P.dV;
+    float *__restrict__ part_k = P.part_k, *__restrict__ part_v = P.part_v;
 
-    // early key tiles see the most queries: they are the slowest-varying index, so they start first
-    const int bh = blockIdx.x % (Hq * (int)(M / S)), kt = blockIdx.x / (Hq * (int)(M / S));
     const int hq = bh % Hq, b = bh / Hq, kvh = hq / group, gi = hq % group;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
     const bool late = wave >= NW / 2;
@@ -870,6 +917,71 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     }
 }
 
+template <int NW, bool FAR>
+__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(const DkvArgs P)
+{
+    __shared__ __attribute__((aligned(1024))) uint16_t sQ[4][kDkvQ * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sD[4][kDkvQ * kHd];
+    __shared__ __attribute__((aligned(1024))) uint16_t sV[32 * NW * kHd];
+    __shared__ __attribute__((aligned(1024))) float sStat[4][2 * kDkvQ];  // lse, then delta
+    // early key tiles see the most queries: they are the slowest-varying index, so they start first
+    const int nbh = P.Hq * (int)(P.M / P.S);
+    sdpa_bwd_dkv_work<NW, FAR>(P, blockIdx.x / nbh, blockIdx.x % nbh, sQ, sD, sV, sStat);
+}
+
+// delta[h][token] = sum of dO O over the head, in the order of sdpa_bwd_dq_work (chunk 2 s + g of a row to lane group g,
+// s ascending, then g 0 and 1): for the kernel below, whose dK/dV blocks cannot wait for its dQ blocks.  One block: 128
+// rows (token, head).  The products' pair sums are formed by coalesced loads and chained through LDS.
+constexpr int kDeltaRows = kAttnThreads / 2;
+__global__ __launch_bounds__(kAttnThreads) void sdpa_delta_kernel(const uint16_t* __restrict__ O, int64_t ldo, const uint16_t* __restrict__ dO,
+                                                                  int64_t lddo, int64_t M, int Hq, float* __restrict__ delta)
+{
+    constexpr int CPR = kHd / 8, PER_THREAD = kDeltaRows * CPR / kAttnThreads;
+    __shared__ float4 terms[kDeltaRows][CPR + 1];  // (a padded row: the chains read one column of all rows)
+    const int64_t row0 = (int64_t)blockIdx.x * kDeltaRows, rows = M * Hq;
+    uint4 o[PER_THREAD], d[PER_THREAD];
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i) {
+        const int rl = (i * kAttnThreads + (int)threadIdx.x) / CPR, c = threadIdx.x % CPR;
+        const int64_t row = row0 + rl < rows ? row0 + rl : rows - 1, tok = row / Hq, col = row % Hq * kHd + 8 * c;
+        o[i] = *reinterpret_cast<const uint4*>(O + tok * ldo + col), d[i] = *reinterpret_cast<const uint4*>(dO + tok * lddo + col);
+    }
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i)
+        terms[(i * kAttnThreads + (int)threadIdx.x) / CPR][threadIdx.x % CPR] =
+            make_float4(delta_term(d[i].x, o[i].x), delta_term(d[i].y, o[i].y), delta_term(d[i].z, o[i].z), delta_term(d[i].w, o[i].w));
+    __syncthreads();
+    const int rl = threadIdx.x / 2, g = threadIdx.x % 2;
+    float dl = 0.0f;
+#pragma unroll
+    for (int s = 0; s < CPR / 2; ++s) {
+        const float4 t = terms[rl][2 * s + g];
+        dl += t.x, dl += t.y, dl += t.z, dl += t.w;
+    }
+    dl += __shfl_xor(dl, 1, kWave);
+    const int64_t row = row0 + rl;
+    if (g == 0 && row < rows) delta[row % Hq * M + row / Hq] = dl;
+}
+
+// dQ and dK/dV in one launch, the blocks of both, longest first (a dK/dV block takes 1.35 times as long as a dQ block of
+// as many tiles), delta beforehand.  A launch of at most one block per compute unit lasts as long as its longest block, and
+// the units of the shorter ones idle: here the other kernel's blocks fill them (4 x 1000 tokens, 16 heads: 48 + 64 us in two
+// launches; this and delta 95).  Same device code, same bits.
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_kernel(const DqArgs Pq, const DkvArgs Pk, int tiles)
+{
+    constexpr size_t kDq = 2 * sizeof(uint16_t[4][kBk * kHd]), kDkv = sizeof(DkvLds<NW>);
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[kDq > kDkv ? kDq : kDkv];
+    const int nbh = Pq.Hq * (int)(Pq.M / Pq.S), k = blockIdx.x / nbh, bh = blockIdx.x % nbh;
+    if (k & 1) {
+        auto* s = reinterpret_cast<uint16_t(*)[4][kBk * kHd]>(lds);
+        sdpa_bwd_dq_work<NW, false, false>(Pq, tiles - 1 - k / 2, bh, s[0], s[1]);
+    } else {
+        auto* s = reinterpret_cast<DkvLds<NW>*>(lds);
+        sdpa_bwd_dkv_work<NW, false>(Pk, k / 2, bh, s->sQ, s->sD, s->sV, s->sStat);
+    }
+}
+
 // out[tok][c] = bf16(sum over the group's query heads, in order, of part[gi][tok][c]); 8 columns per thread
 __global__ __launch_bounds__(kAttnThreads) void sdpa_group_sum_kernel(const float* __restrict__ part_k, const float* __restrict__ part_v,
                                                                       int64_t M, int64_t w, int group,
@@ -900,6 +1012,30 @@ __global__ __launch_bounds__(kAttnThreads) void sdpa_group_sum_kernel(const floa
         if ((threadIdx.x & (kWave - 1)) == 0 && m > __atomic_load_n(amax_dv_bits, __ATOMIC_RELAXED)) atomicMax(amax_dv_bits, m);
     }
 }
+
+// A matrix of `rows` rows of w elements of `size` bytes, a pitch of ld elements apart.
+struct Rows {
+    const void* p;
+    int64_t rows, ld, w;
+    int size;
+};
+static bool apart(const Rows& a, const Rows& b)
+{
+    const uintptr_t p = (uintptr_t)a.p, q = (uintptr_t)b.p;
+    const uintptr_t pe = p + (uintptr_t)(((a.rows - 1) * a.ld + a.w) * a.size), qe = q + (uintptr_t)(((b.rows - 1) * b.ld + b.w) * b.size);
+    if (pe <= q || qe <= p) return true;
+    const int64_t pitch = a.ld * a.size;  // column slices of one matrix
+    if (pitch != b.ld * b.size) return false;
+    const int64_t d = (((int64_t)(q - p)) % pitch + pitch) % pitch;
+    return d >= a.w * a.size && d + b.w * b.size <= pitch;
+}
+
+// Whether the backward takes one launch for dQ and dK/dV.  In two, `blocks` blocks of n, n - 1, ..., 1 tiles take the time of n
+// tiles each or, with more blocks, that of their sum over the units: with less than 2 n / (n + 1) blocks per unit the former
+// is longer.  us of rope, attention and its backward, two launches / one (sequences x tokens, heads): 2 x 512, 8 107 / 84,
+// 1 x 2048, 16 264 / 208, 1 x 8192, 8 844 / 698, 4 x 1000, 16 213 / 197, 5 x 256, 32 131 / 129; at the line 7 x 2048, 8 452 / 443 and
+// 8 x 256, 32 164 / 172, beyond it 2 x 2048, 32 454 / 453 and 1 x 8192, 32 2344 / 2354.
+static bool one_launch(int64_t blocks, int64_t n, int cus) { return blocks * (n + 1) < 2 * n * cus; }
 
 constexpr int kDqWaves = 8;  // 256 queries per block, one block per compute unit
 constexpr int kDkvWaves = 8;             // 256 keys per block, one block per compute unit
@@ -976,22 +1112,34 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
     if ((S + 255) / 256 * Hq * B > (int64_t)0x7FFFFFFF) return F8_ERR_SHAPE;  // one block per 256 tokens and head
     const double sc = 1.0 / sqrt((double)hd);
     const float scale = (float)sc, scale_log2e = (float)(sc * 1.4426950408889634074);
-    const int64_t nqt = (S + 32 * kDqWaves - 1) / (32 * kDqWaves);
-    const auto dq_kernel = far_rows(kBk, ldk) || far_rows(kBk, ldv) ? sdpa_bwd_dq_kernel<kDqWaves, true> : sdpa_bwd_dq_kernel<kDqWaves, false>;
-    dq_kernel<<<(unsigned)(nqt * Hq * B), 64 * kDqWaves, 0, st>>>(
-        (const uint16_t*)q_bf16, ldq, (const uint16_t*)k_bf16, ldk, (const uint16_t*)v_bf16, ldv,
-        (const uint16_t*)o_bf16, ldo, (const uint16_t*)do_bf16, lddo, lse, M, (int)S, (int)Hq, (int)(Hq / Hkv), scale_log2e, scale,
-        (uint16_t*)dq_bf16, lddq, delta, (int)nqt);
     float* part_k = group > 1 ? (float*)workspace : nullptr;
     float* part_v = group > 1 ? part_k + group * M * wk : nullptr;
-    const int64_t nkt = (S + 32 * kDkvWaves - 1) / (32 * kDkvWaves);
-    const auto dkv_kernel = far_rows(kDkvQ, ldq) || far_rows(kDkvQ, lddo) || far_rows(32 * kDkvWaves, ldv)
-                                ? sdpa_bwd_dkv_kernel<kDkvWaves, true>
-                                : sdpa_bwd_dkv_kernel<kDkvWaves, false>;
-    dkv_kernel<<<(unsigned)(nkt * Hq * B), 64 * kDkvWaves, 0, st>>>(
-        (const uint16_t*)q_bf16, ldq, (const uint16_t*)k_bf16, ldk, (const uint16_t*)v_bf16, ldv, (const uint16_t*)do_bf16, lddo,
-        lse, delta, M, (int)S, (int)Hq, (int)group, scale_log2e, scale, (uint16_t*)dk_bf16, lddk, (uint16_t*)dv_bf16, lddv, part_k,
-        part_v);
+    const DqArgs q{(const uint16_t*)q_bf16, (const uint16_t*)k_bf16, (const uint16_t*)v_bf16, (const uint16_t*)o_bf16, (const uint16_t*)do_bf16,
+                   ldq, ldk, ldv, ldo, lddo, lse, M, (int)S, (int)Hq, (int)group, scale_log2e, scale, (uint16_t*)dq_bf16, lddq, delta};
+    const DkvArgs kv{(const uint16_t*)q_bf16, (const uint16_t*)k_bf16, (const uint16_t*)v_bf16, (const uint16_t*)do_bf16, ldq, ldk, ldv, lddo,
+                     lse, delta, M, (int)S, (int)Hq, (int)group, scale_log2e, scale, (uint16_t*)dk_bf16, (uint16_t*)dv_bf16, lddk, lddv, part_k, part_v};
+    const int64_t nqt = (S + 32 * kDqWaves - 1) / (32 * kDqWaves), blocks = nqt * Hq * B;
+    const bool dq_far = far_rows(kBk, ldk) || far_rows(kBk, ldv);
+    const bool dkv_far = far_rows(kDkvQ, ldq) || far_rows(kDkvQ, lddo) || far_rows(32 * kDkvWaves, ldv);
+    static_assert(kDqWaves == kDkvWaves, "as many query tiles as key tiles");
+    // One after the other, dK and dV (or their shares) may lie over what only dQ's kernel still reads, or over dQ: gradients
+    // that replace k and v, or one buffer for both where one is of no use.
+    auto written_apart = [&](const Rows& w) {
+        for (const Rows& r : {Rows{q_bf16, M, ldq, wq, 2}, Rows{k_bf16, M, ldk, wk, 2}, Rows{v_bf16, M, ldv, wk, 2}, Rows{do_bf16, M, lddo, wq, 2},
+                              Rows{lse, Hq, M, M, 4}, Rows{delta, Hq, M, M, 4}, Rows{dq_bf16, M, lddq, wq, 2}})
+            if (!apart(w, r)) return false;
+        return true;
+    };
+    const bool one = !dq_far && !dkv_far && one_launch(blocks, nqt, cu_count()) &&
+                     (group > 1 ? written_apart({workspace, 2 * group, M * wk, M * wk, 4})
+                                : written_apart({dk_bf16, M, lddk, wk, 2}) && written_apart({dv_bf16, M, lddv, wk, 2}));
+    if (one) {
+        sdpa_delta_kernel<<<(unsigned)((M * Hq + kDeltaRows - 1) / kDeltaRows), kAttnThreads, 0, st>>>(q.O, ldo, q.dO, lddo, M, (int)Hq, delta);
+        sdpa_bwd_kernel<kDqWaves><<<(unsigned)(2 * blocks), 64 * kDqWaves, 0, st>>>(q, kv, (int)nqt);
+    } else {
+        (dq_far ? sdpa_bwd_dq_kernel<kDqWaves, true> : sdpa_bwd_dq_kernel<kDqWaves, false>)<<<(unsigned)blocks, 64 * kDqWaves, 0, st>>>(q, (int)nqt);
+        (dkv_far ? sdpa_bwd_dkv_kernel<kDkvWaves, true> : sdpa_bwd_dkv_kernel<kDkvWaves, false>)<<<(unsigned)blocks, 64 * kDkvWaves, 0, st>>>(kv);
+    }
     if (group > 1) {
         int64_t nb = (2 * M * (wk / 8) + kAttnThreads - 1) / kAttnThreads;
         if (nb > 8192) nb = 8192;

@@ -150,6 +150,38 @@ def test_sdpa_backward(B, S, Hq, Hkv):
     assert torch.equal(dqkv.view(torch.int16), dqkv2.view(torch.int16))
 
 
+# Few blocks take dQ and dK/dV in one launch, many in two, by the same device code and sums: the same bits.  Blocks of a launch
+# (256 compute units: one launch below 256 of one tile, 341 of two): 272 and 8 each; 352 and 16.
+@pytest.mark.parametrize("B,S,Hq,Hkv", [(34, 24, 8, 8), (34, 40, 8, 2), (22, 264, 8, 8), (22, 320, 8, 4)])
+def test_sdpa_backward_in_one_launch_has_the_bits_of_two(B, S, Hq, Hkv):
+    a = Attn(B, S, Hq, Hkv, seed=S)
+    a.forward()
+    do_t = gen((B * S, Hq * HD), S + 1, 1e-2)
+    dqkv, delta = run_backward(a, do_t)
+    for b in (0, B // 2, B - 1):
+        rows = slice(b * S, (b + 1) * S)
+        one = Attn(1, S, Hq, Hkv, seed=S)
+        one.q, one.k, one.v, one.o, one.lse = a.q[rows], a.k[rows], a.v[rows], a.o[rows], a.lse[:, rows].contiguous()
+        dqkv1, delta1 = run_backward(one, do_t[rows])
+        assert torch.equal(dqkv1.view(torch.int16), dqkv[rows].view(torch.int16))
+        assert torch.equal(delta1, delta[:, rows])
+
+
+def test_sdpa_backward_gradients_over_k_and_v():
+    """dK and dV in the place of k and v, which dQ needs first: as with buffers of their own."""
+    B, S, H = 2, 328, 2
+    a = Attn(B, S, H, H, seed=5)
+    a.forward()
+    do_t = gen((B * S, H * HD), 6, 1e-2)
+    dqkv, _ = run_backward(a, do_t)
+    do, dq, delta = do_t.cuda(), torch.empty_like(a.o), torch.empty_like(a.lse)
+    t = torch.empty((H * HD, B * S), dtype=torch.bfloat16, device="cuda")
+    k, v = a.k.contiguous(), a.v.contiguous()
+    f8.sdpa_bwd(a.q, t, k, t, v, a.o, do, t, a.lse, B, S, H, H, HD, dq, k, v, delta, None)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat((dq, k, v), 1).view(torch.int16), dqkv.view(torch.int16))
+
+
 def test_sdpa_backward_peaked_scores():
     """Scores of order ten (a softmax close to one-hot, where P (dP - delta) cancels strongly)."""
     B, S, Hq, Hkv = 2, 264, 4, 2
