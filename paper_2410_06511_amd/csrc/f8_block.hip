@@ -33,7 +33,9 @@ __device__ inline uint32_t rotate_word(uint32_t w, float c, float s)
 // x [rows, nh * hd] (row pitch ldx) -> out (row pitch ldo; ROTATE: pairs of adjacent columns turned
 // by pos * freq) and out_t [nh * hd, rows] (packed).  One block: a 64x64 tile at the same place of
 // `hpb` consecutive heads, one head after the other: the sines and cosines depend on the row and
-// on the column inside the head only, so they are taken once and used for every head.  rows, hd
+// on the column inside the head only, so they are taken once and used for every head.  The next head's tile is requested
+// before this one is worked on, the first before the sines: a block has one tile in flight otherwise, and its stores before
+// it (4000 x 16 heads of 128: both outputs 15.2 -> 14.4 us, one 10.2 -> 9.2; 8192 x 32 47.4 -> 44.6 and 29.8 -> 28.2).  rows, hd
 // and the pitches are multiples of 8.  (The plain transposition is the case of one head of width
 // cols.)
 template <bool ROTATE, bool OUT, bool OUT_T>
@@ -52,12 +54,24 @@ __global__ __launch_bounds__(kBlkThreads) void rope_tile_kernel(const uint16_t* 
     const int cc = threadIdx.x & 7, rr = threadIdx.x >> 3;
     const int cih = c0 + cc * 8;            // this thread's column inside the head
     const bool col_ok = cih < hd;
-    float cs[2][4], sn[2][4];
-    if constexpr (ROTATE) {
+    const int h_end = h0 + hpb < nh ? h0 + hpb : nh;
+    auto request = [&](uint4(&v)[2], int h) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int64_t r = r0 + rr + 32 * i;
-            const double pos = (double)(r % S);
+            v[i] = make_uint4(0, 0, 0, 0);
+            if (col_ok && r < rows) v[i] = *reinterpret_cast<const uint4*>(x + r * ldx + (int64_t)h * hd + cih);
+        }
+    };
+    uint4 next[2];
+    request(next, h0);
+    float cs[2][4], sn[2][4];
+    if constexpr (ROTATE) {
+        const bool short_ids = ((uint64_t)rows | (uint64_t)S) >> 32 == 0;  // a 64-bit remainder takes 0.3 us
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int64_t r = r0 + rr + 32 * i;
+            const double pos = short_ids ? (double)((uint32_t)r % (uint32_t)S) : (double)(r % S);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 // the angle reaches thousands of radians: product and reduction to
@@ -69,16 +83,16 @@ __global__ __launch_bounds__(kBlkThreads) void rope_tile_kernel(const uint16_t* 
             }
         }
     }
-    const int h_end = h0 + hpb < nh ? h0 + hpb : nh;
     for (int h = h0; h < h_end; ++h) {
         const int64_t col = (int64_t)h * hd + cih;
+        uint4 here[2] = {next[0], next[1]};
+        if (h + 1 < h_end) request(next, h + 1);  // on its way while this head is rotated, turned and stored
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int rl = rr + 32 * i;
             const int64_t r = r0 + rl;
-            uint4 v = make_uint4(0, 0, 0, 0);
+            uint4 v = here[i];
             if (col_ok && r < rows) {
-                v = *reinterpret_cast<const uint4*>(x + r * ldx + col);
                 if constexpr (ROTATE)
                     v = make_uint4(rotate_word(v.x, cs[i][0], sn[i][0]), rotate_word(v.y, cs[i][1], sn[i][1]),
                                    rotate_word(v.z, cs[i][2], sn[i][2]), rotate_word(v.w, cs[i][3], sn[i][3]));
