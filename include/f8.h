@@ -482,12 +482,24 @@ f8_status f8_linear_bwd_dyq(const f8_linear_desc* d, f8_saved* saved, void* dX, 
  * several calls assemble, such as the gradient of a fused q|k|v output); exact
  * and independent of the order of the updates.
  *
+ * f8_rope_qkv: the three of a fused q|k|v output [M, (Hq + 2 Hkv) hd] (pitch
+ * ldqkv) in one call: q and k as f8_rope gives them (no transposed copies), vt
+ * [Hkv * hd, M] packed as f8_transpose_bf16 gives it.
+ * f8_rope_qk_bwd: f8_rope with inverse != 0 of dq and dk into the first
+ * (Hq + Hkv) hd columns of dqkv (pitch lddqkv), in one call.  Outputs of both
+ * must not overlap their inputs.
  * f8_transpose_bf16: out_t [cols, rows] packed = x [rows, cols]^T (pitch ldx).
  * f8_add: out = bf16(a + b) over n elements (the residual), n multiple of 8.
  */
 f8_status f8_rope(const void* x_bf16, int64_t ldx, int64_t M, int64_t S, int64_t n_heads, int64_t hd,
                   double theta, int inverse, void* out_bf16, int64_t ldo, void* out_t_bf16,
                   float* amax_inout, void* stream);
+f8_status f8_rope_qkv(const void* qkv_bf16, int64_t ldqkv, int64_t M, int64_t S, int64_t Hq, int64_t Hkv,
+                      int64_t hd, double theta, void* q_bf16, int64_t ldq, void* k_bf16, int64_t ldk,
+                      void* vt_bf16, void* stream);
+f8_status f8_rope_qk_bwd(const void* dq_bf16, int64_t lddq, const void* dk_bf16, int64_t lddk, int64_t M,
+                         int64_t S, int64_t Hq, int64_t Hkv, int64_t hd, double theta, void* dqkv_bf16,
+                         int64_t lddqkv, float* amax_inout, void* stream);
 f8_status f8_transpose_bf16(const void* x_bf16, int64_t ldx, int64_t rows, int64_t cols, void* out_t_bf16,
                             void* stream);
 f8_status f8_add(const void* a_bf16, const void* b_bf16, int64_t n, void* out_bf16, void* stream);
@@ -539,6 +551,13 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
                       void* dq_bf16, int64_t lddq, void* dk_bf16, int64_t lddk, void* dv_bf16,
                       int64_t lddv, float* delta, float* amax_dv_inout, void* workspace,
                       size_t workspace_bytes, void* stream);
+/* The same without the copies that the kernels do not read. */
+f8_status f8_sdpa_bwd_rows(const void* q_bf16, int64_t ldq, const void* k_bf16, int64_t ldk,
+                           const void* v_bf16, int64_t ldv, const void* o_bf16, int64_t ldo,
+                           const void* do_bf16, int64_t lddo, const float* lse, int64_t B, int64_t S,
+                           int64_t Hq, int64_t Hkv, int64_t hd, void* dq_bf16, int64_t lddq,
+                           void* dk_bf16, int64_t lddk, void* dv_bf16, int64_t lddv, float* delta,
+                           float* amax_dv_inout, void* workspace, size_t workspace_bytes, void* stream);
 size_t f8_sdpa_bwd_workspace_bytes(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t hd);
 
 /*

@@ -45,7 +45,7 @@ class TransformerBlock:
         self.xn, self.rstd1, self.a_xn = E(M, D), torch.empty(M, **f32), torch.empty(1, **f32)
         self.qkv = E(M, self.Nqkv)
         self.qr, self.kr = E(M, Hq * hd), E(M, Hkv * hd)                 # rotated q, k
-        self.qt, self.kt, self.vt = E(Hq * hd, M), E(Hkv * hd, M), E(Hkv * hd, M)
+        self.qt, self.kt, self.vt = E(Hq * hd, M), E(Hkv * hd, M), E(Hkv * hd, M)   # (qt, kt: separate stages only)
         self.att, self.lse, self.a_att = E(M, D), torch.empty((Hq, M), **f32), torch.empty(1, **f32)
         self.yo, self.h1 = E(M, D), E(M, D)
         self.hn, self.rstd2, self.a_hn = E(M, D), torch.empty(M, **f32), torch.empty(1, **f32)
@@ -54,7 +54,7 @@ class TransformerBlock:
         # backward
         self.dhh, self.dab, self.a_dab = E(M, H), E(M, 2 * H), torch.empty(1, **f32)
         self.dhn, self.dh1 = E(M, D), E(M, D)
-        self.datt, self.datt_t = E(M, D), E(D, M)
+        self.datt, self.datt_t = E(M, D), E(D, M)   # (datt_t: separate stages only)
         self.dqr, self.dkr, self.delta = E(M, Hq * hd), E(M, Hkv * hd), torch.empty((Hq, M), **f32)
         self.att_ws = torch.empty(max(16, f8.sdpa_bwd_workspace_bytes(B, S, Hq, Hkv, hd)), dtype=torch.uint8, device=device)
         self.dqkv = E(M, self.Nqkv)
@@ -68,17 +68,25 @@ class TransformerBlock:
         Hq, Hkv, hd = self.Hq, self.Hkv, self.hd
         return t[:, :Hq * hd], t[:, Hq * hd:(Hq + Hkv) * hd], t[:, (Hq + Hkv) * hd:]
 
-    def forward_stages(self, x, w, stream=None, replay=False):
+    def forward_stages(self, x, w, stream=None, replay=False, joined=False):
         """w: dict with g1, g2 [D], Wqkv [(Hq + 2 Hkv) hd, D], Wo [D, D], W13 [2 H, D], W2 [D, H] (bf16).
         Returns [(name, call, flops, algorithmic bytes)] in execution order.
         replay (delayed scaling only): the forward run AGAIN inside the backward.  It must
         reproduce the forward whose output fed the loss, so every cast uses the scale that forward
         used (kept next to the codes) and no amax history is touched; the glue is run unfused (h is
-        written and cast with the saved scale: the same codes)."""
+        written and cast with the saved scale: the same codes).
+        joined: as forward() runs them, q, k and v in one call and without the transposed copies of q and k."""
         s, M, D, H, B, S = self, self.M, self.D, self.H, self.B, self.S
         Hq, Hkv, hd = self.Hq, self.Hkv, self.hd
         q, k, v = self._slices(self.qkv)
         att_flops = 4 * B * S * S * Hq * hd // 2
+        rope = [
+            ("rope q (+ transposed copy)", lambda: f8.rope(q, S, Hq, hd, s.qr, s.qt, s.theta, False, stream), 0, 6 * M * Hq * hd),
+            ("rope k (+ transposed copy)", lambda: f8.rope(k, S, Hkv, hd, s.kr, s.kt, s.theta, False, stream), 0, 6 * M * Hkv * hd),
+            ("transpose v", lambda: f8.transpose_bf16(v, s.vt, stream), 0, 4 * M * Hkv * hd),
+        ]
+        if joined:
+            rope = [("rope q, k; transpose v", lambda: f8.rope_qkv(s.qkv, S, Hq, Hkv, hd, s.qr, s.kr, s.vt, s.theta, stream), 0, 4 * M * s.Nqkv)]
         if self.delayed and replay:
             if self._replay is None:
                 self._replay = tuple(f8.ReplayState(sv) for sv in (s.s_qkv, s.s_o, s.s_13, s.s_2))
@@ -87,9 +95,7 @@ class TransformerBlock:
                 ("rmsnorm 1", lambda: f8.rmsnorm(x, w["g1"], s.eps, s.xn, s.rstd1, None, None, stream), 0, 4 * M * D),
                 ("linear wq|wk|wv fwd", lambda: f8.linear_fwd_scaled(s.d_qkv, r_qkv, s.xn, w["Wqkv"], s.qkv, s.s_qkv, s.ws, stream),
                  2 * M * D * s.Nqkv, 0),
-                ("rope q (+ transposed copy)", lambda: f8.rope(q, S, Hq, hd, s.qr, s.qt, s.theta, False, stream), 0, 6 * M * Hq * hd),
-                ("rope k (+ transposed copy)", lambda: f8.rope(k, S, Hkv, hd, s.kr, s.kt, s.theta, False, stream), 0, 6 * M * Hkv * hd),
-                ("transpose v", lambda: f8.transpose_bf16(v, s.vt, stream), 0, 4 * M * Hkv * hd),
+                *rope,
                 ("attention fwd", lambda: f8.sdpa_fwd(s.qr, s.kr, s.vt, B, S, Hq, Hkv, hd, s.att, s.lse, stream), att_flops, 0),
                 ("linear wo fwd", lambda: f8.linear_fwd_scaled(s.d_o, r_o, s.att, w["Wo"], s.yo, s.s_o, s.ws, stream), 2 * M * D * D, 0),
                 ("residual 1", lambda: f8.add(x, s.yo, s.h1, stream), 0, 6 * M * D),
@@ -105,9 +111,7 @@ class TransformerBlock:
                 ("rmsnorm 1", lambda: f8.rmsnorm(x, w["g1"], s.eps, s.xn, s.rstd1, None, None, stream), 0, 4 * M * D),
                 ("linear wq|wk|wv fwd", lambda: f8.linear_fwd_scaled(s.d_qkv, s.st_qkv, s.xn, w["Wqkv"], s.qkv, s.s_qkv, s.ws, stream),
                  2 * M * D * s.Nqkv, 0),
-                ("rope q (+ transposed copy)", lambda: f8.rope(q, S, Hq, hd, s.qr, s.qt, s.theta, False, stream), 0, 6 * M * Hq * hd),
-                ("rope k (+ transposed copy)", lambda: f8.rope(k, S, Hkv, hd, s.kr, s.kt, s.theta, False, stream), 0, 6 * M * Hkv * hd),
-                ("transpose v", lambda: f8.transpose_bf16(v, s.vt, stream), 0, 4 * M * Hkv * hd),
+                *rope,
                 ("attention fwd", lambda: f8.sdpa_fwd(s.qr, s.kr, s.vt, B, S, Hq, Hkv, hd, s.att, s.lse, stream), att_flops, 0),
                 ("linear wo fwd", lambda: f8.linear_fwd_scaled(s.d_o, s.st_o, s.att, w["Wo"], s.yo, s.s_o, s.ws, stream), 2 * M * D * D, 0),
                 ("residual 1", lambda: f8.add(x, s.yo, s.h1, stream), 0, 6 * M * D),
@@ -124,9 +128,7 @@ class TransformerBlock:
             ("rmsnorm 1", lambda: f8.rmsnorm(x, w["g1"], s.eps, s.xn, s.rstd1, s.a_xn, s.ws, stream), 0, 4 * M * D),
             ("linear wq|wk|wv fwd", lambda: f8.linear_fwd_chained(s.d_qkv, s.xn, s.a_xn, w["Wqkv"], s.qkv, None, s.s_qkv, s.ws, stream),
              2 * M * D * s.Nqkv, 0),
-            ("rope q (+ transposed copy)", lambda: f8.rope(q, S, Hq, hd, s.qr, s.qt, s.theta, False, stream), 0, 6 * M * Hq * hd),
-            ("rope k (+ transposed copy)", lambda: f8.rope(k, S, Hkv, hd, s.kr, s.kt, s.theta, False, stream), 0, 6 * M * Hkv * hd),
-            ("transpose v", lambda: f8.transpose_bf16(v, s.vt, stream), 0, 4 * M * Hkv * hd),
+            *rope,
             ("attention fwd", lambda: f8.sdpa_fwd(s.qr, s.kr, s.vt, B, S, Hq, Hkv, hd, s.att, s.lse, stream, s.a_att), att_flops, 0),
             ("linear wo fwd", lambda: f8.linear_fwd_chained(s.d_o, s.att, s.a_att, w["Wo"], s.yo, None, s.s_o, s.ws, stream), 2 * M * D * D, 0),
             ("residual 1", lambda: f8.add(x, s.yo, s.h1, stream), 0, 6 * M * D),
@@ -139,7 +141,7 @@ class TransformerBlock:
             ("residual 2", lambda: f8.add(s.h1, s.y2, s.out, stream), 0, 6 * M * D),
         ]
 
-    def backward_stages(self, x, w, dout, stream=None):
+    def backward_stages(self, x, w, dout, stream=None, joined=False):
         s, M, D, H, B, S = self, self.M, self.D, self.H, self.B, self.S
         Hq, Hkv, hd = self.Hq, self.Hkv, self.hd
         q, k, v = self._slices(self.qkv)
@@ -178,29 +180,39 @@ class TransformerBlock:
                 with torch.cuda.stream(stream):
                     s.a_bwd.zero_()
 
-        return [("zero the amax cells", zero_amax, 0, 0)] + ffn + [
-            ("rmsnorm 2 bwd + residual", lambda: f8.rmsnorm_bwd_add(s.h1, w["g2"], s.rstd2, s.dhn, dout, s.dh1, s.dg2, s.ws, stream, a_dh1),
-             0, 12 * M * D),
-            ("linear wo bwd", lin_o, 4 * M * D * D, 0),
+        attention = [
             ("transpose dO", lambda: f8.transpose_bf16(s.datt, s.datt_t, stream), 0, 4 * M * D),
             ("attention bwd", lambda: f8.sdpa_bwd(s.qr, s.qt, s.kr, s.kt, v, s.att, s.datt, s.datt_t, s.lse, B, S, Hq, Hkv, hd,
                                                   s.dqr, s.dkr, dv, s.delta, s.att_ws, stream, a_dqkv),
              5 * att_flops // 2, 0),
             ("rope q bwd", lambda: f8.rope(s.dqr, S, Hq, hd, dq, None, s.theta, True, stream, a_dqkv), 0, 4 * M * Hq * hd),
             ("rope k bwd", lambda: f8.rope(s.dkr, S, Hkv, hd, dk, None, s.theta, True, stream, a_dqkv), 0, 4 * M * Hkv * hd),
+        ]
+        if joined:
+            attention = [
+                ("attention bwd", lambda: f8.sdpa_bwd_rows(s.qr, s.kr, v, s.att, s.datt, s.lse, B, S, Hq, Hkv, hd, s.dqr, s.dkr, dv, s.delta,
+                                                           s.att_ws, stream, a_dqkv), 5 * att_flops // 2, 0),
+                ("rope q, k bwd", lambda: f8.rope_qk_bwd(s.dqr, s.dkr, S, Hq, Hkv, hd, s.dqkv, s.theta, stream, a_dqkv), 0,
+                 4 * M * (Hq + Hkv) * hd),
+            ]
+        return [("zero the amax cells", zero_amax, 0, 0)] + ffn + [
+            ("rmsnorm 2 bwd + residual", lambda: f8.rmsnorm_bwd_add(s.h1, w["g2"], s.rstd2, s.dhn, dout, s.dh1, s.dg2, s.ws, stream, a_dh1),
+             0, 12 * M * D),
+            ("linear wo bwd", lin_o, 4 * M * D * D, 0),
+            *attention,
             ("linear wq|wk|wv bwd", lin_qkv, 4 * M * D * s.Nqkv, 0),
             ("rmsnorm 1 bwd + residual", lambda: f8.rmsnorm_bwd_add(x, w["g1"], s.rstd1, s.dxn, s.dh1, s.dx, s.dg1, s.ws, stream),
              0, 12 * M * D),
         ]
 
     def forward(self, x, w, stream=None):
-        for _, call, _, _ in self.forward_stages(x, w, stream):
+        for _, call, _, _ in self.forward_stages(x, w, stream, joined=True):
             call()
         return self.out
 
     # what selective recomputation runs again: everything the backward reads that is not the output
     # of a matrix product or of the attention (those are kept, as are the fp8 codes of the linears)
-    SELECTIVE = ("rmsnorm 1", "rope q (+ transposed copy)", "rope k (+ transposed copy)", "residual 1", "rmsnorm 2")
+    SELECTIVE = ("rmsnorm 1", "rope q, k; transpose v", "residual 1", "rmsnorm 2")
 
     def backward(self, x, w, dout, stream=None, recompute=False):
         """recompute (Section 2.2.1, activation checkpointing):
@@ -210,16 +222,15 @@ class TransformerBlock:
         histories alone).
         "selective": keep the outputs of the matrix products and of the attention (and the fp8
         codes saved by the linears) and run again only the cheap operations whose results the
-        backward reads: the normalisation statistics, the rotated q and k (the call writes their
-        transposed copies too, which f8_sdpa_bwd asks for but does not read), and the first
-        residual sum."""
+        backward reads: the normalisation statistics, the rotated q and k (the call transposes v
+        too), and the first residual sum."""
         if recompute == "selective":
-            for name, call, _, _ in self.forward_stages(x, w, stream):
+            for name, call, _, _ in self.forward_stages(x, w, stream, joined=True):
                 if name in self.SELECTIVE:
                     call()
         elif recompute:
-            for _, call, _, _ in self.forward_stages(x, w, stream, replay=self.delayed):
+            for _, call, _, _ in self.forward_stages(x, w, stream, replay=self.delayed, joined=True):
                 call()
-        for _, call, _, _ in self.backward_stages(x, w, dout, stream):
+        for _, call, _, _ in self.backward_stages(x, w, dout, stream, joined=True):
             call()
         return self.dx

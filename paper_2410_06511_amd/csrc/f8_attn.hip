@@ -966,7 +966,7 @@ __global__ __launch_bounds__(kAttnThreads) void sdpa_delta_kernel(const uint16_t
 // dQ and dK/dV in one launch, the blocks of both, longest first (a dK/dV block takes 1.35 times as long as a dQ block of
 // as many tiles), delta beforehand.  A launch of at most one block per compute unit lasts as long as its longest block, and
 // the units of the shorter ones idle: here the other kernel's blocks fill them (4 x 1000 tokens, 16 heads: 48 + 64 us in two
-// launches; this and delta 95).  Same device code, same bits.
+// launches; this 90 and delta 7).  Same device code, same bits.
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_kernel(const DqArgs Pq, const DkvArgs Pk, int tiles)
 {
@@ -1084,23 +1084,19 @@ size_t f8_sdpa_bwd_workspace_bytes(int64_t B, int64_t S, int64_t Hq, int64_t Hkv
     return (size_t)2 * (size_t)(B * S) * (size_t)(Hq * hd) * sizeof(float);  // dk and dv shares of every query head
 }
 
-f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, const void* k_bf16, int64_t ldk,
-                      const void* kt_bf16, const void* v_bf16, int64_t ldv, const void* o_bf16, int64_t ldo,
-                      const void* do_bf16, int64_t lddo, const void* dot_bf16, const float* lse, int64_t B, int64_t S,
-                      int64_t Hq, int64_t Hkv, int64_t hd, void* dq_bf16, int64_t lddq, void* dk_bf16, int64_t lddk,
-                      void* dv_bf16, int64_t lddv, float* delta, float* amax_dv_inout, void* workspace, size_t workspace_bytes_,
-                      void* stream)
+static f8_status sdpa_bwd(const void* q_bf16, int64_t ldq, const void* k_bf16, int64_t ldk, const void* v_bf16, int64_t ldv, const void* o_bf16,
+                          int64_t ldo, const void* do_bf16, int64_t lddo, const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv,
+                          int64_t hd, void* dq_bf16, int64_t lddq, void* dk_bf16, int64_t lddk, void* dv_bf16, int64_t lddv, float* delta,
+                          float* amax_dv_inout, void* workspace, size_t workspace_bytes_, void* stream, bool copies_aligned = true)
 {
     f8_status s = check_attn(q_bf16, ldq, k_bf16, ldk, B, S, Hq, Hkv, hd);
     if (s != F8_OK) return s;
-    if (!qt_bf16 || !kt_bf16 || !v_bf16 || !o_bf16 || !do_bf16 || !dot_bf16 || !lse || !dq_bf16 || !dk_bf16 || !dv_bf16 || !delta)
-        return F8_ERR_NULL;
+    if (!v_bf16 || !o_bf16 || !do_bf16 || !lse || !dq_bf16 || !dk_bf16 || !dv_bf16 || !delta) return F8_ERR_NULL;
     const int64_t wq = Hq * hd, wk = Hkv * hd;
     if (ldv < wk || ldo < wq || lddo < wq || lddq < wq || lddk < wk || lddv < wk || (ldv % 8) || (ldo % 8) || (lddo % 8) ||
         (lddq % 8) || (lddk % 8) || (lddv % 8))
         return F8_ERR_SHAPE;
-    if (!aligned16(qt_bf16) || !aligned16(kt_bf16) || !aligned16(v_bf16) || !aligned16(o_bf16) || !aligned16(do_bf16) ||
-        !aligned16(dot_bf16) || !aligned16(dq_bf16) || !aligned16(dk_bf16) || !aligned16(dv_bf16))
+    if (!copies_aligned || !aligned16(v_bf16) || !aligned16(o_bf16) || !aligned16(do_bf16) || !aligned16(dq_bf16) || !aligned16(dk_bf16) || !aligned16(dv_bf16))
         return F8_ERR_ALIGN;
     const int64_t group = Hq / Hkv;
     if (amax_dv_inout && group == 1) return F8_ERR_ENUM;  // the amax of dv is taken where the heads' shares are summed
@@ -1147,6 +1143,30 @@ f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, cons
                                                                    (uint16_t*)dv_bf16, lddv, reinterpret_cast<uint32_t*>(amax_dv_inout));
     }
     return last_launch_status();
+}
+
+f8_status f8_sdpa_bwd(const void* q_bf16, int64_t ldq, const void* qt_bf16, const void* k_bf16, int64_t ldk,
+                      const void* kt_bf16, const void* v_bf16, int64_t ldv, const void* o_bf16, int64_t ldo,
+                      const void* do_bf16, int64_t lddo, const void* dot_bf16, const float* lse, int64_t B, int64_t S,
+                      int64_t Hq, int64_t Hkv, int64_t hd, void* dq_bf16, int64_t lddq, void* dk_bf16, int64_t lddk,
+                      void* dv_bf16, int64_t lddv, float* delta, float* amax_dv_inout, void* workspace, size_t workspace_bytes_,
+                      void* stream)
+{
+    f8_status s = check_attn(q_bf16, ldq, k_bf16, ldk, B, S, Hq, Hkv, hd);
+    if (s != F8_OK) return s;
+    if (!qt_bf16 || !kt_bf16 || !dot_bf16) return F8_ERR_NULL;
+    return sdpa_bwd(q_bf16, ldq, k_bf16, ldk, v_bf16, ldv, o_bf16, ldo, do_bf16, lddo, lse, B, S, Hq, Hkv, hd, dq_bf16, lddq, dk_bf16, lddk,
+                    dv_bf16, lddv, delta, amax_dv_inout, workspace, workspace_bytes_, stream,
+                    aligned16(qt_bf16) && aligned16(kt_bf16) && aligned16(dot_bf16));
+}
+
+f8_status f8_sdpa_bwd_rows(const void* q_bf16, int64_t ldq, const void* k_bf16, int64_t ldk, const void* v_bf16, int64_t ldv,
+                           const void* o_bf16, int64_t ldo, const void* do_bf16, int64_t lddo, const float* lse, int64_t B, int64_t S,
+                           int64_t Hq, int64_t Hkv, int64_t hd, void* dq_bf16, int64_t lddq, void* dk_bf16, int64_t lddk, void* dv_bf16,
+                           int64_t lddv, float* delta, float* amax_dv_inout, void* workspace, size_t workspace_bytes_, void* stream)
+{
+    return sdpa_bwd(q_bf16, ldq, k_bf16, ldk, v_bf16, ldv, o_bf16, ldo, do_bf16, lddo, lse, B, S, Hq, Hkv, hd, dq_bf16, lddq, dk_bf16, lddk,
+                    dv_bf16, lddv, delta, amax_dv_inout, workspace, workspace_bytes_, stream);
 }
 
 }  // extern "C"

@@ -38,18 +38,27 @@ __device__ inline uint32_t rotate_word(uint32_t w, float c, float s)
 // it (4000 x 16 heads of 128: both outputs 15.2 -> 14.4 us, one 10.2 -> 9.2; 8192 x 32 47.4 -> 44.6 and 29.8 -> 28.2).  rows, hd
 // and the pitches are multiples of 8.  (The plain transposition is the case of one head of width
 // cols.)
+struct RopePart {
+    const uint16_t* x;
+    uint16_t *out, *out_t;
+    int64_t ldx, ldo;
+    int nh, hpb;
+    int tiles_c;       // per row of tiles: tiles per head x head groups
+    unsigned blocks;
+};
+// `id`: the block's number within the part; tile: kRt * kRtStride of LDS (OUT_T)
 template <bool ROTATE, bool OUT, bool OUT_T>
-__global__ __launch_bounds__(kBlkThreads) void rope_tile_kernel(const uint16_t* __restrict__ x, int64_t rows, int nh, int hd,
-                                                                int hpb, int64_t ldx, int64_t ldo, int64_t S, float sign, RopeFreq fr,
-                                                                uint16_t* __restrict__ out, uint16_t* __restrict__ out_t,
-                                                                int tiles_c /* per row of tiles: tiles per head x head groups */,
-                                                                uint32_t* __restrict__ amax_bits /* nullable: max-updated */)
+__device__ __forceinline__ void rope_tile_work(const RopePart& P, unsigned id, int64_t rows, int hd, int64_t S, float sign, const RopeFreq& fr,
+                                               uint32_t* __restrict__ amax_bits /* nullable: max-updated */, uint16_t* tile)
 {
-    __shared__ uint16_t tile[kRt * kRtStride];
+    const uint16_t* __restrict__ x = P.x;
+    uint16_t *__restrict__ out = P.out, *__restrict__ out_t = P.out_t;
+    const int64_t ldx = P.ldx, ldo = P.ldo;
+    const int nh = P.nh, hpb = P.hpb;
     uint32_t mag = 0;  // packed pair of the largest 15-bit magnitudes written
     const int tph = (hd + kRt - 1) / kRt;  // tiles per head
-    const int tc = blockIdx.x % tiles_c;
-    const int64_t r0 = (int64_t)(blockIdx.x / tiles_c) * kRt;
+    const int tc = id % P.tiles_c;
+    const int64_t r0 = (int64_t)(id / P.tiles_c) * kRt;
     const int c0 = (tc % tph) * kRt, h0 = (tc / tph) * hpb;  // column inside the head, first head
     const int cc = threadIdx.x & 7, rr = threadIdx.x >> 3;
     const int cih = c0 + cc * 8;            // this thread's column inside the head
@@ -124,6 +133,30 @@ __global__ __launch_bounds__(kBlkThreads) void rope_tile_kernel(const uint16_t* 
     if (amax_bits) {  // a maximum of non-negative floats is a maximum of their bit patterns: order-independent
         const uint32_t m = wave_max_u32(pk_collapse(mag)) << 16;
         if ((threadIdx.x & (kWave - 1)) == 0 && m > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, m);
+    }
+}
+
+template <bool ROTATE, bool OUT, bool OUT_T>
+__global__ __launch_bounds__(kBlkThreads) void rope_tile_kernel(const RopePart part, int64_t rows, int hd, int64_t S, float sign, const RopeFreq fr,
+                                                                uint32_t* __restrict__ amax_bits)
+{
+    __shared__ uint16_t tile[OUT_T ? kRt * kRtStride : 1];
+    rope_tile_work<ROTATE, OUT, OUT_T>(part, blockIdx.x, rows, hd, S, sign, fr, amax_bits, tile);
+}
+
+// q and k rotated and (V) v transposed in one launch: of small tensors each launch takes its own 4 us (1008 tokens, 8 / 2 /
+// 2 heads: 12.5 -> 6.5 us, and turned back 10.0 -> 5.0), of large ones the smaller parts fill the ends of the larger one.  No
+// transposed copies of q and k (8192 tokens, 32 / 8 / 8 heads: with them 67 us, this 37.6; back 51.7 -> 46.2).
+template <bool V>
+__global__ __launch_bounds__(kBlkThreads) void rope_parts_kernel(const RopePart q, const RopePart k, const RopePart v, int64_t rows, int hd, int64_t S,
+                                                                 float sign, const RopeFreq fr, uint32_t* __restrict__ amax_bits)
+{
+    __shared__ uint16_t tile[V ? kRt * kRtStride : 1];
+    if (V && blockIdx.x >= q.blocks + k.blocks) {
+        rope_tile_work<false, false, true>(v, blockIdx.x - q.blocks - k.blocks, rows, hd, S, sign, fr, nullptr, tile);
+    } else {
+        const bool second = blockIdx.x >= q.blocks;
+        rope_tile_work<true, true, false>(second ? k : q, blockIdx.x - (second ? q.blocks : 0), rows, hd, S, sign, fr, amax_bits, tile);
     }
 }
 
@@ -532,30 +565,45 @@ static int elementwise_blocks(int64_t chunks)
     return (int)b;
 }
 
+// Heads per block: as many as leave about four blocks per compute unit, or, since the sines and cosines bound a
+// block of few heads, two where they are taken (4000 x 16 heads: one output 12.3 -> 9.6 us, both 16.4 -> 16.1).
+// `heads`: those of the whole launch.  false: too many blocks.
+static bool plan_rope_part(RopePart& p, int64_t rows, int64_t hd, int64_t heads, bool rotate)
+{
+    const int64_t tiles_r = (rows + kRt - 1) / kRt, tph = (hd + kRt - 1) / kRt;
+    int64_t hpb = (tiles_r * tph * heads) / (rotate ? 512 : 1024);
+    if (hpb < 1) hpb = 1;
+    if (hpb > 8) hpb = 8;
+    if (hpb > p.nh) hpb = p.nh;
+    const int64_t tiles_c = tph * ((p.nh + hpb - 1) / hpb), nb = tiles_r * tiles_c;
+    if (nb > (int64_t)0x7FFFFFFF) return false;
+    p.hpb = (int)hpb, p.tiles_c = (int)tiles_c, p.blocks = (unsigned)nb;
+    return true;
+}
+
 template <bool ROTATE>
 static f8_status launch_rope_tiles(const void* x, int64_t rows, int64_t nh, int64_t hd, int64_t ldx, int64_t ldo, int64_t S,
                                    float sign, const RopeFreq& fr, void* out, void* out_t, float* amax, hipStream_t st)
 {
-    // heads per block: as many as leave about four blocks per compute unit, or, since the sines and cosines bound a
-    // block of few heads, two where they are taken (4000 x 16 heads: one output 12.3 -> 9.6 us, both 16.4 -> 16.1)
-    const int64_t tiles_r = (rows + kRt - 1) / kRt, tph = (hd + kRt - 1) / kRt;
-    int64_t hpb = (tiles_r * tph * nh) / (ROTATE ? 512 : 1024);
-    if (hpb < 1) hpb = 1;
-    if (hpb > 8) hpb = 8;
-    if (hpb > nh) hpb = nh;
-    const int64_t tiles_c = tph * ((nh + hpb - 1) / hpb);
-    const int64_t nb = tiles_r * tiles_c;
-    if (nb == 0) return F8_OK;
-    if (nb > (int64_t)0x7FFFFFFF) return F8_ERR_SHAPE;
-#define F8_ROPE_LAUNCH(O, T)                                                                                              \
-    rope_tile_kernel<ROTATE, O, T><<<(unsigned)nb, kBlkThreads, 0, st>>>((const uint16_t*)x, rows, (int)nh, (int)hd, (int)hpb, ldx, \
-                                                                         ldo, S, sign, fr, (uint16_t*)out, (uint16_t*)out_t, (int)tiles_c, \
-                                                                         reinterpret_cast<uint32_t*>(amax))
-    if (out && out_t) F8_ROPE_LAUNCH(true, true);
-    else if (out) F8_ROPE_LAUNCH(true, false);
-    else F8_ROPE_LAUNCH(false, true);
-#undef F8_ROPE_LAUNCH
+    RopePart p{(const uint16_t*)x, (uint16_t*)out, (uint16_t*)out_t, ldx, ldo, (int)nh, 0, 0, 0};
+    if (!plan_rope_part(p, rows, hd, nh, ROTATE)) return F8_ERR_SHAPE;
+    if (p.blocks == 0) return F8_OK;
+    const auto kernel = out && out_t ? rope_tile_kernel<ROTATE, true, true> : out ? rope_tile_kernel<ROTATE, true, false> : rope_tile_kernel<ROTATE, false, true>;
+    kernel<<<p.blocks, kBlkThreads, 0, st>>>(p, rows, (int)hd, S, sign, fr, reinterpret_cast<uint32_t*>(amax));
     return last_launch_status();
+}
+
+static RopeFreq rope_freq(double theta, int64_t hd)
+{
+    RopeFreq fr;
+    for (int i = 0; i < 128; ++i) fr.f[i] = i < hd / 2 ? pow(theta, -2.0 * (double)i / (double)hd) : 0.0;
+    return fr;
+}
+
+static bool rope_shape_ok(int64_t M, int64_t S, int64_t n_heads, int64_t hd, double theta, int64_t ldx)
+{
+    return M >= 0 && S >= 1 && n_heads >= 1 && hd >= 2 && hd <= 256 && hd % 8 == 0 && M % 8 == 0 && theta > 0.0 &&
+           n_heads < ((int64_t)1 << 23) && n_heads * hd < (1 << 23) && ldx >= n_heads * hd && ldx % 8 == 0;
 }
 
 }  // namespace f8
@@ -568,14 +616,48 @@ f8_status f8_rope(const void* x_bf16, int64_t ldx, int64_t M, int64_t S, int64_t
                   int inverse, void* out_bf16, int64_t ldo, void* out_t_bf16, float* amax_inout, void* stream)
 {
     if (!x_bf16 || (!out_bf16 && !out_t_bf16)) return F8_ERR_NULL;
-    if (M < 0 || S < 1 || n_heads < 1 || hd < 2 || hd > 256 || (hd % 8) || (M % 8) || !(theta > 0.0)) return F8_ERR_SHAPE;
-    if (n_heads * hd >= (1 << 23) || ldx < n_heads * hd || (ldx % 8) || (out_bf16 && (ldo < n_heads * hd || (ldo % 8))))
-        return F8_ERR_SHAPE;
+    if (!rope_shape_ok(M, S, n_heads, hd, theta, ldx) || (out_bf16 && (ldo < n_heads * hd || (ldo % 8)))) return F8_ERR_SHAPE;
     if (!aligned16(x_bf16) || (out_bf16 && !aligned16(out_bf16)) || (out_t_bf16 && !aligned16(out_t_bf16))) return F8_ERR_ALIGN;
-    RopeFreq fr;
-    for (int i = 0; i < 128; ++i) fr.f[i] = i < hd / 2 ? pow(theta, -2.0 * (double)i / (double)hd) : 0.0;
-    return launch_rope_tiles<true>(x_bf16, M, n_heads, hd, ldx, ldo, S, inverse ? -1.0f : 1.0f, fr, out_bf16, out_t_bf16,
+    return launch_rope_tiles<true>(x_bf16, M, n_heads, hd, ldx, ldo, S, inverse ? -1.0f : 1.0f, rope_freq(theta, hd), out_bf16, out_t_bf16,
                                    amax_inout, (hipStream_t)stream);
+}
+
+f8_status f8_rope_qkv(const void* qkv_bf16, int64_t ldqkv, int64_t M, int64_t S, int64_t Hq, int64_t Hkv, int64_t hd, double theta,
+                      void* q_bf16, int64_t ldq, void* k_bf16, int64_t ldk, void* vt_bf16, void* stream)
+{
+    if (!qkv_bf16 || !q_bf16 || !k_bf16 || !vt_bf16) return F8_ERR_NULL;
+    if (Hq < 1 || Hkv < 1 || Hq >= (1 << 20) || Hkv >= (1 << 20) || !rope_shape_ok(M, S, Hq + 2 * Hkv, hd, theta, ldqkv)) return F8_ERR_SHAPE;
+    if (ldq < Hq * hd || ldk < Hkv * hd || (ldq % 8) || (ldk % 8)) return F8_ERR_SHAPE;
+    if (!aligned16(qkv_bf16) || !aligned16(q_bf16) || !aligned16(k_bf16) || !aligned16(vt_bf16)) return F8_ERR_ALIGN;
+    const uint16_t* x = (const uint16_t*)qkv_bf16;
+    RopePart q{x, (uint16_t*)q_bf16, nullptr, ldqkv, ldq, (int)Hq, 0, 0, 0}, k{x + Hq * hd, (uint16_t*)k_bf16, nullptr, ldqkv, ldk, (int)Hkv, 0, 0, 0},
+        v{x + (Hq + Hkv) * hd, nullptr, (uint16_t*)vt_bf16, ldqkv, 0, (int)Hkv, 0, 0, 0};
+    if (!plan_rope_part(q, M, hd, Hq + Hkv, true) || !plan_rope_part(k, M, hd, Hq + Hkv, true) || !plan_rope_part(v, M, hd, Hq + Hkv, true))
+        return F8_ERR_SHAPE;
+    const int64_t blocks = (int64_t)q.blocks + k.blocks + v.blocks;
+    if (blocks > (int64_t)0x7FFFFFFF) return F8_ERR_SHAPE;
+    if (blocks)
+        rope_parts_kernel<true><<<(unsigned)blocks, kBlkThreads, 0, (hipStream_t)stream>>>(q, k, v, M, (int)hd, S, 1.0f, rope_freq(theta, hd), nullptr);
+    return last_launch_status();
+}
+
+f8_status f8_rope_qk_bwd(const void* dq_bf16, int64_t lddq, const void* dk_bf16, int64_t lddk, int64_t M, int64_t S, int64_t Hq, int64_t Hkv,
+                         int64_t hd, double theta, void* dqkv_bf16, int64_t lddqkv, float* amax_inout, void* stream)
+{
+    if (!dq_bf16 || !dk_bf16 || !dqkv_bf16) return F8_ERR_NULL;
+    if (Hq < 1 || Hkv < 1 || Hq >= (1 << 20) || Hkv >= (1 << 20) || !rope_shape_ok(M, S, Hq + Hkv, hd, theta, lddqkv)) return F8_ERR_SHAPE;
+    if (lddq < Hq * hd || lddk < Hkv * hd || (lddq % 8) || (lddk % 8)) return F8_ERR_SHAPE;
+    if (!aligned16(dq_bf16) || !aligned16(dk_bf16) || !aligned16(dqkv_bf16)) return F8_ERR_ALIGN;
+    uint16_t* out = (uint16_t*)dqkv_bf16;
+    RopePart q{(const uint16_t*)dq_bf16, out, nullptr, lddq, lddqkv, (int)Hq, 0, 0, 0},
+        k{(const uint16_t*)dk_bf16, out + Hq * hd, nullptr, lddk, lddqkv, (int)Hkv, 0, 0, 0};
+    if (!plan_rope_part(q, M, hd, Hq + Hkv, true) || !plan_rope_part(k, M, hd, Hq + Hkv, true)) return F8_ERR_SHAPE;
+    const int64_t blocks = (int64_t)q.blocks + k.blocks;
+    if (blocks > (int64_t)0x7FFFFFFF) return F8_ERR_SHAPE;
+    if (blocks)
+        rope_parts_kernel<false><<<(unsigned)blocks, kBlkThreads, 0, (hipStream_t)stream>>>(q, k, k, M, (int)hd, S, -1.0f, rope_freq(theta, hd),
+                                                                                            reinterpret_cast<uint32_t*>(amax_inout));
+    return last_launch_status();
 }
 
 f8_status f8_transpose_bf16(const void* x_bf16, int64_t ldx, int64_t rows, int64_t cols, void* out_t_bf16, void* stream)

@@ -28,7 +28,7 @@ EXPORTS = ["f8_workspace_bytes", "f8_status_string", "f8_amax", "f8_scale", "f8_
            "f8_linear_fwd_chained", "f8_linear_bwd_chained", "f8_quantise",
            "f8_silu_mul", "f8_silu_mul_bwd", "f8_rmsnorm", "f8_silu_mul_quantise_delayed", "f8_linear_fwd_xq",
            "f8_silu_mul_bwd_quantise_delayed", "f8_linear_bwd_dyq",
-           "f8_rope", "f8_transpose_bf16", "f8_add", "f8_rmsnorm_bwd", "f8_sdpa_fwd", "f8_sdpa_bwd", "f8_sdpa_bwd_workspace_bytes",
+           "f8_rope", "f8_rope_qkv", "f8_rope_qk_bwd", "f8_transpose_bf16", "f8_add", "f8_rmsnorm_bwd", "f8_sdpa_fwd", "f8_sdpa_bwd", "f8_sdpa_bwd_rows", "f8_sdpa_bwd_workspace_bytes",
            "f8_rmsnorm_bwd_add", "f8_linear_fwd_wq", "f8_linear_fwd_noalloc", "f8_linear_fwd_quantise",
            "f8_probe_mfma", "f8_probe_copy", "f8_probe_read", "f8_probe_clock"]
 
@@ -101,6 +101,8 @@ def lib():
                                                        _p, C.c_size_t, _p]
         l.f8_linear_bwd_dyq.argtypes = [C.POINTER(LinearDesc), C.POINTER(SavedStruct), _p, _p, _p]
         l.f8_rope.argtypes = [_p, _i64, _i64, _i64, _i64, _i64, C.c_double, _int, _p, _i64, _p, _p, _p]
+        l.f8_rope_qkv.argtypes = [_p, _i64, _i64, _i64, _i64, _i64, _i64, C.c_double, _p, _i64, _p, _i64, _p, _p]
+        l.f8_rope_qk_bwd.argtypes = [_p, _i64, _p, _i64, _i64, _i64, _i64, _i64, _i64, C.c_double, _p, _i64, _p, _p]
         l.f8_transpose_bf16.argtypes = [_p, _i64, _i64, _i64, _p, _p]
         l.f8_add.argtypes = [_p, _p, _i64, _p, _p]
         l.f8_rmsnorm_bwd.argtypes = [_p, _p, _p, _p, _i64, _i64, _p, _p, _p, C.c_size_t, _p]
@@ -114,6 +116,8 @@ def lib():
         l.f8_sdpa_fwd.argtypes = [_p, _i64, _p, _i64, _p, _i64, _i64, _i64, _i64, _i64, _p, _i64, _p, _p, _p]
         l.f8_sdpa_bwd.argtypes = [_p, _i64, _p, _p, _i64, _p, _p, _i64, _p, _i64, _p, _i64, _p, _p, _i64, _i64, _i64, _i64,
                                   _i64, _p, _i64, _p, _i64, _p, _i64, _p, _p, _p, C.c_size_t, _p]
+        l.f8_sdpa_bwd_rows.argtypes = [_p, _i64, _p, _i64, _p, _i64, _p, _i64, _p, _i64, _p, _i64, _i64, _i64, _i64, _i64, _p, _i64, _p, _i64,
+                                       _p, _i64, _p, _p, _p, C.c_size_t, _p]
         l.f8_sdpa_bwd_workspace_bytes.argtypes = [_i64] * 5
         for name in EXPORTS[2:]:
             getattr(l, name).restype = _int
@@ -403,6 +407,18 @@ def rope(x, S, n_heads, hd, out=None, out_t=None, theta=500000.0, inverse=False,
                          out.stride(0) if out is not None else 0, _ptr(out_t), _ptr(amax_inout), _stream(stream)))
 
 
+def rope_qkv(qkv, S, Hq, Hkv, hd, q, k, vt, theta=500000.0, stream=None):
+    """q, k rotated and v transposed, from the fused q|k|v output."""
+    _check(lib().f8_rope_qkv(_ptr(qkv), qkv.stride(0), qkv.shape[0], S, Hq, Hkv, hd, float(theta), _ptr(q), q.stride(0), _ptr(k), k.stride(0),
+                             _ptr(vt), _stream(stream)))
+
+
+def rope_qk_bwd(dq, dk, S, Hq, Hkv, hd, dqkv, theta=500000.0, stream=None, amax_inout=None):
+    """dq, dk turned back into the first (Hq + Hkv) hd columns of dqkv."""
+    _check(lib().f8_rope_qk_bwd(_ptr(dq), dq.stride(0), _ptr(dk), dk.stride(0), dq.shape[0], S, Hq, Hkv, hd, float(theta), _ptr(dqkv),
+                                dqkv.stride(0), _ptr(amax_inout), _stream(stream)))
+
+
 def transpose_bf16(x, out_t, stream=None):
     _check(lib().f8_transpose_bf16(_ptr(x), x.stride(0), x.shape[0], x.shape[1], _ptr(out_t), _stream(stream)))
 
@@ -440,6 +456,14 @@ def sdpa_bwd(q, qt, k, kt, v, o, do, dot, lse, B, S, Hq, Hkv, hd, dq, dk, dv, de
                              _ptr(o), o.stride(0), _ptr(do), do.stride(0), _ptr(dot), _ptr(lse), B, S, Hq, Hkv, hd,
                              _ptr(dq), dq.stride(0), _ptr(dk), dk.stride(0), _ptr(dv), dv.stride(0), _ptr(delta),
                              _ptr(amax_dv_inout), wp, wb, _stream(stream)))
+
+
+def sdpa_bwd_rows(q, k, v, o, do, lse, B, S, Hq, Hkv, hd, dq, dk, dv, delta, workspace=None, stream=None, amax_dv_inout=None):
+    """sdpa_bwd without the transposed copies, which its kernels do not read."""
+    wp, wb = _ws(workspace)
+    _check(lib().f8_sdpa_bwd_rows(_ptr(q), q.stride(0), _ptr(k), k.stride(0), _ptr(v), v.stride(0), _ptr(o), o.stride(0), _ptr(do),
+                                  do.stride(0), _ptr(lse), B, S, Hq, Hkv, hd, _ptr(dq), dq.stride(0), _ptr(dk), dk.stride(0), _ptr(dv),
+                                  dv.stride(0), _ptr(delta), _ptr(amax_dv_inout), wp, wb, _stream(stream)))
 
 
 # ---- measuring helpers ---------------------------------------------------------------

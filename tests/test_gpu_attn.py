@@ -180,6 +180,10 @@ def test_sdpa_backward_gradients_over_k_and_v():
     f8.sdpa_bwd(a.q, t, k, t, v, a.o, do, t, a.lse, B, S, H, H, HD, dq, k, v, delta, None)
     torch.cuda.synchronize()
     assert torch.equal(torch.cat((dq, k, v), 1).view(torch.int16), dqkv.view(torch.int16))
+    dk, dv = torch.empty_like(k), torch.empty_like(v)   # and by the call without the transposed copies
+    f8.sdpa_bwd_rows(a.q, a.k, a.v, a.o, do, a.lse, B, S, H, H, HD, dq, dk, dv, delta)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat((dq, dk, dv), 1).view(torch.int16), dqkv.view(torch.int16))
 
 
 def test_sdpa_backward_peaked_scores():

@@ -241,3 +241,35 @@ def test_rmsnorm_backward_a_row_per_block(M, D):
     # as above: below 1e-5 of the terms' sum
     terms = dy.double() * x.double() * rstd.double()[:, None]
     assert bool(((dg.double() - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0) + 1e-30).all())
+
+
+# 72 tokens: a tile and a bit; hd 72: a tile and a bit of columns; 2048 x (16 + 2 x 4) heads: several heads a block (4),
+# and groups of heads that the key/value heads fill exactly, (5, 3): that neither fills.
+@pytest.mark.parametrize("M,S,Hq,Hkv,hd", [(8, 8, 1, 1, 8), (72, 24, 3, 1, 128), (136, 136, 2, 2, 72), (2048, 512, 16, 4, 128), (2048, 2048, 5, 3, 128)])
+def test_rope_of_fused_qkv_has_the_bits_of_separate_calls(M, S, Hq, Hkv, hd):
+    nq, nk = Hq * hd, Hkv * hd
+    qkv, E = gen((M, nq + 2 * nk), M + Hq).cuda(), lambda *shape: torch.full(shape, 3.0, dtype=torch.bfloat16, device="cuda")
+    q, k, v = qkv[:, :nq], qkv[:, nq:nq + nk], qkv[:, nq + nk:]
+    one, two = (E(M, nq), E(M, nk), E(nk, M)), (E(M, nq), E(M, nk), E(nk, M))
+    f8.rope_qkv(qkv, S, Hq, Hkv, hd, *one, theta=1e4)
+    f8.rope(q, S, Hq, hd, two[0], None, 1e4)
+    f8.rope(k, S, Hkv, hd, two[1], None, 1e4)
+    f8.transpose_bf16(v, two[2])
+    back, sep, cells = E(M, nq + 2 * nk), E(M, nq + 2 * nk), torch.zeros(2, device="cuda")
+    f8.rope_qk_bwd(one[0], one[1], S, Hq, Hkv, hd, back, 1e4, amax_inout=cells[0:1])
+    f8.rope(two[0], S, Hq, hd, sep[:, :nq], None, 1e4, True, amax_inout=cells[1:2])
+    f8.rope(two[1], S, Hkv, hd, sep[:, nq:nq + nk], None, 1e4, True, amax_inout=cells[1:2])
+    torch.cuda.synchronize()
+    for a, b in zip((*one, back), (*two, sep)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert cells[0].item() == cells[1].item() > 0
+    assert (back[:, nq + nk:] == 3.0).all()   # dv's columns are another call's
+
+
+def test_rope_of_fused_qkv_argument_errors():
+    x = torch.zeros((16, 64), dtype=torch.bfloat16, device="cuda")
+    for call in (lambda: f8.rope_qkv(x, 16, 2, 1, 32, x, x, x), lambda: f8.rope_qkv(x, 16, 0, 1, 16, x, x, x), lambda: f8.rope_qkv(x, 0, 2, 1, 16, x, x, x),
+                 lambda: f8.rope_qk_bwd(x, x, 16, 2, 1, 32, x), lambda: f8.rope_qk_bwd(x, x, 16, 2, 1, 12, x)):
+        with pytest.raises(f8.F8Error) as e:
+            call()
+        assert e.value.code == 2
