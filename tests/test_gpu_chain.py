@@ -167,6 +167,35 @@ def test_output_amax_does_not_change_the_backward(M, K, N, gfmt):
     assert torch.equal(dW.view(torch.int16), dW2.view(torch.int16))
 
 
+# X's cast and W's share a launch when X's amax is given: X the larger and the smaller one, less than a block, more blocks than
+# one wave of them; and one after the other where W's codes lie over X, or the amax in X's cell of the scale.
+@pytest.mark.parametrize("over", ["", "w codes over x", "amax in the scale's cell", "amax in its own cell"])
+@pytest.mark.parametrize("M,K,N", [(16, 16, 32), (1008, 528, 272), (272, 2064, 528), (4096, 4096, 512)])
+def test_given_amax_of_x_quantises_as_a_measured_one(M, K, N, over):
+    R = _spread(M + K + N)
+    X, W, dY = R(1.0, M, K), R(0.02, N, K), R(1e-3, M, N)
+    d, ws = f8.linear_desc(M, K, N), f8.new_workspace(max(M, K, N), max(M, K, N))
+    Y, dX, dW, Y2, dX2, dW2 = _bf((M, N)), _bf((M, K)), _bf((N, K)), _bf((M, N)), _bf((M, K)), _bf((N, K))
+    plain, given = f8.Saved(M, K, N), f8.Saved(M, K, N)
+    f8.linear_fwd(d, X, W, Y, plain, ws)
+    f8.linear_bwd(d, dY, plain, dX, dW, ws)
+    X2, a, b = X.clone(), plain.x.amax.clone(), plain.dy.amax.clone()
+    if over == "w codes over x":
+        given.w.q = X2.view(torch.uint8).view(-1)[:N * K].view(N, K)
+        given._struct = f8.SavedStruct(given.x.struct(), given.w.struct(), given.dy.struct())
+    elif over:
+        cells = (given.x.scale, given.dy.scale) if "scale" in over else (given.x.amax, given.dy.amax)
+        cells[0].copy_(a), cells[1].copy_(b)
+        a, b = cells
+    f8.linear_fwd_chained(d, X2, a, W, Y2, None, given, ws)
+    f8.linear_bwd_chained(d, dY, b, given, dX2, None, dW2, ws)
+    torch.cuda.synchronize()
+    for p, q in ((plain.x, given.x), (plain.w, given.w), (plain.dy, given.dy)):
+        assert torch.equal(p.q, q.q) and torch.equal(p.amax, q.amax) and torch.equal(p.scale, q.scale) and torch.equal(p.inv_scale, q.inv_scale)
+    for p, q in ((Y, Y2), (dX, dX2), (dW, dW2)):
+        assert torch.equal(p.view(torch.int16), q.view(torch.int16))
+
+
 def test_chained_argument_errors():
     t = torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda")
     ws = f8.new_workspace(64, 64)
