@@ -559,6 +559,63 @@ __global__ __launch_bounds__(kThreads) void cast_measure_stream_kernel(const Mea
     if (threadIdx.x == 0) J.partial[b] = m;
 }
 
+// The same for a tensor that is formed in registers from the feed-forward glue's inputs (see GLUE at cast_tile_kernel).  ab
+// [M, 2H] as 16-byte chunks, hc chunks to half a row; chunk c of h or dh is row c / hc.
+//   GLUE = 1: out [M, H] = codes of h;  GLUE = 2: out [M, 2H] = codes of [da | db].
+// Bound by memory: one front through each tensor, as in the gate kernels.  As 128 x 128 tiles, 1008 x 2816 is 176 blocks of
+// eight loads a thread; tiles / this in us with the history's launch: forward 128 x 2048 9.4 / 5.5, 1008 x 2816 11.7 / 8.9,
+// 2048 x 14336 39.1 / 32.5, 8192 x 14336 132 / 119; backward 12.2 / 5.9, 15.8 / 11.1, 58.6 / 45.6 and 201 / 190.
+// STREAM (from 8 M elements of h on): loads past the caches, two chunks side by side (through them 2048 x 14336 34.9 and
+// 51.7, and a block of 2048 tokens, 2048 / 8192 wide, 840 instead of 818).  The codes are read by the next call.
+constexpr int64_t kGlueStreamChunks = (int64_t)1 << 20;
+constexpr int kGlueStreamBlocks = 2048;  // (1024: 4096 x 8192 40.7 / 36.2 forward, 53.9 / 51.2 backward)
+static_assert((size_t)kGlueStreamBlocks * sizeof(uint32_t) <= kMinWorkspaceBytes && kGlueStreamChunks <= 2 * kThreads * kGlueStreamBlocks,
+              "one partial maximum per block");
+template <int FMT, int GLUE, bool STREAM, int CHUNKS = STREAM ? 2 : 1>
+__global__ __launch_bounds__(kThreads) void cast_glue_stream_kernel(const uint4* __restrict__ ab, const uint4* __restrict__ dh, int64_t n,
+                                                                   int64_t hc, const float* __restrict__ scale, uint2* __restrict__ out,
+                                                                   uint32_t* __restrict__ partial)
+{
+    __shared__ uint32_t red[kWaves];
+    const float s = scale[0];
+    uint32_t acc = 0;
+    const bool short_ids = (uint64_t)n >> 32 == 0;
+    auto load = [](const uint4* p) {
+        if constexpr (STREAM) return load_once(p);
+        else return *p;
+    };
+    for (int64_t c0 = (int64_t)blockIdx.x * (CHUNKS * kThreads) + threadIdx.x; c0 < n; c0 += (int64_t)gridDim.x * (CHUNKS * kThreads)) {
+        uint4 a[CHUNKS], b[CHUNKS], g[CHUNKS];
+        int64_t at[CHUNKS];  // of a; b's is hc further on
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) {
+            const int64_t c = c0 + u * kThreads < n ? c0 + u * kThreads : c0;
+            at[u] = c + (short_ids ? (int64_t)((uint32_t)c / (uint32_t)hc) : c / hc) * hc;
+            a[u] = load(ab + at[u]), b[u] = load(ab + at[u] + hc);
+            if constexpr (GLUE == 2) g[u] = load(dh + c);
+        }
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) {
+            if (c0 + u * kThreads >= n) break;
+            if constexpr (GLUE == 1) {
+                const uint4 h = make_uint4(silu_mul2(a[u].x, b[u].x), silu_mul2(a[u].y, b[u].y), silu_mul2(a[u].z, b[u].z), silu_mul2(a[u].w, b[u].w));
+                out[c0 + u * kThreads] = cast8<FMT>(h, s);
+                acc = absmax_acc(acc, h);
+            } else {
+                uint4 da, db;
+                silu_mul_bwd2(a[u].x, b[u].x, g[u].x, &da.x, &db.x);
+                silu_mul_bwd2(a[u].y, b[u].y, g[u].y, &da.y, &db.y);
+                silu_mul_bwd2(a[u].z, b[u].z, g[u].z, &da.z, &db.z);
+                silu_mul_bwd2(a[u].w, b[u].w, g[u].w, &da.w, &db.w);
+                out[at[u]] = cast8<FMT>(da, s), out[at[u] + hc] = cast8<FMT>(db, s);
+                acc = absmax_acc(absmax_acc(acc, da), db);
+            }
+        }
+    }
+    const uint32_t m = block_max_u32<kWaves>(pk_collapse(acc), red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = m;
+}
+
 // ---------------------------------------------------------------------------
 // cast, tiled form: 128 x 128 tile per block, writes out and/or out_t.
 // The transposed copy goes through LDS so that both global writes are made of
@@ -1094,8 +1151,16 @@ bool quantise_delayed_pair(const DelayedTensor& a, const DelayedTensor& b, int64
     return true;
 }
 
-// Tensorwise cast with a given scale that also leaves one partial maximum per 128x128 tile in
-// ws (checked tensor).  *npartial = number of partials written (0 for an empty tensor).
+// Blocks of cast_glue_stream_kernel.  Small tensors: two chunks a thread in turn, one while the blocks are few.
+static int64_t glue_blocks(int64_t n)
+{
+    if (n >= kGlueStreamChunks) return kGlueStreamBlocks;
+    const int64_t one = (n + kThreads - 1) / kThreads;
+    return one <= 256 ? one : (one + 1) / 2;
+}
+
+// Tensorwise cast with a given scale that also leaves one partial maximum per block (at most one per 128x128 tile, or
+// kGlueStreamBlocks) in ws (checked tensor).  *npartial = number of partials written (0 for an empty tensor).
 f8_status cast_measure(const void* x, int64_t rows, int64_t cols, int64_t ld, const float* scale, int fmt,
                        uint8_t* out, int64_t ld_out, uint8_t* out_t, int64_t ld_out_t, void* ws,
                        size_t ws_bytes, int* npartial, hipStream_t st, int glue, const void* x2)
@@ -1111,6 +1176,19 @@ f8_status cast_measure(const void* x, int64_t rows, int64_t cols, int64_t ld, co
         launch_measure(jobs, fmt, st);
         *npartial = jobs.j[0].blocks;
         return last_launch_status();
+    }
+    if (glue && out && !out_t && ld_out == cols) {
+        const int64_t hc = kcols / 8, n = rows * hc, blocks = glue_blocks(n);
+        if (blocks * (int64_t)sizeof(uint32_t) <= (int64_t)ws_bytes) {
+            const bool stream = n >= kGlueStreamChunks;
+#define F8_GLUE(F, G) (stream ? cast_glue_stream_kernel<F, G, true> : cast_glue_stream_kernel<F, G, false>)
+            const auto kernel = fmt == F8_E4M3 ? (glue == 1 ? F8_GLUE(F8_E4M3, 1) : F8_GLUE(F8_E4M3, 2))
+                                               : (glue == 1 ? F8_GLUE(F8_E5M2, 1) : F8_GLUE(F8_E5M2, 2));
+#undef F8_GLUE
+            kernel<<<(unsigned)blocks, kThreads, 0, st>>>((const uint4*)x, (const uint4*)x2, n, hc, scale, (uint2*)out, (uint32_t*)ws);
+            *npartial = (int)blocks;
+            return last_launch_status();
+        }
     }
 #define F8_LAUNCH_MEASURE_G(F, O, T, G)                                                                  \
     cast_tile_kernel<F, F8_TENSORWISE, false, O, T, true, G><<<(unsigned)nb, kThreads, 0, st>>>(         \

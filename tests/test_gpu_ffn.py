@@ -394,3 +394,26 @@ def test_fused_glue_backward_argument_checks():
     dW = torch.empty((2 * H, D), dtype=torch.bfloat16, device="cuda")
     with pytest.raises(f8.F8Error):
         f8.linear_bwd_dyq(rw, saved, dX, dW)
+
+
+# Less than a block; the last size with a chunk a thread (256 blocks) and the next; and from 8 M elements on two chunks side by
+# side, the last pair cut short (2064 x 4112 is 1036 chunks a row pair and a rest).
+@pytest.mark.parametrize("fmt", [f8.E4M3, f8.E5M2])
+@pytest.mark.parametrize("M,H", [(16, 16), (512, 1024), (528, 1024), (1008, 2800), (2048, 4096), (2064, 4112)])
+def test_streamed_glue_casts_equal_the_glue_and_a_cast(M, H, fmt):
+    g = torch.Generator("cuda")
+    g.manual_seed(M + H)
+    R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    ab, dh = R(1.5, M, 2 * H), R(1e-2, M, H)
+    ws, hist = f8.new_workspace(M, 2 * H), torch.zeros(3, device="cuda")
+    h, dab, amax = torch.empty_like(dh), torch.empty_like(ab), torch.empty(1, device="cuda")
+    for plain, fused, t, s0 in ((lambda: f8.silu_mul(ab, h, amax, ws), lambda q, sc: f8.silu_mul_quantise_delayed(ab, fmt, hist, sc, q, ws), h, 30.0),
+                                (lambda: f8.silu_mul_bwd(ab, dh, dab, amax, ws),
+                                 lambda q, sc: f8.silu_mul_bwd_quantise_delayed(ab, dh, fmt, hist, sc, q, ws), dab, 5000.0)):
+        plain()
+        used, sc, q = torch.full((1,), s0, device="cuda"), torch.full((1,), s0, device="cuda"), f8.QTensor(M, t.shape[1], False)
+        codes = torch.empty_like(q.q)
+        f8.cast(t, used, f8.TENSORWISE, fmt, codes)
+        fused(q, sc)
+        torch.cuda.synchronize()
+        assert torch.equal(codes, q.q) and torch.equal(amax, q.amax) and q.scale.item() == s0 and hist[0].item() == amax.item()
