@@ -288,3 +288,22 @@ def test_quantise_both_orientations(rows, cols, fmt):
     a, s, inv, codes = o.amax_cast(xb, o.COLWISE, fmt)
     assert np.array_equal(f32(q.amax_t), a) and np.array_equal(f32(q.scale_t), s) and np.array_equal(f32(q.inv_scale_t), inv)
     assert np.array_equal(u8(q.q_t), codes.T)
+
+
+# Row chunks of 64 rows: less than one, a rest, as many as there may be (64) and more rows than that; columns of less than a
+# strip of 128 and a rest; maxima at the first and last row and column of a chunk.
+@pytest.mark.parametrize("rows,cols", [(16, 16), (64, 112), (80, 144), (208, 1040), (4096, 128), (4176, 272)])
+def test_rowwise_maxima_of_chunks_and_strips(rows, cols):
+    g = torch.Generator("cuda")
+    g.manual_seed(rows + cols)
+    x = torch.randn((rows, cols), generator=g, device="cuda").to(torch.bfloat16)
+    for r in (0, 63, 64, rows - 1):
+        for c in (0, 127, 128, cols - 1):
+            if r < rows and c < cols:
+                x[r, c] = 50.0 + r % 7 + c % 5
+    q, ws, col = f8.QTensor(rows, cols, True), f8.new_workspace(rows, cols), torch.empty(cols, device="cuda")
+    f8.quantise(x, f8.ROWWISE, f8.E4M3, q, ws)
+    f8.amax(x, f8.COLWISE, col, ws)
+    torch.cuda.synchronize()
+    a = x.float().abs()
+    assert torch.equal(q.amax, a.amax(1)) and torch.equal(q.amax_t, a.amax(0)) and torch.equal(col, a.amax(0))
