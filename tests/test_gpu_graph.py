@@ -90,3 +90,12 @@ def test_captured_step_replays_like_eager(mode):
         rdX, rdW, dyq = o.linear_bwd(bits(batches[-1][2]), xq, wq)
         assert np.array_equal(u8(saved.x.q), xq.q) and f32(saved.dy.scale)[0] == dyq.scale[0]
         assert_gemm_close(bits(Y), rY), assert_gemm_close(bits(dX), rdX), assert_gemm_close(bits(dW), rdW)
+
+
+def test_calls_go_to_the_current_stream():
+    side = torch.cuda.Stream()
+    assert f8._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert f8._stream(side) == side.cuda_stream
+    with torch.cuda.stream(side):
+        assert f8._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+    assert f8._stream(None) == torch.cuda.default_stream().cuda_stream
