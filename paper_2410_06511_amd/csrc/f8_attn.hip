@@ -221,6 +221,55 @@ struct TokenFrags {
 // whether a tile of `rows` rows of pitch ld needs FAR
 static bool far_rows(int64_t rows, int64_t ld) { return 2 * (rows * ld + kHd) >= ((int64_t)1 << 32); }
 
+// A wave's 32 rows x 128 results (row ln, columns 32 d + 8 j + 4 g + r in acc[d][4 j + r]) to `out` (its first row), rows before
+// `rows` only.  From the registers a store would touch 32 rows with 8 bytes (16 in fp32) of each lane; through `stage`, 8 KB
+// of LDS of the wave's own that nobody reads any more, 16 lanes cover 256 bytes of a row.  A row's chunks are permuted by its
+// number: no bank conflicts.  The eight waves of a block end together, with nothing to hide the stores behind.  us of rope,
+// attention and its backward, straight / so (sequences x tokens, query / key heads): 2 x 512, 8 / 8 82 / 77, 4 x 1000, 16 / 16
+// 202.5 / 196.5, 2 x 2048, 32 / 8 461 / 451, 1 x 8192, 32 / 8 2436 / 2394.
+__device__ inline void store_rows(const f32x16 (&acc)[kHd / 32], float mul, uint16_t* stage, uint16_t* out, int64_t ld, int rows, int lane)
+{
+    const int ln = lane & 31, g = lane >> 5;
+#pragma unroll
+    for (int d = 0; d < kHd / 32; ++d)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<uint2*>(stage + ln * kHd + 8 * ((4 * d + j) ^ (ln & 15)) + 4 * g) =
+                make_uint2(pack2(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul), pack2(acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul));
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = 4 * i + lane / 16, c = lane % 16;
+        const uint4 v = *reinterpret_cast<const uint4*>(stage + row * kHd + 8 * (c ^ (row & 15)));
+        if (row < rows) *reinterpret_cast<uint4*>(out + row * ld + 8 * c) = v;
+    }
+    asm volatile("" ::: "memory");
+}
+__device__ inline void store_rows(const f32x16 (&acc)[kHd / 32], float mul, uint16_t* stage, float* out, int64_t ld, int rows, int lane)
+{
+    const int ln = lane & 31, g = lane >> 5;
+    float* st = reinterpret_cast<float*>(stage);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {  // 64 columns fit the stage
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x16& a = acc[2 * half + d];
+                *reinterpret_cast<float4*>(st + ln * 64 + 4 * ((8 * d + 2 * j + g) ^ (ln & 15))) =
+                    make_float4(a[4 * j] * mul, a[4 * j + 1] * mul, a[4 * j + 2] * mul, a[4 * j + 3] * mul);
+            }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int row = 4 * i + lane / 16, c = lane % 16;
+            const float4 v = *reinterpret_cast<const float4*>(st + row * 64 + 4 * (c ^ (row & 15)));
+            if (row < rows) *reinterpret_cast<float4*>(out + row * ld + 64 * half + 4 * c) = v;
+        }
+        asm volatile("" ::: "memory");
+    }
+}
+
 // ---- forward ------------------------------------------------------------------------------
 // One block: 8 waves of 32 queries each of one (sequence, head), loop over 64-key steps up to the
 // diagonal.  Two waves share a SIMD, and they work in opposite phases: while waves 0 .. 3 feed the matrix
@@ -652,17 +701,10 @@ __device__ __forceinline__ void sdpa_bwd_dq_work(const DqArgs& P, int qt, int bh
         if (t == t_last - 1) products(t_last, C16{});
     }
     if (!late) phase_barrier();
-
-    if (q_ok) {
-        uint16_t* row = dQ + tok * lddq + (int64_t)h * kHd + 4 * g;
-#pragma unroll
-        for (int d = 0; d < kHd / 32; ++d)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<uint2*>(row + 32 * d + 8 * j) =
-                    make_uint2(pack2(acc[d][4 * j] * scale, acc[d][4 * j + 1] * scale),
-                               pack2(acc[d][4 * j + 2] * scale, acc[d][4 * j + 3] * scale));
-    }
+    phase_barrier();  // after it nothing reads the tiles any more
+    int l64 = threadIdx.x & 63;  // (formed anew: what the stores are addressed by would be held over the loop)
+    asm volatile("" : "+v"(l64));
+    store_rows(acc, scale, &sK[0][0] + wave * 32 * kHd, dQ + (tok0 + q_first) * lddq + (int64_t)h * kHd, lddq, S - q_first, l64);
 }
 
 template <int NW, bool FAR>
@@ -888,32 +930,20 @@ __device__ __forceinline__ void sdpa_bwd_dkv_work(const DkvArgs& P, int kt, int 
         if (t == t_last - 1) products(t_last, C16{});
     }
     if (!late) phase_barrier();
-
-    if (!k_ok) return;
+    phase_barrier();  // after it nothing reads the tiles any more
+    uint16_t* stage = sV + wave * 32 * kHd;
+    const int rows = S - key_first;
+    int l64 = threadIdx.x & 63;  // (formed anew: what the stores are addressed by would be held over the loop)
+    asm volatile("" : "+v"(l64));
     if (group == 1) {
-        auto store = [&](const f32x16 (&acc)[kHd / 32], float mul, uint16_t* row) {
-#pragma unroll
-            for (int d = 0; d < kHd / 32; ++d)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    *reinterpret_cast<uint2*>(row + 32 * d + 8 * j) =
-                        make_uint2(pack2(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul), pack2(acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul));
-        };
-        store(acc_k, scale, dK + tok * lddk + (int64_t)kvh * kHd + 4 * g);
-        store(acc_v, 1.0f, dV + tok * lddv + (int64_t)kvh * kHd + 4 * g);
+        const int64_t first = tok0 + key_first, col = (int64_t)kvh * kHd;
+        store_rows(acc_k, scale, stage, dK + first * lddk + col, lddk, rows, l64);
+        store_rows(acc_v, 1.0f, stage, dV + first * lddv + col, lddv, rows, l64);
     } else {
         // this query head's share, fp32: [group][token][Hkv * hd]; summed in a fixed order afterwards
-        const int64_t w = (int64_t)(Hq / group) * kHd, at = ((int64_t)gi * M + tok) * w + (int64_t)kvh * kHd + 4 * g;
-        auto store = [&](const f32x16 (&acc)[kHd / 32], float mul, float* row) {
-#pragma unroll
-            for (int d = 0; d < kHd / 32; ++d)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    *reinterpret_cast<float4*>(row + 32 * d + 8 * j) =
-                        make_float4(acc[d][4 * j] * mul, acc[d][4 * j + 1] * mul, acc[d][4 * j + 2] * mul, acc[d][4 * j + 3] * mul);
-        };
-        store(acc_k, scale, part_k + at);
-        store(acc_v, 1.0f, part_v + at);
+        const int64_t w = (int64_t)(Hq / group) * kHd, at = ((int64_t)gi * M + tok0 + key_first) * w + (int64_t)kvh * kHd;
+        store_rows(acc_k, scale, stage, part_k + at, w, rows, l64);
+        store_rows(acc_v, 1.0f, stage, part_v + at, w, rows, l64);
     }
 }
 

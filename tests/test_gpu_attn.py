@@ -186,6 +186,27 @@ def test_sdpa_backward_gradients_over_k_and_v():
     assert torch.equal(torch.cat((dq, dk, dv), 1).view(torch.int16), dqkv.view(torch.int16))
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (2, 1)])
+@pytest.mark.parametrize("S", [8, 40, 232, 264])
+def test_sdpa_backward_writes_its_rows_and_columns_only(S, Hq, Hkv):
+    """The gradients between guard rows and columns, the heads' shares in a workspace with guard words behind it."""
+    B, M = 2, 2 * S
+    a = Attn(B, S, Hq, Hkv, seed=S)
+    a.forward()
+    do = gen((M, Hq * HD), S, 1e-2).cuda()
+    outs = [torch.full((M + 16, w * HD + 16), 7.0, dtype=torch.bfloat16, device="cuda") for w in (Hq, Hkv, Hkv)]
+    inner = [t[8:8 + M, 8:-8] for t in outs]
+    need = f8.sdpa_bwd_workspace_bytes(B, S, Hq, Hkv, HD)
+    ws, delta = torch.full((need + 64,), 7, dtype=torch.uint8, device="cuda"), torch.empty((Hq, M), device="cuda")
+    f8.sdpa_bwd_rows(a.q, a.k, a.v, a.o, do, a.lse, B, S, Hq, Hkv, HD, *inner, delta, ws[:need] if need else None)
+    dqkv, _ = run_backward(a, do.cpu())
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat(inner, 1).view(torch.int16), dqkv.view(torch.int16)) and (ws[need:] == 7).all()
+    for t in outs:
+        t[8:8 + M, 8:-8] = 7.0
+        assert (t == 7.0).all()
+
+
 def test_sdpa_backward_peaked_scores():
     """Scores of order ten (a softmax close to one-hot, where P (dP - delta) cancels strongly)."""
     B, S, Hq, Hkv = 2, 264, 4, 2
