@@ -108,13 +108,42 @@ static double alone_us(const PairSide& s, bool b_kmajor, bool may_split, size_t 
     return launch + quarter_us(ceil_div(tile_count(s, 128, 128), cus), s.K, 0.49, 2.5, 0.6);
 }
 
-#define F8_PAIR_NAME_(what, fa, g) gemm_pair_##what##fa##_##g
-#define F8_PAIR_NAME(what, fa, g) F8_PAIR_NAME_(what, fa, g)
-
 struct PairChoice {
     int tile;    // 64, 128, 192 (256 x 128) or 256; 0: two launches
     int x_xcds;  // XCDs that work on dX (not with 64)
 };
+
+// A second set of estimates, fitted to whole passes (forward, backward and casts, tensorwise) of 144 random linears, each in
+// one launch in every way and in two: within a pass a launch begins while the one before it ends, the epilogues of two 128 x 128
+// tiles on a unit hide behind each other, and the separate launches fare 0.81 times what they are above.  Beyond 64 K steps the
+// smaller tiles' workgroups drift apart and share less in the L2 (2048 x 4096 with 64 / 128 steps of 128 x 128 tiles: 0.8 / 1.33 us
+// a step).
+static double in_pass_us(const PairSide& x, const PairSide& w, PairChoice c, double separately, int cus)
+{
+    constexpr TileTime kFull{0.82, 5.3}, kHalf{0.56, 2.3}, kQuarter{0.435, 0.52}, kQuarterTwo{0.63, 1.46}, kSmall{0.265, 1.16};
+    if (!c.tile) return 0.81 * separately;
+    auto drifting = [](TileTime t, int k) {
+        const int steps = ksteps_of(k, 1);
+        return t.tile(k) + (steps > 64 ? 0.3 * (steps - 64) * t.step : 0.0);
+    };
+    if (c.tile == kSm) {
+        const double tx = kSmall.tile(x.K), tw = kSmall.tile(w.K), longest = tx > tw ? tx : tw;
+        const double work = (tile_count(x, kSm, kSm) * tx + tile_count(w, kSm, kSm) * tw) / cus + 0.15 * longest;
+        return 4.5 + (work > longest ? work : longest);
+    }
+    auto side_us = [&](const PairSide& s, int xcds) {
+        const int64_t units = (int64_t)(cus / kXcds) * xcds;
+        if (c.tile == 256) return ceil_div(tile_count(s, 256, 256), units) * kFull.tile(s.K);
+        if (c.tile == 192) return ceil_div(tile_count(s, 256, 128), units) * drifting(kHalf, s.K);
+        const int64_t n = ceil_div(tile_count(s, 128, 128), units);
+        return (double)(n / 2) * drifting(kQuarterTwo, s.K) + (double)(n % 2) * kQuarter.tile(s.K);
+    };
+    const double tx = side_us(x, c.x_xcds), tw = side_us(w, kXcds - c.x_xcds);
+    return (c.tile == 256 ? 5.3 : c.tile == 192 ? 3.0 : 3.5) + (tx > tw ? tx : tw);
+}
+
+#define F8_PAIR_NAME_(what, fa, g) gemm_pair_##what##fa##_##g
+#define F8_PAIR_NAME(what, fa, g) F8_PAIR_NAME_(what, fa, g)
 
 // One launch where it is estimated to be enough faster than the separate ones.  dX and dW have the same number of
 // operations, so an even division of the XCDs is mostly right (others are taken only for 3 % more); it is the rounds of
@@ -123,8 +152,8 @@ struct PairChoice {
 // in the mean (the best choice at hand each time: 1.157).  us of a backward, two launches / one: 256 x 512 x 1024 (tokens,
 // inputs, outputs) 15.4 / 12.7, 8192 x 4096 x 1024 101 / 78, 2000 x 4096 x 4096 72 / 67, 8192 x 4096 x 6144 354 / 322,
 // 16384 x 4096 x 14336 1459 / 1441.  The margin is 0.985 for the tiles that large separate launches have too, 0.95 for the
-// others (with less, 192 x 2176 x 11648 takes 1.09 times as long).  Where no round is saved there is nothing to gain: within
-// a whole step 8192 x 3584 x 8192 would be 1 % and rowwise 8192 x 16384 x 2048 3 % slower.
+// others (with less, 192 x 2176 x 11648 takes 1.09 times as long).  Where no round is saved there is little to gain: rowwise
+// 8192 x 16384 x 2048 would be 3 % slower.
 // An amax of dX (tensorwise scaling only) changes nothing in the rule: separately dW may be split, and its sums are then in
 // another order.
 PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, bool may_split, size_t ws_bytes, int cus)
@@ -168,7 +197,28 @@ PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, 
             if (us < best) best = us, c = PairChoice{t, xc};
         }
     }
-    return c;
+    // The estimates within a pass have the last word where the above stays with two launches (it takes no tiles below 256 x 256
+    // beyond two rounds of work, and knows no overlap), or where another way is faster by more than they may be off; up to five
+    // rounds of work, as far as they hold (512 x 15040 x 12800 rowwise by them 663 -> 827).  us of a pass before / after: 16384 x 2048 x
+    // 1024 176 / 149, 16384 x 4096 x 512 204 / 175, 11440 x 5568 x 512 219 / 189, 400 x 5632 x 5760 118 / 100, 8192 x 3584 x
+    // 8192 571 / 552, 448 x 3328 x 10752 rowwise 190 / 165, 4944 x 3328 x 2304 157 / 141, 5920 x 5312 x 320 123 / 107; two launches still: 1664 x 8896 x 6656 (333, in one
+    // 342), 16384 x 1024 x 1024 (116 / 122).
+    // Not for less than a tile's rows of tokens or outputs (160 x 12800 x 3584 109 -> 116), and of row-wise scaled products, whose row-major
+    // operands make both ways faster, only a clear gain (6256 x 7152 x 1024
+    // would take 299 instead of 287).
+    if (tile_count(x, 256, 256) + tile_count(w, 256, 256) > 5 * cus || M < 256 || N < 256) return c;
+    constexpr double kError = 8.0, kWorth = KM ? 0.97 : 0.86;
+    const double two = separately(4.5);
+    PairChoice in_pass = c;
+    best = c.tile ? in_pass_us(x, w, c, two, cus) - kError : in_pass_us(x, w, c, two, cus) * kWorth;
+    auto consider = [&](PairChoice k) {
+        const double us = in_pass_us(x, w, k, two, cus);
+        if (us < best) best = us, in_pass = k;
+    };
+    if (small <= 4 * cus) consider({kSm, 0});
+    for (int xc : {4, 3, 5})
+        for (int t : {256, 192, 128}) consider({t, xc});
+    return in_pass;
 }
 
 bool F8_PAIR_NAME(, F8_PAIR_FA, F8_PAIR_GRAN)(const GemmArgs& gx, const GemmArgs& gw, uint32_t* amax_bits, void* ws, size_t ws_bytes,

@@ -378,6 +378,20 @@ def test_backward_in_one_launch_has_the_bits_of_two(M, K, N, tile, x_xcds, rowwi
         assert torch.equal(dW.view(torch.int16), rW.view(torch.int16))
 
 
+# Ways that the estimates within a pass choose: instead of two launches, and instead of another tile.
+@pytest.mark.parametrize("rowwise", (False, True))
+@pytest.mark.parametrize("M,K,N,tile,x_xcds", [(400, 5632, 5760, 128, 3), (448, 3328, 10752, 128, 4), (1360, 13824, 320, 128, 5),
+                                               (5920, 5312, 320, 192, 5), (12000, 256, 7680, 128, 4)])
+def test_backward_by_the_estimates_within_a_pass(M, K, N, tile, x_xcds, rowwise):
+    test_backward_in_one_launch_has_the_bits_of_two(M, K, N, tile, x_xcds, rowwise)
+
+
+def test_estimates_within_a_pass_keep_to_their_range():
+    """Two launches as before: fewer than 256 tokens or outputs, more than five rounds of work; and where they are faster."""
+    for M, K, N in ((240, 12800, 3584), (7440, 4128, 224), (512, 15040, 12800), (1664, 8896, 6656), (16384, 1024, 1024)):
+        assert pair_choice(M, K, N, False) == (0, 0), (M, K, N)
+
+
 # one launch with 64x64, 128x128, 256x128 and 256x256 tiles
 @pytest.mark.parametrize("rowwise", (False, True))
 @pytest.mark.parametrize("M,K,N", [(256, 512, 1024), (1008, 1024, 1536), (1040, 2064, 2064), (2000, 4096, 4096)])
