@@ -1322,10 +1322,10 @@ f8_status quantise_known_amax(const void* x, int64_t rows, int64_t cols, int64_t
                               out, ld_out, out_t, ld_out_t, st);
 }
 
-// A forward's X, whose amax is known, and W: the amax of W in one launch, both casts in another.  false: nothing enqueued,
-// one after the other then.
+// A forward's X, whose amax is known, and W: the amax of W in one launch, both casts in another, *status whether they were
+// taken.  false: nothing enqueued, one after the other then.
 bool quantise_known_pair(const void* x0, int64_t rows0, int64_t cols0, const float* known, const f8_qtensor* q0, const void* x1, int64_t rows1,
-                         int64_t cols1, const f8_qtensor* q1, int fmt, void* ws, hipStream_t st)
+                         int64_t cols1, const f8_qtensor* q1, int fmt, void* ws, hipStream_t st, f8_status* status)
 {
     if (!streamable(rows0, cols0, cols0, cols0, q0->q, q0->q_t) || !streamable(rows1, cols1, cols1, cols1, q1->q, q1->q_t)) return false;
     const StreamTensor a{x0, rows0 * cols0, q0->amax, q0->scale, q0->inv_scale, q0->q, known}, b{x1, rows1 * cols1, q1->amax, q1->scale, q1->inv_scale, q1->q};
@@ -1337,8 +1337,7 @@ bool quantise_known_pair(const void* x0, int64_t rows0, int64_t cols0, const flo
     for (int i = 0; i < 6; ++i)
         for (int j = 0; j < 6; ++j)
             if (!(i < 2 && j == 0) && !apart(of_a[i], of_b[j])) return false;
-    if (a.n >= b.n) quantise_stream(a, &b, fmt, ws, st);
-    else quantise_stream(b, &a, fmt, ws, st);
+    *status = a.n >= b.n ? quantise_stream(a, &b, fmt, ws, st) : quantise_stream(b, &a, fmt, ws, st);
     return true;
 }
 

@@ -71,10 +71,11 @@ f8_status quantise_known_amax(const void* x, int64_t rows, int64_t cols, int64_t
                               float* amax_out, float* scale_out, float* inv_out, uint8_t* out, int64_t ld_out,
                               uint8_t* out_t, int64_t ld_out_t, hipStream_t st);
 
-// The same for a forward's X together with its W (whose amax is taken): true if both have been enqueued (contiguous, no
-// transposed copies, nothing of the one over the other).  ws: kMinWorkspaceBytes.
+// The same for a forward's X together with its W (whose amax is taken): false if they cannot share their launches (not
+// contiguous, transposed copies, something of the one over the other): nothing is enqueued then.  Else *status is that of the
+// launches, whose error has been read.  ws: kMinWorkspaceBytes.
 bool quantise_known_pair(const void* x0, int64_t rows0, int64_t cols0, const float* known, const f8_qtensor* q0, const void* x1, int64_t rows1,
-                         int64_t cols1, const f8_qtensor* q1, int fmt, void* ws, hipStream_t st);
+                         int64_t cols1, const f8_qtensor* q1, int fmt, void* ws, hipStream_t st, f8_status* status);
 
 // Validated GEMM launch (see f8_gemm); amax_d may be null.  ws (nullable): device scratch of
 // ws_bytes for the fp32 partial results of a product that is better split along its

@@ -381,8 +381,8 @@ f8_status f8_linear_fwd_chained(const f8_linear_desc* d, const void* X, const fl
     if (s != F8_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     const int64_t M = d->M, K = d->K, N = d->N;
-    if (x_amax && quantise_known_pair(X, M, K, x_amax, &saved->x, W, N, K, &saved->w, F8_E4M3, workspace, st)) {
-        s = last_launch_status();
+    if (x_amax && quantise_known_pair(X, M, K, x_amax, &saved->x, W, N, K, &saved->w, F8_E4M3, workspace, st, &s)) {
+        // (s is theirs)
     } else if (x_amax) {
         s = quantise_known_amax(X, M, K, K, F8_E4M3, x_amax, saved->x.amax, saved->x.scale, saved->x.inv_scale,
                                 saved->x.q, K, saved->x.q_t, M, st);
