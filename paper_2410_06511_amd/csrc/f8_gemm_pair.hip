@@ -114,10 +114,12 @@ struct PairChoice {
 };
 
 // A second set of estimates, fitted to whole passes (forward, backward and casts, tensorwise) of 144 random linears, each in
-// one launch in every way and in two: within a pass a launch begins while the one before it ends, the epilogues of two 128 x 128
-// tiles on a unit hide behind each other, and the separate launches fare 0.81 times what they are above.  Beyond 64 K steps the
-// smaller tiles' workgroups drift apart and share less in the L2 (2048 x 4096 with 64 / 128 steps of 128 x 128 tiles: 0.8 / 1.33 us
-// a step).
+// one launch in every way and in two: within a pass a launch begins while the one before it ends, the epilogues of two 128 x
+// 128 tiles on a unit hide behind each other, and the separate launches fare 0.81 times what they are above.  They rank the
+// ways and are no times of a kernel: large products take longer under the lowered clock (8192 x 3584 x 8192 in one launch
+// 236 us by them, 375 in a trace), and a K step of 256 x 256 tiles is less here than the matrix pipe's 0.85 us, the rest of
+// it in other terms.  Beyond 64 K steps the smaller tiles' workgroups drift apart and share less in the L2 (2048 x 4096 with
+// 64 / 128 steps of 128 x 128 tiles: 0.8 / 1.33 us a step).
 static double in_pass_us(const PairSide& x, const PairSide& w, PairChoice c, double separately, int cus)
 {
     constexpr TileTime kFull{0.82, 5.3}, kHalf{0.56, 2.3}, kQuarter{0.435, 0.52}, kQuarterTwo{0.63, 1.46}, kSmall{0.265, 1.16};
@@ -197,27 +199,35 @@ PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, 
             if (us < best) best = us, c = PairChoice{t, xc};
         }
     }
-    // The estimates within a pass have the last word where the above stays with two launches (it takes no tiles below 256 x 256
-    // beyond two rounds of work, and knows no overlap), or where another way is faster by more than they may be off; up to five
-    // rounds of work, as far as they hold (512 x 15040 x 12800 rowwise by them 663 -> 827).  us of a pass before / after: 16384 x 2048 x
-    // 1024 176 / 149, 16384 x 4096 x 512 204 / 175, 11440 x 5568 x 512 219 / 189, 400 x 5632 x 5760 118 / 100, 8192 x 3584 x
-    // 8192 571 / 552, 448 x 3328 x 10752 rowwise 190 / 165, 4944 x 3328 x 2304 157 / 141, 5920 x 5312 x 320 123 / 107; two launches still: 1664 x 8896 x 6656 (333, in one
-    // 342), 16384 x 1024 x 1024 (116 / 122).
-    // Not for less than a tile's rows of tokens or outputs (160 x 12800 x 3584 109 -> 116), and of row-wise scaled products, whose row-major
-    // operands make both ways faster, only a clear gain (6256 x 7152 x 1024
-    // would take 299 instead of 287).
-    if (tile_count(x, 256, 256) + tile_count(w, 256, 256) > 5 * cus || M < 256 || N < 256) return c;
-    constexpr double kError = 8.0, kWorth = KM ? 0.97 : 0.86;
-    const double two = separately(4.5);
+    // The estimates within a pass have the last word where the above stays with two launches (it takes no tiles below 256 x
+    // 256 beyond two rounds of work, and knows no overlap), and choose between the ways of one launch, where they see a
+    // clear gain; up to five rounds of work, as far as they hold (512 x 15040 x 12800 rowwise by them 663 -> 827), and not
+    // for less than a tile's rows of tokens or outputs (160 x 12800 x 3584 109 -> 116).  How clear, by 940 random passes in
+    // the ways that the two sets rank first and 160 of row-wise scaled products of more than three rounds.  Tensorwise,
+    // predicted 0.9 times two launches or less: measured 0.90 in the mean, at most 1.03; 0.9 .. 0.97: 0.985, up to 1.10
+    // (3008 x 2928 x 4528 167 -> 184).  Another tile than the first set's: below 0.85 0.94, at most 1.02, and for 8 us at
+    // least.  Rowwise, more than three rounds, smaller tiles: where dX has more of them 0.98, up to 1.12; where dW has, 0.93
+    // and at most 1.01 if predicted below 0.8, up to 1.06 above.  400 further passes in which this rule changes the choice:
+    // 0.91 tensorwise and 0.93 rowwise, three of them slower by more than 2 % (the worst 4.6 %).  us of a pass, before /
+    // after: 16384 x 2048 x 1024 173 / 153, 16384 x 4096 x 512 205 / 180, 11440 x 5568 x 512 207 / 182, 400 x 5632 x 5760
+    // 119 / 103, 448 x 3328 x 10752 rowwise 188 / 162, 5920 x 5312 x 320 124 / 108; two launches still: 1664 x 8896 x 6656,
+    // 16384 x 1024 x 1024, 8192 x 3584 x 8192 (in one the same).
+    const int64_t full_x = tile_count(x, 256, 256), full_w = tile_count(w, 256, 256), full = full_x + full_w;
+    if (full > 5 * cus || M < 256 || N < 256) return c;
+    const bool many_rows = !KM && full > 3 * cus;
+    constexpr double kLeast = 8.0, kOverOne = KM ? 0.85 : 0.80;
+    const double over_two = KM ? 0.90 : many_rows ? 0.80 : 0.86;
+    const double two = separately(4.5), first = in_pass_us(x, w, c, two, cus);
     PairChoice in_pass = c;
-    best = c.tile ? in_pass_us(x, w, c, two, cus) - kError : in_pass_us(x, w, c, two, cus) * kWorth;
+    best = !c.tile ? first * over_two : first * kOverOne < first - kLeast ? first * kOverOne : first - kLeast;
     auto consider = [&](PairChoice k) {
         const double us = in_pass_us(x, w, k, two, cus);
         if (us < best) best = us, in_pass = k;
     };
     if (small <= 4 * cus) consider({kSm, 0});
     for (int xc : {4, 3, 5})
-        for (int t : {256, 192, 128}) consider({t, xc});
+        for (int t : {256, 192, 128})
+            if (t == 256 || c.tile || !many_rows || full_w > full_x) consider({t, xc});
     return in_pass;
 }
 
