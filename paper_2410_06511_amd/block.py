@@ -13,6 +13,8 @@ of its own.  scaling="delayed": every scale comes from the amax history of earli
 cast is a single pass, and the feed-forward glue is fused into the casts of its consumers (h and
 dAB are never written).
 """
+from functools import cached_property
+
 import torch
 
 from . import f8
@@ -45,7 +47,7 @@ class TransformerBlock:
         self.xn, self.rstd1, self.a_xn = E(M, D), torch.empty(M, **f32), torch.empty(1, **f32)
         self.qkv = E(M, self.Nqkv)
         self.qr, self.kr = E(M, Hq * hd), E(M, Hkv * hd)                 # rotated q, k
-        self.qt, self.kt, self.vt = E(Hq * hd, M), E(Hkv * hd, M), E(Hkv * hd, M)   # (qt, kt: separate stages only)
+        self.vt = E(Hkv * hd, M)
         self.att, self.lse, self.a_att = E(M, D), torch.empty((Hq, M), **f32), torch.empty(1, **f32)
         self.yo, self.h1 = E(M, D), E(M, D)
         self.hn, self.rstd2, self.a_hn = E(M, D), torch.empty(M, **f32), torch.empty(1, **f32)
@@ -54,7 +56,7 @@ class TransformerBlock:
         # backward
         self.dhh, self.dab, self.a_dab = E(M, H), E(M, 2 * H), torch.empty(1, **f32)
         self.dhn, self.dh1 = E(M, D), E(M, D)
-        self.datt, self.datt_t = E(M, D), E(D, M)   # (datt_t: separate stages only)
+        self.datt = E(M, D)
         self.dqr, self.dkr, self.delta = E(M, Hq * hd), E(M, Hkv * hd), torch.empty((Hq, M), **f32)
         self.att_ws = torch.empty(max(16, f8.sdpa_bwd_workspace_bytes(B, S, Hq, Hkv, hd)), dtype=torch.uint8, device=device)
         self.dqkv = E(M, self.Nqkv)
@@ -63,6 +65,20 @@ class TransformerBlock:
         self.dg1, self.dg2 = torch.empty(D, **f32), torch.empty(D, **f32)
         self.dWqkv, self.dWo = E(self.Nqkv, D), E(D, D)
         self.dW13, self.dW2 = E(2 * H, D), E(D, H)
+
+    # Transposed copies of q, k and the attention's gradient: only the separate stages write and hand on these, so they take
+    # memory (144 MiB of an 8B block at 8192 tokens) from the first use of those on.
+    @cached_property
+    def qt(self):
+        return self.qr.new_empty((self.Hq * self.hd, self.M))
+
+    @cached_property
+    def kt(self):
+        return self.kr.new_empty((self.Hkv * self.hd, self.M))
+
+    @cached_property
+    def datt_t(self):
+        return self.datt.new_empty((self.D, self.M))
 
     def _slices(self, t):
         Hq, Hkv, hd = self.Hq, self.Hkv, self.hd
@@ -80,13 +96,15 @@ class TransformerBlock:
         Hq, Hkv, hd = self.Hq, self.Hkv, self.hd
         q, k, v = self._slices(self.qkv)
         att_flops = 4 * B * S * S * Hq * hd // 2
-        rope = [
-            ("rope q (+ transposed copy)", lambda: f8.rope(q, S, Hq, hd, s.qr, s.qt, s.theta, False, stream), 0, 6 * M * Hq * hd),
-            ("rope k (+ transposed copy)", lambda: f8.rope(k, S, Hkv, hd, s.kr, s.kt, s.theta, False, stream), 0, 6 * M * Hkv * hd),
-            ("transpose v", lambda: f8.transpose_bf16(v, s.vt, stream), 0, 4 * M * Hkv * hd),
-        ]
         if joined:
             rope = [("rope q, k; transpose v", lambda: f8.rope_qkv(s.qkv, S, Hq, Hkv, hd, s.qr, s.kr, s.vt, s.theta, stream), 0, 4 * M * s.Nqkv)]
+        else:
+            qt, kt = s.qt, s.kt
+            rope = [
+                ("rope q (+ transposed copy)", lambda: f8.rope(q, S, Hq, hd, s.qr, qt, s.theta, False, stream), 0, 6 * M * Hq * hd),
+                ("rope k (+ transposed copy)", lambda: f8.rope(k, S, Hkv, hd, s.kr, kt, s.theta, False, stream), 0, 6 * M * Hkv * hd),
+                ("transpose v", lambda: f8.transpose_bf16(v, s.vt, stream), 0, 4 * M * Hkv * hd),
+            ]
         if self.delayed and replay:
             if self._replay is None:
                 self._replay = tuple(f8.ReplayState(sv) for sv in (s.s_qkv, s.s_o, s.s_13, s.s_2))
@@ -180,20 +198,22 @@ class TransformerBlock:
                 with torch.cuda.stream(stream):
                     s.a_bwd.zero_()
 
-        attention = [
-            ("transpose dO", lambda: f8.transpose_bf16(s.datt, s.datt_t, stream), 0, 4 * M * D),
-            ("attention bwd", lambda: f8.sdpa_bwd(s.qr, s.qt, s.kr, s.kt, v, s.att, s.datt, s.datt_t, s.lse, B, S, Hq, Hkv, hd,
-                                                  s.dqr, s.dkr, dv, s.delta, s.att_ws, stream, a_dqkv),
-             5 * att_flops // 2, 0),
-            ("rope q bwd", lambda: f8.rope(s.dqr, S, Hq, hd, dq, None, s.theta, True, stream, a_dqkv), 0, 4 * M * Hq * hd),
-            ("rope k bwd", lambda: f8.rope(s.dkr, S, Hkv, hd, dk, None, s.theta, True, stream, a_dqkv), 0, 4 * M * Hkv * hd),
-        ]
         if joined:
             attention = [
                 ("attention bwd", lambda: f8.sdpa_bwd_rows(s.qr, s.kr, v, s.att, s.datt, s.lse, B, S, Hq, Hkv, hd, s.dqr, s.dkr, dv, s.delta,
                                                            s.att_ws, stream, a_dqkv), 5 * att_flops // 2, 0),
                 ("rope q, k bwd", lambda: f8.rope_qk_bwd(s.dqr, s.dkr, S, Hq, Hkv, hd, s.dqkv, s.theta, stream, a_dqkv), 0,
                  4 * M * (Hq + Hkv) * hd),
+            ]
+        else:
+            qt, kt, datt_t = s.qt, s.kt, s.datt_t
+            attention = [
+                ("transpose dO", lambda: f8.transpose_bf16(s.datt, datt_t, stream), 0, 4 * M * D),
+                ("attention bwd", lambda: f8.sdpa_bwd(s.qr, qt, s.kr, kt, v, s.att, s.datt, datt_t, s.lse, B, S, Hq, Hkv, hd,
+                                                      s.dqr, s.dkr, dv, s.delta, s.att_ws, stream, a_dqkv),
+                 5 * att_flops // 2, 0),
+                ("rope q bwd", lambda: f8.rope(s.dqr, S, Hq, hd, dq, None, s.theta, True, stream, a_dqkv), 0, 4 * M * Hq * hd),
+                ("rope k bwd", lambda: f8.rope(s.dkr, S, Hkv, hd, dk, None, s.theta, True, stream, a_dqkv), 0, 4 * M * Hkv * hd),
             ]
         return [("zero the amax cells", zero_amax, 0, 0)] + ffn + [
             ("rmsnorm 2 bwd + residual", lambda: f8.rmsnorm_bwd_add(s.h1, w["g2"], s.rstd2, s.dhn, dout, s.dh1, s.dg2, s.ws, stream, a_dh1),

@@ -245,3 +245,21 @@ def test_delayed_scaling_recomputed_forward_reproduces_the_first():
         for a, b in zip((kept.st_qkv, kept.st_o, kept.st_13, kept.st_2), (redo.st_qkv, redo.st_o, redo.st_13, redo.st_2)):
             for m in ("hist_x", "hist_w", "hist_dy", "scale_x", "scale_w", "scale_dy"):
                 assert torch.equal(getattr(a, m), getattr(b, m)), m
+
+
+def test_copies_of_the_separate_stages_take_no_memory_before_their_use():
+    B, S, Hq, Hkv, hd, H = 1, 128, 2, 1, 128, 256
+    D, M = Hq * hd, B * S
+    x, dout = gen((M, D), 61).cuda(), gen((M, D), 62, 1e-2).cuda()
+    w = {"g1": torch.ones(D, dtype=torch.bfloat16, device="cuda"), "g2": torch.ones(D, dtype=torch.bfloat16, device="cuda"),
+         "Wqkv": gen(((Hq + 2 * Hkv) * hd, D), 63, 0.05).cuda(), "Wo": gen((D, D), 64, 0.05).cuda(),
+         "W13": gen((2 * H, D), 65, 0.05).cuda(), "W2": gen((D, H), 66, 0.05).cuda()}
+    blk = TransformerBlock(B, S, D, H, Hq, Hkv, hd)
+    copies = ("qt", "kt", "datt_t")
+    for recompute in (False, True, "selective"):
+        blk.forward(x, w)
+        blk.backward(x, w, dout, recompute=recompute)
+    assert not any(n in vars(blk) for n in copies)
+    blk.forward_stages(x, w), blk.backward_stages(x, w, dout)
+    assert [tuple(vars(blk)[n].shape) for n in copies] == [(Hq * hd, M), (Hkv * hd, M), (D, M)]
+    assert all(vars(blk)[n] is getattr(blk, n) for n in copies)
