@@ -83,6 +83,7 @@ WRITES = {
     "linear w2 bwd": ["dhh", "dW2"], "silu_mul bwd": ["dab", "a_dab"], "linear w1|w3 bwd": ["dhn", "dW13"],
     "rmsnorm 2 bwd + residual": ["dh1", "dg2"], "linear wo bwd": ["datt", "dWo"],
     "transpose dO": ["datt_t"], "attention bwd": ["dqr", "dkr"], "rope q bwd": [], "rope k bwd": [],
+    "rope q, k; transpose v": ["qr", "kr", "vt"], "rope q, k bwd": [],
     "linear wq|wk|wv bwd": ["dxn", "dWqkv"], "rmsnorm 1 bwd + residual": ["dx", "dg1"],
 }
 EXACT = {"vt", "datt_t"}                      # copies of a tensor that the oracle's has replaced
@@ -112,7 +113,9 @@ def compare_then_replace(blk, ref, names, stage):
             t.copy_(torch.from_numpy(np.asarray(ref[n], dtype=np.float32).reshape(t.shape)))
 
 
-def test_transformer_block_stage_by_stage():
+@pytest.mark.parametrize("joined", (False, True))
+def test_transformer_block_stage_by_stage(joined):
+    """joined: the stages that forward() and backward() run."""
     B, S, Hq, Hkv, hd, H, eps = 2, 136, 4, 2, 128, 768, 1e-5
     D, M = Hq * hd, B * S
     x, dout = gen((M, D), 1), gen((M, D), 2, 1e-2)
@@ -122,7 +125,7 @@ def test_transformer_block_stage_by_stage():
     ref = oracle_block(bits(x), {k: bits(v) for k, v in w.items()}, bits(dout), B, S, Hq, Hkv, hd, eps)
     blk = TransformerBlock(B, S, D, H, Hq, Hkv, hd, eps)
     xd, dd, wd = x.cuda(), dout.cuda(), {k: v.cuda() for k, v in w.items()}
-    for name, call, _, _ in blk.forward_stages(xd, wd) + blk.backward_stages(xd, wd, dd):
+    for name, call, _, _ in blk.forward_stages(xd, wd, joined=joined) + blk.backward_stages(xd, wd, dd, joined=joined):
         call()
         torch.cuda.synchronize()
         if name == "rmsnorm 2 bwd + residual":
@@ -140,7 +143,7 @@ def test_transformer_block_stage_by_stage():
             # dv is written straight into its slice of dqkv; dq, dk get there through the inverse rope
             nq, nk = Hq * hd, Hkv * hd
             close(bits(blk.dqkv)[:, nq + nk:], ref["dqkv"][:, nq + nk:], "attention bwd: dv")
-        if name == "rope k bwd":
+        if name == ("rope q, k bwd" if joined else "rope k bwd"):
             close(bits(blk.dqkv), ref["dqkv"], "dqkv assembled")
             # all three producers (inverse rope of dq and dk, the summed dv) have raised the amax cell
             assert blk.a_bwd[1].item() == o.amax(bits(blk.dqkv))[0]
@@ -149,9 +152,8 @@ def test_transformer_block_stage_by_stage():
 
 
 def test_transformer_block_end_to_end_and_recompute():
-    """The chain run straight through gives the same bits as stage by stage on its own tensors, and
-    the backward after a recomputed forward (full activation checkpointing) gives the same bits
-    as the backward after the kept forward."""
+    """The backward after a recomputed forward (full activation checkpointing, and the cheap stages alone)
+    gives the same bits as the backward after the kept forward."""
     B, S, Hq, Hkv, hd, H = 1, 272, 2, 1, 128, 512
     D, M = Hq * hd, B * S
     x, dout = gen((M, D), 11).cuda(), gen((M, D), 12, 1e-2).cuda()
@@ -263,3 +265,29 @@ def test_copies_of_the_separate_stages_take_no_memory_before_their_use():
     blk.forward_stages(x, w), blk.backward_stages(x, w, dout)
     assert [tuple(vars(blk)[n].shape) for n in copies] == [(Hq * hd, M), (Hkv * hd, M), (D, M)]
     assert all(vars(blk)[n] is getattr(blk, n) for n in copies)
+
+
+# grouped and equal heads (an amax of dqkv from its producers, or none), one sequence and two; 2048 tokens: dQ and dK/dV in a launch each
+@pytest.mark.parametrize("scaling", ("dynamic", "delayed"))
+@pytest.mark.parametrize("B,S,Hq,Hkv", [(1, 272, 2, 1), (2, 136, 2, 2), (2, 2048, 32, 8)])
+def test_joined_stages_have_the_bits_of_the_separate_ones(B, S, Hq, Hkv, scaling):
+    """forward() and backward(), which join the calls around the attention, against every stage on its own: two steps on
+    changing inputs, everything that both write."""
+    hd, H = 128, 512
+    D, M = Hq * hd, B * S
+    w = {"g1": (gen((D,), 73, 0.3) + 1).bfloat16().cuda(), "g2": (gen((D,), 74, 0.3) + 1).bfloat16().cuda(),
+         "Wqkv": gen(((Hq + 2 * Hkv) * hd, D), 75, 0.05).cuda(), "Wo": gen((D, D), 76, 0.05).cuda(),
+         "W13": gen((2 * H, D), 77, 0.05).cuda(), "W2": gen((D, H), 78, 0.05).cuda()}
+    one, each = (TransformerBlock(B, S, D, H, Hq, Hkv, hd, scaling=scaling, history_len=3) for _ in range(2))
+    names = ("xn", "qkv", "qr", "kr", "vt", "att", "lse", "h1", "hn", "ab", "out", "datt", "dqr", "dkr", "dqkv", "dxn", "dx", "a_bwd",
+             "dWqkv", "dWo", "dW13", "dW2", "dg1", "dg2")
+    for step in range(2):
+        x, dout = gen((M, D), 80 + step, 1.0 + step).cuda(), gen((M, D), 90 + step, 1e-2).cuda()
+        one.forward(x, w)
+        one.backward(x, w, dout)
+        for _, call, _, _ in each.forward_stages(x, w) + each.backward_stages(x, w, dout):
+            call()
+        torch.cuda.synchronize()
+        for n in names:
+            assert torch.equal(getattr(one, n).view(torch.uint8), getattr(each, n).view(torch.uint8)), (step, n)
+        assert torch.isfinite(one.out.float()).all() and torch.isfinite(one.dx.float()).all()
