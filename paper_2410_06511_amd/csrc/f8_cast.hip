@@ -648,8 +648,8 @@ __device__ inline void transpose4x4(const uint32_t r[4], uint32_t c[4])
 // MEASURE (delayed scaling): the scale is given, and the block also writes the largest
 // magnitude of its own tile to partial_out[blockIdx.x], so that the tensor's amax of this step
 // comes out of the same single pass over x.
-// GLUE (with MEASURE): the tensor that is cast is formed in registers from the feed-forward glue's
-// inputs and never written itself.
+// GLUE (with MEASURE, OUT and OUT_T; without OUT_T see cast_glue_stream_kernel): the tensor that is cast is formed in
+// registers from the feed-forward glue's inputs and never written itself.
 //   GLUE = 1: x = [a | b], [rows, 2 * cols] with ld = its row length; cast h = bf16(silu(a) * b).
 //   GLUE = 2: x = [a | b] as above, x2 = dh [rows, cols]; cast dab = [bf16(dh * b * silu'(a)) |
 //             bf16(dh * silu(a))], [rows, 2 * cols]: a block reads its tile of a, b and dh once and
@@ -663,6 +663,7 @@ __global__ __launch_bounds__(kThreads) void cast_tile_kernel(
     int tiles_c, uint32_t* __restrict__ partial_out = nullptr, const float* __restrict__ scale_col = nullptr,
     const uint16_t* __restrict__ x2 = nullptr)
 {
+    static_assert(GLUE == 0 || (MEASURE && OUT && OUT_T), "a streamed cast otherwise");
     __shared__ uint32_t red[kWaves];
     __shared__ uint32_t tile[kTile * kLdsStride];
 
@@ -792,7 +793,7 @@ __global__ __launch_bounds__(kThreads) void cast_tile_kernel(
     };
     emit(v, 0);
     if constexpr (GLUE == 2) {
-        if constexpr (OUT_T) __syncthreads();  // the tile in LDS has been read before it is rewritten
+        __syncthreads();  // the tile in LDS has been read before it is rewritten
         emit(v2, cols);
     }
     if constexpr (MEASURE) {
@@ -1175,8 +1176,8 @@ static int64_t glue_blocks(int64_t n)
     return one <= 256 ? one : (one + 1) / 2;
 }
 
-// Tensorwise cast with a given scale that also leaves one partial maximum per block (at most one per 128x128 tile, or
-// kGlueStreamBlocks) in ws (checked tensor).  *npartial = number of partials written (0 for an empty tensor).
+// Tensorwise cast with a given scale that also leaves one partial maximum per block in ws (checked tensor).  *npartial = number
+// of partials written (0 for an empty tensor).  The glue's tensors always come with `out`, contiguous.
 f8_status cast_measure(const void* x, int64_t rows, int64_t cols, int64_t ld, const float* scale, int fmt,
                        uint8_t* out, int64_t ld_out, uint8_t* out_t, int64_t ld_out_t, void* ws,
                        size_t ws_bytes, int* npartial, hipStream_t st, int glue, const void* x2)
@@ -1189,44 +1190,39 @@ f8_status cast_measure(const void* x, int64_t rows, int64_t cols, int64_t ld, co
     if (nb > (int64_t)0x7FFFFFFF || (size_t)nb * sizeof(uint32_t) > ws_bytes) return F8_ERR_WORKSPACE;
     if (glue == 0 && streamable(rows, cols, ld, ld_out, out, out_t)) {
         const MeasureJobs jobs{{measure_job(x, rows, cols, scale, out, (uint32_t*)ws), {}}};
+        if ((size_t)jobs.j[0].blocks * sizeof(uint32_t) > ws_bytes) return F8_ERR_WORKSPACE;
         launch_measure(jobs, fmt, st);
         *npartial = jobs.j[0].blocks;
         return last_launch_status();
     }
-    if (glue && out && !out_t && ld_out == cols) {
+    if (glue && !out_t) {
         const int64_t hc = kcols / 8, n = rows * hc, blocks = glue_blocks(n);
-        if (blocks * (int64_t)sizeof(uint32_t) <= (int64_t)ws_bytes) {
-            const bool stream = n >= kGlueStreamChunks;
+        if ((size_t)blocks * sizeof(uint32_t) > ws_bytes) return F8_ERR_WORKSPACE;
+        const bool stream = n >= kGlueStreamChunks;
 #define F8_GLUE(F, G) (stream ? cast_glue_stream_kernel<F, G, true> : cast_glue_stream_kernel<F, G, false>)
-            const auto kernel = fmt == F8_E4M3 ? (glue == 1 ? F8_GLUE(F8_E4M3, 1) : F8_GLUE(F8_E4M3, 2))
-                                               : (glue == 1 ? F8_GLUE(F8_E5M2, 1) : F8_GLUE(F8_E5M2, 2));
+        const auto kernel = fmt == F8_E4M3 ? (glue == 1 ? F8_GLUE(F8_E4M3, 1) : F8_GLUE(F8_E4M3, 2))
+                                           : (glue == 1 ? F8_GLUE(F8_E5M2, 1) : F8_GLUE(F8_E5M2, 2));
 #undef F8_GLUE
-            kernel<<<(unsigned)blocks, kThreads, 0, st>>>((const uint4*)x, (const uint4*)x2, n, hc, scale, (uint2*)out, (uint32_t*)ws);
-            *npartial = (int)blocks;
-            return last_launch_status();
-        }
+        kernel<<<(unsigned)blocks, kThreads, 0, st>>>((const uint4*)x, (const uint4*)x2, n, hc, scale, (uint2*)out, (uint32_t*)ws);
+        *npartial = (int)blocks;
+        return last_launch_status();
     }
-#define F8_LAUNCH_MEASURE_G(F, O, T, G)                                                                  \
+#define F8_MEASURE(F, O, T, G)                                                                           \
     cast_tile_kernel<F, F8_TENSORWISE, false, O, T, true, G><<<(unsigned)nb, kThreads, 0, st>>>(         \
         (const uint16_t*)x, rows, kcols, ld, scale, nullptr, 0, nullptr, nullptr, nullptr, out, ld_out, out_t, \
         ld_out_t, (int)tiles_c, (uint32_t*)ws, nullptr, (const uint16_t*)x2)
-#define F8_LAUNCH_MEASURE(F, O, T)                       \
+#define F8_MEASURE_FMT(F)                                \
     do {                                                 \
-        if (glue == 1) F8_LAUNCH_MEASURE_G(F, O, T, 1);  \
-        else if (glue == 2) F8_LAUNCH_MEASURE_G(F, O, T, 2); \
-        else F8_LAUNCH_MEASURE_G(F, O, T, 0);            \
-    } while (0)
-#define F8_MEASURE_FMT(F)                               \
-    do {                                                \
-        if (out && out_t) F8_LAUNCH_MEASURE(F, true, true);  \
-        else if (out_t) F8_LAUNCH_MEASURE(F, false, true);   \
-        else F8_LAUNCH_MEASURE(F, true, false);              \
+        if (glue == 1) F8_MEASURE(F, true, true, 1);     \
+        else if (glue == 2) F8_MEASURE(F, true, true, 2); \
+        else if (out && out_t) F8_MEASURE(F, true, true, 0); \
+        else if (out_t) F8_MEASURE(F, false, true, 0);   \
+        else F8_MEASURE(F, true, false, 0);              \
     } while (0)
     if (fmt == F8_E4M3) F8_MEASURE_FMT(F8_E4M3);
     else F8_MEASURE_FMT(F8_E5M2);
 #undef F8_MEASURE_FMT
-#undef F8_LAUNCH_MEASURE
-#undef F8_LAUNCH_MEASURE_G
+#undef F8_MEASURE
     *npartial = (int)nb;
     return last_launch_status();
 }

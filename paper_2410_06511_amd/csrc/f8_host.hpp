@@ -31,7 +31,7 @@ f8_status quantise_pair(const void* x0, int64_t rows0, int64_t cols0, float* ama
                         float* scale1, float* inv1, uint8_t* out1, uint8_t* out_t1, int fmt, void* ws, hipStream_t st);
 
 // Delayed / static scaling pieces (tensorwise, validated arguments).
-// cast with a given scale, leaving one partial maximum per 128x128 tile in ws
+// cast with a given scale, leaving one partial maximum per block in ws (*npartial of them)
 // glue = 1: x is [rows, 2 * cols] = [a | b] (ld = its row length), the tensor cast is bf16(silu(a) * b);
 // glue = 2: x is [a | b] [rows, cols], x2 is dh [rows, cols / 2], the tensor cast is the glue's backward
 f8_status cast_measure(const void* x, int64_t rows, int64_t cols, int64_t ld, const float* scale, int fmt,

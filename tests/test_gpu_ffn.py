@@ -397,10 +397,10 @@ def test_fused_glue_backward_argument_checks():
 
 
 # Less than a block; the last size with a chunk a thread (256 blocks) and the next; and from 8 M elements on two chunks side by
-# side, the last pair cut short (2064 x 4112 is 1036 chunks a row pair and a rest).
+# side: one round of all blocks, and 12320 chunks more, 24 pairs of a block and 32 chunks.
 @pytest.mark.parametrize("fmt", [f8.E4M3, f8.E5M2])
 @pytest.mark.parametrize("M,H", [(16, 16), (512, 1024), (528, 1024), (1008, 2800), (2048, 4096), (2064, 4112)])
-def test_streamed_glue_casts_equal_the_glue_and_a_cast(M, H, fmt):
+def test_streamed_glue_casts_equal_the_glue_and_a_cast(M, H, fmt, transposed=False):
     g = torch.Generator("cuda")
     g.manual_seed(M + H)
     R = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
@@ -411,9 +411,17 @@ def test_streamed_glue_casts_equal_the_glue_and_a_cast(M, H, fmt):
                                 (lambda: f8.silu_mul_bwd(ab, dh, dab, amax, ws),
                                  lambda q, sc: f8.silu_mul_bwd_quantise_delayed(ab, dh, fmt, hist, sc, q, ws), dab, 5000.0)):
         plain()
-        used, sc, q = torch.full((1,), s0, device="cuda"), torch.full((1,), s0, device="cuda"), f8.QTensor(M, t.shape[1], False)
+        used, sc, q = torch.full((1,), s0, device="cuda"), torch.full((1,), s0, device="cuda"), f8.QTensor(M, t.shape[1], False, transposed=transposed)
         codes = torch.empty_like(q.q)
         f8.cast(t, used, f8.TENSORWISE, fmt, codes)
         fused(q, sc)
         torch.cuda.synchronize()
         assert torch.equal(codes, q.q) and torch.equal(amax, q.amax) and q.scale.item() == s0 and hist[0].item() == amax.item()
+        assert not transposed or torch.equal(codes.t(), q.q_t)
+
+
+# With a transposed copy in 128x128 tiles: part of one, and ragged rows and columns of several.
+@pytest.mark.parametrize("fmt", [f8.E4M3, f8.E5M2])
+@pytest.mark.parametrize("M,H", [(16, 16), (144, 272), (1008, 2800)])
+def test_tiled_glue_casts_equal_the_glue_and_a_cast(M, H, fmt):
+    test_streamed_glue_casts_equal_the_glue_and_a_cast(M, H, fmt, transposed=True)
