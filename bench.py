@@ -872,7 +872,7 @@ def layer_main(args, w):
     flops_step = sum(l.flops for l in w.linears)
     tflops = flops_step / (ms_per_step * 1e-3) / 1e12
 
-    calls = blk.forward_stages(x, weights, stream) + blk.backward_stages(x, weights, dout, stream)
+    calls = blk.forward_stages(x, weights, stream, joined=True) + blk.backward_stages(x, weights, dout, stream, joined=True)  # those of step()
     reps = max(3, min(args.steps, 10))
     evs = [[(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in calls] for _ in range(reps)]
     for r in range(reps):
