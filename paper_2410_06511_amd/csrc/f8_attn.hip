@@ -1049,11 +1049,10 @@ struct Rows {
     int64_t rows, ld, w;
     int size;
 };
-static bool apart(const Rows& a, const Rows& b)
+static bool rows_apart(const Rows& a, const Rows& b)
 {
+    if (apart({a.p, ((a.rows - 1) * a.ld + a.w) * a.size}, {b.p, ((b.rows - 1) * b.ld + b.w) * b.size})) return true;
     const uintptr_t p = (uintptr_t)a.p, q = (uintptr_t)b.p;
-    const uintptr_t pe = p + (uintptr_t)(((a.rows - 1) * a.ld + a.w) * a.size), qe = q + (uintptr_t)(((b.rows - 1) * b.ld + b.w) * b.size);
-    if (pe <= q || qe <= p) return true;
     const int64_t pitch = a.ld * a.size;  // column slices of one matrix
     if (pitch != b.ld * b.size) return false;
     const int64_t d = (((int64_t)(q - p)) % pitch + pitch) % pitch;
@@ -1153,7 +1152,7 @@ static f8_status sdpa_bwd(const void* q_bf16, int64_t ldq, const void* k_bf16, i
     auto written_apart = [&](const Rows& w) {
         for (const Rows& r : {Rows{q_bf16, M, ldq, wq, 2}, Rows{k_bf16, M, ldk, wk, 2}, Rows{v_bf16, M, ldv, wk, 2}, Rows{do_bf16, M, lddo, wq, 2},
                               Rows{lse, Hq, M, M, 4}, Rows{delta, Hq, M, M, 4}, Rows{dq_bf16, M, lddq, wq, 2}})
-            if (!apart(w, r)) return false;
+            if (!rows_apart(w, r)) return false;
         return true;
     };
     const bool one = !dq_far && !dkv_far && one_launch(blocks, nqt, cu_count()) &&

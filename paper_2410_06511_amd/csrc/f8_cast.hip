@@ -1058,16 +1058,6 @@ static f8_status quantise_stream(const StreamTensor& t0, const StreamTensor* t1,
     return last_launch_status();
 }
 
-struct Span {
-    const void* p;
-    int64_t bytes;
-};
-static bool apart(const Span& a, const Span& b)
-{
-    const uintptr_t p = (uintptr_t)a.p, q = (uintptr_t)b.p;
-    return p + (uintptr_t)a.bytes <= q || q + (uintptr_t)b.bytes <= p;
-}
-
 static inline bool streamable(int64_t rows, int64_t cols, int64_t ld, int64_t ld_out, const uint8_t* out, const uint8_t* out_t)
 {
     return rows > 0 && cols > 0 && ld == cols && ld_out == cols && out && !out_t;

@@ -9,6 +9,17 @@ namespace f8 {
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Memory that a call reads or writes; `apart`: no byte in common.
+struct Span {
+    const void* p;
+    int64_t bytes;
+};
+inline bool apart(const Span& a, const Span& b)
+{
+    const uintptr_t p = (uintptr_t)a.p, q = (uintptr_t)b.p;
+    return p + (uintptr_t)a.bytes <= q || q + (uintptr_t)b.bytes <= p;
+}
+
 // Launch errors are sticky in the HIP runtime until read; reading also clears them.
 inline f8_status last_launch_status() { return hipGetLastError() == hipSuccess ? F8_OK : F8_ERR_LAUNCH; }
 

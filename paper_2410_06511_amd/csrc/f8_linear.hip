@@ -158,12 +158,6 @@ static f8_status gemm_fwd(const f8_linear_desc* d, const f8_saved* sv, void* Y, 
                 sv->w.inv_scale, d->granularity, Y, d->N, y_amax, st);
 }
 
-static bool disjoint(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
-{
-    const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
-    return p + (uintptr_t)a_bytes <= q || q + (uintptr_t)b_bytes <= p;
-}
-
 // dX [M,K] = dY8 [M,N] . W8 [N,K]: contraction N, W read k-major; with a transposed copy of W's
 //   codes as dY8 . (W8t [K,N])^T.  Rowwise: dY per row m; W per column k = per row of W8t.
 // dW [N,K] = dY8 [M,N]^T . X8 [M,K]: contraction M, both read k-major; with transposed copies of
@@ -186,11 +180,11 @@ static f8_status gemms_bwd(const f8_linear_desc* d, const f8_saved* sv, void* dX
                               : GemmArgs{n, k, m, sv->dy.q, sv->x.q, N, K, sv->dy.inv_scale, sv->x.inv_scale, dw, K};
         // One after the other, dW may lie over what dX's product reads, or over dX: memory that it lends to the
         // weight's codes until then, or one buffer for both where dX is of no use.
-        const int64_t dw_bytes = N * K * 2;
-        const bool apart = disjoint(dW, dw_bytes, dX, M * K * 2) && disjoint(dW, dw_bytes, x.A, M * N) && disjoint(dW, dw_bytes, x.B, N * K) &&
-                           disjoint(dW, dw_bytes, x.isa, (rw ? M : 1) * 4) && disjoint(dW, dw_bytes, x.isb, (rw ? K : 1) * 4) &&
-                           (!dx_amax || disjoint(dW, dw_bytes, dx_amax, 4));
-        if (apart && gemm_pair(gf, d->granularity, x, w, dx_amax, ws, ws_bytes, st)) return last_launch_status();
+        const Span written{dW, N * K * 2};
+        const bool one = apart(written, {dX, M * K * 2}) && apart(written, {x.A, M * N}) && apart(written, {x.B, N * K}) &&
+                         apart(written, {x.isa, (rw ? M : 1) * 4}) && apart(written, {x.isb, (rw ? K : 1) * 4}) &&
+                         (!dx_amax || apart(written, {dx_amax, 4}));
+        if (one && gemm_pair(gf, d->granularity, x, w, dx_amax, ws, ws_bytes, st)) return last_launch_status();
     }
     if (sv->w.q_t)
         s = gemm(F8_NT, M, K, N, sv->dy.q, gf, N, sv->w.q_t, F8_E4M3, N, sv->dy.inv_scale,
