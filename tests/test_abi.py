@@ -141,3 +141,19 @@ def test_missing_library_fails_loudly(monkeypatch):
         f8.lib()
     with pytest.raises(RuntimeError, match="is missing"):
         f8.workspace_bytes(16, 16)
+
+
+def test_stream_handle_without_the_short_way(monkeypatch):
+    """Where torch lacks the names behind the quick look-up, the current stream's object says its handle."""
+    import types
+    current = types.SimpleNamespace(cuda_stream=1234)
+    monkeypatch.setattr(f8.torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(f8.torch.cuda, "current_stream", lambda: current)
+    for name in ("_raw_stream", "_device"):
+        with monkeypatch.context() as m:
+            m.setattr(f8, name, None)
+            assert f8._stream(None) == 1234
+    assert f8._stream(types.SimpleNamespace(cuda_stream=99)) == 99
+    monkeypatch.setattr(f8, "_device", lambda: 3)
+    monkeypatch.setattr(f8, "_raw_stream", lambda d: 5000 + d)
+    assert f8._stream(None) == 5003
