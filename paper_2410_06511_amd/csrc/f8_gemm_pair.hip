@@ -203,26 +203,29 @@ PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, 
     // 256 beyond two rounds of work, and knows no overlap), and choose between the ways of one launch, where they see a
     // clear gain; up to five rounds of work, as far as they hold (512 x 15040 x 12800 rowwise by them 663 -> 827), and not
     // for less than a tile's rows of tokens or outputs (160 x 12800 x 3584 109 -> 116).  How clear, by 940 random passes in
-    // the ways that the two sets rank first and 160 of row-wise scaled products of more than three rounds.  Tensorwise,
-    // predicted 0.9 times two launches or less: measured 0.90 in the mean, at most 1.03; 0.9 .. 0.97: 0.985, up to 1.10
-    // (3008 x 2928 x 4528 167 -> 184).  Another tile than the first set's: below 0.85 0.94, at most 1.02, and for 8 us at
-    // least.  Rowwise, more than three rounds, smaller tiles: where dX has more of them 0.98, up to 1.12; where dW has, 0.93
-    // and at most 1.01 if predicted below 0.8, up to 1.06 above.  400 further passes in which this rule changes the choice:
-    // 0.91 tensorwise and 0.93 rowwise, three of them slower by more than 2 % (the worst 4.6 %).  us of a pass, before /
-    // after: 16384 x 2048 x 1024 173 / 153, 16384 x 4096 x 512 205 / 180, 11440 x 5568 x 512 207 / 182, 400 x 5632 x 5760
-    // 119 / 103, 448 x 3328 x 10752 rowwise 188 / 162, 5920 x 5312 x 320 124 / 108; two launches still: 1664 x 8896 x 6656,
-    // 16384 x 1024 x 1024, 8192 x 3584 x 8192 (in one the same).
+    // the ways that the two sets rank first and 240 more at the lines below.  Tensorwise, predicted 0.9 times two launches
+    // or less: measured 0.90 in the mean, at most 1.03; 0.9 .. 0.97: the large tiles on half the XCDs each, as in the
+    // separate launches, 0.977, at most 1.014, other ways 0.99, up to 1.10 (3008 x 2928 x 4528 167 -> 184).  Another tile
+    // than the first set's: below 0.85 0.94, at most 1.02, and for 8 us at least.  Rowwise, more than three rounds, smaller
+    // tiles: where dX has more of them 0.98, up to 1.12; where dW has, 0.93 and at most 1.01 if predicted below 0.8, up to
+    // 1.06 above.  400 further passes in which this rule changes the choice: 0.91 tensorwise and 0.93 rowwise, three of them
+    // slower by more than 2 % (the worst 4.6 %).  us of a pass, before / after: 16384 x 2048 x 1024 173 / 153, 16384 x 4096
+    // x 512 205 / 180, 11440 x 5568 x 512 207 / 182, 400 x 5632 x 5760 119 / 103, 448 x 3328 x 10752 rowwise 188 / 162, 5920
+    // x 5312 x 320 124 / 108, 8192 x 3584 x 8192 delayed 604 / 598; two launches still: 1664 x 8896 x 6656, 16384 x 1024 x
+    // 1024.
     const int64_t full_x = tile_count(x, 256, 256), full_w = tile_count(w, 256, 256), full = full_x + full_w;
     if (full > 5 * cus || M < 256 || N < 256) return c;
     const bool many_rows = !KM && full > 3 * cus;
     constexpr double kLeast = 8.0, kOverOne = KM ? 0.85 : 0.80;
-    const double over_two = KM ? 0.90 : many_rows ? 0.80 : 0.86;
     const double two = separately(4.5), first = in_pass_us(x, w, c, two, cus);
     PairChoice in_pass = c;
-    best = !c.tile ? first * over_two : first * kOverOne < first - kLeast ? first * kOverOne : first - kLeast;
+    best = first;
     auto consider = [&](PairChoice k) {
         const double us = in_pass_us(x, w, k, two, cus);
-        if (us < best) best = us, in_pass = k;
+        const bool even = KM && k.tile == 256 && k.x_xcds == 4;
+        const double over_two = even ? 0.97 : KM ? 0.90 : many_rows ? 0.80 : 0.86;
+        const bool clear = c.tile ? us < first * kOverOne && us < first - kLeast : us < first * over_two;
+        if (clear && us < best) best = us, in_pass = k;
     };
     if (small <= 4 * cus) consider({kSm, 0});
     for (int xc : {4, 3, 5})
