@@ -187,7 +187,7 @@ def test_sdpa_backward_gradients_over_k_and_v():
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(2, 2), (2, 1)])
-@pytest.mark.parametrize("S", [8, 40, 232, 264])
+@pytest.mark.parametrize("S", [8, 40, 56, 64, 232, 264, 312, 320])  # (a block of up to 56 rows stores them straight)
 def test_sdpa_backward_writes_its_rows_and_columns_only(S, Hq, Hkv):
     """The gradients between guard rows and columns, the heads' shares in a workspace with guard words behind it."""
     B, M = 2, 2 * S
