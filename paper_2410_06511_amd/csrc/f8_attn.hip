@@ -1095,8 +1095,14 @@ static bool rows_apart(const Rows& a, const Rows& b)
 // tiles each or, with more blocks, that of their sum over the units: with less than 2 n / (n + 1) blocks per unit the former
 // is longer.  us of rope, attention and its backward, two launches / one (sequences x tokens, heads): 2 x 512, 8 107 / 84,
 // 1 x 2048, 16 264 / 208, 1 x 8192, 8 844 / 698, 4 x 1000, 16 213 / 197, 5 x 256, 32 131 / 129; at the line 7 x 2048, 8 452 / 443 and
-// 8 x 256, 32 164 / 172, beyond it 2 x 2048, 32 454 / 453 and 1 x 8192, 32 2344 / 2354.
-static bool one_launch(int64_t blocks, int64_t n, int cus) { return blocks * (n + 1) < 2 * n * cus; }
+// 8 x 256, 32 164 / 172, beyond it 2 x 2048, 32 454 / 453 and 1 x 8192, 32 2344 / 2354.  With one tile each, more than half a unit's
+// share of blocks are a second round, which the rest of a short block's time and delta's launch make longer than a second launch.  us of
+// the backward alone, two / one, 17 and 24 sequences of 8 heads: 16 tokens 14.6 / 16.1 and 14.8 / 17.6, 64 18.0 / 18.8 and 19.2 / 20.7, 96 25.5 / 26.2
+// and 27.9 / 26.8, 112 27.9 / 27.7 and 30.3 / 28.0; 8 / 2 heads 48 tokens 22.2 / 23.0 and 24.7 / 26.5, 64 24.9 / 25.0 and 28.4 / 27.9.
+static bool one_launch(int64_t blocks, int64_t n, int64_t S, bool grouped, int cus)
+{
+    return blocks * (n + 1) < 2 * n * cus && (n > 1 || 2 * blocks <= cus || S >= (grouped ? 64 : 112));
+}
 
 constexpr int kDqWaves = 8;  // 256 queries per block, one block per compute unit
 constexpr int kDkvWaves = 8;             // 256 keys per block, one block per compute unit
@@ -1187,7 +1193,7 @@ static f8_status sdpa_bwd(const void* q_bf16, int64_t ldq, const void* k_bf16, i
             if (!rows_apart(w, r)) return false;
         return true;
     };
-    const bool one = !dq_far && !dkv_far && one_launch(blocks, nqt, cu_count()) &&
+    const bool one = !dq_far && !dkv_far && one_launch(blocks, nqt, S, group > 1, cu_count()) &&
                      (group > 1 ? written_apart({workspace, 2 * group, M * wk, M * wk, 4})
                                 : written_apart({dk_bf16, M, lddk, wk, 2}) && written_apart({dv_bf16, M, lddv, wk, 2}));
     if (one) {

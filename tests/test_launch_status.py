@@ -11,8 +11,10 @@ from paper_2410_06511_amd import f8
 
 STAND_IN = r"""
 static int launches, refused = -1, error;
+static unsigned grids[64];
 void f8_test_reset(int k) { launches = 0, refused = k, error = 0; }
 int f8_test_launches(void) { return launches; }
+unsigned f8_test_grid(int k) { return grids[k]; }
 int hipLaunchKernel(const void* f, unsigned long long gxy, unsigned gz, unsigned long long bxy, unsigned bz, void** a, unsigned long s, void* st)
 {
     (void)f, (void)gxy, (void)gz, (void)bxy, (void)bz, (void)a, (void)s, (void)st;
@@ -21,7 +23,8 @@ int hipLaunchKernel(const void* f, unsigned long long gxy, unsigned gz, unsigned
 }
 int __hipPushCallConfiguration(unsigned long long gxy, unsigned gz, unsigned long long bxy, unsigned bz, unsigned long s, void* st)
 {
-    (void)gxy, (void)gz, (void)bxy, (void)bz, (void)s, (void)st;
+    (void)gz, (void)bxy, (void)bz, (void)s, (void)st;
+    if (launches < 64) grids[launches] = (unsigned)gxy;
     return 0;
 }
 int __hipPopCallConfiguration(void* g, void* b, unsigned long* s, void** st) { (void)g, (void)b, *s = 0, *st = 0; return 0; }
