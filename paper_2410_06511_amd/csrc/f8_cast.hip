@@ -1100,17 +1100,20 @@ f8_status quantise(const void* x, int64_t rows, int64_t cols, int64_t ld, int g,
                               out, ld_out, out_t, ld_out_t, st);
 }
 
-// One partial per block, no more blocks than the tiled form has tiles (the workspace is sized for those, and never below
-// kMinWorkspaceBytes) or kMeasureBlocks, and at least four chunks per thread.  With the tiles alone a small tensor's threads make
-// several rounds (208 x 1184 x 2112, forward and backward, 31.8 -> 30.7 us; a block of 3 x 336 tokens 266.6 -> 260.1); 1024
-// loses 1 % of 4096 x 2048 x 2048.
+// One partial per block, at least four chunks per thread, and no more blocks than the tiled form has tiles (the workspace is
+// sized for those), but up to kMeasureBlocks (never below kMinWorkspaceBytes) for a tensor that these read in one round of four
+// loads and two more: with the tiles alone a small tensor's threads make two rounds (208 x 1184 x 2112, forward and backward,
+// 31.8 -> 30.7 us; a block of 3 x 336 tokens 266.6 -> 260.1; 1024 x 2048 alone 5.6 -> 5.0, 1024 x 4608 7.3 -> 6.2).  With more
+// left over, one load at a time, two even rounds on the tiles' blocks are no slower: delayed forwards of 32 and 256 tokens,
+// tiles / 512 blocks, 2048 x 2816 15.0 / 14.2 and 18.5 / 18.0 us, 1024 x 6144 15.7 / 15.2 and 19.3 / 19.1, 1776 x 3968 15.8 / 16.1
+// and 19.1 / 19.8.  1024 blocks lose 1 % of 4096 x 2048 x 2048.
 constexpr int64_t kMeasureBlocks = 512;
 static_assert(2 * kMeasureBlocks * sizeof(uint32_t) <= kMinWorkspaceBytes, "two tensors' partial maxima");
 static MeasureJob measure_job(const void* x, int64_t rows, int64_t cols, const float* scale, uint8_t* out, uint32_t* partial)
 {
     const int64_t tiles = ((rows + kTile - 1) / kTile) * ((cols + kTile - 1) / kTile), chunks = rows * (cols / 8);
     int64_t b = (chunks + kThreads * 4 - 1) / (kThreads * 4);
-    const int64_t most = tiles > kMeasureBlocks ? tiles : kMeasureBlocks;
+    const int64_t most = tiles < kMeasureBlocks && b <= kMeasureBlocks * 3 / 2 ? kMeasureBlocks : tiles;
     b = b < most ? b : most;
     b = b < kJobCastBlocks ? b : kJobCastBlocks;
     return MeasureJob{(const uint4*)x, chunks, scale, (uint2*)out, partial, (int)b};
