@@ -113,9 +113,7 @@ def compare_then_replace(blk, ref, names, stage):
             t.copy_(torch.from_numpy(np.asarray(ref[n], dtype=np.float32).reshape(t.shape)))
 
 
-@pytest.mark.parametrize("joined", (False, True))
-def test_transformer_block_stage_by_stage(joined):
-    """joined: the stages that forward() and backward() run."""
+def test_transformer_block_stage_by_stage(joined=False):
     B, S, Hq, Hkv, hd, H, eps = 2, 136, 4, 2, 128, 768, 1e-5
     D, M = Hq * hd, B * S
     x, dout = gen((M, D), 1), gen((M, D), 2, 1e-2)
@@ -149,6 +147,11 @@ def test_transformer_block_stage_by_stage(joined):
             assert blk.a_bwd[1].item() == o.amax(bits(blk.dqkv))[0]
             blk.dqkv.copy_(to_dev(ref["dqkv"]))
             blk.a_bwd[1:2].copy_(torch.from_numpy(o.amax(ref["dqkv"])))
+
+
+def test_joined_stages_stage_by_stage():
+    """Those that forward() and backward() run."""
+    test_transformer_block_stage_by_stage(joined=True)
 
 
 def test_transformer_block_end_to_end_and_recompute():
