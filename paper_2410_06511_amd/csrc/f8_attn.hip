@@ -270,8 +270,8 @@ __device__ inline void store_rows(const f32x16 (&acc)[kHd / 32], float mul, uint
     }
 }
 
-// The same straight from the registers: where one or two waves of the block have rows, little competes with their stores, and the
-// barrier before the stage and the way through it are what they would wait for.
+// The same straight from the registers: where one or two waves of the block have rows, little competes with their stores, and
+// the barrier before the stage, the other waves' empty stores and the way through the stage are what they would wait for.
 template <typename T>
 __device__ inline void store_rows_straight(const f32x16 (&acc)[kHd / 32], float mul, T* out, int64_t ld, int rows, int lane)
 {
@@ -287,10 +287,11 @@ __device__ inline void store_rows_straight(const f32x16 (&acc)[kHd / 32], float 
             else *reinterpret_cast<float4*>(row + 32 * d + 8 * j) = make_float4(v0, v1, v2, v3);
         }
 }
-// Blocks of at most so many rows (two waves) store them straight.  us of the backward through the stage by every wave / so:
-// 64 sequences, 32 / 8 heads, of 16 tokens 124.6 / 111.9, 48 tokens 162.0 / 154.6; 32 / 32 heads 16 tokens 110.9 / 104.1; of 64 tokens
-// and 32 / 32 heads the stage is the better one, 163.0 / 155.1, with 8 key heads as good.
-constexpr int kStraightRows = 56;
+// Sequences of at most so many tokens (bf16 gradients; fp32 shares) store their rows straight, in instances of their own: as a
+// branch of the others it costs longer sequences 0.8 % (4 x 1000 tokens, 16 heads 80.2 -> 80.7 us).  us of the backward, through the
+// stage / straight, 64 sequences, 32 / 32 heads: 16 tokens 110.2 / 102.9, 40 127.3 / 125.5, 48 131.0 / 132.3, 56 134.5 / 138.6, 64
+// 142.8 / 149.3; 32 / 8 heads (dQ by the same line) 16 tokens 124.0 / 111.1, 48 158.3 / 152.8, 64 182.0 / 179.1.
+constexpr int kStraightRows = 40, kStraightShares = 64;
 
 // ---- forward ------------------------------------------------------------------------------
 // One block: 8 waves of 32 queries each of one (sequence, head), loop over 64-key steps up to the
@@ -558,6 +559,7 @@ __device__ inline float delta_term(uint32_t d, uint32_t o) { return bf16_lo(d) *
 // K^T comes from the K tile itself, by transposing reads.  (All waves in step, three tiles through registers: 821 us for
 // 1 x 8192 tokens, 32/8 heads; this: 700.  Phase M is what it waits for: 48 products, 1536 cycles, in about 1900.)
 // The work of one block: query tile qt of (sequence, head) bh.  DELTA: delta is formed and stored here, else it is read.
+// STRAIGHT: see store_rows_straight.
 struct DqArgs {
     const uint16_t *Q, *K, *V, *O, *dO;
     int64_t ldq, ldk, ldv, ldo, lddo;
@@ -569,7 +571,7 @@ struct DqArgs {
     int64_t lddq;
     float* delta;
 };
-template <int NW, bool FAR, bool DELTA>
+template <int NW, bool FAR, bool DELTA, bool STRAIGHT>
 __device__ __forceinline__ void sdpa_bwd_dq_work(const DqArgs& P, int qt, int bh, uint16_t (&sK)[4][kBk * kHd], uint16_t (&sV)[4][kBk * kHd])
 {
     static_assert(NW == 8, "two waves per SIMD in opposite phases");
@@ -723,24 +725,23 @@ __device__ __forceinline__ void sdpa_bwd_dq_work(const DqArgs& P, int qt, int bh
         if (t == t_last - 1) products(t_last, C16{});
     }
     if (!late) phase_barrier();
-    const bool straight = S - qt * QB <= kStraightRows;
-    if (!straight) phase_barrier();  // after it nothing reads the tiles any more
-    if (q_first >= S) return;
+    if constexpr (!STRAIGHT) phase_barrier();  // after it nothing reads the tiles any more
+    if (STRAIGHT && q_first >= S) return;      // (not STRAIGHT: 1 % of 1 x 2048 tokens)
     int l64 = threadIdx.x & 63;  // (formed anew: what the stores are addressed by would be held over the loop)
     asm volatile("" : "+v"(l64));
     uint16_t* out = dQ + (tok0 + q_first) * lddq + (int64_t)h * kHd;
-    if (straight) store_rows_straight(acc, scale, out, lddq, S - q_first, l64);
+    if constexpr (STRAIGHT) store_rows_straight(acc, scale, out, lddq, S - q_first, l64);
     else store_rows(acc, scale, &sK[0][0] + wave * 32 * kHd, out, lddq, S - q_first, l64);
 }
 
-template <int NW, bool FAR>
+template <int NW, bool FAR, bool STRAIGHT = false>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dq_kernel(const DqArgs P, int nqt)
 {
     __shared__ __attribute__((aligned(1024))) uint16_t sK[4][kBk * kHd];
     __shared__ __attribute__((aligned(1024))) uint16_t sV[4][kBk * kHd];
     // long (late) query tiles first, over all heads
     const int nbh = P.Hq * (int)(P.M / P.S), qt = nqt - 1 - (int)(blockIdx.x / nbh);
-    sdpa_bwd_dq_work<NW, FAR, true>(P, qt, blockIdx.x % nbh, sK, sV);
+    sdpa_bwd_dq_work<NW, FAR, true, STRAIGHT>(P, qt, blockIdx.x % nbh, sK, sV);
 }
 
 // dV^T = dO^T P and dK^T = Q^T dS in one pass over the scores.  One block: 8 waves, 32 keys each (one key per lane),
@@ -771,7 +772,7 @@ struct DkvLds {
     float sStat[4][2 * kDkvQ];  // lse, then delta
 };
 // The work of one block: key tile kt of (sequence, query head) bh.
-template <int NW, bool FAR>
+template <int NW, bool FAR, bool STRAIGHT>
 __device__ __forceinline__ void sdpa_bwd_dkv_work(const DkvArgs& P, int kt, int bh, uint16_t (&sQ)[4][kDkvQ * kHd], uint16_t (&sD)[4][kDkvQ * kHd],
                                                   uint16_t (&sV)[32 * NW * kHd], float (&sStat)[4][2 * kDkvQ])
 {
@@ -956,15 +957,14 @@ __device__ __forceinline__ void sdpa_bwd_dkv_work(const DkvArgs& P, int kt, int 
         if (t == t_last - 1) products(t_last, C16{});
     }
     if (!late) phase_barrier();
-    const bool straight = S - q_start <= kStraightRows;
-    if (!straight) phase_barrier();  // after it nothing reads the tiles any more
+    if constexpr (!STRAIGHT) phase_barrier();  // after it nothing reads the tiles any more
     const int rows = S - key_first;
-    if (rows <= 0) return;
+    if (STRAIGHT && rows <= 0) return;
     uint16_t* stage = sV + wave * 32 * kHd;
     int l64 = threadIdx.x & 63;  // (formed anew: what the stores are addressed by would be held over the loop)
     asm volatile("" : "+v"(l64));
     auto store = [&](const f32x16(&acc)[kHd / 32], float mul, auto* out, int64_t ld) {
-        if (straight) store_rows_straight(acc, mul, out, ld, rows, l64);
+        if constexpr (STRAIGHT) store_rows_straight(acc, mul, out, ld, rows, l64);
         else store_rows(acc, mul, stage, out, ld, rows, l64);
     };
     if (group == 1) {
@@ -979,7 +979,7 @@ __device__ __forceinline__ void sdpa_bwd_dkv_work(const DkvArgs& P, int kt, int 
     }
 }
 
-template <int NW, bool FAR>
+template <int NW, bool FAR, bool STRAIGHT = false>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(const DkvArgs P)
 {
     __shared__ __attribute__((aligned(1024))) uint16_t sQ[4][kDkvQ * kHd];
@@ -988,7 +988,7 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_dkv_kernel(
     __shared__ __attribute__((aligned(1024))) float sStat[4][2 * kDkvQ];  // lse, then delta
     // early key tiles see the most queries: they are the slowest-varying index, so they start first
     const int nbh = P.Hq * (int)(P.M / P.S);
-    sdpa_bwd_dkv_work<NW, FAR>(P, blockIdx.x / nbh, blockIdx.x % nbh, sQ, sD, sV, sStat);
+    sdpa_bwd_dkv_work<NW, FAR, STRAIGHT>(P, blockIdx.x / nbh, blockIdx.x % nbh, sQ, sD, sV, sStat);
 }
 
 // delta[h][token] = sum of dO O over the head, in the order of sdpa_bwd_dq_work (chunk 2 s + g of a row to lane group g,
@@ -1029,7 +1029,7 @@ __global__ __launch_bounds__(kAttnThreads) void sdpa_delta_kernel(const uint16_t
 // as many tiles), delta beforehand.  A launch of at most one block per compute unit lasts as long as its longest block, and
 // the units of the shorter ones idle: here the other kernel's blocks fill them (4 x 1000 tokens, 16 heads: 48 + 64 us in two
 // launches; this 90 and delta 7).  Same device code, same bits.
-template <int NW>
+template <int NW, bool STRAIGHT>
 __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_kernel(const DqArgs Pq, const DkvArgs Pk, int tiles)
 {
     constexpr size_t kDq = 2 * sizeof(uint16_t[4][kBk * kHd]), kDkv = sizeof(DkvLds<NW>);
@@ -1037,10 +1037,10 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void sdpa_bwd_kernel(cons
     const int nbh = Pq.Hq * (int)(Pq.M / Pq.S), k = blockIdx.x / nbh, bh = blockIdx.x % nbh;
     if (k & 1) {
         auto* s = reinterpret_cast<uint16_t(*)[4][kBk * kHd]>(lds);
-        sdpa_bwd_dq_work<NW, false, false>(Pq, tiles - 1 - k / 2, bh, s[0], s[1]);
+        sdpa_bwd_dq_work<NW, false, false, STRAIGHT>(Pq, tiles - 1 - k / 2, bh, s[0], s[1]);
     } else {
         auto* s = reinterpret_cast<DkvLds<NW>*>(lds);
-        sdpa_bwd_dkv_work<NW, false>(Pk, k / 2, bh, s->sQ, s->sD, s->sV, s->sStat);
+        sdpa_bwd_dkv_work<NW, false, STRAIGHT>(Pk, k / 2, bh, s->sQ, s->sD, s->sV, s->sStat);
     }
 }
 
@@ -1193,15 +1193,18 @@ static f8_status sdpa_bwd(const void* q_bf16, int64_t ldq, const void* k_bf16, i
             if (!rows_apart(w, r)) return false;
         return true;
     };
+    const bool dq_straight = S <= kStraightRows, dkv_straight = group > 1 ? S <= kStraightShares : dq_straight;
     const bool one = !dq_far && !dkv_far && one_launch(blocks, nqt, S, group > 1, cu_count()) &&
                      (group > 1 ? written_apart({workspace, 2 * group, M * wk, M * wk, 4})
                                 : written_apart({dk_bf16, M, lddk, wk, 2}) && written_apart({dv_bf16, M, lddv, wk, 2}));
     if (one) {
         sdpa_delta_kernel<<<(unsigned)((M * Hq + kDeltaRows - 1) / kDeltaRows), kAttnThreads, 0, st>>>(q.O, ldo, q.dO, lddo, M, (int)Hq, delta);
-        sdpa_bwd_kernel<kDqWaves><<<(unsigned)(2 * blocks), 64 * kDqWaves, 0, st>>>(q, kv, (int)nqt);
+        (dkv_straight ? sdpa_bwd_kernel<kDqWaves, true> : sdpa_bwd_kernel<kDqWaves, false>)<<<(unsigned)(2 * blocks), 64 * kDqWaves, 0, st>>>(q, kv, (int)nqt);
     } else {
-        (dq_far ? sdpa_bwd_dq_kernel<kDqWaves, true> : sdpa_bwd_dq_kernel<kDqWaves, false>)<<<(unsigned)blocks, 64 * kDqWaves, 0, st>>>(q, (int)nqt);
-        (dkv_far ? sdpa_bwd_dkv_kernel<kDkvWaves, true> : sdpa_bwd_dkv_kernel<kDkvWaves, false>)<<<(unsigned)blocks, 64 * kDkvWaves, 0, st>>>(kv);
+        const auto dq_kernel = dq_far ? sdpa_bwd_dq_kernel<kDqWaves, true> : dq_straight ? sdpa_bwd_dq_kernel<kDqWaves, false, true> : sdpa_bwd_dq_kernel<kDqWaves, false>;
+        const auto dkv_kernel = dkv_far ? sdpa_bwd_dkv_kernel<kDkvWaves, true> : dkv_straight ? sdpa_bwd_dkv_kernel<kDkvWaves, false, true> : sdpa_bwd_dkv_kernel<kDkvWaves, false>;
+        dq_kernel<<<(unsigned)blocks, 64 * kDqWaves, 0, st>>>(q, (int)nqt);
+        dkv_kernel<<<(unsigned)blocks, 64 * kDkvWaves, 0, st>>>(kv);
     }
     if (group > 1) {
         int64_t nb = (2 * M * (wk / 8) + kAttnThreads - 1) / kAttnThreads;

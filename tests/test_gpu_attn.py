@@ -152,7 +152,7 @@ def test_sdpa_backward(B, S, Hq, Hkv):
 
 # Few blocks take dQ and dK/dV in one launch, many in two, by the same device code and sums: the same bits.  Blocks of a launch
 # (256 compute units: one launch below 256 of one tile, 341 of two): 272 and 8 each; 352 and 16.
-@pytest.mark.parametrize("B,S,Hq,Hkv", [(34, 24, 8, 8), (34, 40, 8, 2), (22, 264, 8, 8), (22, 320, 8, 4)])
+@pytest.mark.parametrize("B,S,Hq,Hkv", [(34, 24, 8, 8), (34, 40, 8, 2), (34, 56, 8, 2), (34, 64, 8, 2), (22, 264, 8, 8), (22, 320, 8, 4)])
 def test_sdpa_backward_in_one_launch_has_the_bits_of_two(B, S, Hq, Hkv):
     a = Attn(B, S, Hq, Hkv, seed=S)
     a.forward()
@@ -187,7 +187,7 @@ def test_sdpa_backward_gradients_over_k_and_v():
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(2, 2), (2, 1)])
-@pytest.mark.parametrize("S", [8, 40, 56, 64, 232, 264, 312, 320])  # (a block of up to 56 rows stores them straight)
+@pytest.mark.parametrize("S", [8, 40, 48, 56, 64, 72, 232, 264, 312, 320])  # (up to 40 or, with grouped heads, 64 tokens store them straight)
 def test_sdpa_backward_writes_its_rows_and_columns_only(S, Hq, Hkv):
     """The gradients between guard rows and columns, the heads' shares in a workspace with guard words behind it."""
     B, M = 2, 2 * S
