@@ -200,37 +200,38 @@ PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, 
         }
     }
     // The estimates within a pass have the last word where the above stays with two launches (it takes no tiles below 256 x
-    // 256 beyond two rounds of work, and knows no overlap), and choose between the ways of one launch, where they see a
-    // clear gain; up to five rounds of work, as far as they hold (512 x 15040 x 12800 rowwise by them 663 -> 827), and not
-    // for less than a tile's rows of tokens or outputs (160 x 12800 x 3584 109 -> 116).  How clear, by 940 random passes in
-    // the ways that the two sets rank first and 240 more at the lines below.  Tensorwise, predicted 0.9 times two launches
-    // or less: measured 0.90 in the mean, at most 1.03; 0.9 .. 0.97: the large tiles on half the XCDs each, as in the
-    // separate launches, 0.977, at most 1.014, other ways 0.99, up to 1.10 (3008 x 2928 x 4528 167 -> 184).  Another tile
-    // than the first set's: below 0.85 0.94, at most 1.02, and for 8 us at least.  Rowwise, more than three rounds, smaller
-    // tiles: where dX has more of them 0.98, up to 1.12; where dW has, 0.93 and at most 1.01 if predicted below 0.8, up to
-    // 1.06 above.  400 further passes in which this rule changes the choice: 0.91 tensorwise and 0.93 rowwise, three of them
-    // slower by more than 2 % (the worst 4.6 %).  us of a pass, before / after: 16384 x 2048 x 1024 173 / 153, 16384 x 4096
-    // x 512 205 / 180, 11440 x 5568 x 512 207 / 182, 400 x 5632 x 5760 119 / 103, 448 x 3328 x 10752 rowwise 188 / 162, 5920
-    // x 5312 x 320 124 / 108, 8192 x 3584 x 8192 delayed 604 / 598; two launches still: 1664 x 8896 x 6656, 16384 x 1024 x
-    // 1024.
-    const int64_t full_x = tile_count(x, 256, 256), full_w = tile_count(w, 256, 256), full = full_x + full_w;
-    if (full > 5 * cus || M < 256 || N < 256) return c;
-    const bool many_rows = !KM && full > 3 * cus;
-    constexpr double kLeast = 8.0, kOverOne = KM ? 0.85 : 0.80;
+    // 256 beyond two rounds of work, and knows no overlap), and choose between the ways of one launch, where they see 8 us or
+    // more; up to five rounds of work, as far as they hold (512 x 15040 x 12800 rowwise by them 663 -> 827), and not for less
+    // than a tile's rows of tokens or outputs (160 x 12800 x 3584 109 -> 116).  How much they have to see, by 1500 random
+    // passes in the ways that the two sets rank first.  Another tile of one launch: 0.943 in the mean, four of 457 slower by
+    // more than 2 % (the worst 4.3 %).  Tensorwise, predicted 0.9 times two launches or less: 0.90; 0.9 .. 0.97: the large
+    // tiles on half the XCDs each, as in the separate launches, 0.98; where the product of fewer tiles is one round of its
+    // units, or either contraction at most 8 steps, 0.95 (1600 x 2048 x 15360 delayed 200 -> 187), else 1.03, up to 1.10:
+    // smaller tiles read their operands more often (3008 x 2928 x 4528 167 -> 184).  Rowwise, predicted 0.86 or less: 0.94,
+    // and smaller tiles of more than three rounds by the box: where dX alone is 3.5 to 4 rounds, 1.02, up to 1.12, on one, and
+    // 0.94, at most 1.02, on another.
+    // us of a pass, before / after: 16384 x 2048 x 1024 173 / 153, 16384 x 4096 x 512 205 / 180, 11440 x 5568 x 512 207 /
+    // 182, 400 x 5632 x 5760 119 / 103, 448 x 3328 x 10752 rowwise 188 / 162, 5920 x 5312 x 320 124 / 108, 8192 x 3584 x
+    // 8192 delayed 604 / 598; two launches still: 1664 x 8896 x 6656, 16384 x 1024 x 1024.
+    if (tile_count(x, 256, 256) + tile_count(w, 256, 256) > 5 * cus || M < 256 || N < 256) return c;
+    constexpr double kLeast = 8.0;
     const double two = separately(4.5), first = in_pass_us(x, w, c, two, cus);
     PairChoice in_pass = c;
     best = first;
+    auto few_reads = [&](PairChoice k) {
+        if (k.tile == kSm || (k.tile == 256 && k.x_xcds == 4)) return true;
+        const int bm = k.tile == 128 ? 128 : 256, bn = k.tile == 256 ? 256 : 128, at_once = k.tile == 128 ? 2 : 1;
+        return tile_count(x, bm, bn) <= (int64_t)at_once * per_xcd * k.x_xcds || tile_count(w, bm, bn) <= (int64_t)at_once * per_xcd * (kXcds - k.x_xcds) ||
+               (k.tile != 256 && (ksteps_of(x.K, 1) <= 8 || ksteps_of(w.K, 1) <= 8));
+    };
     auto consider = [&](PairChoice k) {
         const double us = in_pass_us(x, w, k, two, cus);
-        const bool even = KM && k.tile == 256 && k.x_xcds == 4;
-        const double over_two = even ? 0.97 : KM ? 0.90 : many_rows ? 0.80 : 0.86;
-        const bool clear = c.tile ? us < first * kOverOne && us < first - kLeast : us < first * over_two;
+        const bool clear = c.tile ? us < first - kLeast : us < first * (!KM ? 0.86 : few_reads(k) ? 0.97 : 0.90);
         if (clear && us < best) best = us, in_pass = k;
     };
     if (small <= 4 * cus) consider({kSm, 0});
     for (int xc : {4, 3, 5})
-        for (int t : {256, 192, 128})
-            if (t == 256 || c.tile || !many_rows || full_w > full_x) consider({t, xc});
+        for (int t : {256, 192, 128}) consider({t, xc});
     return in_pass;
 }
 
