@@ -1098,10 +1098,11 @@ static bool rows_apart(const Rows& a, const Rows& b)
 // 8 x 256, 32 164 / 172, beyond it 2 x 2048, 32 454 / 453 and 1 x 8192, 32 2344 / 2354.  With one tile each, more than half a unit's
 // share of blocks are a second round, which the rest of a short block's time and delta's launch make longer than a second launch.  us of
 // the backward alone, two / one, 17 and 24 sequences of 8 heads: 16 tokens 14.6 / 16.1 and 14.8 / 17.6, 64 18.0 / 18.8 and 19.2 / 20.7, 96 25.5 / 26.2
-// and 27.9 / 26.8, 112 27.9 / 27.7 and 30.3 / 28.0; 8 / 2 heads 48 tokens 22.2 / 23.0 and 24.7 / 26.5, 64 24.9 / 25.0 and 28.4 / 27.9.
+// and 27.9 / 26.8, 112 27.9 / 27.7 and 30.3 / 28.0; 8 / 2 heads 48 tokens 22.5 / 22.5 and 24.0 / 24.9, 64 24.9 / 25.0 and 28.4 / 27.9; 28 and 30 sequences of 40
+// tokens 23.2 / 24.0 and 23.9 / 24.0, 48 24.7 / 24.4 and 25.4 / 24.1, 56 26.5 / 24.6 and 27.2 / 25.2.
 static bool one_launch(int64_t blocks, int64_t n, int64_t S, bool grouped, int cus)
 {
-    return blocks * (n + 1) < 2 * n * cus && (n > 1 || 2 * blocks <= cus || S >= (grouped ? 64 : 112));
+    return blocks * (n + 1) < 2 * n * cus && (n > 1 || 2 * blocks <= cus || S >= (!grouped ? 112 : 8 * blocks < 7 * cus ? 64 : 48));
 }
 
 constexpr int kDqWaves = 8;  // 256 queries per block, one block per compute unit

@@ -208,7 +208,7 @@ PairChoice F8_PAIR_NAME(choice_, F8_PAIR_FA, F8_PAIR_GRAN)(int M, int K, int N, 
     // tiles on half the XCDs each, as in the separate launches, 0.98; where the product of fewer tiles is one round of its
     // units, or either contraction at most 8 steps, 0.95 (1600 x 2048 x 15360 delayed 200 -> 187), else 1.03, up to 1.10:
     // smaller tiles read their operands more often (3008 x 2928 x 4528 167 -> 184).  Rowwise, predicted 0.86 or less: 0.94,
-    // and smaller tiles of more than three rounds by the box: where dX alone is 3.5 to 4 rounds, 1.02, up to 1.12, on one, and
+    // and smaller tiles of more than three rounds by the card: where dX alone is 3.5 to 4 rounds, 1.02, up to 1.12, on one, and
     // 0.94, at most 1.02, on another.
     // us of a pass, before / after: 16384 x 2048 x 1024 173 / 153, 16384 x 4096 x 512 205 / 180, 11440 x 5568 x 512 207 /
     // 182, 400 x 5632 x 5760 119 / 103, 448 x 3328 x 10752 rowwise 188 / 162, 5920 x 5312 x 320 124 / 108, 8192 x 3584 x

@@ -26,7 +26,7 @@ print(s, *[stand_in.f8_test_grid(k) for k in range(2)])
 @pytest.mark.parametrize("B,S,Hq,Hkv,one", [
     # a tile to a sequence and head: in one launch while all blocks find a unit, or long enough for a second round
     (16, 16, 8, 8, True), (17, 16, 8, 8, False), (30, 48, 8, 8, False), (17, 104, 8, 8, False), (17, 112, 8, 8, True), (31, 256, 8, 8, True),
-    (16, 16, 8, 2, True), (17, 56, 8, 2, False), (17, 64, 8, 2, True), (31, 256, 8, 2, True), (32, 256, 8, 8, False),
+    (16, 16, 8, 2, True), (17, 56, 8, 2, False), (17, 64, 8, 2, True), (27, 56, 8, 2, False), (28, 40, 8, 2, False), (28, 48, 8, 2, True), (31, 256, 8, 2, True), (32, 256, 8, 8, False),
     # several: by the blocks to a unit
     (4, 1000, 16, 16, True), (21, 512, 8, 8, True), (22, 512, 8, 8, False), (1, 8192, 8, 8, True), (1, 8192, 32, 8, False)])
 def test_one_launch_or_two(stand_in, B, S, Hq, Hkv, one):  # noqa: F811
